@@ -119,11 +119,12 @@ typedef struct {
   int32_t n_problems;
   int32_t n_stacks;
   int32_t n_bricks;         /* 8x8x8 voxel bricks over all problems */
-  int64_t n_bin_pairs;      /* sub-brick/patch pairs of the adjoint's index
-                               (0 until a back-projection built it) */
+  int64_t n_bin_pairs;      /* pairs of the adjoint's second-level index (half
+                               bricks or 4^3 sub-bricks with patches; 0 until
+                               a back-projection built it) */
   int64_t device_bytes;     /* bytes of the attached workspace (0 if none) */
   int64_t bin_capacity;     /* brick/patch pairs the workspace holds */
-  int64_t sub_capacity;     /* sub-brick/patch pairs the workspace holds */
+  int64_t sub_capacity;     /* second-level pairs the workspace holds */
 } pvr_plan_sizes;
 
 /* EM state of one reconstruction, kept on the device so that an SR iteration

@@ -2,11 +2,13 @@
 // order, the contributions of the samples whose PSF support covers it, so no
 // two lanes ever write the same address and the result is bitwise repeatable.
 //
-// Patches are indexed per 4^3 sub-brick (one wavefront), in patch order.  For
-// a voxel and a patch, the voxel is mapped (FP64 affine G) into the patch's
-// unmoved pixel frame; the PSF is axis-aligned there, so the candidate pixels
-// are the integer (u, v) inside an ellipse around the mapped point, on the
-// patch's single slice.
+// For a voxel and a patch, the voxel is mapped (FP64 affine G) into the
+// patch's unmoved pixel frame; the PSF is axis-aligned there, so the candidate
+// pixels are the integer (u, v) inside an ellipse around the mapped point, on
+// the patch's single slice.  Two kernels: k_gather_blocks (2 x 2 voxels per
+// lane, where pixels are about as wide as voxels and the PSF about as wide as
+// a pixel: pvr_plan::gather_blocks) and k_backproject (one voxel per lane, any
+// sizes; patches indexed per 4^3 sub-brick).
 #include <math.h>
 
 #include "pvr_internal.h"
@@ -20,6 +22,25 @@ template <typename T> struct Vec2Of;
 template <> struct Vec2Of<float> { using type = float2; };
 template <> struct Vec2Of<double> { using type = double2; };
 
+// Where the inputs rq of a patch lie.  FP32: rows padded by RQ_PAD zeros, from
+// the patch's rq_off; FP64: packed like the samples, one guard entry before and
+// after all N.  lead: index of pixel (0, 0) in the view; pitch: entries per row.
+template <typename T> struct Rq;
+template <> struct Rq<float> {
+  static constexpr int lead = RQ_PAD;
+  static __device__ __forceinline__ int pitch(int w) { return rq_pitch(w); }
+  static __device__ __forceinline__ __amdgpu_buffer_rsrc_t view(const float2 *rq, const PatchDev &pt) {
+    return raw_buffer(rq + pt.rq_off, (unsigned)rq_entries(pt.w, pt.h) * (unsigned)sizeof(float2));
+  }
+};
+template <> struct Rq<double> {
+  static constexpr int lead = 1;
+  static __device__ __forceinline__ int pitch(int w) { return w; }
+  static __device__ __forceinline__ __amdgpu_buffer_rsrc_t view(const double2 *rq, const PatchDev &pt) {
+    return raw_buffer(rq + pt.off - 1, (unsigned)(pt.w * pt.h + 2) * (unsigned)sizeof(double2));
+  }
+};
+
 // rq_j = (p_j e_j / Z_j, p_j / Z_j) for valid samples, 0 otherwise (the
 // patch weight W_s is applied by the gather, per patch).
 template <typename T>
@@ -31,8 +52,11 @@ k_bp_prep(const PatchDev *__restrict__ patches, const BlockWork *__restrict__ wo
   const PatchDev pt = patches[wk.patch];
   const int n = pt.w * pt.h;
   const int l1 = min(n, wk.l0 + SIM_CHUNK);
-  // one sample (invalid samples, 1/Z = 0, get 0)
-  auto one = [&](long long j, T iz, T pj, T ej) {
+  typename Vec2Of<T>::type *out =
+      sizeof(T) == 4 ? rq + pt.rq_off + RQ_PAD : rq + pt.off;
+  // one sample (invalid samples, 1/Z = 0, get 0); a padded row adds RQ_PAD
+  // entries per pixel row before it
+  auto one = [&](int l, T iz, T pj, T ej) {
     typename Vec2Of<T>::type o;
     if (iz > (T)0) {
       const T q = pj * iz;
@@ -42,7 +66,7 @@ k_bp_prep(const PatchDev *__restrict__ patches, const BlockWork *__restrict__ wo
       o.x = 0;
       o.y = 0;
     }
-    rq[j] = o;
+    out[sizeof(T) == 4 ? l + RQ_PAD * (l / pt.w) : l] = o;
   };
   // four samples per thread in flight: their reads are independent (e and p
   // are defined for every sample)
@@ -57,29 +81,21 @@ k_bp_prep(const PatchDev *__restrict__ patches, const BlockWork *__restrict__ wo
       ej[u] = e[j];
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) one(pt.off + l + u * SIM_THREADS, iz[u], pj[u], ej[u]);
+    for (int u = 0; u < 4; ++u) one(l + u * SIM_THREADS, iz[u], pj[u], ej[u]);
   }
   for (; l < l1; l += SIM_THREADS) {
     const long long j = pt.off + l;
-    one(j, invz[j], p ? p[j] : (T)1, e[j]);
+    one(l, invz[j], p ? p[j] : (T)1, e[j]);
   }
 }
 
-// Raw buffer view of one patch's n rq entries plus one entry on either side
-// (the neighbouring patches' entries, or the zero guards around the whole
-// array), so byte offset (i + 1) sizeof(V2) addresses entry i, i in [-1, n].
-// A buffer load never faults: outside the view it returns 0, so candidate
-// pixels off the patch need no address clamp.  Their weights are zeroed
-// explicitly, so whatever such a load returns never contributes.  The one
-// entry of margin matters because the compiler merges the loads of two
-// adjacent candidates into one 16-byte load, and a partly out-of-range load
-// may return 0 for all of it: with the margin, a pair holding an in-patch
-// entry is always wholly in range.
-template <typename V2>
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t patch_rsrc(const V2 *patch_base, int n) {
-  return raw_buffer(patch_base - 1, (unsigned)(n + 2) * (unsigned)sizeof(V2));
-}
-
+// A buffer load never faults: outside the patch's view it returns 0, so
+// candidate pixels off the patch need no address clamp.  Their weights are
+// zeroed explicitly, so whatever such a load returns never contributes.  The
+// margin around the patch's entries (Rq::lead, the row padding) matters
+// because the compiler merges the loads of two adjacent candidates into one
+// 16-byte load, and a partly out-of-range load may return 0 for all of it:
+// with the margin, a pair holding an in-patch entry is always wholly in range.
 template <typename V2> __device__ __forceinline__ V2 load_rq(__amdgpu_buffer_rsrc_t r, int off);
 template <> __device__ __forceinline__ float2 load_rq<float2>(__amdgpu_buffer_rsrc_t r, int off) {
   return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
@@ -125,9 +141,9 @@ __device__ __forceinline__ void adj_patch(const GEO &g, const PatchDev &pt, doub
     const bool in = (unsigned)(rv + b) < (unsigned)pt.h;
     E[b + HV] = in ? fast_exp2<T>(-fma(wv, wv, qk)) : (T)0;
   }
-  const __amdgpu_buffer_rsrc_t r = patch_rsrc(rq + pt.off, pt.w * pt.h);
-  const int row_bytes = pt.w * (int)sizeof(V2);
-  int off = ((rv - HV) * pt.w + (ru - HU) + 1) * (int)sizeof(V2);
+  const __amdgpu_buffer_rsrc_t r = Rq<T>::view(rq, pt);
+  const int pitch = Rq<T>::pitch(pt.w), row_bytes = pitch * (int)sizeof(V2);
+  int off = ((rv - HV) * pitch + (ru - HU) + Rq<T>::lead) * (int)sizeof(V2);
 #pragma unroll
   for (int b = 0; b < 2 * HV + 1; ++b) {
 #pragma unroll
@@ -152,16 +168,17 @@ __device__ __forceinline__ void adj_patch_rt(const GEO &g, const PatchDev &pt, d
   const int ru = (int)rud - pt.x0, rv = (int)rvd - pt.y0;
   const T fu = (T)(pu - rud), fv = (T)(pv - rvd);
   const T cu = (T)g.cu, cv = (T)g.cv, cut = (T)g.cut;
-  const __amdgpu_buffer_rsrc_t r = patch_rsrc(rq + pt.off, pt.w * pt.h);
+  const __amdgpu_buffer_rsrc_t r = Rq<T>::view(rq, pt);
+  const int pitch = Rq<T>::pitch(pt.w);
   for (int b = -hv; b <= hv; ++b) {
     const T wv = ((T)b - fv) * cv;
     const T qkv = fma(wv, wv, qk);
-    const int row = (rv + b) * pt.w;
+    const int row = (rv + b) * pitch;
     for (int a = -hu; a <= hu; ++a) {
       const T wu = ((T)a - fu) * cu;
       const bool in = ((unsigned)(ru + a) < (unsigned)pt.w) & ((unsigned)(rv + b) < (unsigned)pt.h);
       const T gh = in ? fma_clamp0<T>(fast_exp2<T>(-fma(wu, wu, qkv)), (T)1, cut) : (T)0;
-      const V2 q = load_rq<V2>(r, (row + ru + a + 1) * (int)sizeof(V2));
+      const V2 q = load_rq<V2>(r, (row + ru + a + Rq<T>::lead) * (int)sizeof(V2));
       sn = fma(gh, q.x, sn);
       if (DEN) sd = fma(gh, q.y, sd);
     }
@@ -184,17 +201,18 @@ __device__ __forceinline__ void adj_patch_sinc(const GEO &g, const PatchDev &pt,
   const T cu = (T)g.cu, cv = (T)g.cv, cut = (T)g.cut;
   T gz = fast_exp2<T>(-qk) - cut;
   gz = gz > (T)0 ? gz : (T)0;
-  const __amdgpu_buffer_rsrc_t r = patch_rsrc(rq + pt.off, pt.w * pt.h);
+  const __amdgpu_buffer_rsrc_t r = Rq<T>::view(rq, pt);
+  const int pitch = Rq<T>::pitch(pt.w);
   for (int b = -hv; b <= hv; ++b) {
     const T tv = ((T)b - fv) * cv;
     const bool inb = ((unsigned)(rv + b) < (unsigned)pt.h) & (fabs(tv) < (T)1);
     const T e = inb ? sinc_poly<T>(tv) * gz : (T)0;
-    const int row = (rv + b) * pt.w;
+    const int row = (rv + b) * pitch;
     for (int a = -hu; a <= hu; ++a) {
       const T tu = ((T)a - fu) * cu;
       const bool ina = ((unsigned)(ru + a) < (unsigned)pt.w) & (fabs(tu) < (T)1);
       const T gh = ina ? sinc_poly<T>(tu) * e : (T)0;
-      const V2 q = load_rq<V2>(r, (row + ru + a + 1) * (int)sizeof(V2));
+      const V2 q = load_rq<V2>(r, (row + ru + a + Rq<T>::lead) * (int)sizeof(V2));
       sn = fma(gh, q.x, sn);
       if (DEN) sd = fma(gh, q.y, sd);
     }
@@ -262,11 +280,288 @@ k_backproject(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ pa
   }
 }
 
+// ---------------------------------------------------------------------------
+// Block gather: each lane owns the 2 x 2 voxels (along the patch's in-plane
+// axes) of one layer along its normal axis, a wavefront 8 x 8 x 4 voxels, a
+// workgroup of two wavefronts one 8^3 brick.  See AdjPatch for the voxels'
+// forced nearest pixels.  The four voxels share
+//  * the 4 x 4 pixel window, 16 bytes per load (8 loads for four voxels instead
+//    of 6 per voxel: the per-voxel gather kept the vector-memory path 80-90 %
+//    busy);
+//  * the FP64 voxel -> pixel map, taken once at the block's centre;
+//  * with the Gaussian, the factors 2^-(c (a - f))^2 of the six candidate rows
+//    and columns: a voxel's own deviation d enters as 2^(2 c^2 a d), a constant
+//    of the patch, and one exponential per voxel that also holds its
+//    through-plane term (10 exponentials instead of 24).
+// About 70 vector issue slots per voxel and patch instead of 111: the kernel is
+// bound by vector issue.  256^3 benchmark, 11 760 patches: 2.27 ms per launch with
+// the per-voxel gather, 1.31 ms with this one.  The
+// patches of a brick are taken normal axis by normal axis (lists of
+// k_half_lists), so that the two wavefronts' voxels are disjoint; between axes
+// the sums move through LDS.  The order (axis, then patch, then candidate) is
+// fixed: the result is bitwise repeatable.
+//
+// A brick's lists are split over `parts` pairs of wavefronts (entry q to part
+// (q - q0) mod parts, each part with its own LDS sums, added in part order at
+// the end), so that a small grid still fills the chip: gather_parts.
+constexpr int GB_THREADS = 128;  // of one part
+template <typename T> constexpr int GB_MAX_PARTS = sizeof(T) == 4 ? 8 : 4;  // registers
+
+// Measured, whole passes in us with 1 / 2 / 4 / 8 parts: build and first volume at
+// 160^3 (16 000 wavefronts at one part) 766 / 743 / 767 / 952; SR iteration at 128^3,
+// sinc PSF (8 192) 696 / 674 / 718 / 805; gradients at 96^3 (3 456) 494 / - / 448 /
+// 484; SR iteration at 32^3 (128) 198 / - / - / 142.  A workgroup of 8 parts waits for
+// 16 free wavefront slots of one CU, so it pays only where a CU has one
+// workgroup at most.
+static int gather_parts(int n_bricks, int most) {
+  int parts = 1;
+  while (parts < most && 2LL * n_bricks * parts < (parts < 4 ? 16384 : 4096)) parts *= 2;
+  return parts;
+}
+
+template <typename T, bool DEN> struct GbAcc;
+template <typename T> struct GbAcc<T, true> { T n, d; };
+template <typename T> struct GbAcc<T, false> { T n; };
+
+// The 4 x 4 window whose first column and row are the patch-local pixel
+// (u0, v0); in: the window meets the patch.  Pixels outside the patch read 0.
+__device__ __forceinline__ void load_window(const AdjPatch<float> &g, const float2 *__restrict__ rq,
+                                            int u0, int v0, bool in, float2 q[4][4]) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  const int pitch = rq_pitch(g.w);
+  const __amdgpu_buffer_rsrc_t r =
+      raw_buffer(rq + g.rq_off, (unsigned)rq_entries(g.w, g.h) * (unsigned)sizeof(float2));
+  int off = in ? (v0 * pitch + u0 + RQ_PAD) * (int)sizeof(float2) : -64;
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    // a row before the patch gives a negative offset, out of range as unsigned
+    const f4 x = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+    const f4 y = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, off + 16, 0, 0));
+    q[b][0] = make_float2(x.x, x.y);
+    q[b][1] = make_float2(x.z, x.w);
+    q[b][2] = make_float2(y.x, y.y);
+    q[b][3] = make_float2(y.z, y.w);
+    off += pitch * (int)sizeof(float2);
+  }
+}
+__device__ __forceinline__ void load_window(const AdjPatch<double> &g, const double2 *__restrict__ rq,
+                                            int u0, int v0, bool in, double2 q[4][4]) {
+  const __amdgpu_buffer_rsrc_t r =
+      raw_buffer(rq + g.rq_off, (unsigned)(g.w * g.h) * (unsigned)sizeof(double2));
+  int off[4];  // packed rows: a column outside the patch reads past the view
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+    off[a] = in && (unsigned)(u0 + a) < (unsigned)g.w ? (v0 * g.w + u0 + a) * (int)sizeof(double2)
+                                                      : 0x70000000;
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+      q[b][a] = __builtin_bit_cast(
+          double2, __builtin_amdgcn_raw_buffer_load_b128(r, off[a] + b * g.w * (int)sizeof(double2), 0, 0));
+}
+
+// Rounds x (|x| < 2^51) to the nearest integer, ties to even; returns it and
+// its value as a double (the low word of x + 1.5 2^52 holds the integer).
+__device__ __forceinline__ int round_split(double x, double &r) {
+  const double m = x + 6755399441055744.0;
+  r = m - 6755399441055744.0;
+  return (int)(__builtin_bit_cast(long long, m) & 0xffffffffll);
+}
+
+template <typename T, bool DEN, bool SINC>
+__global__ void __launch_bounds__(GB_THREADS * GB_MAX_PARTS<T>)
+k_gather_blocks(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ patches,
+                const typename GeoOf<T>::type *__restrict__ geo,
+                const AdjPatch<T> *__restrict__ adj, const int *__restrict__ brick_prob,
+                const int *__restrict__ off, const int *__restrict__ list,
+                const typename Vec2Of<T>::type *__restrict__ rq, const T *__restrict__ patch_w,
+                T *__restrict__ num, T *__restrict__ den, int n_bricks, int granule) {
+  using GEO = typename GeoOf<T>::type;
+  using V2 = typename Vec2Of<T>::type;
+  using Acc = GbAcc<T, DEN>;
+  constexpr int NV = BRICK * BRICK * BRICK;
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  const int bi = xcd_work(blockIdx.x, granule);
+  if (bi >= n_bricks) return;
+  const ProbDev pr = probs[brick_prob[bi]];
+  const int local = bi - pr.brick_base;
+  const int bx = local % pr.nbx, by = (local / pr.nbx) % pr.nby, bz = local / (pr.nbx * pr.nby);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int w = wave & 1, part = wave >> 1, parts = blockDim.x / GB_THREADS;
+  const int l = threadIdx.x & 63;
+  const int lp = l & 3, lq = (l >> 2) & 3, ln = l >> 4;
+  Acc *const acc = reinterpret_cast<Acc *>(lds) + part * NV;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) acc[q * GB_THREADS + (threadIdx.x & (GB_THREADS - 1))] = Acc{};
+  T sn[4], sd[4];  // sub-window (ou, ov) at 2 ov + ou
+  for (int an = 0; an < 3; ++an) {
+    __syncthreads();
+    const int li = bi * 6 + 2 * an + w;
+    const int q0 = off[li] + part, q1 = off[li + 1];
+    int cur = -1;
+    double xu = 0, xv = 0, xn = 0;  // the block's centre along (au, av, an)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) sn[t] = sd[t] = (T)0;
+    // adds the lane's sums of the class `cur` to its voxels and clears them
+    auto flush = [&]() {
+      const int au = cur & 3, av = (cur >> 2) & 3;
+      const int tu = au == 0 ? 1 : au == 1 ? BRICK : BRICK * BRICK;
+      const int tv = av == 0 ? 1 : av == 1 ? BRICK : BRICK * BRICK;
+      const int tn = an == 0 ? 1 : an == 1 ? BRICK : BRICK * BRICK;
+      const int base = 2 * lp * tu + 2 * lq * tv + (SUB * w + ln) * tn;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int du = (t & 1) ^ ((cur >> 4) & 1), dv = (t >> 1) ^ ((cur >> 5) & 1);
+        Acc &o = acc[base + du * tu + dv * tv];
+        o.n += sn[t];
+        if constexpr (DEN) o.d += sd[t];
+        sn[t] = sd[t] = (T)0;
+      }
+    };
+    for (int q = q0; q < q1; q += parts) {
+      const int s = list[q];
+      // the patch weight scales the patch's whole contribution; an excluded
+      // patch (weight 0) is skipped
+      const T ws = patch_w ? patch_w[s] : (T)1;
+      if (ws == (T)0) continue;
+      const AdjPatch<T> &g = adj[s];
+      const int cls = g.cls & ADJ_MAP;
+      if (cls != cur) {  // (uniform; the patches of a stack share their class)
+        if (cur >= 0) flush();
+        cur = cls;
+        const int au = cls & 3, av = (cls >> 2) & 3;
+        xu = sel3(au, bx, by, bz) * BRICK + 2 * lp + 0.5;
+        xv = sel3(av, bx, by, bz) * BRICK + 2 * lq + 0.5;
+        xn = sel3(an, bx, by, bz) * BRICK + SUB * w + ln;
+      }
+      if (g.cls & ADJ_FAST) {
+        const T wk = (T)fma(g.Gk[0], xu, fma(g.Gk[1], xv, fma(g.Gk[2], xn, g.Gk[3])));
+        const double pu = fma(g.Gu[0], xu, fma(g.Gu[1], xv, fma(g.Gu[2], xn, g.Gu[3])));
+        const double pv = fma(g.Gv[0], xu, fma(g.Gv[1], xv, fma(g.Gv[2], xn, g.Gv[3])));
+        double rud, rvd;
+        const int ru = round_split(pu, rud), rv = round_split(pv, rvd);
+        const T f = (T)(pu - rud), h = (T)(pv - rvd);
+        // through-plane offsets of the four voxels, and the lanes with none
+        // inside the support or off the patch
+        const T wt[4] = {wk - g.dk11, wk + g.dk10, wk - g.dk10, wk + g.dk11};
+        const T reach = fmin(fmin(wt[0] * wt[0], wt[1] * wt[1]), fmin(wt[2] * wt[2], wt[3] * wt[3]));
+        const bool in = reach <= g.K2 && (unsigned)(ru + 2) <= (unsigned)(g.w + 2) &&
+                        (unsigned)(rv + 2) <= (unsigned)(g.h + 2);
+        if (!__any(in)) continue;
+        V2 x[4][4];
+        load_window(g, rq, ru - 1, rv - 1, in, x);
+        const T cut = g.cut;
+        T U[4][3], E[4][3];  // column and row factors of the four voxels
+        if constexpr (SINC) {
+          const T du[4] = {-g.P11, g.P10, -g.P10, g.P11}, dv[4] = {-g.Q11, g.Q10, -g.Q10, g.Q11};
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const T gz = fmax(fast_exp2<T>(-wt[t] * wt[t]) - cut, (T)0);
+#pragma unroll
+            for (int a = -1; a <= 1; ++a) {
+              const T tu = ((T)a - (f + du[t])) * g.cu, tv = ((T)a - (h + dv[t])) * g.cv;
+              U[t][a + 1] = fabs(tu) < (T)1 ? sinc_poly<T>(tu) : (T)0;
+              E[t][a + 1] = fabs(tv) < (T)1 ? sinc_poly<T>(tv) * gz : (T)0;
+            }
+          }
+        } else {
+          const T fu = f * g.cu, hv = h * g.cv;
+          T B[3], C[3];
+#pragma unroll
+          for (int a = -1; a <= 1; ++a) {
+            const T yu = (T)a * g.cu - fu, yv = (T)a * g.cv - hv;
+            B[a + 1] = fast_exp2<T>(-yu * yu);
+            C[a + 1] = fast_exp2<T>(-yv * yv);
+          }
+          const T P[4] = {-g.P11, g.P10, -g.P10, g.P11}, Q[4] = {-g.Q11, g.Q10, -g.Q10, g.Q11};
+          const T R[4] = {g.R11, g.R10, g.R10, g.R11};
+          const T ku[4] = {g.ki11, g.ku10, g.ki10, g.ku11}, ki[4] = {g.ku11, g.ki10, g.ku10, g.ki11};
+          const T kv[4] = {g.ji11, g.kv10, g.ji10, g.kv11}, ji[4] = {g.kv11, g.ji10, g.kv10, g.ji11};
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const T S = fast_exp2<T>(-fma(wt[t], wt[t], fma(f, P[t], fma(h, Q[t], R[t]))));
+            U[t][0] = B[0] * ki[t];
+            U[t][1] = B[1];
+            U[t][2] = B[2] * ku[t];
+            E[t][0] = (C[0] * ji[t]) * S;
+            E[t][1] = C[1] * S;
+            E[t][2] = (C[2] * kv[t]) * S;
+          }
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int ou = t & 1, ov = t >> 1;
+          T pn = 0, pd = 0;
+#pragma unroll
+          for (int b = 0; b < 3; ++b)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+              const T gh = SINC ? U[t][a] * E[t][b] : fma_clamp0<T>(E[t][b], U[t][a], cut);
+              const V2 &e = x[ov + b][ou + a];
+              pn = fma(gh, e.x, pn);
+              if (DEN) pd = fma(gh, e.y, pd);
+            }
+          if (in && wt[t] * wt[t] <= g.K2) {  // outside, a non-finite input stays out
+            sn[t] = fma(ws, pn, sn[t]);
+            if (DEN) sd[t] = fma(ws, pd, sd[t]);
+          }
+        }
+      } else {
+        // deviations too large for shared windows: the four voxels one by one
+        const GEO &ge = geo[s];
+        const PatchDev pt = patches[s];
+        const int au = cls & 3, av = (cls >> 2) & 3;
+#pragma unroll 1
+        for (int t = 0; t < 4; ++t) {
+          const int tu = (t & 1) ^ ((cls >> 4) & 1), tv = (t >> 1) ^ ((cls >> 5) & 1);
+          const int vu = sel3(au, bx, by, bz) * BRICK + 2 * lp + tu;
+          const int vv = sel3(av, bx, by, bz) * BRICK + 2 * lq + tv;
+          const int vn = sel3(an, bx, by, bz) * BRICK + SUB * w + ln;
+          const double fi = au == 0 ? vu : av == 0 ? vv : vn, fj = au == 1 ? vu : av == 1 ? vv : vn,
+                       fk = au == 2 ? vu : av == 2 ? vv : vn;
+          const double pk = fma(ge.G[8], fi, fma(ge.G[9], fj, fma(ge.G[10], fk, ge.G[11])));
+          const T wk = (T)(pk - (double)pt.slice) * (T)ge.ck;
+          const T qk = wk * wk;
+          T pn = 0, pd = 0;
+          if (qk <= (T)ge.K2) {
+            const double pu = fma(ge.G[0], fi, fma(ge.G[1], fj, fma(ge.G[2], fk, ge.G[3])));
+            const double pv = fma(ge.G[4], fi, fma(ge.G[5], fj, fma(ge.G[6], fk, ge.G[7])));
+            if (SINC) adj_patch_sinc<T, GEO, V2, 1, 1, DEN>(ge, pt, pu, pv, qk, rq, pn, pd);
+            else adj_patch<T, GEO, V2, 1, 1, DEN>(ge, pt, pu, pv, qk, rq, pn, pd);
+          }
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            sn[k] = k == t ? fma(ws, pn, sn[k]) : sn[k];
+            if (DEN) sd[k] = k == t ? fma(ws, pd, sd[k]) : sd[k];
+          }
+        }
+      }
+    }
+    if (cur >= 0) flush();
+  }
+  __syncthreads();
+  for (int v = threadIdx.x; v < NV; v += blockDim.x) {
+    Acc r = reinterpret_cast<Acc *>(lds)[v];
+    for (int q = 1; q < parts; ++q) {
+      const Acc &o = reinterpret_cast<Acc *>(lds)[q * NV + v];
+      r.n += o.n;
+      if constexpr (DEN) r.d += o.d;
+    }
+    const int i = bx * BRICK + (v & 7), jj = by * BRICK + ((v >> 3) & 7), kk = bz * BRICK + (v >> 6);
+    if (i < pr.nx && jj < pr.ny && kk < pr.nz) {
+      const long long idx = pr.vol_off + ((long long)kk * pr.ny + jj) * pr.nx + i;
+      num[idx] = r.n;
+      if constexpr (DEN) den[idx] = r.d;
+    }
+  }
+}
+
 // The preparation pass on its own (FP32), for pvr_robust_weights.
 pvr_status pvr::launch_bp_prep(const pvr_plan *p, const float *e, const float *pp,
                                hipStream_t stream) {
   hipLaunchKernelGGL(k_bp_prep<float>, dim3(p->n_sim_blocks), dim3(SIM_THREADS), 0, stream,
-                     p->d_patch, p->d_sim_blocks, p->d_invz, e, pp, p->d_rq + 1);
+                     p->d_patch, p->d_sim_blocks, p->d_invz, e, pp, p->d_rq);
   HIP_TRY(hipGetLastError());
   return PVR_OK;
 }
@@ -276,8 +571,8 @@ static pvr_status backproject_impl(const pvr_plan *p, const T *e, const T *pp, c
                                    T *num, T *den, const T *invz, typename Vec2Of<T>::type *rq,
                                    hipStream_t stream) {
   if (!e || !num) return fail(PVR_EINVAL, "pvr_backproject: e and num are required");
-  if (!p->index_valid) {
-    const pvr_status st = plan_build_index(const_cast<pvr_plan *>(p), stream);
+  if (!p->index_valid || p->index_blocks != p->gather_blocks) {
+    const pvr_status st = plan_build_index(const_cast<pvr_plan *>(p), p->gather_blocks, stream);
     if (st != PVR_OK) return st;
   }
   // the preparation pass, unless pvr_robust_weights (PVR_EM_PREP_ADJOINT)
@@ -304,7 +599,23 @@ static pvr_status backproject_impl(const pvr_plan *p, const T *e, const T *pp, c
   else if (hw == 2) BP_LAUNCH(D, 2, SC); \
   else BP_LAUNCH(D, 0, SC)
   const bool sinc = p->psf == PVR_PSF_SINC;
-  if (den) {
+  if (p->gather_blocks) {
+    const void *adj = sizeof(T) == 4 ? (const void *)p->d_adj : (const void *)p->d_adj64;
+    const int parts = gather_parts(p->n_bricks, GB_MAX_PARTS<T>);
+#define GB_LAUNCH(D, SC)                                                                          \
+  hipLaunchKernelGGL((k_gather_blocks<T, D, SC>), grid, dim3(GB_THREADS * parts),                 \
+                     sizeof(GbAcc<T, D>) * BRICK * BRICK * BRICK * parts, stream, p->d_prob,      \
+                     p->d_patch, geot, (const AdjPatch<T> *)adj, p->d_brick_prob, p->d_sub_off,   \
+                     p->d_sub_patch, rq, patch_w, num, den, p->n_bricks, p->bp_granule)
+    if (den) {
+      if (sinc) GB_LAUNCH(true, true);
+      else GB_LAUNCH(true, false);
+    } else {
+      if (sinc) GB_LAUNCH(false, true);
+      else GB_LAUNCH(false, false);
+    }
+#undef GB_LAUNCH
+  } else if (den) {
     if (sinc) { BP_LAUNCH_HW(true, true); }
     else { BP_LAUNCH_HW(true, false); }
   } else {
@@ -332,7 +643,7 @@ extern "C" pvr_status pvr_backproject(const pvr_plan *p, const float *e, const f
   PVR_TRY_STATUS(debug_finite(p, "pvr_backproject", "e", e, p->N, stream));
   PVR_TRY_STATUS(debug_finite(p, "pvr_backproject", "p", pp, p->N, stream));
   PVR_TRY_STATUS(debug_weights(p, "pvr_backproject", "patch_w", patch_w, p->M, stream));
-  return backproject_impl<float>(p, e, pp, patch_w, num, den, p->d_invz, p->d_rq + 1, stream);
+  return backproject_impl<float>(p, e, pp, patch_w, num, den, p->d_invz, p->d_rq, stream);
   PVR_API_END();
 }
 

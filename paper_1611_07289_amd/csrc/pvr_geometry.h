@@ -222,5 +222,60 @@ __device__ inline void make_geometry(const ProbDev &pr, const StackDev &st, cons
   for (int q = 0; q < 3; ++q) gf.perm[q] = g.perm[q];
 }
 
+// Block-gather constants of one patch (AdjPatch) from its geometry.  A patch
+// is fast when every candidate that can carry weight lies within one pixel of
+// the forced nearest pixel: the in-plane reach R plus the largest deviation d
+// is below 3/2 on both axes; with the Gaussian the in-plane scale is bounded
+// too, so that the exponents of the shared factors stay small and their FP32
+// rounding at the size of the per-voxel form's.
+template <typename T>
+__device__ inline void make_adj(const GeoD &g, const PatchDev &pt, AdjPatch<T> &o) {
+  const double *U = g.G, *V = g.G + 4, *N = g.G + 8;
+  int an = 0;
+  if (fabs(N[1]) > fabs(N[an])) an = 1;
+  if (fabs(N[2]) > fabs(N[an])) an = 2;
+  const int a0 = an == 0 ? 1 : 0, a1 = 3 - an - a0;
+  const int au = fabs(U[a0]) >= fabs(U[a1]) ? a0 : a1, av = a0 + a1 - au;
+  const double su = U[au] < 0 ? -1.0 : 1.0, sv = V[av] < 0 ? -1.0 : 1.0;
+  const int ax[3] = {au, av, an};
+  for (int c = 0; c < 3; ++c) {
+    o.Gu[c] = U[ax[c]];
+    o.Gv[c] = V[ax[c]];
+    o.Gk[c] = N[ax[c]] * g.ck;
+  }
+  o.Gu[3] = U[3] - pt.x0 - 0.5;
+  o.Gv[3] = V[3] - pt.y0 - 0.5;
+  o.Gk[3] = (N[3] - pt.slice) * g.ck;
+  const double Au = su * U[au] - 1.0, Bu = sv * U[av], Av = su * V[au], Bv = sv * V[av] - 1.0;
+  const double du11 = 0.5 * (Au + Bu), du10 = 0.5 * (Au - Bu);
+  const double dv11 = 0.5 * (Av + Bv), dv10 = 0.5 * (Av - Bv);
+  const double Du = fmax(fabs(du11), fabs(du10)), Dv = fmax(fabs(dv11), fabs(dv10));
+  o.dk11 = (T)(0.5 * (su * N[au] + sv * N[av]) * g.ck);
+  o.dk10 = (T)(0.5 * (su * N[au] - sv * N[av]) * g.ck);
+  const bool sinc = g.psf == PVR_PSF_SINC;
+  const double Ru = sinc ? 1.0 / g.cu : sqrt(g.K2) / g.cu, Rv = sinc ? 1.0 / g.cv : sqrt(g.K2) / g.cv;
+  // (false for a motion that is not finite)
+  bool fast = Ru + Du < 1.5 - 1e-4 && Rv + Dv < 1.5 - 1e-4;
+  if (sinc) {
+    o.P11 = (T)du11; o.P10 = (T)du10; o.Q11 = (T)dv11; o.Q10 = (T)dv10;
+  } else {
+    fast = fast && g.cu <= 2.5 && g.cv <= 2.5;
+    const double qu = 2.0 * g.cu * g.cu, qv = 2.0 * g.cv * g.cv;
+    o.P11 = (T)(qu * du11); o.P10 = (T)(qu * du10);
+    o.Q11 = (T)(qv * dv11); o.Q10 = (T)(qv * dv10);
+    o.R11 = (T)(0.5 * (qu * du11 * du11 + qv * dv11 * dv11));
+    o.R10 = (T)(0.5 * (qu * du10 * du10 + qv * dv10 * dv10));
+    if (fast) {
+      o.ku11 = (T)exp2(qu * du11); o.ki11 = (T)exp2(-qu * du11);
+      o.ku10 = (T)exp2(qu * du10); o.ki10 = (T)exp2(-qu * du10);
+      o.kv11 = (T)exp2(qv * dv11); o.ji11 = (T)exp2(-qv * dv11);
+      o.kv10 = (T)exp2(qv * dv10); o.ji10 = (T)exp2(-qv * dv10);
+    }
+  }
+  o.cu = (T)g.cu; o.cv = (T)g.cv; o.cut = (T)g.cut; o.K2 = (T)g.K2;
+  o.w = pt.w; o.h = pt.h; o.rq_off = sizeof(T) == 4 ? pt.rq_off : pt.off; o.pad_ = 0;
+  // patches off the fast path walk the block's voxels one by one
+  o.cls = au | av << 2 | (su < 0) << 4 | (sv < 0) << 5 | (fast ? ADJ_FAST : 0);
+}
 
 }  // namespace pvr

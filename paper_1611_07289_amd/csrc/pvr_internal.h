@@ -56,7 +56,18 @@ struct PatchDev {
   int stack, slice, x0, y0, w, h, problem;
   int layout;  // volume copy the forward walks read: 0 = X (x fastest), 1 = y fastest
   long long off;
+  long long rq_off;  // first guard entry of the patch in the padded adjoint inputs (RQ_PAD)
 };
+
+// The FP32 adjoint inputs rq of a patch are stored with RQ_PAD zero entries
+// before the first row and after every row (entry (u, v) at RQ_PAD +
+// v (w + RQ_PAD) + u from rq_off), so a row of candidates that leaves the
+// patch by up to RQ_PAD columns on either side reads zeros.
+constexpr int RQ_PAD = 3;
+__host__ __device__ __forceinline__ int rq_pitch(int w) { return w + RQ_PAD; }
+__host__ __device__ __forceinline__ long long rq_entries(int w, int h) {
+  return RQ_PAD + (long long)h * rq_pitch(w);
+}
 
 // Motion-dependent per-patch constants, double precision.
 struct GeoD {
@@ -95,6 +106,36 @@ struct GeoF {
   float L[9];               // sinc PSF: voxel offset -> (t_u, t_v, t_n), row-major
   float kcut;               // k
 };
+
+// Constants of one patch for the block gather of the adjoint
+// (k_gather_blocks), where a lane owns the 2 x 2 voxels of one layer along
+// the patch's normal axis.  The voxel axes (au, av) are the ones the pixel
+// axes u, v run along (signs su, sv), an the remaining one; stepping one voxel
+// along au moves the pixel position by su plus a small deviation.  Sub-window
+// (ou, ov) in {0, 1}^2 belongs to the voxel whose nearest pixel is (r_u + ou,
+// r_v + ov), r the rounded position of sub-window (0, 0) without the
+// deviations; its pixel offset from that pixel is f + d, f the lane's common
+// fraction and d_u (ou, ov) = +-du11 or +-du10 (antisymmetric about the
+// block's centre: du00 = -du11, du01 = -du10).
+template <typename T>
+struct AdjPatch {
+  double Gu[4], Gv[4], Gk[4];  // voxel (au, av, an, 1) at the block's centre -> patch-local
+                               // pixel position minus 1/2 in u and v, (slice offset) ck in k
+  T cu, cv, cut, K2;
+  // Gaussian: factors 2^(+-2 c^2 d) of the candidates +-1 and the linear and
+  // constant terms 2 c^2 d, c_u^2 d_u^2 + c_v^2 d_v^2 of the exponent; sinc: the
+  // deviations themselves in (P11, P10, Q11, Q10)
+  T ku11, ki11, ku10, ki10, kv11, ji11, kv10, ji10;
+  T P11, P10, Q11, Q10, R11, R10;
+  T dk11, dk10;            // through-plane offsets of the voxels from the block's centre
+  int w, h;
+  int cls;                     // au | av << 2 | (su < 0) << 4 | (sv < 0) << 5 | ADJ_FAST
+  int pad_;
+  long long rq_off;            // FP32: the patch's padded inputs; FP64: its first sample
+};
+constexpr int ADJ_MAP = 63;    // the bits of cls that fix the lane's voxels
+constexpr int ADJ_FAST = 64;   // the deviations are small enough for the block gather
+__host__ __device__ __forceinline__ int adj_normal_axis(int cls) { return 3 - (cls & 3) - ((cls >> 2) & 3); }
 
 template <typename T> struct GeoOf;
 template <> struct GeoOf<float> { using type = GeoF; };
@@ -585,6 +626,8 @@ struct pvr_plan {
   int P, S, M;
   int max_problem_patches;
   int max_hu, max_hv;         // adjoint candidate half-widths over all stacks
+  bool gather_blocks;         // adjoint by blocks of 2 x 2 voxels per lane (k_gather_blocks)
+  long long n_rq;             // entries of the padded FP32 adjoint inputs
   long long N, V;
   int n_bricks;
   double k;
@@ -625,6 +668,8 @@ struct pvr_plan {
   double *d_theta;           // [M][6]
   pvr::GeoD *d_geod;
   pvr::GeoF *d_geof;
+  pvr::AdjPatch<float> *d_adj;     // [M] block-gather constants
+  pvr::AdjPatch<double> *d_adj64;  // [M] the same for the FP64 calls
   float *d_invz;             // [N]
   double *d_invz64;          // [N] (workspaces with PVR_WS_F64)
   uint8_t *d_mask;           // [N]
@@ -637,13 +682,14 @@ struct pvr_plan {
   int *d_bin_off;            // [n_bricks + 1]
   int *d_bin_patch;          // [bin_cap]
   long long bin_cap;         // host bound on brick/patch pairs over all motions
-  int *d_sub_count;          // [8 n_bricks]
+  int *d_sub_count;          // [8 n_bricks]; block gather: 6 n_bricks (normal axis, half)
   int *d_sub_off;            // [8 n_bricks + 1]
   int *d_sub_patch;          // [sub_cap]
   long long sub_cap;         // host bound on sub-brick/patch pairs
   bool built, built64, index_valid;
+  bool index_blocks;         // the lists are those of the block gather (else 4^3 sub-bricks)
   // scratch
-  float2 *d_rq;              // [N + 2]: zero guard, N entries, zero guard
+  float2 *d_rq;              // [n_rq]: padded rows (RQ_PAD), the padding always zero
   double2 *d_rq64;           // [N + 2] likewise (workspaces with PVR_WS_F64)
   double *d_pstat;           // [M][10] per-patch EM partials
   float *d_pbar;             // [M] potentials when the caller passes none

@@ -18,6 +18,41 @@ using namespace pvr;
 
 static pvr_status make_tiles(pvr_plan *p, int tile_w, int tile_h);
 
+// Whether the adjoint gathers by blocks (k_gather_blocks): at least half
+// of the samples must lie in stacks whose unmoved patches are on its fast
+// path (make_adj) with room for a motion of ten degrees, i.e. pixels about as
+// wide as voxels and stack axes near the grid's; the other patches of such a
+// plan run its per-voxel walk, which costs what the per-voxel kernel costs.
+static bool use_blocks(const pvr_plan *p) {
+  if (p->max_hu > 1 || p->max_hv > 1) return false;
+  std::vector<char> ok(p->S);
+  const double sk = sqrt(KAPPA), K2 = KAPPA * p->k * p->k;
+  for (int s = 0; s < p->S; ++s) {
+    const StackDev &st = p->h_stack[s];
+    const ProbDev &pr = p->h_prob[st.problem];
+    double A[9], W[9], H[9], G[9], t[3];
+    aff_split(st.p2w, A, t);
+    aff_split(pr.w2v, W, t);
+    mat3_mul(W, A, H);
+    mat3_inv(H, G);
+    int an = 0;
+    for (int c = 1; c < 3; ++c) if (fabs(G[6 + c]) > fabs(G[6 + an])) an = c;
+    const int a0 = an == 0 ? 1 : 0, a1 = 3 - an - a0;
+    const int au = fabs(G[a0]) >= fabs(G[a1]) ? a0 : a1, av = a0 + a1 - au;
+    const bool sinc = p->psf == PVR_PSF_SINC;
+    const double cu = sinc ? st.spacing[0] / st.wz[0] : sk * st.spacing[0] / st.sigma[0];
+    const double cv = sinc ? st.spacing[1] / st.wz[1] : sk * st.spacing[1] / st.sigma[1];
+    const double reach = sinc ? 1.0 : sqrt(K2);
+    const double Du = 0.5 * (fabs(fabs(G[au]) - 1) + fabs(G[av]));
+    const double Dv = 0.5 * (fabs(fabs(G[3 + av]) - 1) + fabs(G[3 + au]));
+    ok[s] = reach / cu + Du < 1.4 && reach / cv + Dv < 1.4 && (sinc || (cu <= 2.5 && cv <= 2.5));
+  }
+  long long in = 0;
+  for (int s = 0; s < p->M; ++s)
+    if (ok[p->h_patch[s].stack]) in += (long long)p->h_patch[s].w * p->h_patch[s].h;
+  return 2 * in >= p->N;
+}
+
 // Largest capacity of an adjoint index list (its offsets are int32).
 constexpr long long INDEX_CAP_MAX = 0x7ffffff0LL;
 
@@ -85,7 +120,9 @@ __global__ void k_copy_theta(const double *__restrict__ th, double *__restrict__
 __global__ void k_geometry(const ProbDev *__restrict__ probs, const StackDev *__restrict__ stacks,
                            const PatchDev *__restrict__ patches, const double *__restrict__ theta,
                            int M, double k, int psf, GeoD *__restrict__ gd, GeoF *__restrict__ gf,
-                           int *__restrict__ bb, double *__restrict__ sbox) {
+                           AdjPatch<float> *__restrict__ adj, AdjPatch<double> *__restrict__ adj64,
+                           int *__restrict__ bb,
+                           double *__restrict__ sbox) {
   int s = blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= M) return;
   const PatchDev pt = patches[s];
@@ -98,6 +135,14 @@ __global__ void k_geometry(const ProbDev *__restrict__ probs, const StackDev *__
     make_geometry<PVR_PSF_GAUSSIAN>(probs[pt.problem], st, pt, theta + 6 * s, k, g, f, bb + 6 * s);
   gd[s] = g;
   gf[s] = f;
+  AdjPatch<float> a;
+  make_adj(g, pt, a);
+  adj[s] = a;
+  if (adj64) {
+    AdjPatch<double> a64;
+    make_adj(g, pt, a64);
+    adj64[s] = a64;
+  }
   // voxel -> pixel map and the pixel-frame support box of the patch
   double *o = sbox + 18 * s;
   for (int q = 0; q < 12; ++q) o[q] = g.G[q];
@@ -255,6 +300,69 @@ k_sub_fill(const ProbDev *__restrict__ probs, const int *__restrict__ brick_prob
       if (h && pos < end[w]) slist[pos] = sp;
       c[w] += __popcll(bal);
     }
+  }
+}
+
+// The block gather's lists: per brick, normal axis and half of the brick
+// along it (list 6 bi + 2 axis + half), the patches of the brick's list with
+// that normal axis whose support box meets the half (8 x 8 x 4 voxels, one
+// wavefront of the gather).
+__device__ __forceinline__ unsigned half_mask(const ProbDev &pr, int bi, int an,
+                                              const double *__restrict__ sb) {
+  const int local = bi - pr.brick_base;
+  const int b[3] = {local % pr.nbx, (local / pr.nbx) % pr.nby, local / (pr.nbx * pr.nby)};
+  unsigned m = 0;
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    double lo[3], hi[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      lo[a] = b[a] * BRICK + (a == an ? half * SUB : 0);
+      hi[a] = lo[a] + (a == an ? SUB : BRICK) - 1;
+    }
+    m |= box_meets_patch(sb, lo, hi) ? 1u << (2 * an + half) : 0u;
+  }
+  return m;
+}
+
+template <bool FILL>
+__global__ void __launch_bounds__(256)
+k_half_lists(const ProbDev *__restrict__ probs, const int *__restrict__ brick_prob,
+             const double *__restrict__ sbox, const AdjPatch<float> *__restrict__ adj, int nb,
+             const int *__restrict__ off, const int *__restrict__ list,
+             int *__restrict__ count, const int *__restrict__ soff, int *__restrict__ slist) {
+  const int lane = threadIdx.x & 63;
+  const int bi = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+  if (bi >= nb) return;  // uniform over the wavefront
+  const ProbDev pr = probs[brick_prob[bi]];
+  const unsigned long long below = (1ull << lane) - 1ull;
+  int c[6], end[6];
+#pragma unroll
+  for (int w = 0; w < 6; ++w) {
+    c[w] = FILL ? soff[bi * 6 + w] : 0;
+    end[w] = FILL ? soff[bi * 6 + w + 1] : 0;  // clamped to the capacity
+  }
+  for (int q0 = off[bi]; q0 < off[bi + 1]; q0 += 64) {
+    const int q = q0 + lane;
+    const bool ok = q < off[bi + 1];
+    const int sp = ok ? list[q] : 0;
+    const unsigned m = ok ? half_mask(pr, bi, adj_normal_axis(adj[sp].cls), sbox + 18 * sp) : 0u;
+#pragma unroll
+    for (int w = 0; w < 6; ++w) {
+      const bool h = (m >> w) & 1u;
+      const unsigned long long bal = __ballot(h);
+      if (FILL) {
+        const int pos = c[w] + __popcll(bal & below);
+        if (h && pos < end[w]) slist[pos] = sp;
+      }
+      c[w] += __popcll(bal);
+    }
+  }
+  if (!FILL && lane < 6) {
+    int v = c[0];
+#pragma unroll
+    for (int w = 1; w < 6; ++w) v = lane == w ? c[w] : v;
+    count[bi * 6 + lane] = v;
   }
 }
 
@@ -584,6 +692,8 @@ extern "C" pvr_status pvr_plan_create(const pvr_grid *grids, int32_t n_problems,
     PatchDev &d = p->h_patch[s];
     d.stack = q.stack; d.slice = q.slice; d.x0 = q.x0; d.y0 = q.y0; d.w = q.w; d.h = q.h;
     d.problem = prob; d.off = so;
+    d.rq_off = p->n_rq;
+    p->n_rq += rq_entries(q.w, q.h);
     {
       // rows of the patch run along the stack's u axis: when that is closer
       // to voxel y than to voxel x, the forward walks read the y-fastest copy
@@ -670,11 +780,14 @@ extern "C" pvr_status pvr_plan_create(const pvr_grid *grids, int32_t n_problems,
       const ProbDev &pr = p->h_prob[q.problem];
       const long long b = pair_bound(pr, p->h_stack[q.stack], q, cutoff_k, BRICK, pr.n_bricks);
       bins += b;
-      subs += std::min(8 * b, pair_bound(pr, p->h_stack[q.stack], q, cutoff_k, SUB, 8LL * pr.n_bricks));
+      // the 4^3 lists, or the block gather's (at most two halves of every brick)
+      subs += std::max(2 * b, std::min(8 * b, pair_bound(pr, p->h_stack[q.stack], q, cutoff_k, SUB,
+                                                         8LL * pr.n_bricks)));
     }
     p->bin_cap = std::min(bins, (long long)INDEX_CAP_MAX);
     p->sub_cap = std::min(subs, (long long)INDEX_CAP_MAX);
   }
+  p->gather_blocks = use_blocks(p);
   p->device = -1;  // the device of the first workspace
   guard.release();
   *out = p;
@@ -698,6 +811,8 @@ static size_t layout(pvr_plan *p, char *base, int flags) {
   p->d_theta = ws_take<double>(c, 6 * M);
   p->d_geod = ws_take<GeoD>(c, M);
   p->d_geof = ws_take<GeoF>(c, M);
+  p->d_adj = ws_take<AdjPatch<float>>(c, M);
+  p->d_adj64 = ws_take<AdjPatch<double>>(c, M);
   p->d_bb = ws_take<int>(c, 6 * M);
   p->d_gbox = ws_take<int>(c, 6 * ((M + 63) / 64));
   p->d_scan = ws_take<long long>(c, (8 * nb + 4095) / 4096 + 1);
@@ -711,9 +826,7 @@ static size_t layout(pvr_plan *p, char *base, int flags) {
   p->d_sub_count = ws_take<int>(c, 8 * nb);
   p->d_sub_off = ws_take<int>(c, 8 * nb + 1);
   p->d_sub_patch = ws_take<int>(c, p->sub_cap);
-  // one guard entry (zero) before and after the N entries: the adjoint's
-  // wide loads may pair a patch's first or last entry with its neighbour
-  p->d_rq = ws_take<float2>(c, N + 2);
+  p->d_rq = ws_take<float2>(c, p->n_rq);
   p->d_pstat = ws_take<double>(c, 10 * M);
   p->d_pbar = ws_take<float>(c, M);
   p->d_pval = ws_take<float>(c, M);
@@ -724,6 +837,8 @@ static size_t layout(pvr_plan *p, char *base, int flags) {
   p->d_status = ws_take<unsigned>(c, 1);
   p->d_dbg = ws_take<unsigned long long>(c, 1);
   p->d_invz64 = (flags & PVR_WS_F64) ? ws_take<double>(c, N) : nullptr;
+  // one guard entry (zero) before and after the N entries: the FP64 adjoint's
+  // candidates may reach one entry past a patch
   p->d_rq64 = (flags & PVR_WS_F64) ? ws_take<double2>(c, N + 2) : nullptr;
   return (c.off + 255) & ~(size_t)255;
 }
@@ -777,7 +892,7 @@ extern "C" pvr_status pvr_plan_attach(pvr_plan *p, void *workspace, size_t bytes
                          hipMemcpyHostToDevice, stream));
   HIP_TRY(hipMemcpyAsync(p->d_plane_prob, p->h_plane_prob, sizeof(int) * (p->n_planes + p->P),
                          hipMemcpyHostToDevice, stream));
-  launch_fill_f32((float *)p->d_rq, 0.f, 2 * (p->N + 2), stream);
+  launch_fill_f32((float *)p->d_rq, 0.f, 2 * p->n_rq, stream);
   if (p->d_rq64) launch_fill_f64((double *)p->d_rq64, 0.0, 2 * (p->N + 2), stream);
   launch_fill_i32((int *)p->d_status, 0, 1, stream);
   launch_fill_i32(p->d_total, 0, 4, stream);
@@ -886,6 +1001,7 @@ extern "C" pvr_status pvr_plan_set_psf(pvr_plan *p, int32_t kind) {
     p->max_hu = std::max(p->max_hu, hu);
     p->max_hv = std::max(p->max_hv, hv);
   }
+  p->gather_blocks = use_blocks(p);
   p->built = p->built64 = false;
   p->index_valid = false;
   p->stats_valid = false;
@@ -937,8 +1053,9 @@ extern "C" pvr_status pvr_plan_set_granules(pvr_plan *p, int32_t sim_granule,
 
 // brick -> patch and sub-brick -> patch lists of the gather adjoint for the
 // geometry of the last build, into lists of the capacities bounded at plan
-// creation: no count is read back, nothing is synchronised.
-pvr_status pvr::plan_build_index(pvr_plan *p, hipStream_t stream) {
+// creation: no count is read back, nothing is synchronised.  blocks: the
+// second level lists are those of the block gather.
+pvr_status pvr::plan_build_index(pvr_plan *p, bool blocks, hipStream_t stream) {
   const int nb = p->n_bricks;
   const int nbw = (nb + BIN_THREADS / 64 - 1) / (BIN_THREADS / 64);
   hipLaunchKernelGGL(k_group_box, dim3((p->M + 255) / 256), dim3(256), 0, stream, p->d_bb, p->M,
@@ -953,17 +1070,29 @@ pvr_status pvr::plan_build_index(pvr_plan *p, hipStream_t stream) {
                      p->d_brick_prob, p->d_bb, p->d_gbox, p->d_sbox, nb, p->d_bin_off,
                      p->d_bin_patch);
   HIP_TRY(hipGetLastError());
-  const int nsb = nb * 8;
-  hipLaunchKernelGGL(k_sub_count, dim3((nb + 3) / 4), dim3(256), 0, stream, p->d_prob,
-                     p->d_brick_prob, p->d_sbox, nb, p->d_bin_off, p->d_bin_patch, p->d_sub_count);
+  const int nsb = nb * (blocks ? 6 : 8);
+  if (blocks)
+    hipLaunchKernelGGL(k_half_lists<false>, dim3((nb + 3) / 4), dim3(256), 0, stream, p->d_prob,
+                       p->d_brick_prob, p->d_sbox, p->d_adj, nb, p->d_bin_off, p->d_bin_patch,
+                       p->d_sub_count, nullptr, nullptr);
+  else
+    hipLaunchKernelGGL(k_sub_count, dim3((nb + 3) / 4), dim3(256), 0, stream, p->d_prob,
+                       p->d_brick_prob, p->d_sbox, nb, p->d_bin_off, p->d_bin_patch,
+                       p->d_sub_count);
   HIP_TRY(hipGetLastError());
   PVR_TRY_STATUS(launch_scan(p->d_sub_count, nsb, p->d_scan, p->d_sub_off, p->d_total + 1,
                              p->sub_cap, p->d_status, stream));
-  hipLaunchKernelGGL(k_sub_fill, dim3((nb + 3) / 4), dim3(256), 0, stream, p->d_prob,
-                     p->d_brick_prob, p->d_sbox, nb, p->d_bin_off, p->d_bin_patch, p->d_sub_off,
-                     p->d_sub_patch);
+  if (blocks)
+    hipLaunchKernelGGL(k_half_lists<true>, dim3((nb + 3) / 4), dim3(256), 0, stream, p->d_prob,
+                       p->d_brick_prob, p->d_sbox, p->d_adj, nb, p->d_bin_off, p->d_bin_patch,
+                       nullptr, p->d_sub_off, p->d_sub_patch);
+  else
+    hipLaunchKernelGGL(k_sub_fill, dim3((nb + 3) / 4), dim3(256), 0, stream, p->d_prob,
+                       p->d_brick_prob, p->d_sbox, nb, p->d_bin_off, p->d_bin_patch, p->d_sub_off,
+                       p->d_sub_patch);
   HIP_TRY(hipGetLastError());
   p->index_valid = true;
+  p->index_blocks = blocks;
   ++p->generation;
   return PVR_OK;
 }
@@ -983,8 +1112,8 @@ static pvr_status plan_build_common(pvr_plan *p, const uint8_t *active, const ui
     launch_fill_u8(p->d_mask, 1, p->N, stream);
   }
   hipLaunchKernelGGL(k_geometry, dim3((M + T - 1) / T), dim3(T), 0, stream, p->d_prob, p->d_stack,
-                     p->d_patch, p->d_theta, M, p->k, p->psf, p->d_geod, p->d_geof, p->d_bb,
-                     p->d_sbox);
+                     p->d_patch, p->d_theta, M, p->k, p->psf, p->d_geod, p->d_geof, p->d_adj,
+                     f64 && p->d_invz64 ? p->d_adj64 : nullptr, p->d_bb, p->d_sbox);
   HIP_TRY(hipGetLastError());
   // an FP64 build also writes FP64 normalisers when the workspace has room
   // for them (PVR_WS_F64); the FP32 ones are written either way
