@@ -114,13 +114,13 @@ k_em_patch_stats(const PatchDev *__restrict__ patches, const float *__restrict__
 // per-chunk records (stride 5) over the problem's chunk range.
 __global__ void __launch_bounds__(EMP_T)
 k_em_problem(const ProbDev *__restrict__ probs, const double *__restrict__ pstat,
-             const double *__restrict__ chunk_stats, pvr_em_state *__restrict__ em, int init,
+             const double *__restrict__ chunk_stats, int planes, pvr_em_state *__restrict__ em, int init,
              unsigned *__restrict__ status) {
   __shared__ double lds[8 * (EMP_T / 64)];
   const ProbDev pr = probs[blockIdx.x];
   double mn = INFINITY, mx = -INFINITY, ym = 0, se2 = 0, cnt = 0;
-  const int r0 = chunk_stats ? pr.chunk_begin : pr.patch_begin;
-  const int r1 = chunk_stats ? pr.chunk_end : pr.patch_end;
+  const int r0 = chunk_stats ? (planes ? pr.pblk_begin : pr.chunk_begin) : pr.patch_begin;
+  const int r1 = chunk_stats ? (planes ? pr.pblk_end : pr.chunk_end) : pr.patch_end;
   for (int s = r0 + threadIdx.x; s < r1; s += EMP_T) {
     const double *o = chunk_stats ? chunk_stats + 5 * (long long)s : pstat + PSTAT * s;
     mn = fmin(mn, o[0]);
@@ -565,7 +565,8 @@ extern "C" pvr_status pvr_robust_weights(pvr_plan *p, const float *resid, const 
     HIP_TRY(hipGetLastError());
   }
   hipLaunchKernelGGL(k_em_problem, dim3(p->P), dim3(EMP_T), 0, stream, p->d_prob, p->d_pstat,
-                     fresh ? (const double *)p->d_chunk_stats : nullptr, em, init, p->d_status);
+                     fresh ? (const double *)p->d_chunk_stats : nullptr, p->stats_planes ? 1 : 0, em,
+                     init, p->d_status);
   HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(k_em_estep, dim3(p->M), dim3(EM_T), 0, stream, p->d_patch, p->d_invz, resid,
                      em, pp, pb, p->d_pstat);

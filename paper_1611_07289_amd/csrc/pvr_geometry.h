@@ -81,7 +81,7 @@ __host__ __device__ static inline void rot_zyx(const double *th, double *R) {
 // PSF: PVR_PSF_GAUSSIAN or PVR_PSF_SINC, a template parameter so that code
 // which only ever uses one PSF (registration) carries no code for the other.
 template <int PSF = PVR_PSF_GAUSSIAN>
-__device__ inline void make_geometry(const ProbDev &pr, const StackDev &st, const PatchDev &pt,
+__host__ __device__ inline void make_geometry(const ProbDev &pr, const StackDev &st, const PatchDev &pt,
                               const double *th, double k, GeoD &g, GeoF &gf, int *bb) {
   constexpr int psf = PSF;
   double R[9];
@@ -229,7 +229,7 @@ __device__ inline void make_geometry(const ProbDev &pr, const StackDev &st, cons
 // too, so that the exponents of the shared factors stay small and their FP32
 // rounding at the size of the per-voxel form's.
 template <typename T>
-__device__ inline void make_adj(const GeoD &g, const PatchDev &pt, AdjPatch<T> &o) {
+__host__ __device__ inline void make_adj(const GeoD &g, const PatchDev &pt, AdjPatch<T> &o) {
   const double *U = g.G, *V = g.G + 4, *N = g.G + 8;
   int an = 0;
   if (fabs(N[1]) > fabs(N[an])) an = 1;

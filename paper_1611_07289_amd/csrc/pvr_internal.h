@@ -37,6 +37,7 @@ struct ProbDev {
   int brick_base, n_bricks;
   int patch_begin, patch_end;
   int chunk_begin, chunk_end;   // forward work chunks (BlockWork) of the problem
+  int pblk_begin, pblk_end;     // plane-walk work (BlockWork) of the problem
   long long vol_off;
   long long sample_begin, sample_end;
   double v2w[12];
@@ -141,10 +142,27 @@ template <typename T> struct GeoOf;
 template <> struct GeoOf<float> { using type = GeoF; };
 template <> struct GeoOf<double> { using type = GeoD; };
 
+// Constants of one patch for the plane walk (pvr_planes.h).
+template <typename T>
+struct FwdPatch {
+  double Ha[3], Hb[3], Hc[3];  // (u, v, 1) -> block centre along a, b, c (voxels)
+  double ta, tb;               // slope of the conditional in-plane centre
+  T fta, ftb;
+  T Aaa, Aab2, Abb, Scc, cut;  // A_ab doubled
+  T ga11, ga10, gb11, gb10, D11, D10, e11, e10;
+  T ka11, ia11, ka10, ia10, kb11, ib11, kb10, ib10;
+  T xm, xp;
+  int rows;                    // window rows per sample: 3 or 4; 0: not this walk
+  int half;                    // planes on either side of the middle one
+  int st_a, st_b, st_c, na, nb, nc;
+  int flip;                    // bit 0 / 1: u / v run against a / b
+};
+
 struct BlockWork {   // one forward workgroup: a chunk of one patch
   int patch;
-  int l0;            // first local sample
+  int l0;            // first local sample (plane walk: first 2 x 2 pixel block)
 };
+constexpr int PLANE_BLOCKS = 256;  // pixel blocks per plane-walk workgroup, one per lane
 
 // Workgroups are dealt to the 8 XCDs round-robin by block index, and every
 // XCD has its own L2.  xcd_work regroups the work list into granules of g
@@ -201,7 +219,7 @@ template <> __device__ __forceinline__ double fast_exp2<double>(double x) {
   return exp2(x);
 }
 
-__device__ __forceinline__ int sel3(int i, int a0, int a1, int a2) {
+__host__ __device__ __forceinline__ int sel3(int i, int a0, int a1, int a2) {
   return i == 0 ? a0 : (i == 1 ? a1 : a2);
 }
 template <typename T>
@@ -626,6 +644,7 @@ struct pvr_plan {
   int P, S, M;
   int max_problem_patches;
   int max_hu, max_hv;         // adjoint candidate half-widths over all stacks
+  bool planes, planes64;      // FP32 / FP64 forward passes by the plane walk (pvr_planes.h)
   bool gather_blocks;         // adjoint by blocks of 2 x 2 voxels per lane (k_gather_blocks)
   long long n_rq;             // entries of the padded FP32 adjoint inputs
   long long N, V;
@@ -642,6 +661,8 @@ struct pvr_plan {
   int *h_plane_prob;         // [n_planes + P]
   int *h_tile_off;           // [M+1] tiles before each patch (current tile shape)
   int n_sim_blocks;
+  pvr::BlockWork *h_pblocks;     // [n_pblocks] plane-walk work
+  int n_pblocks;
   // caller's device workspace (pvr_plan_attach); every d_ pointer below lies
   // inside it.  The plan allocates no device memory.
   void *ws;
@@ -653,6 +674,7 @@ struct pvr_plan {
   pvr::StackDev *d_stack;
   pvr::PatchDev *d_patch;
   pvr::BlockWork *d_sim_blocks;
+  pvr::BlockWork *d_pblocks;
   int *d_tile_off;           // [M+1]
   int n_tiles, tile_w, tile_h;
   int sim_granule, bp_granule;  // XCD granules of the forward work and the adjoint bricks
@@ -694,12 +716,15 @@ struct pvr_plan {
   double *d_pstat;           // [M][10] per-patch EM partials
   float *d_pbar;             // [M] potentials when the caller passes none
   float *d_pval;             // [M] classification scratch (problems beyond the LDS copy)
-  double *d_chunk_stats;     // [n_sim_blocks][5] residual statistics of the last simulate
+  pvr::FwdPatch<float> *d_fwd;     // [M] plane-walk constants
+  pvr::FwdPatch<double> *d_fwd64;  // [M] the same for the FP64 calls
+  double *d_chunk_stats;     // [max(n_sim_blocks, n_pblocks)][5] residual statistics of the last
+                             // simulate, per work item of the list it ran
   float *d_xt;               // [V] y-fastest copy of the volume (plans with layout-1 patches)
   bool any_xt;
   int psf;                   // PVR_PSF_GAUSSIAN (default) or PVR_PSF_SINC
   const void *stats_resid, *stats_y;  // ... and the buffers they describe
-  bool stats_valid;
+  bool stats_valid, stats_planes;  // ... and whether the list was the plane walk's
   // adjoint inputs prepared by pvr_robust_weights (PVR_EM_PREP_ADJOINT) for
   // these residual / posterior buffers, on a second stream beside the
   // patch classification

@@ -13,44 +13,52 @@
 #include "pvr_internal.h"
 #include "pvr_util.h"
 #include "pvr_geometry.h"
+#include "pvr_planes.h"
 
 using namespace pvr;
 
 static pvr_status make_tiles(pvr_plan *p, int tile_w, int tile_h);
 
-// Whether the adjoint gathers by blocks (k_gather_blocks): at least half
-// of the samples must lie in stacks whose unmoved patches are on its fast
-// path (make_adj) with room for a motion of ten degrees, i.e. pixels about as
-// wide as voxels and stack axes near the grid's; the other patches of such a
-// plan run its per-voxel walk, which costs what the per-voxel kernel costs.
-static bool use_blocks(const pvr_plan *p) {
-  if (p->max_hu > 1 || p->max_hv > 1) return false;
-  std::vector<char> ok(p->S);
-  const double sk = sqrt(KAPPA), K2 = KAPPA * p->k * p->k;
-  for (int s = 0; s < p->S; ++s) {
-    const StackDev &st = p->h_stack[s];
-    const ProbDev &pr = p->h_prob[st.problem];
-    double A[9], W[9], H[9], G[9], t[3];
-    aff_split(st.p2w, A, t);
-    aff_split(pr.w2v, W, t);
-    mat3_mul(W, A, H);
-    mat3_inv(H, G);
-    int an = 0;
-    for (int c = 1; c < 3; ++c) if (fabs(G[6 + c]) > fabs(G[6 + an])) an = c;
-    const int a0 = an == 0 ? 1 : 0, a1 = 3 - an - a0;
-    const int au = fabs(G[a0]) >= fabs(G[a1]) ? a0 : a1, av = a0 + a1 - au;
-    const bool sinc = p->psf == PVR_PSF_SINC;
-    const double cu = sinc ? st.spacing[0] / st.wz[0] : sk * st.spacing[0] / st.sigma[0];
-    const double cv = sinc ? st.spacing[1] / st.wz[1] : sk * st.spacing[1] / st.sigma[1];
-    const double reach = sinc ? 1.0 : sqrt(K2);
-    const double Du = 0.5 * (fabs(fabs(G[au]) - 1) + fabs(G[av]));
-    const double Dv = 0.5 * (fabs(fabs(G[3 + av]) - 1) + fabs(G[3 + au]));
-    ok[s] = reach / cu + Du < 1.4 && reach / cv + Dv < 1.4 && (sinc || (cu <= 2.5 && cv <= 2.5));
+// Which walks the plan uses, from every stack's first patch at rest: the block
+// gather (make_adj) and the plane walks (make_fwd) where at least half of the
+// samples lie in stacks on their fast path, i.e. pixels about as wide as voxels
+// and the PSF about as wide as a pixel; the patches of such a plan that leave
+// it (a large tilt) run the per-voxel or per-sample walk inside the same
+// kernels at what it costs in its own.
+static void choose_walks(pvr_plan *p) {
+  std::vector<char> adj(p->S, 0), fwd(p->S, 0), fwd64(p->S, 0), seen(p->S, 0);
+  long long n_adj = 0, n_fwd = 0, n_fwd64 = 0;
+  for (int s = 0; s < p->M; ++s) {
+    const PatchDev &q = p->h_patch[s];
+    const int t = q.stack;
+    if (!seen[t]) {
+      seen[t] = 1;
+      const double th[6] = {0, 0, 0, 0, 0, 0};
+      GeoD g;
+      GeoF f;
+      int bb[6];
+      if (p->psf == PVR_PSF_SINC)
+        make_geometry<PVR_PSF_SINC>(p->h_prob[q.problem], p->h_stack[t], q, th, p->k, g, f, bb);
+      else
+        make_geometry<PVR_PSF_GAUSSIAN>(p->h_prob[q.problem], p->h_stack[t], q, th, p->k, g, f, bb);
+      AdjPatch<float> a;
+      FwdPatch<float> w;
+      FwdPatch<double> w64;
+      make_adj(g, q, a);
+      make_fwd(g, p->h_prob[q.problem], q, w);
+      make_fwd(g, p->h_prob[q.problem], q, w64);
+      adj[t] = (a.cls & ADJ_FAST) != 0;
+      fwd[t] = w.rows != 0;
+      fwd64[t] = w64.rows != 0;
+    }
+    const long long n = (long long)q.w * q.h;
+    n_adj += adj[t] ? n : 0;
+    n_fwd += fwd[t] ? n : 0;
+    n_fwd64 += fwd64[t] ? n : 0;
   }
-  long long in = 0;
-  for (int s = 0; s < p->M; ++s)
-    if (ok[p->h_patch[s].stack]) in += (long long)p->h_patch[s].w * p->h_patch[s].h;
-  return 2 * in >= p->N;
+  p->gather_blocks = p->max_hu <= 1 && p->max_hv <= 1 && 2 * n_adj >= p->N;
+  p->planes = 2 * n_fwd >= p->N;
+  p->planes64 = 2 * n_fwd64 >= p->N;
 }
 
 // Largest capacity of an adjoint index list (its offsets are int32).
@@ -117,10 +125,12 @@ __global__ void k_copy_theta(const double *__restrict__ th, double *__restrict__
   if (i < n) out[i] = th[i];
 }
 
-__global__ void k_geometry(const ProbDev *__restrict__ probs, const StackDev *__restrict__ stacks,
+__global__ void __launch_bounds__(64)
+k_geometry(const ProbDev *__restrict__ probs, const StackDev *__restrict__ stacks,
                            const PatchDev *__restrict__ patches, const double *__restrict__ theta,
                            int M, double k, int psf, GeoD *__restrict__ gd, GeoF *__restrict__ gf,
                            AdjPatch<float> *__restrict__ adj, AdjPatch<double> *__restrict__ adj64,
+                           FwdPatch<float> *__restrict__ fwd, FwdPatch<double> *__restrict__ fwd64,
                            int *__restrict__ bb,
                            double *__restrict__ sbox) {
   int s = blockIdx.x * blockDim.x + threadIdx.x;
@@ -138,10 +148,12 @@ __global__ void k_geometry(const ProbDev *__restrict__ probs, const StackDev *__
   AdjPatch<float> a;
   make_adj(g, pt, a);
   adj[s] = a;
+  make_fwd(g, probs[pt.problem], pt, fwd[s]);
   if (adj64) {
     AdjPatch<double> a64;
     make_adj(g, pt, a64);
     adj64[s] = a64;
+    make_fwd(g, probs[pt.problem], pt, fwd64[s]);
   }
   // voxel -> pixel map and the pixel-frame support box of the patch
   double *o = sbox + 18 * s;
@@ -184,6 +196,78 @@ k_normalisers(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ pa
     }
     ok = ok && z > (T)0;
     const T iz = ok ? (T)1 / z : (T)0;
+    invz[j] = (float)iz;
+    if (invz64) invz64[j] = (double)iz;
+  }
+}
+
+// The same by the plane walk: one lane per 2 x 2 pixel block.  Bound by vector
+// issue: 10.5 M samples of a 160^3 plan take 198 us one sample per lane, 167 us here
+// (1.8 M at 96^3: 45 and 37 us).
+template <typename T>
+__global__ void __launch_bounds__(PLANE_BLOCKS)
+k_normalisers_planes(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ patches,
+                     const BlockWork *__restrict__ work,
+                     const typename GeoOf<T>::type *__restrict__ geo,
+                     const FwdPatch<T> *__restrict__ fwd, const uint8_t *__restrict__ mask,
+                     const uint8_t *__restrict__ active, float *__restrict__ invz,
+                     double *__restrict__ invz64) {
+  const BlockWork wk = work[blockIdx.x];
+  const PatchDev pt = patches[wk.patch];
+  const ProbDev pr = probs[pt.problem];
+  const typename GeoOf<T>::type &g = geo[wk.patch];
+  const FwdPatch<T> &fw = fwd[wk.patch];
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  const PlaneLane pl = plane_lane(pt, wk.l0);
+  const int nbu = (pt.w + 1) / 2;
+  const int u0 = 2 * (pl.blk % nbu), v0 = 2 * (pl.blk / nbu);
+  const bool act = active ? active[wk.patch] != 0 : true;
+  bool ok[4];  // pixel (u0 + i, v0 + j) at 2 j + i
+  T z[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int u = u0 + (t & 1), v = v0 + (t >> 1);
+    int b[3];
+    T f[3];
+    ok[t] = pl.on && u < pt.w && v < pt.h && act &&
+            sample_centre(g, pr, pt.x0 + u, pt.y0 + v, pt.slice, b, f) &&
+            (!mask || mask[pt.off + (long long)v * pt.w + u]);
+    z[t] = 0;
+  }
+  const bool live = ok[0] || ok[1] || ok[2] || ok[3];
+  const __amdgpu_buffer_rsrc_t none = raw_buffer((const T *)nullptr, 0u);
+  if (fw.rows) {
+    T zw[4] = {0, 0, 0, 0};  // by sub-window
+    if (__any(live)) {
+      if (fw.rows == 3) plane_walk<T, 3, false, true>(fw, u0, v0, live, pl.part, pl.parts, none, 0u, nullptr, zw);
+      else plane_walk<T, 4, false, true>(fw, u0, v0, live, pl.part, pl.parts, none, 0u, nullptr, zw);
+    }
+    combine_parts(pl, zw, reinterpret_cast<T(*)[4]>(lds));
+    const bool fu = fw.flip & 1, fv = fw.flip & 2;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const T a = fu ? zw[t ^ 1] : zw[t], b = fu ? zw[t ^ 3] : zw[t ^ 2];
+      z[t] = fv ? b : a;
+    }
+  } else if (pl.part == 0) {
+#pragma unroll 1
+    for (int t = 0; t < 4; ++t) {
+      if (!(t == 0 ? ok[0] : t == 1 ? ok[1] : t == 2 ? ok[2] : ok[3])) continue;
+      int b[3];
+      T f[3], zs = 0, acc = 0;
+      sample_centre(g, pr, pt.x0 + u0 + (t & 1), pt.y0 + v0 + (t >> 1), pt.slice, b, f);
+      psf_walk<T, typename GeoOf<T>::type, false>(g, pr, b, f, nullptr, zs, acc);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) z[k] = k == t ? zs : z[k];
+    }
+  }
+  if (pl.part != 0 || !pl.on) return;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int u = u0 + (t & 1), v = v0 + (t >> 1);
+    if (u >= pt.w || v >= pt.h) continue;
+    const T iz = ok[t] && z[t] > (T)0 ? (T)1 / z[t] : (T)0;
+    const long long j = pt.off + (long long)v * pt.w + u;
     invz[j] = (float)iz;
     if (invz64) invz64[j] = (double)iz;
   }
@@ -676,7 +760,7 @@ extern "C" pvr_status pvr_plan_create(const pvr_grid *grids, int32_t n_problems,
   // patches: grouped by problem in problem order, each inside its slice
   long long so = 0;
   int prev_prob = 0;
-  std::vector<BlockWork> blocks;
+  std::vector<BlockWork> blocks, pblocks;
   std::vector<int> pcount(n_problems, 0);
   std::vector<long long> scount(n_problems, 0);
   for (int s = 0; s < n_patches; ++s) {
@@ -706,6 +790,8 @@ extern "C" pvr_status pvr_plan_create(const pvr_grid *grids, int32_t n_problems,
     p->h_sample_off[s] = so;
     const int n = q.w * q.h;
     for (int l0 = 0; l0 < n; l0 += SIM_CHUNK) blocks.push_back(BlockWork{s, l0});
+    const int nblk = ((q.w + 1) / 2) * ((q.h + 1) / 2);
+    for (int l0 = 0; l0 < nblk; l0 += PLANE_BLOCKS) pblocks.push_back(BlockWork{s, l0});
     so += n;
     pcount[prob] += 1;
     scount[prob] += n;
@@ -733,11 +819,18 @@ extern "C" pvr_status pvr_plan_create(const pvr_grid *grids, int32_t n_problems,
       while (c < (int)blocks.size() && blocks[c].patch < p->h_prob[b].patch_end) ++c;
       p->h_prob[b].chunk_end = c;
     }
+    c = 0;
+    for (int b = 0; b < n_problems; ++b) {
+      p->h_prob[b].pblk_begin = c;
+      while (c < (int)pblocks.size() && pblocks[c].patch < p->h_prob[b].patch_end) ++c;
+      p->h_prob[b].pblk_end = c;
+    }
   }
   p->h_sample_off[n_patches] = so;
   p->N = so;
   if (so > 0x7fffffffLL * 4) return fail(PVR_ESHAPE, "pvr_plan_create: too many samples");
   p->n_sim_blocks = (int)blocks.size();
+  p->n_pblocks = (int)pblocks.size();
   for (int s = 0; s < n_patches; ++s)
     if (patches[s].w > 32767 || patches[s].h > 32767 ||
         (long long)patches[s].w * patches[s].h > (1LL << 26))
@@ -771,6 +864,8 @@ extern "C" pvr_status pvr_plan_create(const pvr_grid *grids, int32_t n_problems,
     for (int i = 0; i < p->h_prob[b].n_bricks; ++i) p->h_brick_prob[p->h_prob[b].brick_base + i] = b;
   p->h_sim_blocks = (BlockWork *)malloc(sizeof(BlockWork) * std::max<size_t>(blocks.size(), 1));
   std::copy(blocks.begin(), blocks.end(), p->h_sim_blocks);
+  p->h_pblocks = (BlockWork *)malloc(sizeof(BlockWork) * std::max<size_t>(pblocks.size(), 1));
+  std::copy(pblocks.begin(), pblocks.end(), p->h_pblocks);
   // capacity of the adjoint's index: bounds over every motion, so that no
   // build needs to read a count back or to grow a list
   {
@@ -787,7 +882,7 @@ extern "C" pvr_status pvr_plan_create(const pvr_grid *grids, int32_t n_problems,
     p->bin_cap = std::min(bins, (long long)INDEX_CAP_MAX);
     p->sub_cap = std::min(subs, (long long)INDEX_CAP_MAX);
   }
-  p->gather_blocks = use_blocks(p);
+  choose_walks(p);
   p->device = -1;  // the device of the first workspace
   guard.release();
   *out = p;
@@ -804,6 +899,7 @@ static size_t layout(pvr_plan *p, char *base, int flags) {
   p->d_stack = ws_take<StackDev>(c, p->S);
   p->d_patch = ws_take<PatchDev>(c, M);
   p->d_sim_blocks = ws_take<BlockWork>(c, p->n_sim_blocks);
+  p->d_pblocks = ws_take<BlockWork>(c, p->n_pblocks);
   p->d_tile_off = ws_take<int>(c, M + 1);
   p->d_box_max = ws_take<int>(c, 4);
   p->d_brick_prob = ws_take<int>(c, nb);
@@ -813,6 +909,8 @@ static size_t layout(pvr_plan *p, char *base, int flags) {
   p->d_geof = ws_take<GeoF>(c, M);
   p->d_adj = ws_take<AdjPatch<float>>(c, M);
   p->d_adj64 = ws_take<AdjPatch<double>>(c, M);
+  p->d_fwd = ws_take<FwdPatch<float>>(c, M);
+  p->d_fwd64 = ws_take<FwdPatch<double>>(c, M);
   p->d_bb = ws_take<int>(c, 6 * M);
   p->d_gbox = ws_take<int>(c, 6 * ((M + 63) / 64));
   p->d_scan = ws_take<long long>(c, (8 * nb + 4095) / 4096 + 1);
@@ -830,7 +928,7 @@ static size_t layout(pvr_plan *p, char *base, int flags) {
   p->d_pstat = ws_take<double>(c, 10 * M);
   p->d_pbar = ws_take<float>(c, M);
   p->d_pval = ws_take<float>(c, M);
-  p->d_chunk_stats = ws_take<double>(c, 5LL * p->n_sim_blocks);
+  p->d_chunk_stats = ws_take<double>(c, 5LL * std::max(p->n_sim_blocks, p->n_pblocks));
   p->d_xt = p->any_xt ? ws_take<float>(c, p->V) : nullptr;
   p->d_total = ws_take<int>(c, 4);
   p->d_reg_stats = ws_take<unsigned long long>(c, 4);
@@ -886,6 +984,8 @@ extern "C" pvr_status pvr_plan_attach(pvr_plan *p, void *workspace, size_t bytes
   HIP_TRY(hipMemcpyAsync(p->d_stack, p->h_stack, sizeof(StackDev) * p->S, hipMemcpyHostToDevice, stream));
   HIP_TRY(hipMemcpyAsync(p->d_patch, p->h_patch, sizeof(PatchDev) * M, hipMemcpyHostToDevice, stream));
   HIP_TRY(hipMemcpyAsync(p->d_sim_blocks, p->h_sim_blocks, sizeof(BlockWork) * p->n_sim_blocks,
+                         hipMemcpyHostToDevice, stream));
+  HIP_TRY(hipMemcpyAsync(p->d_pblocks, p->h_pblocks, sizeof(BlockWork) * p->n_pblocks,
                          hipMemcpyHostToDevice, stream));
   HIP_TRY(hipMemcpyAsync(p->d_tile_off, p->h_tile_off, sizeof(int) * (M + 1), hipMemcpyHostToDevice, stream));
   HIP_TRY(hipMemcpyAsync(p->d_brick_prob, p->h_brick_prob, sizeof(int) * p->n_bricks,
@@ -1001,7 +1101,7 @@ extern "C" pvr_status pvr_plan_set_psf(pvr_plan *p, int32_t kind) {
     p->max_hu = std::max(p->max_hu, hu);
     p->max_hv = std::max(p->max_hv, hv);
   }
-  p->gather_blocks = use_blocks(p);
+  choose_walks(p);
   p->built = p->built64 = false;
   p->index_valid = false;
   p->stats_valid = false;
@@ -1100,7 +1200,6 @@ pvr_status pvr::plan_build_index(pvr_plan *p, bool blocks, hipStream_t stream) {
 static pvr_status plan_build_common(pvr_plan *p, const uint8_t *active, const uint8_t *mask,
                                     bool f64, hipStream_t stream) {
   const int M = p->M;
-  const int T = 256;
   if (active) {
     HIP_TRY(hipMemcpyAsync(p->d_active, active, M, hipMemcpyDeviceToDevice, stream));
   } else {
@@ -1111,21 +1210,26 @@ static pvr_status plan_build_common(pvr_plan *p, const uint8_t *active, const ui
   } else {
     launch_fill_u8(p->d_mask, 1, p->N, stream);
   }
-  hipLaunchKernelGGL(k_geometry, dim3((M + T - 1) / T), dim3(T), 0, stream, p->d_prob, p->d_stack,
+  hipLaunchKernelGGL(k_geometry, dim3((M + 63) / 64), dim3(64), 0, stream, p->d_prob, p->d_stack,
                      p->d_patch, p->d_theta, M, p->k, p->psf, p->d_geod, p->d_geof, p->d_adj,
-                     f64 && p->d_invz64 ? p->d_adj64 : nullptr, p->d_bb, p->d_sbox);
+                     f64 && p->d_invz64 ? p->d_adj64 : nullptr, p->d_fwd, p->d_fwd64, p->d_bb, p->d_sbox);
   HIP_TRY(hipGetLastError());
   // an FP64 build also writes FP64 normalisers when the workspace has room
   // for them (PVR_WS_F64); the FP32 ones are written either way
-  if (f64 && p->d_invz64) {
-    hipLaunchKernelGGL(k_normalisers<double>, dim3(p->n_sim_blocks), dim3(SIM_THREADS), 0, stream,
-                       p->d_prob, p->d_patch, p->d_sim_blocks, p->d_geod, p->d_mask, p->d_active,
-                       p->d_invz, p->d_invz64);
-  } else {
-    hipLaunchKernelGGL(k_normalisers<float>, dim3(p->n_sim_blocks), dim3(SIM_THREADS), 0, stream,
-                       p->d_prob, p->d_patch, p->d_sim_blocks, p->d_geof, p->d_mask, p->d_active,
-                       p->d_invz, (double *)nullptr);
-  }
+  const bool wide = f64 && p->d_invz64;
+#define NORM_LAUNCH(T, GEO, FWD, OUT64)                                                            \
+  if (wide ? p->planes64 : p->planes)                                                              \
+    hipLaunchKernelGGL(k_normalisers_planes<T>, dim3(p->n_pblocks), dim3(PLANE_BLOCKS),              \
+                       PLANE_BLOCKS * 4 * sizeof(T), stream,                                       \
+                       p->d_prob, p->d_patch, p->d_pblocks, GEO, FWD, p->d_mask, p->d_active,      \
+                       p->d_invz, OUT64);                                                          \
+  else                                                                                             \
+    hipLaunchKernelGGL(k_normalisers<T>, dim3(p->n_sim_blocks), dim3(SIM_THREADS), 0, stream,      \
+                       p->d_prob, p->d_patch, p->d_sim_blocks, GEO, p->d_mask, p->d_active,        \
+                       p->d_invz, OUT64)
+  if (wide) { NORM_LAUNCH(double, p->d_geod, p->d_fwd64, p->d_invz64); }
+  else { NORM_LAUNCH(float, p->d_geof, p->d_fwd, (double *)nullptr); }
+#undef NORM_LAUNCH
   HIP_TRY(hipGetLastError());
   // forward-tile boxes (LDS size of the staged forward pass)
   if (p->use_tiles) {

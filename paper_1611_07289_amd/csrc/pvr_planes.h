@@ -1,0 +1,306 @@
+// Plane walk of the Gaussian PSF ("volume-pixel" direction): a lane takes the
+// 2 x 2 samples of one pixel block and walks the voxel planes across their
+// supports along the voxel axis c nearest the patch's normal; in a plane the
+// four samples share one window of voxels.
+//
+// With the quadratic form conditioned on c (t_a, t_b the slope of the
+// conditional centre, S_cc the Schur complement),
+//   Q = S_cc (c - x_c)^2 + q(a - p_a, b - p_b),  p = x + t (c - x_c),
+// q the 2 x 2 in-plane form.  Stepping one pixel along u moves the centre in a
+// plane by one voxel along a (the voxel axis u runs along, with sign su) plus
+// a small deviation, and v likewise along b: the sample of sub-window (i, j)
+// in {0, 1}^2 is centred at (r_a + i + f + d_a, r_b + j + h + d_b) with (r, f),
+// (r, h) the rounded block position and its fraction and d the sample's own
+// deviation (constants of the patch, antisymmetric about the block's centre).
+// Its weight at the voxel (alpha, beta) from its own nearest one is
+//   2^-Q = U_alpha V_beta kappa_a^alpha kappa_b^beta 2^(-2 A_ab alpha beta) S,
+// U and V exponentials of the lane shared by the four samples, kappa constants
+// of the sample, and S one exponential of the sample: 10 exponentials for 36
+// weights, no row bounds, and loads of whole window rows.  A patch takes this
+// walk when every voxel that can carry weight lies in the window (3 x 3 per
+// sample, or 3 x 4 for planes cut at a larger tilt): make_fwd.
+#pragma once
+
+#include "pvr_geometry.h"
+#include "pvr_internal.h"
+
+namespace pvr {
+
+// Constants of the walk; a, b, c as above, suffix 11 / 10: sub-window (1, 1) /
+// (1, 0), the opposite ones having the opposite sign (reciprocal factor).
+template <typename T>
+__host__ __device__ inline void make_fwd(const GeoD &g, const ProbDev &pr, const PatchDev &pt, FwdPatch<T> &o) {
+  o.rows = 0;
+  if (g.psf != PVR_PSF_GAUSSIAN) return;
+  int a = 0;
+  for (int r = 1; r < 3; ++r) if (fabs(g.H[4 * r]) > fabs(g.H[4 * a])) a = r;
+  const int b0 = a == 0 ? 1 : 0, b1 = 3 - a - b0;
+  const int b = fabs(g.H[4 * b0 + 1]) >= fabs(g.H[4 * b1 + 1]) ? b0 : b1, c = 3 - a - b;
+  const int ax[3] = {a, b, c};
+  double A[9];
+  const double w2[3] = {g.cu * g.cu, g.cv * g.cv, g.ck * g.ck};
+  for (int i = 0; i < 3; ++i)
+    for (int j = 0; j < 3; ++j)
+      A[3 * i + j] = w2[0] * g.G[ax[i]] * g.G[ax[j]] + w2[1] * g.G[4 + ax[i]] * g.G[4 + ax[j]] +
+                     w2[2] * g.G[8 + ax[i]] * g.G[8 + ax[j]];
+  const double Aaa = A[0], Aab = A[1], Aac = A[2], Abb = A[4], Abc = A[5], Acc = A[8];
+  const double idet = 1.0 / (Aaa * Abb - Aab * Aab);
+  const double ta = -(Abb * Aac - Aab * Abc) * idet, tb = -(Aaa * Abc - Aab * Aac) * idet;
+  const double Scc = Acc + ta * Aac + tb * Abc;
+  const double *Ha = g.H + 4 * a, *Hb = g.H + 4 * b, *Hc = g.H + 4 * c;
+  const double su = Ha[0] < 0 ? -1.0 : 1.0, sv = Hb[1] < 0 ? -1.0 : 1.0;
+  const double Au = su * (Ha[0] - ta * Hc[0]) - 1.0, Av = sv * (Ha[1] - ta * Hc[1]);
+  const double Bu = su * (Hb[0] - tb * Hc[0]), Bv = sv * (Hb[1] - tb * Hc[1]) - 1.0;
+  const double da11 = 0.5 * (Au + Av), da10 = 0.5 * (Au - Av);
+  const double db11 = 0.5 * (Bu + Bv), db10 = 0.5 * (Bu - Bv);
+  const double e11 = 0.5 * (su * Hc[0] + sv * Hc[1]), e10 = 0.5 * (su * Hc[0] - sv * Hc[1]);
+  const double Ra = sqrt(g.K2 * Abb * idet) + fmax(fabs(da11), fabs(da10));
+  const double Rb = sqrt(g.K2 * Aaa * idet) + fmax(fabs(db11), fabs(db10));
+  const double Rc = sqrt(g.K2 / Scc) + 0.5 + fmax(fabs(e11), fabs(e10));
+  // the voxels of a window row are read together: u must run along the fastest
+  // axis of the volume copy the patch reads (FP32; the FP64 walk reads voxel
+  // by voxel).  In-plane scales beyond 7 would make the shared exponentials'
+  // FP32 rounding larger than the per-voxel form's.  (All comparisons are
+  // false for a motion that is not finite.)
+  const bool xt = sizeof(T) == 4 && pt.layout == 1;
+  const bool ok = Ra < 1.5 - 1e-4 && Rb < 2.0 - 1e-4 && Rc < 32.0 && Aaa <= 7.0 && Abb <= 7.0 &&
+                  (sizeof(T) == 8 || a == (xt ? 1 : 0));
+  if (!ok) return;
+  o.rows = Rb < 1.5 - 1e-4 ? 3 : 4;
+  o.half = (int)floor(Rc + 1e-6);
+  for (int i = 0; i < 2; ++i) { o.Ha[i] = Ha[i]; o.Hb[i] = Hb[i]; o.Hc[i] = Hc[i]; }
+  // block centre: pixel (u, v) + 1/2 of the block's first pixel, patch-local
+  for (int r = 0; r < 3; ++r) {
+    const double *H = g.H + 4 * ax[r];
+    double *t = r == 0 ? o.Ha : r == 1 ? o.Hb : o.Hc;
+    t[2] = H[0] * (pt.x0 + 0.5) + H[1] * (pt.y0 + 0.5) + H[2] * pt.slice + H[3];
+  }
+  o.ta = ta; o.tb = tb;
+  o.fta = (T)ta; o.ftb = (T)tb;
+  o.Aaa = (T)Aaa; o.Aab2 = (T)(2 * Aab); o.Abb = (T)Abb; o.Scc = (T)Scc; o.cut = (T)g.cut;
+  const double ga11 = 2 * (Aaa * da11 + Aab * db11), gb11 = 2 * (Aab * da11 + Abb * db11);
+  const double ga10 = 2 * (Aaa * da10 + Aab * db10), gb10 = 2 * (Aab * da10 + Abb * db10);
+  o.ga11 = (T)ga11; o.ga10 = (T)ga10; o.gb11 = (T)gb11; o.gb10 = (T)gb10;
+  o.D11 = (T)(0.5 * (ga11 * da11 + gb11 * db11));
+  o.D10 = (T)(0.5 * (ga10 * da10 + gb10 * db10));
+  o.e11 = (T)e11; o.e10 = (T)e10;
+  o.ka11 = (T)exp2(ga11); o.ia11 = (T)exp2(-ga11); o.ka10 = (T)exp2(ga10); o.ia10 = (T)exp2(-ga10);
+  o.kb11 = (T)exp2(gb11); o.ib11 = (T)exp2(-gb11); o.kb10 = (T)exp2(gb10); o.ib10 = (T)exp2(-gb10);
+  o.xm = (T)exp2(-2 * Aab); o.xp = (T)exp2(2 * Aab);
+  const int sx = xt ? pr.ny : 1, sy = xt ? 1 : pr.nx, sz = pr.nx * pr.ny;
+  o.st_a = sel3(a, sx, sy, sz); o.st_b = sel3(b, sx, sy, sz); o.st_c = sel3(c, sx, sy, sz);
+  o.na = sel3(a, pr.nx, pr.ny, pr.nz); o.nb = sel3(b, pr.nx, pr.ny, pr.nz);
+  o.nc = sel3(c, pr.nx, pr.ny, pr.nz);
+  o.flip = (su < 0 ? 1 : 0) | (sv < 0 ? 2 : 0);
+}
+
+// The pixel block and the share of its planes of a thread: a work item's nb
+// blocks (at most PLANE_BLOCKS) take ceil(nb / 64) of the workgroup's four
+// wavefronts, and where two or four times as many fit, the others share the
+// planes of the same blocks (16-pixel patches at 32^3: 14.9 -> 10.5 us; larger
+// workgroups, to split the planes of larger patches too, gained nothing at
+// 32^3 and 48^3 and lost 8 % at 96^3).  Part 0 ends with the sums
+// (combine_parts).
+struct PlaneLane {
+  int blk, part, parts, span;
+  bool on;  // holds a block
+};
+__device__ __forceinline__ PlaneLane plane_lane(const PatchDev &pt, int l0) {
+  PlaneLane p;
+  const int nblk = ((pt.w + 1) / 2) * ((pt.h + 1) / 2);
+  const int nb = min(PLANE_BLOCKS, nblk - l0);
+  p.span = (nb + 63) & ~63;
+  p.parts = (int)blockDim.x / p.span;
+  const int thread = threadIdx.x;
+  p.part = __builtin_amdgcn_readfirstlane(thread / p.span);
+  const int i = thread - p.part * p.span;
+  p.blk = l0 + i;
+  p.on = i < nb && p.part < p.parts;
+  return p;
+}
+// Adds the parts' sums s[4] in part order into part 0's (all threads of the
+// workgroup call; lds: blockDim.x entries of 4 T).
+template <typename T>
+__device__ __forceinline__ void combine_parts(const PlaneLane &p, T s[4], T (*lds)[4]) {
+  if (p.parts == 1) return;  // uniform over the workgroup
+#pragma unroll
+  for (int t = 0; t < 4; ++t) lds[threadIdx.x][t] = s[t];
+  __syncthreads();
+  if (p.part == 0) {
+    for (int q = 1; q < p.parts; ++q)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) s[t] += lds[threadIdx.x + q * p.span][t];
+  }
+}
+
+// Nearest integer (ties to even) or floor of a float / double as a value.
+template <bool FLOOR> __device__ __forceinline__ float round_val(float x) {
+  return FLOOR ? __builtin_floorf(x) : __builtin_rintf(x);
+}
+template <bool FLOOR> __device__ __forceinline__ double round_val(double x) {
+  return FLOOR ? __builtin_floor(x) : __builtin_rint(x);
+}
+
+// The window rows: NB + 1 rows of four voxels from (ia, ib) in plane ic.
+// A voxel outside the grid reads 0 (inside: the whole window is in the grid).
+template <int NB>
+__device__ __forceinline__ void load_rows(const FwdPatch<float> &g, __amdgpu_buffer_rsrc_t xr,
+                                          unsigned nbytes, int ia, int ib, int ic, bool inside,
+                                          float x[NB + 1][4]) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  int off = (ic * g.st_c + ib * g.st_b + ia) * 4;
+  const int row = g.st_b * 4;
+  if (__all(inside)) {
+#pragma unroll
+    for (int r = 0; r <= NB; ++r) {
+      const f4 v = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0));
+      x[r][0] = v.x; x[r][1] = v.y; x[r][2] = v.z; x[r][3] = v.w;
+      off += row;
+    }
+  } else {
+    const bool pc = (unsigned)ic < (unsigned)g.nc;
+#pragma unroll
+    for (int r = 0; r <= NB; ++r) {
+      const bool pr = pc && (unsigned)(ib + r) < (unsigned)g.nb;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const bool in = pr && (unsigned)(ia + k) < (unsigned)g.na;
+        x[r][k] = load_vox<float>(xr, in ? (unsigned)(off + 4 * k) : nbytes);
+      }
+      off += row;
+    }
+  }
+}
+template <int NB>
+__device__ __forceinline__ void load_rows(const FwdPatch<double> &g, __amdgpu_buffer_rsrc_t xr,
+                                          unsigned nbytes, int ia, int ib, int ic, bool inside,
+                                          double x[NB + 1][4]) {
+  unsigned off = (unsigned)(ic * g.st_c + ib * g.st_b + ia * g.st_a) * 8u;
+  const bool pc = (unsigned)ic < (unsigned)g.nc;
+#pragma unroll
+  for (int r = 0; r <= NB; ++r) {
+    const bool pr = pc && (unsigned)(ib + r) < (unsigned)g.nb;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const bool in = inside || (pr && (unsigned)(ia + k) < (unsigned)g.na);
+      x[r][k] = load_vox<double>(xr, in ? off + (unsigned)(k * g.st_a) * 8u : nbytes);
+    }
+    off += (unsigned)g.st_b * 8u;
+  }
+}
+
+// The walk for the block whose first pixel is (u, v), patch-local: sums
+// g_hat X (HAS_X) and g_hat (HAS_Z) over in-grid voxels of the four samples,
+// sub-window (i, j) at 2 j + i.  live: the lane's sums are used (a wavefront
+// whose live lanes stay inside the grid skips the border handling).  The
+// planes part, part + parts, ... are taken (PlaneLane).
+template <typename T, int NB, bool HAS_X, bool HAS_Z>
+__device__ __forceinline__ void plane_walk(const FwdPatch<T> &g, int u, int v, bool live, int part,
+                                           int parts,
+                                           __amdgpu_buffer_rsrc_t xr, unsigned nbytes, T y[4], T z[4]) {
+  const double du = u, dv = v;
+  const double xa = fma(g.Ha[0], du, fma(g.Ha[1], dv, g.Ha[2]));
+  const double xb = fma(g.Hb[0], du, fma(g.Hb[1], dv, g.Hb[2]));
+  const double xc = fma(g.Hc[0], du, fma(g.Hc[1], dv, g.Hc[2]));
+  const double rc = __builtin_rint(xc), dc = rc - xc;
+  // block position in the middle plane, minus the half of sub-window (0, 0)
+  const double pa = fma(g.ta, dc, xa) - 0.5, pb = fma(g.tb, dc, xb) - 0.5;
+  const double ra = __builtin_rint(pa), rb = __builtin_rint(pb);
+  const T f0 = (T)(pa - ra), h0 = (T)(pb - rb), z0 = (T)dc;
+  const int ia0 = (int)ra - 1, ib0 = (int)rb - 1, ic0 = (int)rc;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    if (HAS_X) y[t] = (T)0;
+    if (HAS_Z) z[t] = (T)0;
+  }
+  const T ga[4] = {-g.ga11, g.ga10, -g.ga10, g.ga11}, gb[4] = {-g.gb11, g.gb10, -g.gb10, g.gb11};
+  const T D[4] = {g.D11, g.D10, g.D10, g.D11}, e[4] = {-g.e11, g.e10, -g.e10, g.e11};
+  const T ka[4] = {g.ia11, g.ka10, g.ia10, g.ka11}, ja[4] = {g.ka11, g.ia10, g.ka10, g.ia11};
+  const T kb[4] = {g.ib11, g.kb10, g.ib10, g.kb11}, jb[4] = {g.kb11, g.ib10, g.kb10, g.ib11};
+  const T cut = g.cut;
+#pragma unroll 1
+  for (int k = part - g.half; k <= g.half; k += parts) {
+    const T kk = (T)k;
+    const T qa = fma(kk, g.fta, f0), qb = fma(kk, g.ftb, h0);
+    const T sa = round_val<false>(qa), sb = round_val<NB == 4>(qb);
+    const T f = qa - sa, h = qb - sb, wz = z0 + kk;
+    const int ia = ia0 + (int)sa, ib = ib0 + (int)sb, ic = ic0 + k;
+    const bool inside = !live || ((unsigned)ic < (unsigned)g.nc && ia >= 0 && ia + 4 <= g.na &&
+                                  ib >= 0 && ib + NB + 1 <= g.nb);
+    T x[NB + 1][4];
+    if (HAS_X) load_rows<NB>(g, xr, nbytes, ia, ib, ic, inside, x);
+    // U_alpha, V_beta: exponents -A (alpha - f)^2 + 2 A_ab alpha h as sums of small terms
+    const T m = g.Aab2 * f * h;
+    const T ea = -g.Aaa * f * f, eb = -g.Abb * h * h;
+    const T sla = fma(g.Aab2, h, (T)2 * g.Aaa * f), slb = fma(g.Aab2, f, (T)2 * g.Abb * h);
+    T U[3], V[NB];
+    U[0] = fast_exp2<T>(ea - g.Aaa - sla);
+    U[1] = fast_exp2<T>(ea);
+    U[2] = fast_exp2<T>(ea - g.Aaa + sla);
+    V[0] = fast_exp2<T>(eb - g.Abb - slb);
+    V[1] = fast_exp2<T>(eb);
+    V[2] = fast_exp2<T>(eb - g.Abb + slb);
+    if constexpr (NB == 4) V[3] = fast_exp2<T>(fma((T)-4, g.Abb, fma((T)2, slb, eb)));
+    if (HAS_Z && !__all(inside)) {
+      // voxels outside the grid do not count: window columns and rows are
+      // masked per sample below through the factors of their own columns
+      const bool pc = (unsigned)ic < (unsigned)g.nc;
+      T ca[4], cb[NB + 1];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) ca[i] = (unsigned)(ia + i) < (unsigned)g.na ? (T)1 : (T)0;
+#pragma unroll
+      for (int j = 0; j <= NB; ++j) cb[j] = pc && (unsigned)(ib + j) < (unsigned)g.nb ? (T)1 : (T)0;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int i = t & 1, j = t >> 1;
+        const T w = wz - e[t];
+        const T S = fast_exp2<T>(-fma(g.Scc * w, w, fma(f, ga[t], fma(h, gb[t], D[t] + m))));
+        const T Um = U[0] * ja[t] * ca[i], Uc = U[1] * ca[i + 1], Up = U[2] * ka[t] * ca[i + 2];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+          T E = V[b] * S * cb[j + b];
+          if (b == 0) E *= jb[t];
+          if (b == 2) E *= kb[t];
+          if (b == 3) E *= kb[t] * kb[t];
+          const T Em = b == 0 ? E * g.xm : b == 1 ? E : b == 2 ? E * g.xp : E * g.xp * g.xp;
+          const T Ep = b == 0 ? E * g.xp : b == 1 ? E : b == 2 ? E * g.xm : E * g.xm * g.xm;
+          const T g0 = clamp01<T>(fma(Em, Um, -cut)), g1 = clamp01<T>(fma(E, Uc, -cut)),
+                  g2 = clamp01<T>(fma(Ep, Up, -cut));
+          z[t] += g0 + g1 + g2;
+          if (HAS_X) {
+            y[t] = fma(g0, x[j + b][i], y[t]);
+            y[t] = fma(g1, x[j + b][i + 1], y[t]);
+            y[t] = fma(g2, x[j + b][i + 2], y[t]);
+          }
+        }
+      }
+      continue;
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int i = t & 1, j = t >> 1;
+      const T w = wz - e[t];
+      const T S = fast_exp2<T>(-fma(g.Scc * w, w, fma(f, ga[t], fma(h, gb[t], D[t] + m))));
+      const T Um = U[0] * ja[t], Up = U[2] * ka[t];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        T E = V[b] * S;
+        if (b == 0) E *= jb[t];
+        if (b == 2) E *= kb[t];
+        if (b == 3) E *= kb[t] * kb[t];
+        const T Em = b == 0 ? E * g.xm : b == 1 ? E : b == 2 ? E * g.xp : E * (g.xp * g.xp);
+        const T Ep = b == 0 ? E * g.xp : b == 1 ? E : b == 2 ? E * g.xm : E * (g.xm * g.xm);
+        const T g0 = clamp01<T>(fma(Em, Um, -cut)), g1 = clamp01<T>(fma(E, U[1], -cut)),
+                g2 = clamp01<T>(fma(Ep, Up, -cut));
+        if (HAS_Z) z[t] += g0 + g1 + g2;
+        if (HAS_X) {
+          y[t] = fma(g0, x[j + b][i], y[t]);
+          y[t] = fma(g1, x[j + b][i + 1], y[t]);
+          y[t] = fma(g2, x[j + b][i + 2], y[t]);
+        }
+      }
+    }
+  }
+}
+
+}  // namespace pvr
