@@ -392,7 +392,7 @@ pvr_status pvr_sr_update(const pvr_plan *plan, const float *X,
                          const pvr_sr_params *params, float *X_out,
                          hipStream_t stream);
 
-/* Per-patch rigid registration (one workgroup per patch): maximise
+/* Per-patch rigid registration (every patch its own optimiser): maximise
  * NCC(y_s, A_s(theta) X) over the six parameters, where the simulated patch
  * uses the full PSF forward model and NCC runs over samples valid at theta.
  * Optimiser: variables (rho * angles, translations) with rho the patch
@@ -404,10 +404,9 @@ pvr_status pvr_sr_update(const pvr_plan *plan, const float *X,
  * trial steps.  Patches with std(y_s) < min_std keep theta.
  * theta [M][6] in/out; ncc [M] out (nullable); reg [M] (nullable = all):
  * only patches with reg != 0 move; params (host); sample_mask of the last
- * build applies.  With max_iter = 0 it only evaluates NCC at theta.  The
- * patches whose rows run closer to voxel y than to x are registered on the
- * plan's second stream, concurrently with the others; `stream` waits for
- * them before any later work. */
+ * build applies.  With max_iter = 0 it only evaluates NCC at theta.  Part of
+ * the work may run on the plan's second stream, concurrently with the rest;
+ * `stream` waits for it before any later work. */
 pvr_status pvr_register_patches(const pvr_plan *plan, const float *X,
                                 const float *y_obs, float *theta, float *ncc,
                                 const uint8_t *reg,

@@ -68,10 +68,36 @@ __host__ __device__ static inline int sinc_halfwidth(double c) {
   return (int)floor(1.0 / c + 0.5);
 }
 
+// Cosines and sines of the three rotation angles.
+struct Trig {
+  double c[3], s[3];
+};
+__host__ __device__ static inline Trig make_trig(const double *th) {
+  Trig t;
+  for (int i = 0; i < 3; ++i) {
+    t.c[i] = cos(th[i]);
+    t.s[i] = sin(th[i]);
+  }
+  return t;
+}
+// The same with one angle per lane (a wavefront's first three lanes).
+__device__ static inline Trig wave_trig(const double *th) {
+  const int lane = threadIdx.x & 63;
+  const double a = th[lane < 3 ? lane : 0];
+  const double c = cos(a), s = sin(a);
+  Trig t;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    t.c[i] = __shfl(c, i, 64);
+    t.s[i] = __shfl(s, i, 64);
+  }
+  return t;
+}
+
 // R = Rz(rz) Ry(ry) Rx(rx)
-__host__ __device__ static inline void rot_zyx(const double *th, double *R) {
-  double cx = cos(th[0]), sx = sin(th[0]), cy = cos(th[1]), sy = sin(th[1]);
-  double cz = cos(th[2]), sz = sin(th[2]);
+__host__ __device__ static inline void rot_zyx(const Trig &t, double *R) {
+  const double cx = t.c[0], sx = t.s[0], cy = t.c[1], sy = t.s[1];
+  const double cz = t.c[2], sz = t.s[2];
   R[0] = cz * cy; R[1] = cz * sy * sx - sz * cx; R[2] = cz * sy * cx + sz * sx;
   R[3] = sz * cy; R[4] = sz * sy * sx + cz * cx; R[5] = sz * sy * cx - cz * sx;
   R[6] = -sy;     R[7] = cy * sx;                R[8] = cy * cx;
@@ -82,10 +108,11 @@ __host__ __device__ static inline void rot_zyx(const double *th, double *R) {
 // which only ever uses one PSF (registration) carries no code for the other.
 template <int PSF = PVR_PSF_GAUSSIAN>
 __host__ __device__ inline void make_geometry(const ProbDev &pr, const StackDev &st, const PatchDev &pt,
-                              const double *th, double k, GeoD &g, GeoF &gf, int *bb) {
+                              const double *th, const Trig &trig, double k, GeoD &g, GeoF &gf,
+                              int *bb) {
   constexpr int psf = PSF;
   double R[9];
-  rot_zyx(th, R);
+  rot_zyx(trig, R);
   double A[9], o[3];
   aff_split(st.p2w, A, o);
   double pc[3] = {pt.x0 + 0.5 * (pt.w - 1), pt.y0 + 0.5 * (pt.h - 1), (double)pt.slice};
@@ -220,6 +247,13 @@ __host__ __device__ inline void make_geometry(const ProbDev &pr, const StackDev 
   }
   gf.inv_cu = (float)g.inv_cu; gf.inv_cv = (float)g.inv_cv;
   for (int q = 0; q < 3; ++q) gf.perm[q] = g.perm[q];
+}
+
+template <int PSF = PVR_PSF_GAUSSIAN>
+__host__ __device__ inline void make_geometry(const ProbDev &pr, const StackDev &st,
+                                              const PatchDev &pt, const double *th, double k,
+                                              GeoD &g, GeoF &gf, int *bb) {
+  make_geometry<PSF>(pr, st, pt, th, make_trig(th), k, g, gf, bb);
 }
 
 // Block-gather constants of one patch (AdjPatch) from its geometry.  A patch

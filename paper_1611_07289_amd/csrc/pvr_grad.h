@@ -29,9 +29,9 @@ struct GradConst {
 };
 
 __device__ inline void make_grad_const(const ProbDev &pr, const StackDev &st, const PatchDev &pt,
-                                const double *th, GradConst &gc) {
+                                const double *th, const Trig &trig, GradConst &gc) {
   double R[9];
-  rot_zyx(th, R);
+  rot_zyx(trig, R);
   double F[9];
   mat3_mul(R, st.E, F);
   for (int i = 0; i < 3; ++i)
@@ -40,7 +40,7 @@ __device__ inline void make_grad_const(const ProbDev &pr, const StackDev &st, co
       for (int a = 0; a < 3; ++a) s += F[3 * i + a] * F[3 * j + a] / (st.sigma[a] * st.sigma[a]);
       gc.M[3 * i + j] = s;
     }
-  const double cz = cos(th[2]), sz = sin(th[2]), cy = cos(th[1]), sy = sin(th[1]);
+  const double cz = trig.c[2], sz = trig.s[2], cy = trig.c[1], sy = trig.s[1];
   // omega_x = Rz Ry e_x, omega_y = Rz e_y, omega_z = e_z
   gc.om[0] = cz * cy; gc.om[1] = sz * cy; gc.om[2] = -sy;
   gc.om[3] = -sz;     gc.om[4] = cz;      gc.om[5] = 0.0;

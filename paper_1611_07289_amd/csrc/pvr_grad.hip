@@ -34,7 +34,7 @@ k_grad_theta(const ProbDev *__restrict__ probs, const StackDev *__restrict__ sta
   const StackDev st = stacks[pt.stack];
   const typename GeoOf<T>::type &g = geo[s];
   GradConst gc;
-  make_grad_const(pr, st, pt, theta + 6 * s, gc);
+  make_grad_const(pr, st, pt, theta + 6 * s, make_trig(theta + 6 * s), gc);
   const T *Xp = X + pr.vol_off;
   GradMom gm;
   if constexpr (sizeof(T) == 4) make_grad_mom(gc, g.perm, gm);

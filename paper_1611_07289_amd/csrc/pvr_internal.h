@@ -150,13 +150,16 @@ struct FwdPatch {
   T fta, ftb;
   T Aaa, Aab2, Abb, Scc, cut;  // A_ab doubled
   T ga11, ga10, gb11, gb10, D11, D10, e11, e10;
-  T ka11, ia11, ka10, ia10, kb11, ib11, kb10, ib10;
-  T xm, xp;
+  T da11, da10, db11, db10;    // the deviations themselves
+  T kap[10];                   // 2^exponent: ga11, -ga11, ga10, -ga10, gb11, -gb11, gb10, -gb10,
+                               // -2 A_ab, 2 A_ab (KA11 ... XP)
   int rows;                    // window rows per sample: 3 or 4; 0: not this walk
   int half;                    // planes on either side of the middle one
   int st_a, st_b, st_c, na, nb, nc;
   int flip;                    // bit 0 / 1: u / v run against a / b
+  int ax[3];                   // voxel axes a, b, c
 };
+enum { KA11, IA11, KA10, IA10, KB11, IB11, KB10, IB10, XM, XP };
 
 struct BlockWork {   // one forward workgroup: a chunk of one patch
   int patch;
@@ -663,6 +666,7 @@ struct pvr_plan {
   int n_sim_blocks;
   pvr::BlockWork *h_pblocks;     // [n_pblocks] plane-walk work
   int n_pblocks;
+  int *h_item_off;               // [M+1]
   // caller's device workspace (pvr_plan_attach); every d_ pointer below lies
   // inside it.  The plan allocates no device memory.
   void *ws;
@@ -675,6 +679,7 @@ struct pvr_plan {
   pvr::PatchDev *d_patch;
   pvr::BlockWork *d_sim_blocks;
   pvr::BlockWork *d_pblocks;
+  int *d_item_off;           // [M+1] forward chunks (d_sim_blocks) before each patch
   int *d_tile_off;           // [M+1]
   int n_tiles, tile_w, tile_h;
   int sim_granule, bp_granule;  // XCD granules of the forward work and the adjoint bricks
@@ -736,6 +741,7 @@ struct pvr_plan {
   unsigned long long *d_dbg; // [1] first offending index of a debug-mode input check
   long long generation;      // bumped whenever launches recorded earlier would go stale
   int *d_total;              // [4] index totals: brick pairs, sub-brick pairs
+  char *d_reg;               // registration in step: states, geometry, partial sums (reg_state_bytes)
   unsigned long long *d_reg_stats;  // [4] registration evaluations and samples walked
                                     // (plain, then exact gradient) since the last read
   int h_total[4];            // host readback

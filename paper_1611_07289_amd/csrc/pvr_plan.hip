@@ -840,6 +840,9 @@ extern "C" pvr_status pvr_plan_create(const pvr_grid *grids, int32_t n_problems,
   p->use_tiles = false;
   p->sim_granule = SIM_XCD_GRANULE;
   p->bp_granule = BP_XCD_GRANULE;
+  p->h_item_off = (int *)calloc(n_patches + 1, sizeof(int));
+  for (const BlockWork &w : blocks) p->h_item_off[w.patch + 1] += 1;
+  for (int s = 0; s < n_patches; ++s) p->h_item_off[s + 1] += p->h_item_off[s];
   p->h_tile_off = (int *)calloc(n_patches + 1, sizeof(int));
   {
     const pvr_status st = make_tiles(p, TILE, TILE);
@@ -900,6 +903,7 @@ static size_t layout(pvr_plan *p, char *base, int flags) {
   p->d_patch = ws_take<PatchDev>(c, M);
   p->d_sim_blocks = ws_take<BlockWork>(c, p->n_sim_blocks);
   p->d_pblocks = ws_take<BlockWork>(c, p->n_pblocks);
+  p->d_item_off = ws_take<int>(c, M + 1);
   p->d_tile_off = ws_take<int>(c, M + 1);
   p->d_box_max = ws_take<int>(c, 4);
   p->d_brick_prob = ws_take<int>(c, nb);
@@ -932,6 +936,10 @@ static size_t layout(pvr_plan *p, char *base, int flags) {
   p->d_xt = p->any_xt ? ws_take<float>(c, p->V) : nullptr;
   p->d_total = ws_take<int>(c, 4);
   p->d_reg_stats = ws_take<unsigned long long>(c, 4);
+  {
+    size_t off[4];
+    p->d_reg = ws_take<char>(c, (long long)reg_state_bytes(p, off));
+  }
   p->d_status = ws_take<unsigned>(c, 1);
   p->d_dbg = ws_take<unsigned long long>(c, 1);
   p->d_invz64 = (flags & PVR_WS_F64) ? ws_take<double>(c, N) : nullptr;
@@ -985,6 +993,7 @@ extern "C" pvr_status pvr_plan_attach(pvr_plan *p, void *workspace, size_t bytes
   HIP_TRY(hipMemcpyAsync(p->d_patch, p->h_patch, sizeof(PatchDev) * M, hipMemcpyHostToDevice, stream));
   HIP_TRY(hipMemcpyAsync(p->d_sim_blocks, p->h_sim_blocks, sizeof(BlockWork) * p->n_sim_blocks,
                          hipMemcpyHostToDevice, stream));
+  HIP_TRY(hipMemcpyAsync(p->d_item_off, p->h_item_off, sizeof(int) * (M + 1), hipMemcpyHostToDevice, stream));
   HIP_TRY(hipMemcpyAsync(p->d_pblocks, p->h_pblocks, sizeof(BlockWork) * p->n_pblocks,
                          hipMemcpyHostToDevice, stream));
   HIP_TRY(hipMemcpyAsync(p->d_tile_off, p->h_tile_off, sizeof(int) * (M + 1), hipMemcpyHostToDevice, stream));

@@ -28,8 +28,11 @@ namespace pvr {
 
 // Constants of the walk; a, b, c as above, suffix 11 / 10: sub-window (1, 1) /
 // (1, 0), the opposite ones having the opposite sign (reciprocal factor).
+// ex: the exponents of o.kap, which the caller raises (all zero off the walk).
 template <typename T>
-__host__ __device__ inline void make_fwd(const GeoD &g, const ProbDev &pr, const PatchDev &pt, FwdPatch<T> &o) {
+__host__ __device__ inline void make_fwd_args(const GeoD &g, const ProbDev &pr, const PatchDev &pt,
+                                              FwdPatch<T> &o, double ex[10]) {
+  for (int i = 0; i < 10; ++i) ex[i] = 0.0;
   o.rows = 0;
   if (g.psf != PVR_PSF_GAUSSIAN) return;
   int a = 0;
@@ -84,9 +87,10 @@ __host__ __device__ inline void make_fwd(const GeoD &g, const ProbDev &pr, const
   o.D11 = (T)(0.5 * (ga11 * da11 + gb11 * db11));
   o.D10 = (T)(0.5 * (ga10 * da10 + gb10 * db10));
   o.e11 = (T)e11; o.e10 = (T)e10;
-  o.ka11 = (T)exp2(ga11); o.ia11 = (T)exp2(-ga11); o.ka10 = (T)exp2(ga10); o.ia10 = (T)exp2(-ga10);
-  o.kb11 = (T)exp2(gb11); o.ib11 = (T)exp2(-gb11); o.kb10 = (T)exp2(gb10); o.ib10 = (T)exp2(-gb10);
-  o.xm = (T)exp2(-2 * Aab); o.xp = (T)exp2(2 * Aab);
+  o.da11 = (T)da11; o.da10 = (T)da10; o.db11 = (T)db11; o.db10 = (T)db10;
+  const double x[10] = {ga11, -ga11, ga10, -ga10, gb11, -gb11, gb10, -gb10, -2 * Aab, 2 * Aab};
+  for (int i = 0; i < 10; ++i) ex[i] = x[i];
+  for (int i = 0; i < 3; ++i) o.ax[i] = ax[i];
   const int sx = xt ? pr.ny : 1, sy = xt ? 1 : pr.nx, sz = pr.nx * pr.ny;
   o.st_a = sel3(a, sx, sy, sz); o.st_b = sel3(b, sx, sy, sz); o.st_c = sel3(c, sx, sy, sz);
   o.na = sel3(a, pr.nx, pr.ny, pr.nz); o.nb = sel3(b, pr.nx, pr.ny, pr.nz);
@@ -131,6 +135,13 @@ __device__ __forceinline__ void combine_parts(const PlaneLane &p, T s[4], T (*ld
 #pragma unroll
       for (int t = 0; t < 4; ++t) s[t] += lds[threadIdx.x + q * p.span][t];
   }
+}
+
+template <typename T>
+__host__ __device__ inline void make_fwd(const GeoD &g, const ProbDev &pr, const PatchDev &pt, FwdPatch<T> &o) {
+  double ex[10];
+  make_fwd_args(g, pr, pt, o, ex);
+  for (int i = 0; i < 10; ++i) o.kap[i] = (T)exp2(ex[i]);
 }
 
 // Nearest integer (ties to even) or floor of a float / double as a value.
@@ -215,8 +226,10 @@ __device__ __forceinline__ void plane_walk(const FwdPatch<T> &g, int u, int v, b
   }
   const T ga[4] = {-g.ga11, g.ga10, -g.ga10, g.ga11}, gb[4] = {-g.gb11, g.gb10, -g.gb10, g.gb11};
   const T D[4] = {g.D11, g.D10, g.D10, g.D11}, e[4] = {-g.e11, g.e10, -g.e10, g.e11};
-  const T ka[4] = {g.ia11, g.ka10, g.ia10, g.ka11}, ja[4] = {g.ka11, g.ia10, g.ka10, g.ia11};
-  const T kb[4] = {g.ib11, g.kb10, g.ib10, g.kb11}, jb[4] = {g.kb11, g.ib10, g.kb10, g.ib11};
+  const T ka[4] = {g.kap[IA11], g.kap[KA10], g.kap[IA10], g.kap[KA11]},
+          ja[4] = {g.kap[KA11], g.kap[IA10], g.kap[KA10], g.kap[IA11]},
+          kb[4] = {g.kap[IB11], g.kap[KB10], g.kap[IB10], g.kap[KB11]},
+          jb[4] = {g.kap[KB11], g.kap[IB10], g.kap[KB10], g.kap[IB11]}, xm = g.kap[XM], xp = g.kap[XP];
   const T cut = g.cut;
 #pragma unroll 1
   for (int k = part - g.half; k <= g.half; k += parts) {
@@ -262,8 +275,8 @@ __device__ __forceinline__ void plane_walk(const FwdPatch<T> &g, int u, int v, b
           if (b == 0) E *= jb[t];
           if (b == 2) E *= kb[t];
           if (b == 3) E *= kb[t] * kb[t];
-          const T Em = b == 0 ? E * g.xm : b == 1 ? E : b == 2 ? E * g.xp : E * g.xp * g.xp;
-          const T Ep = b == 0 ? E * g.xp : b == 1 ? E : b == 2 ? E * g.xm : E * g.xm * g.xm;
+          const T Em = b == 0 ? E * xm : b == 1 ? E : b == 2 ? E * xp : E * xp * xp;
+          const T Ep = b == 0 ? E * xp : b == 1 ? E : b == 2 ? E * xm : E * xm * xm;
           const T g0 = clamp01<T>(fma(Em, Um, -cut)), g1 = clamp01<T>(fma(E, Uc, -cut)),
                   g2 = clamp01<T>(fma(Ep, Up, -cut));
           z[t] += g0 + g1 + g2;
@@ -288,8 +301,8 @@ __device__ __forceinline__ void plane_walk(const FwdPatch<T> &g, int u, int v, b
         if (b == 0) E *= jb[t];
         if (b == 2) E *= kb[t];
         if (b == 3) E *= kb[t] * kb[t];
-        const T Em = b == 0 ? E * g.xm : b == 1 ? E : b == 2 ? E * g.xp : E * (g.xp * g.xp);
-        const T Ep = b == 0 ? E * g.xp : b == 1 ? E : b == 2 ? E * g.xm : E * (g.xm * g.xm);
+        const T Em = b == 0 ? E * xm : b == 1 ? E : b == 2 ? E * xp : E * (xp * xp);
+        const T Ep = b == 0 ? E * xp : b == 1 ? E : b == 2 ? E * xm : E * (xm * xm);
         const T g0 = clamp01<T>(fma(Em, Um, -cut)), g1 = clamp01<T>(fma(E, U[1], -cut)),
                 g2 = clamp01<T>(fma(Ep, Up, -cut));
         if (HAS_Z) z[t] += g0 + g1 + g2;
@@ -299,6 +312,141 @@ __device__ __forceinline__ void plane_walk(const FwdPatch<T> &g, int u, int v, b
           y[t] = fma(g2, x[j + b][i + 2], y[t]);
         }
       }
+    }
+  }
+}
+
+// The plane walk with the derivative's moments (pvr_grad.h: psf_walk_grad, along
+// the axes a, b, c): relative to the value xb of one voxel near the block,
+// per sample acc = sum g_hat (X - xb), z = sum g_hat, and the nine offset
+// moments of e^{-Q/2} (X - xb) in mx and of e^{-Q/2} in me.  In a plane the
+// moments are taken about each sample's nearest voxel, where they are sums and
+// differences, and moved to the sample's centre once.
+template <int NB>
+__device__ __forceinline__ void plane_walk_grad(const FwdPatch<float> &g, int u, int v, bool live,
+                                                __amdgpu_buffer_rsrc_t xr, unsigned nbytes, float &xb,
+                                                float acc[4], float z[4], float mx[4][9], float me[4][9]) {
+  const double du = u, dv = v;
+  const double xa = fma(g.Ha[0], du, fma(g.Ha[1], dv, g.Ha[2]));
+  const double xbd = fma(g.Hb[0], du, fma(g.Hb[1], dv, g.Hb[2]));
+  const double xc = fma(g.Hc[0], du, fma(g.Hc[1], dv, g.Hc[2]));
+  const double rc = __builtin_rint(xc), dc = rc - xc;
+  const double pa = fma(g.ta, dc, xa) - 0.5, pb = fma(g.tb, dc, xbd) - 0.5;
+  const double ra = __builtin_rint(pa), rb = __builtin_rint(pb);
+  const float f0 = (float)(pa - ra), h0 = (float)(pb - rb), z0 = (float)dc;
+  const int ia0 = (int)ra - 1, ib0 = (int)rb - 1, ic0 = (int)rc;
+  {
+    const int a = min(max(ia0 + 1, 0), g.na - 1), b = min(max(ib0 + 1, 0), g.nb - 1),
+              c = min(max(ic0, 0), g.nc - 1);
+    xb = load_vox<float>(xr, (unsigned)(c * g.st_c + b * g.st_b + a * g.st_a) * 4u);
+  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    acc[t] = z[t] = 0.f;
+#pragma unroll
+    for (int q = 0; q < 9; ++q) mx[t][q] = me[t][q] = 0.f;
+  }
+  const float cut = g.cut;
+#pragma unroll 1
+  for (int k = -g.half; k <= g.half; ++k) {
+    const float kk = (float)k;
+    const float qa = fma(kk, g.fta, f0), qb = fma(kk, g.ftb, h0);
+    const float sa = round_val<false>(qa), sb = round_val<NB == 4>(qb);
+    const float f = qa - sa, h = qb - sb, wz = z0 + kk;
+    const int ia = ia0 + (int)sa, ib = ib0 + (int)sb, ic = ic0 + k;
+    const bool inside = !live || ((unsigned)ic < (unsigned)g.nc && ia >= 0 && ia + 4 <= g.na &&
+                                  ib >= 0 && ib + NB + 1 <= g.nb);
+    float x[NB + 1][4];
+    load_rows<NB>(g, xr, nbytes, ia, ib, ic, inside, x);
+#pragma unroll
+    for (int r = 0; r <= NB; ++r)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[r][i] -= xb;
+    const float m = g.Aab2 * f * h;
+    const float ea = -g.Aaa * f * f, eb = -g.Abb * h * h;
+    const float sla = fma(g.Aab2, h, 2.f * g.Aaa * f), slb = fma(g.Aab2, f, 2.f * g.Abb * h);
+    float U[3], V[NB];
+    U[0] = fast_exp2<float>(ea - g.Aaa - sla);
+    U[1] = fast_exp2<float>(ea);
+    U[2] = fast_exp2<float>(ea - g.Aaa + sla);
+    V[0] = fast_exp2<float>(eb - g.Abb - slb);
+    V[1] = fast_exp2<float>(eb);
+    V[2] = fast_exp2<float>(eb - g.Abb + slb);
+    if constexpr (NB == 4) V[3] = fast_exp2<float>(fma(-4.f, g.Abb, fma(2.f, slb, eb)));
+    float ca[4] = {1.f, 1.f, 1.f, 1.f}, cb[NB + 1];
+#pragma unroll
+    for (int j = 0; j <= NB; ++j) cb[j] = 1.f;
+    const bool edge = !__all(inside);  // voxels outside the grid do not count
+    if (edge) {
+      const bool pc = (unsigned)ic < (unsigned)g.nc;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) ca[i] = (unsigned)(ia + i) < (unsigned)g.na ? 1.f : 0.f;
+#pragma unroll
+      for (int j = 0; j <= NB; ++j) cb[j] = pc && (unsigned)(ib + j) < (unsigned)g.nb ? 1.f : 0.f;
+    }
+    const float xm = g.kap[XM], xp = g.kap[XP];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int i = t & 1, j = t >> 1;
+      const float ga = t == 0 ? -g.ga11 : t == 1 ? g.ga10 : t == 2 ? -g.ga10 : g.ga11;
+      const float gb = t == 0 ? -g.gb11 : t == 1 ? g.gb10 : t == 2 ? -g.gb10 : g.gb11;
+      const float da = t == 0 ? -g.da11 : t == 1 ? g.da10 : t == 2 ? -g.da10 : g.da11;
+      const float db = t == 0 ? -g.db11 : t == 1 ? g.db10 : t == 2 ? -g.db10 : g.db11;
+      const float ka = g.kap[t == 0 ? IA11 : t == 1 ? KA10 : t == 2 ? IA10 : KA11];
+      const float ja = g.kap[t == 0 ? KA11 : t == 1 ? IA10 : t == 2 ? KA10 : IA11];
+      const float kb = g.kap[t == 0 ? IB11 : t == 1 ? KB10 : t == 2 ? IB10 : KB11];
+      const float jb = g.kap[t == 0 ? KB11 : t == 1 ? IB10 : t == 2 ? KB10 : IB11];
+      const float w = wz - (t == 0 ? -g.e11 : t == 1 ? g.e10 : t == 2 ? -g.e10 : g.e11);
+      const float D = (t == 0 || t == 3) ? g.D11 : g.D10;
+      const float S = fast_exp2<float>(-fma(g.Scc * w, w, fma(f, ga, fma(h, gb, D + m))));
+      const float Um = U[0] * ja * ca[i], Uc = U[1] * ca[i + 1], Up = U[2] * ka * ca[i + 2];
+      // plane moments about the nearest voxel: m00, m10, m20, m01, m11, m02
+      float px[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, pe[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        float E = V[b] * S * cb[j + b];
+        if (b == 0) E *= jb;
+        if (b == 2) E *= kb;
+        if (b == 3) E *= kb * kb;
+        const float Em = b == 0 ? E * xm : b == 1 ? E : b == 2 ? E * xp : E * (xp * xp);
+        const float Ep = b == 0 ? E * xp : b == 1 ? E : b == 2 ? E * xm : E * (xm * xm);
+        const float w0 = Em * Um, w1 = E * Uc, w2 = Ep * Up;
+        const float g0 = clamp01<float>(w0 - cut), g1 = clamp01<float>(w1 - cut),
+                    g2 = clamp01<float>(w2 - cut);
+        const float e0 = g0 > 0.f ? w0 : 0.f, e1 = g1 > 0.f ? w1 : 0.f, e2 = g2 > 0.f ? w2 : 0.f;
+        const float v0 = x[j + b][i], v1 = x[j + b][i + 1], v2 = x[j + b][i + 2];
+        acc[t] = fma(g0, v0, acc[t]);
+        acc[t] = fma(g1, v1, acc[t]);
+        acc[t] = fma(g2, v2, acc[t]);
+        z[t] += g0 + g1 + g2;
+        const float a0 = e0 * v0, a1 = e1 * v1, a2 = e2 * v2;
+        const float xs = a0 + a2, es = e0 + e2, xd = a2 - a0, ed = e2 - e0;
+        const float x0 = xs + a1, n0 = es + e1;
+        px[0] += x0; px[1] += xd; px[2] += xs;
+        pe[0] += n0; pe[1] += ed; pe[2] += es;
+        if (b != 1) {
+          const float s1 = b == 0 ? -1.f : b == 2 ? 1.f : 2.f, s2 = s1 * s1;
+          px[3] = fma(s1, x0, px[3]); px[4] = fma(s1, xd, px[4]); px[5] = fma(s2, x0, px[5]);
+          pe[3] = fma(s1, n0, pe[3]); pe[4] = fma(s1, ed, pe[4]); pe[5] = fma(s2, n0, pe[5]);
+        }
+      }
+      // about the sample's centre, at (fa, hb) from its nearest voxel (the plane's
+      // conditional centre lies t w beside it)
+      const float fa = fma(-g.fta, w, f + da), hb = fma(-g.ftb, w, h + db);
+      auto move = [&](const float p[6], float o[9]) {
+        const float sa1 = fma(-fa, p[0], p[1]), sb1 = fma(-hb, p[0], p[3]);
+        o[0] += sa1;
+        o[1] += sb1;
+        o[2] = fma(w, p[0], o[2]);
+        o[3] += fma(-fa, p[1] + sa1, p[2]);
+        o[4] += fma(-fa, sb1, fma(-hb, p[1], p[4]));
+        o[5] = fma(w, sa1, o[5]);
+        o[6] += fma(-hb, p[3] + sb1, p[5]);
+        o[7] = fma(w, sb1, o[7]);
+        o[8] = fma(w * w, p[0], o[8]);
+      };
+      move(px, mx[t]);
+      move(pe, me[t]);
     }
   }
 }

@@ -61,6 +61,7 @@ void plan_free(pvr_plan *p) {
   free(p->h_vol_off);
   free(p->h_sim_blocks);
   free(p->h_pblocks);
+  free(p->h_item_off);
   free(p->h_brick_prob);
   free(p->h_plane_prob);
   free(p->h_tile_off);
