@@ -148,22 +148,25 @@ __device__ __forceinline__ void grad_walk(const GEO &g, const ProbDev &p, const 
 // with q = x_j - (c_s + t), since z x y = (M D) x D + (M D) x q.  The walk
 // therefore accumulates nine moments per weight set instead of evaluating
 // the derivative at every voxel.
-struct GradMom {
-  float V[9];   // V[3 r + a]: world component r of the step along walk axis a
-  float P[9];   // M V
-  float om[9];  // rotation axes omega_k as rows
+template <typename T>
+struct GradMomT {
+  T V[9];   // V[3 r + a]: world component r of the step along walk axis a
+  T P[9];   // M V
+  T om[9];  // rotation axes omega_k as rows
 };
+using GradMom = GradMomT<float>;
 
-__device__ inline void make_grad_mom(const GradConst &gc, const int perm[3], GradMom &gm) {
+template <typename T>
+__device__ inline void make_grad_mom(const GradConst &gc, const int perm[3], GradMomT<T> &gm) {
   for (int r = 0; r < 3; ++r)
-    for (int a = 0; a < 3; ++a) gm.V[3 * r + a] = (float)gc.Vl[3 * r + perm[a]];
+    for (int a = 0; a < 3; ++a) gm.V[3 * r + a] = (T)gc.Vl[3 * r + perm[a]];
   for (int r = 0; r < 3; ++r)
     for (int a = 0; a < 3; ++a) {
       double s = 0;
       for (int m = 0; m < 3; ++m) s += gc.M[3 * r + m] * gc.Vl[3 * m + perm[a]];
-      gm.P[3 * r + a] = (float)s;
+      gm.P[3 * r + a] = (T)s;
     }
-  for (int q = 0; q < 9; ++q) gm.om[q] = (float)gc.om[q];
+  for (int q = 0; q < 9; ++q) gm.om[q] = (T)gc.om[q];
 }
 
 // One walk over the support of a sample (as psf_walk_fwd, FP32, with its ROW
@@ -267,15 +270,16 @@ __device__ __forceinline__ void psf_walk_grad(const GeoF &g, const ProbDev &p, c
 
 // The six derivative sums sum_i w_i d g_hat_i / d theta (rotations, then
 // translations) from the nine moments m of the weights w_i (see GradMom).
-__device__ __forceinline__ void grad_from_moments(const GradMom &gm, const float m[9],
-                                                  const float q[3], float a6[6]) {
+template <typename F>
+__device__ __forceinline__ void grad_from_moments(const GradMomT<F> &gm, const F m[9],
+                                                  const F q[3], F a6[6]) {
   // t = P n
-  float t[3];
+  F t[3];
 #pragma unroll
   for (int r = 0; r < 3; ++r) t[r] = gm.P[3 * r] * m[0] + gm.P[3 * r + 1] * m[1] + gm.P[3 * r + 2] * m[2];
-  const float S[9] = {m[3], m[4], m[5], m[4], m[6], m[7], m[5], m[7], m[8]};
+  const F S[9] = {m[3], m[4], m[5], m[4], m[6], m[7], m[5], m[7], m[8]};
   // T = S V^T: T[u][c] = sum_v S[u][v] V[c][v]
-  float T[9];
+  F T[9];
 #pragma unroll
   for (int u = 0; u < 3; ++u)
 #pragma unroll
@@ -285,9 +289,9 @@ __device__ __forceinline__ void grad_from_moments(const GradMom &gm, const float
   auto C = [&](int r, int c) {
     return gm.P[3 * r] * T[c] + gm.P[3 * r + 1] * T[3 + c] + gm.P[3 * r + 2] * T[6 + c];
   };
-  const float c0 = C(1, 2) - C(2, 1) + (t[1] * q[2] - t[2] * q[1]);
-  const float c1 = C(2, 0) - C(0, 2) + (t[2] * q[0] - t[0] * q[2]);
-  const float c2 = C(0, 1) - C(1, 0) + (t[0] * q[1] - t[1] * q[0]);
+  const F c0 = C(1, 2) - C(2, 1) + (t[1] * q[2] - t[2] * q[1]);
+  const F c1 = C(2, 0) - C(0, 2) + (t[2] * q[0] - t[0] * q[2]);
+  const F c2 = C(0, 1) - C(1, 0) + (t[0] * q[1] - t[1] * q[0]);
 #pragma unroll
   for (int k = 0; k < 3; ++k) a6[k] = -(gm.om[3 * k] * c0 + gm.om[3 * k + 1] * c1 + gm.om[3 * k + 2] * c2);
   a6[3] = t[0];

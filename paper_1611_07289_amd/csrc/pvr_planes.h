@@ -322,10 +322,10 @@ __device__ __forceinline__ void plane_walk(const FwdPatch<T> &g, int u, int v, b
 // moments of e^{-Q/2} (X - xb) in mx and of e^{-Q/2} in me.  In a plane the
 // moments are taken about each sample's nearest voxel, where they are sums and
 // differences, and moved to the sample's centre once.
-template <int NB>
-__device__ __forceinline__ void plane_walk_grad(const FwdPatch<float> &g, int u, int v, bool live,
-                                                __amdgpu_buffer_rsrc_t xr, unsigned nbytes, float &xb,
-                                                float acc[4], float z[4], float mx[4][9], float me[4][9]) {
+template <typename T, int NB>
+__device__ __forceinline__ void plane_walk_grad(const FwdPatch<T> &g, int u, int v, bool live,
+                                                __amdgpu_buffer_rsrc_t xr, unsigned nbytes, T &xb,
+                                                T acc[4], T z[4], T mx[4][9], T me[4][9]) {
   const double du = u, dv = v;
   const double xa = fma(g.Ha[0], du, fma(g.Ha[1], dv, g.Ha[2]));
   const double xbd = fma(g.Hb[0], du, fma(g.Hb[1], dv, g.Hb[2]));
@@ -333,108 +333,108 @@ __device__ __forceinline__ void plane_walk_grad(const FwdPatch<float> &g, int u,
   const double rc = __builtin_rint(xc), dc = rc - xc;
   const double pa = fma(g.ta, dc, xa) - 0.5, pb = fma(g.tb, dc, xbd) - 0.5;
   const double ra = __builtin_rint(pa), rb = __builtin_rint(pb);
-  const float f0 = (float)(pa - ra), h0 = (float)(pb - rb), z0 = (float)dc;
+  const T f0 = (T)(pa - ra), h0 = (T)(pb - rb), z0 = (T)dc;
   const int ia0 = (int)ra - 1, ib0 = (int)rb - 1, ic0 = (int)rc;
   {
     const int a = min(max(ia0 + 1, 0), g.na - 1), b = min(max(ib0 + 1, 0), g.nb - 1),
               c = min(max(ic0, 0), g.nc - 1);
-    xb = load_vox<float>(xr, (unsigned)(c * g.st_c + b * g.st_b + a * g.st_a) * 4u);
+    xb = load_vox<T>(xr, (unsigned)(c * g.st_c + b * g.st_b + a * g.st_a) * (unsigned)sizeof(T));
   }
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    acc[t] = z[t] = 0.f;
+    acc[t] = z[t] = (T)0;
 #pragma unroll
-    for (int q = 0; q < 9; ++q) mx[t][q] = me[t][q] = 0.f;
+    for (int q = 0; q < 9; ++q) mx[t][q] = me[t][q] = (T)0;
   }
-  const float cut = g.cut;
+  const T cut = g.cut;
 #pragma unroll 1
   for (int k = -g.half; k <= g.half; ++k) {
-    const float kk = (float)k;
-    const float qa = fma(kk, g.fta, f0), qb = fma(kk, g.ftb, h0);
-    const float sa = round_val<false>(qa), sb = round_val<NB == 4>(qb);
-    const float f = qa - sa, h = qb - sb, wz = z0 + kk;
+    const T kk = (T)k;
+    const T qa = fma(kk, g.fta, f0), qb = fma(kk, g.ftb, h0);
+    const T sa = round_val<false>(qa), sb = round_val<NB == 4>(qb);
+    const T f = qa - sa, h = qb - sb, wz = z0 + kk;
     const int ia = ia0 + (int)sa, ib = ib0 + (int)sb, ic = ic0 + k;
     const bool inside = !live || ((unsigned)ic < (unsigned)g.nc && ia >= 0 && ia + 4 <= g.na &&
                                   ib >= 0 && ib + NB + 1 <= g.nb);
-    float x[NB + 1][4];
+    T x[NB + 1][4];
     load_rows<NB>(g, xr, nbytes, ia, ib, ic, inside, x);
 #pragma unroll
     for (int r = 0; r <= NB; ++r)
 #pragma unroll
       for (int i = 0; i < 4; ++i) x[r][i] -= xb;
-    const float m = g.Aab2 * f * h;
-    const float ea = -g.Aaa * f * f, eb = -g.Abb * h * h;
-    const float sla = fma(g.Aab2, h, 2.f * g.Aaa * f), slb = fma(g.Aab2, f, 2.f * g.Abb * h);
-    float U[3], V[NB];
-    U[0] = fast_exp2<float>(ea - g.Aaa - sla);
-    U[1] = fast_exp2<float>(ea);
-    U[2] = fast_exp2<float>(ea - g.Aaa + sla);
-    V[0] = fast_exp2<float>(eb - g.Abb - slb);
-    V[1] = fast_exp2<float>(eb);
-    V[2] = fast_exp2<float>(eb - g.Abb + slb);
-    if constexpr (NB == 4) V[3] = fast_exp2<float>(fma(-4.f, g.Abb, fma(2.f, slb, eb)));
-    float ca[4] = {1.f, 1.f, 1.f, 1.f}, cb[NB + 1];
+    const T m = g.Aab2 * f * h;
+    const T ea = -g.Aaa * f * f, eb = -g.Abb * h * h;
+    const T sla = fma(g.Aab2, h, (T)2 * g.Aaa * f), slb = fma(g.Aab2, f, (T)2 * g.Abb * h);
+    T U[3], V[NB];
+    U[0] = fast_exp2<T>(ea - g.Aaa - sla);
+    U[1] = fast_exp2<T>(ea);
+    U[2] = fast_exp2<T>(ea - g.Aaa + sla);
+    V[0] = fast_exp2<T>(eb - g.Abb - slb);
+    V[1] = fast_exp2<T>(eb);
+    V[2] = fast_exp2<T>(eb - g.Abb + slb);
+    if constexpr (NB == 4) V[3] = fast_exp2<T>(fma((T)-4, g.Abb, fma((T)2, slb, eb)));
+    T ca[4] = {(T)1, (T)1, (T)1, (T)1}, cb[NB + 1];
 #pragma unroll
-    for (int j = 0; j <= NB; ++j) cb[j] = 1.f;
+    for (int j = 0; j <= NB; ++j) cb[j] = (T)1;
     const bool edge = !__all(inside);  // voxels outside the grid do not count
     if (edge) {
       const bool pc = (unsigned)ic < (unsigned)g.nc;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) ca[i] = (unsigned)(ia + i) < (unsigned)g.na ? 1.f : 0.f;
+      for (int i = 0; i < 4; ++i) ca[i] = (unsigned)(ia + i) < (unsigned)g.na ? (T)1 : (T)0;
 #pragma unroll
-      for (int j = 0; j <= NB; ++j) cb[j] = pc && (unsigned)(ib + j) < (unsigned)g.nb ? 1.f : 0.f;
+      for (int j = 0; j <= NB; ++j) cb[j] = pc && (unsigned)(ib + j) < (unsigned)g.nb ? (T)1 : (T)0;
     }
-    const float xm = g.kap[XM], xp = g.kap[XP];
+    const T xm = g.kap[XM], xp = g.kap[XP];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       const int i = t & 1, j = t >> 1;
-      const float ga = t == 0 ? -g.ga11 : t == 1 ? g.ga10 : t == 2 ? -g.ga10 : g.ga11;
-      const float gb = t == 0 ? -g.gb11 : t == 1 ? g.gb10 : t == 2 ? -g.gb10 : g.gb11;
-      const float da = t == 0 ? -g.da11 : t == 1 ? g.da10 : t == 2 ? -g.da10 : g.da11;
-      const float db = t == 0 ? -g.db11 : t == 1 ? g.db10 : t == 2 ? -g.db10 : g.db11;
-      const float ka = g.kap[t == 0 ? IA11 : t == 1 ? KA10 : t == 2 ? IA10 : KA11];
-      const float ja = g.kap[t == 0 ? KA11 : t == 1 ? IA10 : t == 2 ? KA10 : IA11];
-      const float kb = g.kap[t == 0 ? IB11 : t == 1 ? KB10 : t == 2 ? IB10 : KB11];
-      const float jb = g.kap[t == 0 ? KB11 : t == 1 ? IB10 : t == 2 ? KB10 : IB11];
-      const float w = wz - (t == 0 ? -g.e11 : t == 1 ? g.e10 : t == 2 ? -g.e10 : g.e11);
-      const float D = (t == 0 || t == 3) ? g.D11 : g.D10;
-      const float S = fast_exp2<float>(-fma(g.Scc * w, w, fma(f, ga, fma(h, gb, D + m))));
-      const float Um = U[0] * ja * ca[i], Uc = U[1] * ca[i + 1], Up = U[2] * ka * ca[i + 2];
+      const T ga = t == 0 ? -g.ga11 : t == 1 ? g.ga10 : t == 2 ? -g.ga10 : g.ga11;
+      const T gb = t == 0 ? -g.gb11 : t == 1 ? g.gb10 : t == 2 ? -g.gb10 : g.gb11;
+      const T da = t == 0 ? -g.da11 : t == 1 ? g.da10 : t == 2 ? -g.da10 : g.da11;
+      const T db = t == 0 ? -g.db11 : t == 1 ? g.db10 : t == 2 ? -g.db10 : g.db11;
+      const T ka = g.kap[t == 0 ? IA11 : t == 1 ? KA10 : t == 2 ? IA10 : KA11];
+      const T ja = g.kap[t == 0 ? KA11 : t == 1 ? IA10 : t == 2 ? KA10 : IA11];
+      const T kb = g.kap[t == 0 ? IB11 : t == 1 ? KB10 : t == 2 ? IB10 : KB11];
+      const T jb = g.kap[t == 0 ? KB11 : t == 1 ? IB10 : t == 2 ? KB10 : IB11];
+      const T w = wz - (t == 0 ? -g.e11 : t == 1 ? g.e10 : t == 2 ? -g.e10 : g.e11);
+      const T D = (t == 0 || t == 3) ? g.D11 : g.D10;
+      const T S = fast_exp2<T>(-fma(g.Scc * w, w, fma(f, ga, fma(h, gb, D + m))));
+      const T Um = U[0] * ja * ca[i], Uc = U[1] * ca[i + 1], Up = U[2] * ka * ca[i + 2];
       // plane moments about the nearest voxel: m00, m10, m20, m01, m11, m02
-      float px[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, pe[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      T px[6] = {(T)0, (T)0, (T)0, (T)0, (T)0, (T)0}, pe[6] = {(T)0, (T)0, (T)0, (T)0, (T)0, (T)0};
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
-        float E = V[b] * S * cb[j + b];
+        T E = V[b] * S * cb[j + b];
         if (b == 0) E *= jb;
         if (b == 2) E *= kb;
         if (b == 3) E *= kb * kb;
-        const float Em = b == 0 ? E * xm : b == 1 ? E : b == 2 ? E * xp : E * (xp * xp);
-        const float Ep = b == 0 ? E * xp : b == 1 ? E : b == 2 ? E * xm : E * (xm * xm);
-        const float w0 = Em * Um, w1 = E * Uc, w2 = Ep * Up;
-        const float g0 = clamp01<float>(w0 - cut), g1 = clamp01<float>(w1 - cut),
-                    g2 = clamp01<float>(w2 - cut);
-        const float e0 = g0 > 0.f ? w0 : 0.f, e1 = g1 > 0.f ? w1 : 0.f, e2 = g2 > 0.f ? w2 : 0.f;
-        const float v0 = x[j + b][i], v1 = x[j + b][i + 1], v2 = x[j + b][i + 2];
+        const T Em = b == 0 ? E * xm : b == 1 ? E : b == 2 ? E * xp : E * (xp * xp);
+        const T Ep = b == 0 ? E * xp : b == 1 ? E : b == 2 ? E * xm : E * (xm * xm);
+        const T w0 = Em * Um, w1 = E * Uc, w2 = Ep * Up;
+        const T g0 = clamp01<T>(w0 - cut), g1 = clamp01<T>(w1 - cut),
+                    g2 = clamp01<T>(w2 - cut);
+        const T e0 = g0 > (T)0 ? w0 : (T)0, e1 = g1 > (T)0 ? w1 : (T)0, e2 = g2 > (T)0 ? w2 : (T)0;
+        const T v0 = x[j + b][i], v1 = x[j + b][i + 1], v2 = x[j + b][i + 2];
         acc[t] = fma(g0, v0, acc[t]);
         acc[t] = fma(g1, v1, acc[t]);
         acc[t] = fma(g2, v2, acc[t]);
         z[t] += g0 + g1 + g2;
-        const float a0 = e0 * v0, a1 = e1 * v1, a2 = e2 * v2;
-        const float xs = a0 + a2, es = e0 + e2, xd = a2 - a0, ed = e2 - e0;
-        const float x0 = xs + a1, n0 = es + e1;
+        const T a0 = e0 * v0, a1 = e1 * v1, a2 = e2 * v2;
+        const T xs = a0 + a2, es = e0 + e2, xd = a2 - a0, ed = e2 - e0;
+        const T x0 = xs + a1, n0 = es + e1;
         px[0] += x0; px[1] += xd; px[2] += xs;
         pe[0] += n0; pe[1] += ed; pe[2] += es;
         if (b != 1) {
-          const float s1 = b == 0 ? -1.f : b == 2 ? 1.f : 2.f, s2 = s1 * s1;
+          const T s1 = b == 0 ? -(T)1 : b == 2 ? (T)1 : (T)2, s2 = s1 * s1;
           px[3] = fma(s1, x0, px[3]); px[4] = fma(s1, xd, px[4]); px[5] = fma(s2, x0, px[5]);
           pe[3] = fma(s1, n0, pe[3]); pe[4] = fma(s1, ed, pe[4]); pe[5] = fma(s2, n0, pe[5]);
         }
       }
       // about the sample's centre, at (fa, hb) from its nearest voxel (the plane's
       // conditional centre lies t w beside it)
-      const float fa = fma(-g.fta, w, f + da), hb = fma(-g.ftb, w, h + db);
-      auto move = [&](const float p[6], float o[9]) {
-        const float sa1 = fma(-fa, p[0], p[1]), sb1 = fma(-hb, p[0], p[3]);
+      const T fa = fma(-g.fta, w, f + da), hb = fma(-g.ftb, w, h + db);
+      auto move = [&](const T p[6], T o[9]) {
+        const T sa1 = fma(-fa, p[0], p[1]), sb1 = fma(-hb, p[0], p[3]);
         o[0] += sa1;
         o[1] += sb1;
         o[2] = fma(w, p[0], o[2]);

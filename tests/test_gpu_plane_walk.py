@@ -93,3 +93,36 @@ def test_work_items_of_one_to_several_wavefronts(w, h):
     P = synth.Patches(*[np.array(v, np.int32) for v in
                         zip(*[(i, 1, 64 - w, 0, w, h) for i in range(3)])])
     _check(g, st, P, _motion(P.M, 8.0, 2.0), f64=False)
+
+
+@pytest.mark.parametrize("deg", [0.0, 12.0, 30.0, 60.0])
+def test_fp64_motion_derivative_by_finite_differences_of_the_walk(deg):
+    # every frame's signs and both windows, patches reaching outside the grid;
+    # a central difference of the FP64 simulation is no derivative where a voxel
+    # enters or leaves a support, so the loss takes the samples whose value is
+    # smooth: those whose differences at two steps agree
+    g, st, P = _problem(FRAMES[::5] + synth.orthogonal_frames([35.0]), 21, 18, 24)
+    rng = np.random.default_rng(4)
+    th = _motion(P.M, deg, 2.0)
+    ctx = oracle.Ctx(g, st, P)
+    X = rng.uniform(0.0, 1000.0, (g.nz, g.ny, g.nx))
+    d = rng.normal(size=(P.M, 6)) * np.array([1e-2] * 3 + [1.0] * 3)  # one direction per patch
+
+    def diff(h):
+        yp, _, vp = ctx.simulate(X, th + h * d)
+        ym, _, vm = ctx.simulate(X, th - h * d)
+        return (yp - ym) / (2 * h), (vp > 0) & (vm > 0)
+    d1, v1 = diff(1e-5)
+    d2, v2 = diff(2e-6)
+    smooth = v1 & v2 & (np.abs(d1 - d2) <= 1e-5 * np.abs(d1).max())
+    assert smooth.mean() > 0.5
+    gy = np.where(smooth, rng.normal(size=smooth.shape), 0.0)
+    plan = pvr.Plan([g], [st], [P], f64=True)
+    plan.build(dev(th))
+    out = torch.full((P.M, 6), float("nan"), dtype=torch.float64, device="cuda")
+    plan.grad_theta(dev(X.reshape(-1)), dev(gy), out)
+    off = plan.sample_off
+    want = np.array([(gy * d2)[off[s]:off[s + 1]].sum() for s in range(P.M)])
+    got = (host(out) * d).sum(1)
+    scale = np.array([np.abs(gy * d2)[off[s]:off[s + 1]].sum() for s in range(P.M)])
+    assert np.all(np.abs(got - want) <= 1e-5 * np.maximum(scale, 1e-3 * scale.max()))
