@@ -123,7 +123,7 @@ typedef struct {
                                bricks or 4^3 sub-bricks with patches; 0 until
                                a back-projection built it) */
   int64_t device_bytes;     /* bytes of the attached workspace (0 if none) */
-  int64_t bin_capacity;     /* brick/patch pairs the workspace holds */
+  int64_t bin_capacity;     /* host bound on brick/patch pairs       */
   int64_t sub_capacity;     /* second-level pairs the workspace holds */
 } pvr_plan_sizes;
 

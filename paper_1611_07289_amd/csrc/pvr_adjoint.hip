@@ -244,7 +244,7 @@ k_backproject(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ pa
   const int kk = bz * BRICK + (w >> 2) * SUB + (l >> 4);
   const bool inside = i < pr.nx && jj < pr.ny && kk < pr.nz;
   T sn = 0, sd = 0;
-  const int sbi = bi * 8 + w;
+  const int sbi = bi * 9 + w;
   const int q0 = sub_off[sbi], q1 = sub_off[sbi + 1];
   const double fi = i, fj = jj, fk = kk;
   for (int q = q0; q < q1; ++q) {
@@ -297,7 +297,7 @@ k_backproject(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ pa
 // bound by vector issue.  256^3 benchmark, 11 760 patches: 2.27 ms per launch with
 // the per-voxel gather, 1.31 ms with this one.  The
 // patches of a brick are taken normal axis by normal axis (lists of
-// k_half_lists), so that the two wavefronts' voxels are disjoint; between axes
+// k_adj_lists), so that the two wavefronts' voxels are disjoint; between axes
 // the sums move through LDS.  The order (axis, then patch, then candidate) is
 // fixed: the result is bitwise repeatable.
 //
@@ -397,7 +397,7 @@ k_gather_blocks(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ 
   T sn[4], sd[4];  // sub-window (ou, ov) at 2 ov + ou
   for (int an = 0; an < 3; ++an) {
     __syncthreads();
-    const int li = bi * 6 + 2 * an + w;
+    const int li = bi * 7 + 2 * an + w;
     const int q0 = off[li] + part, q1 = off[li + 1];
     int cur = -1;
     double xu = 0, xv = 0, xn = 0;  // the block's centre along (au, av, an)
@@ -571,8 +571,8 @@ static pvr_status backproject_impl(const pvr_plan *p, const T *e, const T *pp, c
                                    T *num, T *den, const T *invz, typename Vec2Of<T>::type *rq,
                                    hipStream_t stream) {
   if (!e || !num) return fail(PVR_EINVAL, "pvr_backproject: e and num are required");
-  if (!p->index_valid || p->index_blocks != p->gather_blocks) {
-    const pvr_status st = plan_build_index(const_cast<pvr_plan *>(p), p->gather_blocks, stream);
+  if (!p->index_valid) {
+    const pvr_status st = plan_build_index(const_cast<pvr_plan *>(p), stream);
     if (st != PVR_OK) return st;
   }
   // the preparation pass, unless pvr_robust_weights (PVR_EM_PREP_ADJOINT)

@@ -72,8 +72,8 @@ extern "C" pvr_status pvr_sr_graph_create(pvr_plan *plan, float *X, float *X_alt
   if (!plan->built) return fail(PVR_EINVAL, "pvr_sr_graph_create: build the plan first");
   if (plan->timing)
     return fail(PVR_EUNSUPPORTED, "pvr_sr_graph_create: switch kernel timing off before capturing");
-  if (!plan->index_valid || plan->index_blocks != plan->gather_blocks) {
-    const pvr_status st = plan_build_index(plan, plan->gather_blocks, stream);
+  if (!plan->index_valid) {
+    const pvr_status st = plan_build_index(plan, stream);
     if (st != PVR_OK) return st;
   }
   HIP_TRY(hipStreamSynchronize(stream));

@@ -703,18 +703,13 @@ struct pvr_plan {
   uint8_t *d_active;         // [M]
   int *d_bb;                 // [M][6] brick range per patch
   int *d_gbox;               // [ceil(M / 64)][6] union of the ranges of 64 consecutive patches
-  long long *d_scan;         // block sums of the index scans
   double *d_sbox;            // [M][18] voxel->pixel map and pixel support box
-  int *d_bin_count;          // [n_bricks]
-  int *d_bin_off;            // [n_bricks + 1]
-  int *d_bin_patch;          // [bin_cap]
   long long bin_cap;         // host bound on brick/patch pairs over all motions
-  int *d_sub_count;          // [8 n_bricks]; block gather: 6 n_bricks (normal axis, half)
-  int *d_sub_off;            // [8 n_bricks + 1]
+  int *d_sub_off;            // per brick the starts of its parts' lists (8 sub-bricks or 6 halves)
+                             // and the end of the last: 9 or 7 entries
   int *d_sub_patch;          // [sub_cap]
   long long sub_cap;         // host bound on sub-brick/patch pairs
   bool built, built64, index_valid;
-  bool index_blocks;         // the lists are those of the block gather (else 4^3 sub-bricks)
   // scratch
   float2 *d_rq;              // [n_rq]: padded rows (RQ_PAD), the padding always zero
   double2 *d_rq64;           // [N + 2] likewise (workspaces with PVR_WS_F64)
@@ -740,7 +735,7 @@ struct pvr_plan {
   unsigned *d_status;        // [1] fault flags (PVR_FAULT_*), read by pvr_check
   unsigned long long *d_dbg; // [1] first offending index of a debug-mode input check
   long long generation;      // bumped whenever launches recorded earlier would go stale
-  int *d_total;              // [4] index totals: brick pairs, sub-brick pairs
+  unsigned long long *d_cursor;  // [2] the index's cursor (zero between builds), pairs it listed
   char *d_reg;               // registration in step: states, geometry, partial sums (reg_state_bytes)
   unsigned long long *d_reg_stats;  // [4] registration evaluations and samples walked
                                     // (plain, then exact gradient) since the last read

@@ -115,78 +115,128 @@ static long long pair_bound(const ProbDev &pr, const StackDev &st, const PatchDe
   return n >= (double)cap ? cap : (long long)n;
 }
 
-__global__ void k_theta_to_f64(const float *__restrict__ th, double *__restrict__ out, int n) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = (double)th[i];
-}
-
-__global__ void k_copy_theta(const double *__restrict__ th, double *__restrict__ out, int n) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = th[i];
-}
-
-__global__ void __launch_bounds__(64)
+// Per-patch geometry of a build: four wavefronts per 64 patches.  The first
+// runs the motion geometry, one patch per lane; then the wavefronts derive from
+// it (through LDS) the support boxes and the group's brick range, the block
+// gather's constants, the plane walk's, and the FP64 versions of both, side by
+// side: the launch is as long as its longest chain of dependent FP64 steps and
+// strided stores (29 us with one thread per patch doing all in turn, 16 here, 2 560
+// patches).  The FP64 geometry is stored for FP64 builds only.  Keeps
+// the motion and the active set (all patches if null) for later passes.
+struct MiniGeo {
+  double G[12], H[12], cu, cv, ck, K2, cut;
+};
+template <typename TH>
+__global__ void __launch_bounds__(256)
 k_geometry(const ProbDev *__restrict__ probs, const StackDev *__restrict__ stacks,
-                           const PatchDev *__restrict__ patches, const double *__restrict__ theta,
-                           int M, double k, int psf, GeoD *__restrict__ gd, GeoF *__restrict__ gf,
-                           AdjPatch<float> *__restrict__ adj, AdjPatch<double> *__restrict__ adj64,
-                           FwdPatch<float> *__restrict__ fwd, FwdPatch<double> *__restrict__ fwd64,
-                           int *__restrict__ bb,
-                           double *__restrict__ sbox) {
-  int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= M) return;
+           const PatchDev *__restrict__ patches, const TH *__restrict__ theta_in,
+           const uint8_t *__restrict__ active_in, int M, double k, int psf, int f64,
+           double *__restrict__ theta, uint8_t *__restrict__ active, GeoD *__restrict__ gd,
+           GeoF *__restrict__ gf, AdjPatch<float> *__restrict__ adj,
+           AdjPatch<double> *__restrict__ adj64, FwdPatch<float> *__restrict__ fwd,
+           FwdPatch<double> *__restrict__ fwd64, int *__restrict__ bb, int *__restrict__ gbox,
+           double *__restrict__ sbox) {
+  __shared__ MiniGeo mini[64];
+  const int lane = threadIdx.x & 63, role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int s = blockIdx.x * 64 + lane;
+  const bool on = s < M;
+  int r6[6] = {INT_MAX, INT_MAX, INT_MAX, INT_MIN, INT_MIN, INT_MIN};
+  if (role == 0 && on) {
+    const PatchDev pt = patches[s];
+    const StackDev &st = stacks[pt.stack];
+    double th[6];
+    for (int a = 0; a < 6; ++a) {
+      th[a] = (double)theta_in[6 * s + a];
+      theta[6 * s + a] = th[a];
+    }
+    GeoD g;
+    GeoF f;
+    if (psf == PVR_PSF_SINC) make_geometry<PVR_PSF_SINC>(probs[pt.problem], st, pt, th, k, g, f, r6);
+    else make_geometry<PVR_PSF_GAUSSIAN>(probs[pt.problem], st, pt, th, k, g, f, r6);
+    MiniGeo &m = mini[lane];
+    for (int q = 0; q < 12; ++q) {
+      m.G[q] = g.G[q];
+      m.H[q] = g.H[q];
+    }
+    m.cu = g.cu; m.cv = g.cv; m.ck = g.ck; m.K2 = g.K2; m.cut = g.cut;
+    gf[s] = f;
+    if (f64) gd[s] = g;
+    active[s] = active_in ? active_in[s] : 1;
+  }
+  __syncthreads();
+  if (role == 0) {
+    if (on)
+      for (int q = 0; q < 6; ++q) bb[6 * s + q] = r6[q];
+    // union of the brick ranges of the 64 patches: a brick outside it meets none
+    // of them (empty ranges, low end above the high end, only widen it)
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        r6[r] = min(r6[r], __shfl_xor(r6[r], o, 64));
+        r6[3 + r] = max(r6[3 + r], __shfl_xor(r6[3 + r], o, 64));
+      }
+    int v = r6[0];
+#pragma unroll
+    for (int r = 1; r < 6; ++r) v = lane == r ? r6[r] : v;
+    if (lane < 6) gbox[6 * blockIdx.x + lane] = v;
+  }
+  if (!on) return;
   const PatchDev pt = patches[s];
-  const StackDev st = stacks[pt.stack];
+  const MiniGeo &m = mini[lane];
+  if (role == 0) {
+    // voxel -> pixel map and the pixel-frame support box of the patch
+    const StackDev &st = stacks[pt.stack];
+    double *o = sbox + 18 * s;
+    for (int q = 0; q < 12; ++q) o[q] = m.G[q];
+    const bool sinc = psf == PVR_PSF_SINC;
+    const double ru = sinc ? st.wz[0] / st.spacing[0] : k * st.sigma[0] / st.spacing[0],
+                 rv = sinc ? st.wz[1] / st.spacing[1] : k * st.sigma[1] / st.spacing[1],
+                 rk = k * st.sigma[2] / st.spacing[2];
+    o[12] = pt.x0 - ru; o[13] = pt.x0 + pt.w - 1 + ru;
+    o[14] = pt.y0 - rv; o[15] = pt.y0 + pt.h - 1 + rv;
+    o[16] = pt.slice - rk; o[17] = pt.slice + rk;
+    return;
+  }
+  if (role == 3 && !f64) return;
   GeoD g;
-  GeoF f;
-  if (psf == PVR_PSF_SINC)
-    make_geometry<PVR_PSF_SINC>(probs[pt.problem], st, pt, theta + 6 * s, k, g, f, bb + 6 * s);
-  else
-    make_geometry<PVR_PSF_GAUSSIAN>(probs[pt.problem], st, pt, theta + 6 * s, k, g, f, bb + 6 * s);
-  gd[s] = g;
-  gf[s] = f;
-  AdjPatch<float> a;
-  make_adj(g, pt, a);
-  adj[s] = a;
-  make_fwd(g, probs[pt.problem], pt, fwd[s]);
-  if (adj64) {
-    AdjPatch<double> a64;
-    make_adj(g, pt, a64);
-    adj64[s] = a64;
+  for (int q = 0; q < 12; ++q) {
+    g.G[q] = m.G[q];
+    g.H[q] = m.H[q];
+  }
+  g.cu = m.cu; g.cv = m.cv; g.ck = m.ck; g.K2 = m.K2; g.cut = m.cut;
+  g.psf = psf;
+  if (role == 1) make_adj(g, pt, adj[s]);
+  if (role == 2) make_fwd(g, probs[pt.problem], pt, fwd[s]);
+  if (role == 3) {
+    make_adj(g, pt, adj64[s]);
     make_fwd(g, probs[pt.problem], pt, fwd64[s]);
   }
-  // voxel -> pixel map and the pixel-frame support box of the patch
-  double *o = sbox + 18 * s;
-  for (int q = 0; q < 12; ++q) o[q] = g.G[q];
-  const bool sinc = psf == PVR_PSF_SINC;
-  const double ru = sinc ? st.wz[0] / st.spacing[0] : k * st.sigma[0] / st.spacing[0],
-               rv = sinc ? st.wz[1] / st.spacing[1] : k * st.sigma[1] / st.spacing[1],
-               rk = k * st.sigma[2] / st.spacing[2];
-  o[12] = pt.x0 - ru; o[13] = pt.x0 + pt.w - 1 + ru;
-  o[14] = pt.y0 - rv; o[15] = pt.y0 + pt.h - 1 + rv;
-  o[16] = pt.slice - rk; o[17] = pt.slice + rk;
 }
 
-// Per-sample inverse normaliser 1/Z_j (0 marks an invalid sample).
+// Per-sample inverse normaliser 1/Z_j (0 marks an invalid sample).  Keeps the
+// sample mask (all ones if null) for later passes.
 template <typename T>
 __global__ void __launch_bounds__(SIM_THREADS)
 k_normalisers(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ patches,
               const BlockWork *__restrict__ work, const typename GeoOf<T>::type *__restrict__ geo,
               const uint8_t *__restrict__ mask, const uint8_t *__restrict__ active,
-              float *__restrict__ invz, double *__restrict__ invz64) {
+              uint8_t *__restrict__ keep, float *__restrict__ invz, double *__restrict__ invz64) {
   const BlockWork wk = work[blockIdx.x];
   const PatchDev pt = patches[wk.patch];
   const ProbDev pr = probs[pt.problem];
   const typename GeoOf<T>::type &g = geo[wk.patch];
   const int n = pt.w * pt.h;
   const int l1 = min(n, wk.l0 + SIM_CHUNK);
-  const bool act = active ? active[wk.patch] != 0 : true;
+  const bool act = active[wk.patch] != 0;
   for (int l = wk.l0 + threadIdx.x; l < l1; l += SIM_THREADS) {
     const long long j = pt.off + l;
     const int u = pt.x0 + l % pt.w, v = pt.y0 + l / pt.w;
     int b[3];
     T f[3];
-    bool ok = sample_centre(g, pr, u, v, pt.slice, b, f) && act && (!mask || mask[j]);
+    const uint8_t kept = mask ? mask[j] : 1;
+    keep[j] = kept;
+    bool ok = sample_centre(g, pr, u, v, pt.slice, b, f) && act && kept;
     T z = 0, acc = 0;
     if (ok && g.psf == PVR_PSF_SINC) {
       const __amdgpu_buffer_rsrc_t none = raw_buffer((const T *)nullptr, 0u);
@@ -210,8 +260,8 @@ k_normalisers_planes(const ProbDev *__restrict__ probs, const PatchDev *__restri
                      const BlockWork *__restrict__ work,
                      const typename GeoOf<T>::type *__restrict__ geo,
                      const FwdPatch<T> *__restrict__ fwd, const uint8_t *__restrict__ mask,
-                     const uint8_t *__restrict__ active, float *__restrict__ invz,
-                     double *__restrict__ invz64) {
+                     const uint8_t *__restrict__ active, uint8_t *__restrict__ keep,
+                     float *__restrict__ invz, double *__restrict__ invz64) {
   const BlockWork wk = work[blockIdx.x];
   const PatchDev pt = patches[wk.patch];
   const ProbDev pr = probs[pt.problem];
@@ -221,7 +271,7 @@ k_normalisers_planes(const ProbDev *__restrict__ probs, const PatchDev *__restri
   const PlaneLane pl = plane_lane(pt, wk.l0);
   const int nbu = (pt.w + 1) / 2;
   const int u0 = 2 * (pl.blk % nbu), v0 = 2 * (pl.blk / nbu);
-  const bool act = active ? active[wk.patch] != 0 : true;
+  const bool act = active[wk.patch] != 0;
   bool ok[4];  // pixel (u0 + i, v0 + j) at 2 j + i
   T z[4];
 #pragma unroll
@@ -230,8 +280,13 @@ k_normalisers_planes(const ProbDev *__restrict__ probs, const PatchDev *__restri
     int b[3];
     T f[3];
     ok[t] = pl.on && u < pt.w && v < pt.h && act &&
-            sample_centre(g, pr, pt.x0 + u, pt.y0 + v, pt.slice, b, f) &&
-            (!mask || mask[pt.off + (long long)v * pt.w + u]);
+            sample_centre(g, pr, pt.x0 + u, pt.y0 + v, pt.slice, b, f);
+    if (pl.on && u < pt.w && v < pt.h) {
+      const long long j = pt.off + (long long)v * pt.w + u;
+      const uint8_t kept = mask ? mask[j] : 1;
+      if (pl.part == 0) keep[j] = kept;
+      ok[t] = ok[t] && kept;
+    }
     z[t] = 0;
   }
   const bool live = ok[0] || ok[1] || ok[2] || ok[3];
@@ -273,13 +328,12 @@ k_normalisers_planes(const ProbDev *__restrict__ probs, const PatchDev *__restri
   }
 }
 
-// brick -> patch index: count, scan, fill.  Every brick scans the patches of
-// its problem in order, so each list is sorted by patch (deterministic).  A
+// Adjoint index: per brick the lists of the patches that reach its parts.  A
 // patch is listed when the brick is inside its voxel bounding box and the
-// brick's corner voxels, mapped into the patch's pixel frame, overlap the
-// patch's support box on each of the three stack axes (separating-axis
-// test; conservative).
-__device__ __forceinline__ bool box_meets_patch(const double *__restrict__ sb, const double lo[3],
+// part's corner voxels, mapped into the patch's pixel frame, overlap the
+// patch's support box on each of the three stack axes (separating-axis test;
+// conservative).
+__device__ __forceinline__ bool box_meets_patch(const double *sb, const double lo[3],
                                                 const double hi[3]) {
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
@@ -296,263 +350,195 @@ __device__ __forceinline__ bool box_meets_patch(const double *__restrict__ sb, c
   return true;
 }
 
-__device__ __forceinline__ bool brick_meets_patch(const int *__restrict__ r, const double *__restrict__ sb,
-                                                  int bx, int by, int bz) {
-  if (!((bx >= r[0]) & (bx <= r[3]) & (by >= r[1]) & (by <= r[4]) & (bz >= r[2]) & (bz <= r[5])))
-    return false;
-  const double lo[3] = {(double)(bx * BRICK), (double)(by * BRICK), (double)(bz * BRICK)};
-  const double hi[3] = {lo[0] + BRICK - 1, lo[1] + BRICK - 1, lo[2] + BRICK - 1};
-  return box_meets_patch(sb, lo, hi);
-}
-
-// Second level: each brick's 8 sub-bricks (SUB^3 voxels, one wavefront of the
-// adjoint each) keep the patches of the brick's list that reach them.
-__device__ __forceinline__ void sub_box(const ProbDev &pr, int sbi, double lo[3], double hi[3]) {
-  const int bi = sbi >> 3, w = sbi & 7;
-  const int local = bi - pr.brick_base;
-  const int bx = local % pr.nbx, by = (local / pr.nbx) % pr.nby, bz = local / (pr.nbx * pr.nby);
-  lo[0] = bx * BRICK + (w & 1) * SUB;
-  lo[1] = by * BRICK + ((w >> 1) & 1) * SUB;
-  lo[2] = bz * BRICK + (w >> 2) * SUB;
-  for (int a = 0; a < 3; ++a) hi[a] = lo[a] + SUB - 1;
-}
-
-// One wavefront per brick: the lanes take 64 entries of the brick's list at
-// a time and test each entry's patch against the 8 sub-bricks; per
-// sub-brick a ballot counts the hits (k_sub_count) or places them in list
-// order, which is ascending patch order (k_sub_fill).
-__device__ __forceinline__ unsigned sub_mask(const ProbDev &pr, int bi,
-                                             const double *__restrict__ sb) {
+// The parts of brick b that a patch reaches, one bit each.  NL = 8: the
+// sub-bricks (SUB^3 voxels, one wavefront of the per-voxel gather each).
+// NL = 6: the halves along the patch's normal axis an (bit 2 an + half,
+// 8 x 8 x 4 voxels, one wavefront of the block gather each).
+template <int NL>
+__device__ __forceinline__ unsigned part_mask(const int b[3], int an, const double *__restrict__ sb) {
+  double g[18];
+  const double2 *s2 = reinterpret_cast<const double2 *>(sb);  // 144-byte rows
+#pragma unroll
+  for (int q = 0; q < 9; ++q) {
+    const double2 v = s2[q];
+    g[2 * q] = v.x;
+    g[2 * q + 1] = v.y;
+  }
   unsigned m = 0;
 #pragma unroll
-  for (int w = 0; w < 8; ++w) {
-    double lo[3], hi[3];
-    sub_box(pr, bi * 8 + w, lo, hi);
-    m |= box_meets_patch(sb, lo, hi) ? 1u << w : 0u;
-  }
-  return m;
-}
-
-__global__ void __launch_bounds__(256)
-k_sub_count(const ProbDev *__restrict__ probs, const int *__restrict__ brick_prob,
-            const double *__restrict__ sbox, int nb, const int *__restrict__ off,
-            const int *__restrict__ list, int *__restrict__ count) {
-  const int lane = threadIdx.x & 63;
-  const int bi = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-  if (bi >= nb) return;  // uniform over the wavefront
-  const ProbDev pr = probs[brick_prob[bi]];
-  int c[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int q0 = off[bi]; q0 < off[bi + 1]; q0 += 64) {
-    const int q = q0 + lane;
-    const unsigned m = q < off[bi + 1] ? sub_mask(pr, bi, sbox + 18 * list[q]) : 0u;
-#pragma unroll
-    for (int w = 0; w < 8; ++w) c[w] += __popcll(__ballot((m >> w) & 1u));
-  }
-  if (lane < 8) {
-    int v = c[0];
-#pragma unroll
-    for (int w = 1; w < 8; ++w) v = lane == w ? c[w] : v;
-    count[bi * 8 + lane] = v;
-  }
-}
-
-__global__ void __launch_bounds__(256)
-k_sub_fill(const ProbDev *__restrict__ probs, const int *__restrict__ brick_prob,
-           const double *__restrict__ sbox, int nb, const int *__restrict__ off,
-           const int *__restrict__ list, const int *__restrict__ soff,
-           int *__restrict__ slist) {
-  const int lane = threadIdx.x & 63;
-  const int bi = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-  if (bi >= nb) return;  // uniform over the wavefront
-  const ProbDev pr = probs[brick_prob[bi]];
-  const unsigned long long below = (1ull << lane) - 1ull;
-  int c[8], end[8];
-#pragma unroll
-  for (int w = 0; w < 8; ++w) {
-    c[w] = soff[bi * 8 + w];
-    end[w] = soff[bi * 8 + w + 1];  // clamped to the capacity
-  }
-  for (int q0 = off[bi]; q0 < off[bi + 1]; q0 += 64) {
-    const int q = q0 + lane;
-    const int sp = q < off[bi + 1] ? list[q] : 0;
-    const unsigned m = q < off[bi + 1] ? sub_mask(pr, bi, sbox + 18 * sp) : 0u;
-#pragma unroll
-    for (int w = 0; w < 8; ++w) {
-      const bool h = (m >> w) & 1u;
-      const unsigned long long bal = __ballot(h);
-      const int pos = c[w] + __popcll(bal & below);
-      if (h && pos < end[w]) slist[pos] = sp;
-      c[w] += __popcll(bal);
-    }
-  }
-}
-
-// The block gather's lists: per brick, normal axis and half of the brick
-// along it (list 6 bi + 2 axis + half), the patches of the brick's list with
-// that normal axis whose support box meets the half (8 x 8 x 4 voxels, one
-// wavefront of the gather).
-__device__ __forceinline__ unsigned half_mask(const ProbDev &pr, int bi, int an,
-                                              const double *__restrict__ sb) {
-  const int local = bi - pr.brick_base;
-  const int b[3] = {local % pr.nbx, (local / pr.nbx) % pr.nby, local / (pr.nbx * pr.nby)};
-  unsigned m = 0;
-#pragma unroll
-  for (int half = 0; half < 2; ++half) {
+  for (int w = 0; w < (NL == 6 ? 2 : 8); ++w) {
     double lo[3], hi[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      lo[a] = b[a] * BRICK + (a == an ? half * SUB : 0);
-      hi[a] = lo[a] + (a == an ? SUB : BRICK) - 1;
+      const bool cut = NL == 8 || a == an;
+      const int o = NL == 8 ? (w >> a) & 1 : w;
+      lo[a] = b[a] * BRICK + (cut ? o * SUB : 0);
+      hi[a] = lo[a] + (cut ? SUB : BRICK) - 1;
     }
-    m |= box_meets_patch(sb, lo, hi) ? 1u << (2 * an + half) : 0u;
+    m |= box_meets_patch(g, lo, hi) ? (NL == 6 ? 1u << (2 * an + w) : 1u << w) : 0u;
   }
   return m;
 }
 
-template <bool FILL>
-__global__ void __launch_bounds__(256)
-k_half_lists(const ProbDev *__restrict__ probs, const int *__restrict__ brick_prob,
-             const double *__restrict__ sbox, const AdjPatch<float> *__restrict__ adj, int nb,
-             const int *__restrict__ off, const int *__restrict__ list,
-             int *__restrict__ count, const int *__restrict__ soff, int *__restrict__ slist) {
+constexpr int PGROUP = 64;  // patches per range union (k_geometry)
+__device__ __forceinline__ bool brick_in_range(const int *__restrict__ r, const int b[3]) {
+  return b[0] >= r[0] && b[0] <= r[3] && b[1] >= r[1] && b[1] <= r[4] && b[2] >= r[2] && b[2] <= r[5];
+}
+
+// The lists of NL parts per brick in one launch, one wavefront per brick: the
+// lanes first test 64 patch groups' range unions at once, then the 64 patches
+// of each group whose union holds the brick, four groups' loads in flight; the
+// patches whose own range holds it queue up in LDS and are taken 64 at a time
+// through the separating-axis tests.  The hits (patch and parts) wait in LDS
+// until the workgroup has reserved space for its bricks' lists with one
+// addition to the cursor; then each list is written in ascending patch order
+// (ballot prefix counts), the order that fixes the adjoint's summation order.
+// Where the reserved space lies varies from run to run, the lists do not.  A
+// brick with more hits than LDS holds tests its patches again instead.  off:
+// NL + 1 entries per brick, clamped to the capacity `cap`; a total beyond it
+// (which the host bound on the pairs rules out) raises PVR_FAULT_INDEX.
+// Bound by each wavefront's chain of loads.  Before, eleven launches (brick
+// lists, then lists of their parts, each counted, scanned and filled): 160^3,
+// 2 560 patches 195 us, now 33; 96^3 92 and 15, 48^3 66 and 12; testing each group's
+// 64 patches where they stand, with no queue, 107, 36 and 20.  At 80 registers
+// (6 wavefronts a SIMD) 256^3 with 11 760 patches takes 208 us, at 82 registers 230,
+// at 64 (spills) 336.
+constexpr int LIST_BRICKS = 8, LIST_HITS = 512;
+template <int NL>
+__global__ void __launch_bounds__(64 * LIST_BRICKS, NL == 6 ? 6 : 4)
+k_adj_lists(const ProbDev *__restrict__ probs, const int *__restrict__ brick_prob,
+            const int *__restrict__ bb, const int *__restrict__ gbox,
+            const double *__restrict__ sbox, const AdjPatch<float> *__restrict__ adj, int nb,
+            unsigned long long *__restrict__ cursor, int *__restrict__ off,
+            int *__restrict__ list, long long cap, unsigned *__restrict__ status) {
+  __shared__ unsigned hits[LIST_BRICKS][LIST_HITS];  // (patch - patch_begin) << 8 | parts
+  __shared__ int queue[LIST_BRICKS][320];            // candidates: under 64 left, four groups added
+  __shared__ int total[LIST_BRICKS];
+  __shared__ unsigned long long base;
   const int lane = threadIdx.x & 63;
-  const int bi = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-  if (bi >= nb) return;  // uniform over the wavefront
-  const ProbDev pr = probs[brick_prob[bi]];
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int bi = blockIdx.x * LIST_BRICKS + wv;
+  const bool on = bi < nb;  // uniform over the wavefront
+  const ProbDev &pr = probs[brick_prob[on ? bi : 0]];
+  const int local = bi - pr.brick_base;
+  const int b[3] = {local % pr.nbx, (local / pr.nbx) % pr.nby, local / (pr.nbx * pr.nby)};
+  const int p0 = pr.patch_begin, p1 = pr.patch_end;
   const unsigned long long below = (1ull << lane) - 1ull;
-  int c[6], end[6];
+  int c[NL];
 #pragma unroll
-  for (int w = 0; w < 6; ++w) {
-    c[w] = FILL ? soff[bi * 6 + w] : 0;
-    end[w] = FILL ? soff[bi * 6 + w + 1] : 0;  // clamped to the capacity
+  for (int w = 0; w < NL; ++w) c[w] = 0;
+  // calls f(s, m) for 64 candidate patches at a time, m the lane's parts
+  auto each = [&](auto &&f) {
+    if (!on || p1 <= p0) return;
+    int nq = 0;
+    auto take = [&](int q0, int n) {  // queue[q0 .. q0 + n), n <= 64
+      const int s = lane < n ? queue[wv][q0 + lane] : -1;
+      unsigned m = 0;
+      if (s >= 0)
+        m = part_mask<NL>(b, NL == 6 ? adj_normal_axis(adj[s].cls) : 0, sbox + 18 * s);
+      f(s, m);
+    };
+    const int g1 = (p1 - 1) / PGROUP;
+    for (int G0 = p0 / PGROUP; G0 <= g1; G0 += 64) {
+      const int Gl = G0 + lane;
+      unsigned long long hit = __ballot(Gl <= g1 && brick_in_range(gbox + 6 * Gl, b));
+      while (hit) {
+        int s[4];
+        int2 r[4][3];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          s[i] = hit ? (G0 + __builtin_ctzll(hit)) * PGROUP + lane : -1;
+          hit &= hit - 1;
+          if (s[i] < p0 || s[i] >= p1) s[i] = -1;
+          const int2 *q = reinterpret_cast<const int2 *>(bb + 6 * (s[i] < 0 ? p0 : s[i]));
+#pragma unroll
+          for (int k = 0; k < 3; ++k) r[i][k] = q[k];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int rr[6] = {r[i][0].x, r[i][0].y, r[i][1].x, r[i][1].y, r[i][2].x, r[i][2].y};
+          const bool in = s[i] >= 0 && brick_in_range(rr, b);
+          const unsigned long long bal = __ballot(in);
+          if (in) queue[wv][nq + __popcll(bal & below)] = s[i];
+          nq += __popcll(bal);
+        }
+        if (nq >= 64) {
+          __builtin_amdgcn_wave_barrier();
+          int q0 = 0;
+          for (; q0 + 64 <= nq; q0 += 64) take(q0, 64);
+          const int rest = nq - q0;
+          const int keep = lane < rest ? queue[wv][q0 + lane] : 0;
+          __builtin_amdgcn_wave_barrier();
+          if (lane < rest) queue[wv][lane] = keep;
+          nq = rest;
+        }
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (nq) take(0, nq);
+  };
+  int n = 0;
+  each([&](int s, unsigned m) {
+    const unsigned long long any = __ballot(m != 0);
+    if (!any) return;
+    const int pos = n + __popcll(any & below);
+    if (m && pos < LIST_HITS) hits[wv][pos] = (unsigned)(s - p0) << 8 | m;
+    n += __popcll(any);
+#pragma unroll
+    for (int w = 0; w < NL; ++w) c[w] += __popcll(__ballot((m >> w) & 1u));
+  });
+  int sum = 0;
+#pragma unroll
+  for (int w = 0; w < NL; ++w) sum += c[w];
+  if (lane == 0) total[wv] = sum;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    unsigned long long t = 0;
+    for (int w = 0; w < LIST_BRICKS; ++w) t += (unsigned)total[w];
+    // low 40 bits: pairs reserved, above: workgroups that did; the last one
+    // leaves the cursor at zero for the next index and the total beside it
+    const unsigned long long was = atomicAdd(cursor, t | 1ull << 40);
+    base = was & ((1ull << 40) - 1);
+    if (base + t > (unsigned long long)cap) atomicOr(status, PVR_FAULT_INDEX);
+    if ((was >> 40) == gridDim.x - 1) {
+      cursor[1] = base + t;
+      cursor[0] = 0;
+    }
   }
-  for (int q0 = off[bi]; q0 < off[bi + 1]; q0 += 64) {
-    const int q = q0 + lane;
-    const bool ok = q < off[bi + 1];
-    const int sp = ok ? list[q] : 0;
-    const unsigned m = ok ? half_mask(pr, bi, adj_normal_axis(adj[sp].cls), sbox + 18 * sp) : 0u;
+  __syncthreads();
+  if (!on) return;
+  long long at = (long long)base;
+  for (int w = 0; w < wv; ++w) at += total[w];
+  int end[NL];
+  int first = 0;  // lane w: start of list w, lane NL: the end
 #pragma unroll
-    for (int w = 0; w < 6; ++w) {
+  for (int w = 0; w < NL; ++w) {
+    const int start = (int)min(at, cap);
+    first = lane == w ? start : first;
+    at += c[w];
+    end[w] = (int)min(at, cap);
+    c[w] = start;
+  }
+  first = lane == NL ? end[NL - 1] : first;
+  if (lane <= NL) off[(long long)bi * (NL + 1) + lane] = first;
+  auto put = [&](int s, unsigned m) {
+#pragma unroll
+    for (int w = 0; w < NL; ++w) {
       const bool h = (m >> w) & 1u;
       const unsigned long long bal = __ballot(h);
-      if (FILL) {
-        const int pos = c[w] + __popcll(bal & below);
-        if (h && pos < end[w]) slist[pos] = sp;
-      }
+      const int pos = c[w] + __popcll(bal & below);
+      if (h && pos < end[w]) list[pos] = s;
       c[w] += __popcll(bal);
     }
+  };
+  if (n > LIST_HITS) {
+    each(put);
+    return;
   }
-  if (!FILL && lane < 6) {
-    int v = c[0];
-#pragma unroll
-    for (int w = 1; w < 6; ++w) v = lane == w ? c[w] : v;
-    count[bi * 6 + lane] = v;
-  }
-}
-
-// Union of the brick ranges of 64 consecutive patches (group G holds the
-// patches 64 G .. 64 G + 63 of the whole table): a brick outside it meets
-// none of them.  Empty ranges (low end above the high end) only widen it.
-constexpr int PGROUP = 64;
-__global__ void __launch_bounds__(256)
-k_group_box(const int *__restrict__ bb, int M, int *__restrict__ gbox) {
-  const int lane = threadIdx.x & 63;
-  const int G = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (G * PGROUP >= M) return;  // uniform over the wavefront
-  const int s = G * PGROUP + lane;
-  const bool ok = s < M;
-  int v[6];
-#pragma unroll
-  for (int r = 0; r < 3; ++r) {
-    v[r] = ok ? bb[6 * s + r] : INT_MAX;
-    v[3 + r] = ok ? bb[6 * s + 3 + r] : INT_MIN;
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-      v[r] = min(v[r], __shfl_xor(v[r], o, 64));
-      v[3 + r] = max(v[3 + r], __shfl_xor(v[3 + r], o, 64));
-    }
-  if (lane < 6) gbox[6 * G + lane] = v[lane];
-}
-
-__device__ __forceinline__ bool brick_in_group(const int *__restrict__ gb, int bx, int by, int bz) {
-  return bx >= gb[0] && bx <= gb[3] && by >= gb[1] && by <= gb[4] && bz >= gb[2] && bz <= gb[5];
-}
-
-// One wavefront per brick: over the groups that hold the brick's problem's
-// patches, the lanes first test 64 group ranges at once, then the 64
-// patches of each group whose range union holds the brick.  The count is a
-// wave sum; the fill writes the meeting patches in ascending patch order
-// (ballot prefix counts), the order that fixes the adjoint's summation
-// order.
-constexpr int BIN_THREADS = 256;
-
-__global__ void __launch_bounds__(BIN_THREADS)
-k_bin_count(const ProbDev *__restrict__ probs, const int *__restrict__ brick_prob,
-            const int *__restrict__ bb, const int *__restrict__ gbox,
-            const double *__restrict__ sbox, int nb, int *__restrict__ count) {
-  const int lane = threadIdx.x & 63;
-  const int bi = __builtin_amdgcn_readfirstlane(blockIdx.x * (BIN_THREADS / 64) + (threadIdx.x >> 6));
-  if (bi >= nb) return;  // uniform over the wavefront
-  const ProbDev pr = probs[brick_prob[bi]];
-  const int local = bi - pr.brick_base;
-  const int bx = local % pr.nbx, by = (local / pr.nbx) % pr.nby, bz = local / (pr.nbx * pr.nby);
-  int c = 0;
-  if (pr.patch_end > pr.patch_begin) {
-    const int g1 = (pr.patch_end - 1) / PGROUP;
-    for (int G0 = pr.patch_begin / PGROUP; G0 <= g1; G0 += 64) {
-      // the lanes test 64 groups at once; the groups that hold the brick
-      // are then taken in ascending order
-      const int Gl = G0 + lane;
-      unsigned long long hit = __ballot(Gl <= g1 && brick_in_group(gbox + 6 * Gl, bx, by, bz));
-      while (hit) {
-        const int G = G0 + __builtin_ctzll(hit);
-        hit &= hit - 1;
-        const int s = G * PGROUP + lane;
-        if (s >= pr.patch_begin && s < pr.patch_end &&
-            brick_meets_patch(bb + 6 * s, sbox + 18 * s, bx, by, bz))
-          ++c;
-      }
-    }
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
-  if (lane == 0) count[bi] = c;
-}
-
-__global__ void __launch_bounds__(BIN_THREADS)
-k_bin_fill(const ProbDev *__restrict__ probs, const int *__restrict__ brick_prob,
-           const int *__restrict__ bb, const int *__restrict__ gbox,
-           const double *__restrict__ sbox, int nb, const int *__restrict__ off,
-           int *__restrict__ list) {
-  const int lane = threadIdx.x & 63;
-  const int bi = __builtin_amdgcn_readfirstlane(blockIdx.x * (BIN_THREADS / 64) + (threadIdx.x >> 6));
-  if (bi >= nb) return;  // uniform over the wavefront
-  const ProbDev pr = probs[brick_prob[bi]];
-  const int local = bi - pr.brick_base;
-  const int bx = local % pr.nbx, by = (local / pr.nbx) % pr.nby, bz = local / (pr.nbx * pr.nby);
-  const unsigned long long below = (1ull << lane) - 1ull;
-  int c = off[bi];
-  const int end = off[bi + 1];  // the list's end, clamped to its capacity
-  if (pr.patch_end > pr.patch_begin) {
-    const int g1 = (pr.patch_end - 1) / PGROUP;
-    for (int G0 = pr.patch_begin / PGROUP; G0 <= g1; G0 += 64) {
-      const int Gl = G0 + lane;
-      unsigned long long hit = __ballot(Gl <= g1 && brick_in_group(gbox + 6 * Gl, bx, by, bz));
-      while (hit) {
-        const int G = G0 + __builtin_ctzll(hit);
-        hit &= hit - 1;
-        const int s = G * PGROUP + lane;
-        const bool m = s >= pr.patch_begin && s < pr.patch_end &&
-                       brick_meets_patch(bb + 6 * s, sbox + 18 * s, bx, by, bz);
-        const unsigned long long bal = __ballot(m);
-        const int pos = c + __popcll(bal & below);
-        if (m && pos < end) list[pos] = s;
-        c += __popcll(bal);
-      }
-    }
+  for (int q0 = 0; q0 < n; q0 += 64) {
+    const int q = q0 + lane;
+    const unsigned e = q < n ? hits[wv][q] : 0u;
+    put(p0 + (int)(e >> 8), e & 255u);
   }
 }
 
@@ -567,105 +553,6 @@ __global__ void k_tile_boxmax(const ProbDev *__restrict__ probs, const PatchDev 
   int lo[3], hi[3];
   const int c = tile_box(geo[tw.patch], probs[pt.problem], pt, tw, lo, hi);
   atomicMax(out, c);
-}
-
-// Exclusive scan of count[0..n) into off[0..n], off[n] = total, in three
-// passes: block sums over chunks of SCAN_CHUNK counts (each thread four
-// consecutive ones), one workgroup scanning the block sums (tiles of
-// SCAN_T with a carry) and writing the total, then every block scanning its
-// chunk from its base.  The offsets are clamped to the list's capacity
-// `cap`; a total beyond it (which the host bound on the pairs rules out)
-// raises PVR_FAULT_INDEX, and the lists then keep only what fits.
-constexpr int SCAN_T = 1024, SCAN_PER = 4, SCAN_CHUNK = SCAN_T * SCAN_PER;
-
-static int scan_blocks(long long n) { return (int)((n + SCAN_CHUNK - 1) / SCAN_CHUNK); }
-
-// inclusive scan of one value per thread across the workgroup (Hillis-Steele)
-__device__ __forceinline__ long long block_incl_scan(long long v, long long *lds) {
-  const int tid = threadIdx.x;
-  lds[tid] = v;
-  __syncthreads();
-  for (int d = 1; d < SCAN_T; d <<= 1) {
-    const long long u = tid >= d ? lds[tid - d] : 0;
-    __syncthreads();
-    lds[tid] += u;
-    __syncthreads();
-  }
-  return lds[tid];
-}
-
-__global__ void __launch_bounds__(SCAN_T)
-k_scan_sums(const int *__restrict__ count, int n, long long *__restrict__ bsum) {
-  __shared__ long long lds[SCAN_T / 64];
-  const int base = blockIdx.x * SCAN_CHUNK + threadIdx.x * SCAN_PER;
-  long long v = 0;
-#pragma unroll
-  for (int q = 0; q < SCAN_PER; ++q)
-    if (base + q < n) v += count[base + q];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    long long t = 0;
-    for (int w = 0; w < SCAN_T / 64; ++w) t += lds[w];
-    bsum[blockIdx.x] = t;
-  }
-}
-
-__global__ void __launch_bounds__(SCAN_T)
-k_scan_top(long long *__restrict__ bsum, int nblk, int n, int *__restrict__ off,
-           int *__restrict__ total, long long cap, unsigned *__restrict__ status) {
-  __shared__ long long lds[SCAN_T];
-  long long carry = 0;
-  for (int t0 = 0; t0 < nblk; t0 += SCAN_T) {
-    const int i = t0 + threadIdx.x;
-    const long long v = i < nblk ? bsum[i] : 0;
-    const long long incl = block_incl_scan(v, lds);
-    if (i < nblk) bsum[i] = carry + incl - v;  // the block's base
-    carry += lds[SCAN_T - 1];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    off[n] = (int)min(carry, cap);
-    total[0] = (int)min(carry, cap);
-    if (carry > cap) atomicOr(status, PVR_FAULT_INDEX);
-  }
-}
-
-__global__ void __launch_bounds__(SCAN_T)
-k_scan_apply(const int *__restrict__ count, int n, const long long *__restrict__ bbase,
-             int *__restrict__ off, long long cap) {
-  __shared__ long long lds[SCAN_T];
-  const int base = blockIdx.x * SCAN_CHUNK + threadIdx.x * SCAN_PER;
-  int c[SCAN_PER];
-  long long v = 0;
-#pragma unroll
-  for (int q = 0; q < SCAN_PER; ++q) {
-    c[q] = base + q < n ? count[base + q] : 0;
-    v += c[q];
-  }
-  long long run = bbase[blockIdx.x] + block_incl_scan(v, lds) - v;
-#pragma unroll
-  for (int q = 0; q < SCAN_PER; ++q)
-    if (base + q < n) {
-      off[base + q] = (int)min(run, cap);
-      run += c[q];
-    }
-}
-
-static pvr_status launch_scan(const int *count, int n, long long *scratch, int *off, int *total,
-                              long long cap, unsigned *status, hipStream_t stream) {
-  const int nblk = scan_blocks(n);
-  hipLaunchKernelGGL(k_scan_sums, dim3(nblk), dim3(SCAN_T), 0, stream, count, n, scratch);
-  HIP_TRY(hipGetLastError());
-  hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(SCAN_T), 0, stream, scratch, nblk, n, off, total,
-                     cap, status);
-  HIP_TRY(hipGetLastError());
-  hipLaunchKernelGGL(k_scan_apply, dim3(nblk), dim3(SCAN_T), 0, stream, count, n,
-                     (const long long *)scratch, off, cap);
-  HIP_TRY(hipGetLastError());
-  return PVR_OK;
 }
 
 // ---------------------------------------------------------------------------
@@ -917,16 +804,11 @@ static size_t layout(pvr_plan *p, char *base, int flags) {
   p->d_fwd64 = ws_take<FwdPatch<double>>(c, M);
   p->d_bb = ws_take<int>(c, 6 * M);
   p->d_gbox = ws_take<int>(c, 6 * ((M + 63) / 64));
-  p->d_scan = ws_take<long long>(c, (8 * nb + 4095) / 4096 + 1);
   p->d_sbox = ws_take<double>(c, 18 * M);
   p->d_invz = ws_take<float>(c, N);
   p->d_mask = ws_take<uint8_t>(c, N);
   p->d_active = ws_take<uint8_t>(c, M);
-  p->d_bin_count = ws_take<int>(c, nb);
-  p->d_bin_off = ws_take<int>(c, nb + 1);
-  p->d_bin_patch = ws_take<int>(c, p->bin_cap);
-  p->d_sub_count = ws_take<int>(c, 8 * nb);
-  p->d_sub_off = ws_take<int>(c, 8 * nb + 1);
+  p->d_sub_off = ws_take<int>(c, 9 * nb);
   p->d_sub_patch = ws_take<int>(c, p->sub_cap);
   p->d_rq = ws_take<float2>(c, p->n_rq);
   p->d_pstat = ws_take<double>(c, 10 * M);
@@ -934,7 +816,7 @@ static size_t layout(pvr_plan *p, char *base, int flags) {
   p->d_pval = ws_take<float>(c, M);
   p->d_chunk_stats = ws_take<double>(c, 5LL * std::max(p->n_sim_blocks, p->n_pblocks));
   p->d_xt = p->any_xt ? ws_take<float>(c, p->V) : nullptr;
-  p->d_total = ws_take<int>(c, 4);
+  p->d_cursor = ws_take<unsigned long long>(c, 2);
   p->d_reg_stats = ws_take<unsigned long long>(c, 4);
   {
     size_t off[4];
@@ -1004,7 +886,7 @@ extern "C" pvr_status pvr_plan_attach(pvr_plan *p, void *workspace, size_t bytes
   launch_fill_f32((float *)p->d_rq, 0.f, 2 * p->n_rq, stream);
   if (p->d_rq64) launch_fill_f64((double *)p->d_rq64, 0.0, 2 * (p->N + 2), stream);
   launch_fill_i32((int *)p->d_status, 0, 1, stream);
-  launch_fill_i32(p->d_total, 0, 4, stream);
+  launch_fill_i32((int *)p->d_cursor, 0, 4, stream);
   launch_fill_i32((int *)p->d_reg_stats, 0, 8, stream);
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipStreamSynchronize(stream));  // the uploads read pageable host tables of the plan
@@ -1034,10 +916,10 @@ extern "C" pvr_status pvr_plan_info(const pvr_plan *p, pvr_plan_sizes *out) {
   out->n_bricks = p->n_bricks;
   out->n_bin_pairs = 0;
   if (p->attached && p->index_valid) {
-    int tot[4];
+    unsigned long long n = 0;
     HIP_TRY(hipDeviceSynchronize());
-    HIP_TRY(hipMemcpy(tot, p->d_total, sizeof tot, hipMemcpyDeviceToHost));
-    out->n_bin_pairs = tot[1];
+    HIP_TRY(hipMemcpy(&n, p->d_cursor + 1, sizeof n, hipMemcpyDeviceToHost));
+    out->n_bin_pairs = std::min((long long)n, p->sub_cap);
   }
   out->device_bytes = p->attached ? (int64_t)p->ws_bytes : 0;
   out->bin_capacity = p->bin_cap;
@@ -1160,81 +1042,47 @@ extern "C" pvr_status pvr_plan_set_granules(pvr_plan *p, int32_t sim_granule,
   PVR_API_END();
 }
 
-// brick -> patch and sub-brick -> patch lists of the gather adjoint for the
-// geometry of the last build, into lists of the capacities bounded at plan
-// creation: no count is read back, nothing is synchronised.  blocks: the
-// second level lists are those of the block gather.
-pvr_status pvr::plan_build_index(pvr_plan *p, bool blocks, hipStream_t stream) {
+// The gather adjoint's lists for the geometry of the last build, into a list
+// array of the capacity bounded at plan creation: no count is read back,
+// nothing is synchronised.
+pvr_status pvr::plan_build_index(pvr_plan *p, hipStream_t stream) {
   const int nb = p->n_bricks;
-  const int nbw = (nb + BIN_THREADS / 64 - 1) / (BIN_THREADS / 64);
-  hipLaunchKernelGGL(k_group_box, dim3((p->M + 255) / 256), dim3(256), 0, stream, p->d_bb, p->M,
-                     p->d_gbox);
-  HIP_TRY(hipGetLastError());
-  hipLaunchKernelGGL(k_bin_count, dim3(nbw), dim3(BIN_THREADS), 0, stream, p->d_prob,
-                     p->d_brick_prob, p->d_bb, p->d_gbox, p->d_sbox, nb, p->d_bin_count);
-  HIP_TRY(hipGetLastError());
-  PVR_TRY_STATUS(launch_scan(p->d_bin_count, nb, p->d_scan, p->d_bin_off, p->d_total, p->bin_cap,
-                             p->d_status, stream));
-  hipLaunchKernelGGL(k_bin_fill, dim3(nbw), dim3(BIN_THREADS), 0, stream, p->d_prob,
-                     p->d_brick_prob, p->d_bb, p->d_gbox, p->d_sbox, nb, p->d_bin_off,
-                     p->d_bin_patch);
-  HIP_TRY(hipGetLastError());
-  const int nsb = nb * (blocks ? 6 : 8);
-  if (blocks)
-    hipLaunchKernelGGL(k_half_lists<false>, dim3((nb + 3) / 4), dim3(256), 0, stream, p->d_prob,
-                       p->d_brick_prob, p->d_sbox, p->d_adj, nb, p->d_bin_off, p->d_bin_patch,
-                       p->d_sub_count, nullptr, nullptr);
-  else
-    hipLaunchKernelGGL(k_sub_count, dim3((nb + 3) / 4), dim3(256), 0, stream, p->d_prob,
-                       p->d_brick_prob, p->d_sbox, nb, p->d_bin_off, p->d_bin_patch,
-                       p->d_sub_count);
-  HIP_TRY(hipGetLastError());
-  PVR_TRY_STATUS(launch_scan(p->d_sub_count, nsb, p->d_scan, p->d_sub_off, p->d_total + 1,
-                             p->sub_cap, p->d_status, stream));
-  if (blocks)
-    hipLaunchKernelGGL(k_half_lists<true>, dim3((nb + 3) / 4), dim3(256), 0, stream, p->d_prob,
-                       p->d_brick_prob, p->d_sbox, p->d_adj, nb, p->d_bin_off, p->d_bin_patch,
-                       nullptr, p->d_sub_off, p->d_sub_patch);
-  else
-    hipLaunchKernelGGL(k_sub_fill, dim3((nb + 3) / 4), dim3(256), 0, stream, p->d_prob,
-                       p->d_brick_prob, p->d_sbox, nb, p->d_bin_off, p->d_bin_patch, p->d_sub_off,
-                       p->d_sub_patch);
+  const dim3 grid((nb + LIST_BRICKS - 1) / LIST_BRICKS), block(64 * LIST_BRICKS);
+#define LIST_LAUNCH(NL)                                                                            \
+  hipLaunchKernelGGL(k_adj_lists<NL>, grid, block, 0, stream, p->d_prob, p->d_brick_prob, p->d_bb, \
+                     p->d_gbox, p->d_sbox, p->d_adj, nb, p->d_cursor, p->d_sub_off, p->d_sub_patch, \
+                     p->sub_cap, p->d_status)
+  if (p->gather_blocks) LIST_LAUNCH(6);
+  else LIST_LAUNCH(8);
+#undef LIST_LAUNCH
   HIP_TRY(hipGetLastError());
   p->index_valid = true;
-  p->index_blocks = blocks;
   ++p->generation;
   return PVR_OK;
 }
 
-static pvr_status plan_build_common(pvr_plan *p, const uint8_t *active, const uint8_t *mask,
-                                    bool f64, hipStream_t stream) {
+template <typename TH>
+static pvr_status plan_build_common(pvr_plan *p, const TH *theta, const uint8_t *active,
+                                    const uint8_t *mask, hipStream_t stream) {
   const int M = p->M;
-  if (active) {
-    HIP_TRY(hipMemcpyAsync(p->d_active, active, M, hipMemcpyDeviceToDevice, stream));
-  } else {
-    launch_fill_u8(p->d_active, 1, M, stream);
-  }
-  if (mask) {
-    HIP_TRY(hipMemcpyAsync(p->d_mask, mask, p->N, hipMemcpyDeviceToDevice, stream));
-  } else {
-    launch_fill_u8(p->d_mask, 1, p->N, stream);
-  }
-  hipLaunchKernelGGL(k_geometry, dim3((M + 63) / 64), dim3(64), 0, stream, p->d_prob, p->d_stack,
-                     p->d_patch, p->d_theta, M, p->k, p->psf, p->d_geod, p->d_geof, p->d_adj,
-                     f64 && p->d_invz64 ? p->d_adj64 : nullptr, p->d_fwd, p->d_fwd64, p->d_bb, p->d_sbox);
+  const bool f64 = sizeof(TH) == 8;
+  const bool wide = f64 && p->d_invz64;
+  hipLaunchKernelGGL(k_geometry<TH>, dim3((M + 63) / 64), dim3(256), 0, stream, p->d_prob, p->d_stack,
+                     p->d_patch, theta, active, M, p->k, p->psf, wide ? 1 : 0, p->d_theta,
+                     p->d_active, p->d_geod, p->d_geof, p->d_adj, p->d_adj64, p->d_fwd, p->d_fwd64, p->d_bb, p->d_gbox,
+                     p->d_sbox);
   HIP_TRY(hipGetLastError());
   // an FP64 build also writes FP64 normalisers when the workspace has room
   // for them (PVR_WS_F64); the FP32 ones are written either way
-  const bool wide = f64 && p->d_invz64;
 #define NORM_LAUNCH(T, GEO, FWD, OUT64)                                                            \
   if (wide ? p->planes64 : p->planes)                                                              \
     hipLaunchKernelGGL(k_normalisers_planes<T>, dim3(p->n_pblocks), dim3(PLANE_BLOCKS),              \
                        PLANE_BLOCKS * 4 * sizeof(T), stream,                                       \
-                       p->d_prob, p->d_patch, p->d_pblocks, GEO, FWD, p->d_mask, p->d_active,      \
+                       p->d_prob, p->d_patch, p->d_pblocks, GEO, FWD, mask, p->d_active, p->d_mask,  \
                        p->d_invz, OUT64);                                                          \
   else                                                                                             \
     hipLaunchKernelGGL(k_normalisers<T>, dim3(p->n_sim_blocks), dim3(SIM_THREADS), 0, stream,      \
-                       p->d_prob, p->d_patch, p->d_sim_blocks, GEO, p->d_mask, p->d_active,        \
+                       p->d_prob, p->d_patch, p->d_sim_blocks, GEO, mask, p->d_active, p->d_mask,    \
                        p->d_invz, OUT64)
   if (wide) { NORM_LAUNCH(double, p->d_geod, p->d_fwd64, p->d_invz64); }
   else { NORM_LAUNCH(float, p->d_geof, p->d_fwd, (double *)nullptr); }
@@ -1261,10 +1109,7 @@ extern "C" pvr_status pvr_plan_build(pvr_plan *p, const float *theta, const uint
   if (!p || !theta) return fail(PVR_EINVAL, "pvr_plan_build: NULL plan or theta");
   if (!p->attached) return fail(PVR_EINVAL, "pvr_plan_build: no workspace attached (pvr_plan_attach)");
   PVR_TRY_STATUS(debug_finite(p, "pvr_plan_build", "theta", theta, 6LL * p->M, stream));
-  const int n = 6 * p->M;
-  hipLaunchKernelGGL(k_theta_to_f64, dim3((n + 255) / 256), dim3(256), 0, stream, theta, p->d_theta, n);
-  HIP_TRY(hipGetLastError());
-  return plan_build_common(p, active, sample_mask, false, stream);
+  return plan_build_common(p, theta, active, sample_mask, stream);
   PVR_API_END();
 }
 
@@ -1275,9 +1120,6 @@ extern "C" pvr_status pvr_plan_build_f64(pvr_plan *p, const double *theta, const
   if (!p || !theta) return fail(PVR_EINVAL, "pvr_plan_build_f64: NULL plan or theta");
   if (!p->attached) return fail(PVR_EINVAL, "pvr_plan_build_f64: no workspace attached (pvr_plan_attach)");
   PVR_TRY_STATUS(debug_finite(p, "pvr_plan_build_f64", "theta", theta, 6LL * p->M, stream));
-  const int n = 6 * p->M;
-  hipLaunchKernelGGL(k_copy_theta, dim3((n + 255) / 256), dim3(256), 0, stream, theta, p->d_theta, n);
-  HIP_TRY(hipGetLastError());
-  return plan_build_common(p, active, sample_mask, true, stream);
+  return plan_build_common(p, theta, active, sample_mask, stream);
   PVR_API_END();
 }

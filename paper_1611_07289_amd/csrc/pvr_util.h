@@ -14,7 +14,7 @@ namespace pvr {
 pvr_status fail(pvr_status st, const char *fmt, ...) __attribute__((format(printf, 2, 3)));
 void clear_error();
 void plan_free(pvr_plan *p);
-pvr_status plan_build_index(pvr_plan *p, bool blocks, hipStream_t stream);
+pvr_status plan_build_index(pvr_plan *p, hipStream_t stream);
 pvr_status launch_bp_prep(const pvr_plan *p, const float *e, const float *pp, hipStream_t stream);
 // The registration with all patches in step (pvr_register.hip), for at most
 // REG_STEP_MAX trial steps and, with the exact gradient, at least
@@ -24,7 +24,6 @@ pvr_status register_in_step(const pvr_plan *p, const float *X, const float *XT, 
                             float *theta, float *ncc, const uint8_t *reg, const pvr_reg_params &prm,
                             hipStream_t stream);
 size_t reg_state_bytes(const pvr_plan *p, size_t off[4]);
-void launch_fill_u8(uint8_t *dst, uint8_t v, long long n, hipStream_t stream);
 void launch_fill_i32(int *dst, int v, long long n, hipStream_t stream);
 void launch_fill_f32(float *dst, float v, long long n, hipStream_t stream);
 void launch_fill_f64(double *dst, double v, long long n, hipStream_t stream);

@@ -35,7 +35,6 @@ static void fill(T *dst, T v, long long n, hipStream_t stream) {
   hipLaunchKernelGGL(k_fill<T>, dim3((unsigned)blocks), dim3(256), 0, stream, dst, v, n);
 }
 
-void launch_fill_u8(uint8_t *dst, uint8_t v, long long n, hipStream_t s) { fill<uint8_t>(dst, v, n, s); }
 void launch_fill_i32(int *dst, int v, long long n, hipStream_t s) { fill<int>(dst, v, n, s); }
 void launch_fill_f32(float *dst, float v, long long n, hipStream_t s) { fill<float>(dst, v, n, s); }
 void launch_fill_f64(double *dst, double v, long long n, hipStream_t s) { fill<double>(dst, v, n, s); }

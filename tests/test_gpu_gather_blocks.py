@@ -122,3 +122,22 @@ def test_a_non_finite_input_stays_where_its_support_is():
     # slice 2 of 5 at 4 mm lies at z = 11.5; 3 sigma through-plane is 5.1 mm
     assert bad.size and np.all(np.abs(bad[:, 0] - 11.5) <= 5.1)
     assert len(np.unique(bad[:, 1])) <= 4 and len(np.unique(bad[:, 2])) <= 4
+
+
+@pytest.mark.parametrize("spacing", [1.0, 1.8])  # halves of the block gather, sub-bricks of the other
+@pytest.mark.parametrize("n", [63, 64, 65, 700])
+def test_lists_up_to_more_patches_than_a_brick_holds_in_lds(n, spacing):
+    # n patches over every brick (more than 512 hits test their patches again)
+    g, st, P = _problem(synth.orthogonal_frames()[:1], 9, 8, 8, spacing, (spacing, spacing, 4.0))
+    P = synth.Patches(*[np.resize(np.asarray(a)[:2], n) for a in
+                        (P.stack, P.slice, P.x0, P.y0, P.w, P.h)])
+    th = _motion(n, 6.0, 1.0)
+    _check(g, st, P, th, f64=False)
+    plan = pvr.Plan([g], [st], [P])
+    r = dev(np.random.default_rng(5).normal(size=plan.N).astype(np.float32))
+    out = []
+    for _ in range(3):  # the lists are made anew: the same lists, the same sums
+        plan.build(dev(np.asarray(th, np.float32)))
+        out.append(torch.empty(plan.V, device="cuda"))
+        plan.backproject(r, None, None, out[-1], None)
+    assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
