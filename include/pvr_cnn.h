@@ -47,6 +47,16 @@ pvr_status pvr_cnn_conv_fwd(const uint16_t *in, const uint16_t *w,
                             int32_t H, int32_t W, int32_t cin, int32_t cout,
                             int32_t stride, int32_t relu, hipStream_t stream);
 
+/* The network's first two layers in one pass for a forward pass that keeps no
+ * activations: out = relu(conv3x3(relu(conv3x3(in) + b1), stride 2) + b2), the
+ * inner result rounded to BF16 as pvr_cnn_conv_fwd stores it.  in
+ * [B][H][W][2], w1 [32][3][3][2], w2 [32][3][3][32], out [B][Ho][Wo][32] with
+ * Ho = (H - 1)/2 + 1. */
+pvr_status pvr_cnn_stem_fwd(const uint16_t *in, const uint16_t *w1,
+                            const float *b1, const uint16_t *w2,
+                            const float *b2, uint16_t *out, int32_t B,
+                            int32_t H, int32_t W, hipStream_t stream);
+
 /* Gradient with respect to the layer input: gin = conv^T(gout * [out > 0]).
  * gout, out [B][Ho][Wo][cout] (out = the layer's ReLU output), wt
  * [3][3][cin][cout], gin [B][H][W][cin]. */

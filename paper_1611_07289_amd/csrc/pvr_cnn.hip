@@ -18,6 +18,8 @@
 #include "pvr_internal.h"
 #include "pvr_util.h"
 
+#include <algorithm>
+
 using namespace pvr;
 
 typedef short bf16x8 __attribute__((ext_vector_type(8)));
@@ -25,12 +27,13 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 namespace {
 
-__device__ __forceinline__ uint16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7f800000u) == 0x7f800000u) return (uint16_t)(u >> 16) | ((u & 0xffff) ? 0x40 : 0);
-  u += 0x7fffu + ((u >> 16) & 1u);  // round to nearest even
-  return (uint16_t)(u >> 16);
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+// two FP32 values to BF16, round to nearest even (one instruction)
+__device__ __forceinline__ uint32_t f2bf2(float lo, float hi) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){lo, hi}, bf16x2));
 }
+__device__ __forceinline__ uint16_t f2bf(float f) { return (uint16_t)f2bf2(f, f); }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
 union V8 {
@@ -55,19 +58,252 @@ constexpr int CT = 256;  // threads per conv workgroup (4 waves)
 }  // namespace
 
 // ---------------------------------------------------------------------------
-// forward: out = relu(conv3x3(in, W, stride S, pad 1) + bias)
+// Tiled 3x3 convolution, the forward pass (out = relu(conv3x3(in, W, stride S,
+// pad 1) + bias)) and, DG, the stride-1 data gradient (the same sum with the
+// taps mirrored, over gout * [out > 0], no bias).
 //
-// Implicit GEMM with the weights as the A operand (M = COUT) and the
-// gathered input as B (N = output pixels), K = 9 CIN, so that each lane ends
-// with four consecutive channels of one pixel and stores them as one 8-byte
-// word: no LDS staging of the output and no barrier inside the tile loop.
-// The layer's weights are staged once per workgroup into LDS, rows of K padded
-// by 8 elements; the workgroup (16 waves) then loops over tiles of 256 output
-// pixels, one 16-pixel MFMA column block per wave, so each weight is read from
-// memory once per workgroup.  The B operand is gathered from global memory, 8
-// channels (16 bytes) of one input pixel per lane per tap, zero outside the
-// image; all taps are loaded before the first MFMA so that their latencies
-// overlap.
+// Implicit GEMM with the weights as the A operand (M = NO output channels)
+// and the input as B (N = output pixels), K = 9 KC, tap after tap, so that each
+// lane ends with four consecutive channels of one pixel and stores them as one
+// 8-byte word.  A workgroup stages the layer's weights into LDS once (rows of
+// K padded by 8 elements) and loops over groups of NSUB tiles of TW x TH output
+// pixels; the tiles' input, with its border, zero outside the image, is staged
+// too (pixels padded by 8 channels; for stride 2 even columns before odd ones,
+// so that neighbouring lanes read neighbouring pixels), the next group's read
+// into registers while this one is multiplied.  A wavefront takes PB blocks of 16
+// pixels times all channels: NT + PB 16-byte LDS reads per lane and NT PB matrix
+// instructions a step, and every input value is read once from memory instead of
+// once a tap, and masked (DG) once.
+// Bound by memory where the layer is large (32x32, 32 -> 64 channels, 1024 images:
+// 201 MB in 58 us, 3.5 TB/s; 87 with each tap gathered from memory by 16 pixels a
+// wavefront), by LDS reads where it is not (16x16, 64 -> 64: 29 us; 51).  Weights in
+// registers instead of LDS were as fast (no room for the next group's input).
+// ---------------------------------------------------------------------------
+template <int KC_, int NO_, int S, int TW, int TH, int NSUB, int WAVES>
+struct TileShape {
+  static constexpr int KC = KC_, NO = NO_, K = 9 * KC, LS = K + 8;
+  static constexpr int IW = (TW - 1) * S + 3, IH = (TH - 1) * S + 3;  // input tile with its border
+  static constexpr int NE = S == 2 ? (IW + 1) / 2 : 0;                // even columns
+  static constexpr int CS = KC + 8;                                   // LDS stride of a pixel
+  static constexpr int PIX = IW * IH;
+  static constexpr int THREADS = 64 * WAVES;
+  static constexpr int CHUNKS = NSUB * PIX * (KC / 8);
+  static constexpr int NL = (CHUNKS + THREADS - 1) / THREADS;
+  static constexpr int PB = NSUB * TW * TH / 16 / WAVES, NT = NO / 16;
+  static constexpr int W_ELEMS = NO * LS, I_ELEMS = NSUB * PIX * CS;
+  static constexpr int LDS_BYTES = (W_ELEMS + I_ELEMS) * 2;
+  // column ix of an input row in LDS
+  __device__ static constexpr int slot(int ix) { return S == 2 ? (ix >> 1) + (ix & 1) * NE : ix; }
+};
+
+// One block group's products: acc[pb][nt] += W x input, tap after tap.
+template <class SH, int S, bool DG>
+__device__ __forceinline__ void tile_mma(const uint16_t *Wl, const uint16_t *It, const int (&px)[SH::PB],
+                                         int r16, int kq, f32x4 (&acc)[SH::PB][SH::NT]) {
+  constexpr int CB = SH::KC / 32;
+#pragma unroll
+  for (int tap = 0; tap < 9; ++tap) {
+    const int dy = DG ? 2 - tap / 3 : tap / 3, dx = DG ? 2 - tap % 3 : tap % 3;
+    const int o = (dy * SH::IW + SH::slot(dx)) * SH::CS;
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+      bf16x8 a[SH::PB];
+#pragma unroll
+      for (int b = 0; b < SH::PB; ++b)
+        a[b] = *reinterpret_cast<const bf16x8 *>(It + px[b] + o + cb * 32);
+#pragma unroll
+      for (int nt = 0; nt < SH::NT; ++nt) {
+        const bf16x8 w = *reinterpret_cast<const bf16x8 *>(
+            Wl + (nt * 16 + r16) * SH::LS + tap * SH::KC + cb * 32 + 8 * kq);
+#pragma unroll
+        for (int b = 0; b < SH::PB; ++b)
+          acc[b][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, a[b], acc[b][nt], 0, 0, 0);
+      }
+    }
+  }
+}
+
+// bias, ReLU, BF16: lane (kq, r16) holds channels nt*16 + 4kq .. +3 of
+// pixel p, one 8-byte store per 16-channel block
+template <int COUT, int NT>
+__device__ __forceinline__ void conv_store(uint16_t *__restrict__ out, long long p, int kq,
+                                           const f32x4 (&acc)[NT], const float (&bb)[NT][4],
+                                           int relu) {
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    float v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[i] = acc[nt][i] + bb[nt][i];
+      if (relu) v[i] = fmaxf(v[i], 0.f);  // (NaN gives 0)
+    }
+    *reinterpret_cast<uint2 *>(out + p * COUT + nt * 16 + 4 * kq) =
+        make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
+  }
+}
+
+// Image, row and column of a tile, ntx by nty an image.  ONE: a single tile an
+// image (8 x 8 tiles are used for images no larger), which saves the divisions
+// where the tile differs from lane to lane.
+struct TileAt {
+  int im, y, x;
+};
+template <bool ONE>
+__device__ __forceinline__ TileAt tile_of(int sid, int ntx, int nty) {
+  if constexpr (ONE) return TileAt{sid, 0, 0};
+  const int im = sid / (ntx * nty), t = sid - im * (ntx * nty), y = t / ntx;
+  return TileAt{im, y, t - y * ntx};
+}
+
+// Hi x Wi: the input's size, Ho x Wo the output's; n_sub tiles, ntx by nty an
+// image.
+template <int KC, int NO, int S, int TW, int TH, int NSUB, int WAVES, bool DG>
+__global__ void __launch_bounds__(64 * WAVES)
+k_conv_tile(const uint16_t *__restrict__ in, const uint16_t *__restrict__ mask,
+            const uint16_t *__restrict__ W, const float *__restrict__ bias,
+            uint16_t *__restrict__ out, int Hi, int Wi, int Ho, int Wo, int relu, int n_sub, int ntx,
+            int nty) {
+  using SH = TileShape<KC, NO, S, TW, TH, NSUB, WAVES>;
+  constexpr int NL = SH::NL, PB = SH::PB, NT = SH::NT, C8 = KC / 8;
+  __shared__ __attribute__((aligned(16))) uint16_t Wl[SH::W_ELEMS];
+  __shared__ __attribute__((aligned(16))) uint16_t It[SH::I_ELEMS];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int kq = lane >> 4, r16 = lane & 15;
+  const int n_groups = (n_sub + NSUB - 1) / NSUB;
+  uint4 g[NL], y[DG ? NL : 1];
+  const auto load = [&](int group) {
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+      const int e = j * SH::THREADS + threadIdx.x;
+      g[j] = make_uint4(0, 0, 0, 0);
+      if constexpr (DG) y[j] = g[j];
+      const int pix = e / C8, sub = NSUB == 1 ? 0 : pix / SH::PIX, rr = pix - sub * SH::PIX;
+      const int sid = group * NSUB + sub;
+      const TileAt t = tile_of<TW == 8>(sid, ntx, nty);
+      const int iy = t.y * (TH * S) - 1 + rr / SH::IW, ix = t.x * (TW * S) - 1 + rr % SH::IW;
+      if (e < SH::CHUNKS && sid < n_sub && (unsigned)iy < (unsigned)Hi && (unsigned)ix < (unsigned)Wi) {
+        const long long o = (((long long)t.im * Hi + iy) * Wi + ix) * KC + 8 * (e % C8);
+        g[j] = *reinterpret_cast<const uint4 *>(in + o);
+        if constexpr (DG) y[j] = *reinterpret_cast<const uint4 *>(mask + o);
+      }
+    }
+  };
+  const auto put = [&]() {
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+      const int e = j * SH::THREADS + threadIdx.x;
+      if (e >= SH::CHUNKS) break;
+      const int pix = e / C8, sub = NSUB == 1 ? 0 : pix / SH::PIX, rr = pix - sub * SH::PIX;
+      V8 v;
+      v.u = g[j];
+      if constexpr (DG) {
+        V8 m;
+        m.u = y[j];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (!(bf2f(m.h[i]) > 0.f)) v.h[i] = 0;
+      }
+      *reinterpret_cast<uint4 *>(
+          &It[(sub * SH::PIX + (rr / SH::IW) * SH::IW + SH::slot(rr % SH::IW)) * SH::CS + 8 * (e % C8)]) = v.u;
+    }
+  };
+  load(blockIdx.x);
+  if constexpr (DG) {  // [tap][NO][KC] -> rows of K per output channel
+    for (int e = threadIdx.x; e < 9 * NO * C8; e += SH::THREADS) {
+      const int k8 = e % C8, q = e / C8, tap = q / NO, no = q % NO;
+      *reinterpret_cast<uint4 *>(&Wl[no * SH::LS + tap * KC + 8 * k8]) =
+          *reinterpret_cast<const uint4 *>(W + (long long)q * KC + 8 * k8);
+    }
+  } else {
+    for (int e = threadIdx.x; e < NO * (SH::K / 8); e += SH::THREADS) {
+      const int no = e / (SH::K / 8), k8 = e % (SH::K / 8);
+      *reinterpret_cast<uint4 *>(&Wl[no * SH::LS + 8 * k8]) =
+          *reinterpret_cast<const uint4 *>(W + (long long)no * SH::K + 8 * k8);
+    }
+  }
+  float bb[NT][4];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bb[nt][i] = DG ? 0.f : bias[nt * 16 + 4 * kq + i];
+  int px[PB];  // LDS offset of the lane's pixel of each block (upper left tap, 8 kq channels on)
+#pragma unroll
+  for (int b = 0; b < PB; ++b) {
+    const int q = (wave * PB + b) * 16 + r16, sub = q / (TW * TH), rr = q % (TW * TH);
+    px[b] = (sub * SH::PIX + (rr / TW) * S * SH::IW + rr % TW) * SH::CS + 8 * kq;
+  }
+  put();
+  __syncthreads();
+  for (int group = blockIdx.x; group < n_groups; group += gridDim.x) {
+    const bool more = group + (int)gridDim.x < n_groups;
+    if (more) load(group + gridDim.x);
+    f32x4 acc[PB][NT];
+#pragma unroll
+    for (int b = 0; b < PB; ++b)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[b][nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    tile_mma<SH, S, DG>(Wl, It, px, r16, kq, acc);
+#pragma unroll
+    for (int b = 0; b < PB; ++b) {
+      const int q = (wave * PB + b) * 16 + r16, sub = q / (TW * TH), rr = q % (TW * TH);
+      const int sid = group * NSUB + sub;
+      const TileAt t = tile_of<TW == 8>(sid, ntx, nty);
+      const int oy = t.y * TH + rr / TW, ox = t.x * TW + rr % TW;
+      if (sid < n_sub && oy < Ho && ox < Wo)
+        conv_store<NO, NT>(out, ((long long)t.im * Ho + oy) * Wo + ox, kq, acc[b], bb, DG ? 0 : relu);
+    }
+    if (!more) break;
+    __syncthreads();
+    put();
+    __syncthreads();
+  }
+}
+
+// Workgroups: as many as fit on the chip at once by LDS, at most one a group.
+template <class SH>
+static unsigned tile_grid(long long n_groups) {
+  const long long cap = 256LL * std::max(1, std::min(4, 160 * 1024 / SH::LDS_BYTES));
+  return (unsigned)std::min(n_groups, cap);
+}
+
+template <int KC, int NO, int S, int TW, int TH, int NSUB, int WAVES, bool DG>
+static pvr_status tile_launch(const uint16_t *in, const uint16_t *mask, const uint16_t *W,
+                              const float *bias, uint16_t *out, int B, int Hi, int Wi, int Ho, int Wo,
+                              int relu, hipStream_t stream) {
+  using SH = TileShape<KC, NO, S, TW, TH, NSUB, WAVES>;
+  const int ntx = (Wo + TW - 1) / TW, nty = (Ho + TH - 1) / TH;
+  const long long n_sub = (long long)B * ntx * nty;
+  if (n_sub > 0x7fff0000LL) return fail(PVR_ESHAPE, "pvr_cnn: more than 2^31 tiles");
+  hipLaunchKernelGGL((k_conv_tile<KC, NO, S, TW, TH, NSUB, WAVES, DG>),
+                     dim3(tile_grid<SH>((n_sub + NSUB - 1) / NSUB)), dim3(SH::THREADS), 0, stream, in,
+                     mask, W, bias, out, Hi, Wi, Ho, Wo, relu, (int)n_sub, ntx, nty);
+  HIP_TRY(hipGetLastError());
+  return PVR_OK;
+}
+
+// Tiles of a layer: 16 x 16 pixels, 16 x 8 with stride 2 (their input is as
+// large), or 8 x 8 ones, four or two at a time, where the image is no larger and
+// one image a workgroup would take the chip more than a round (8x8, 64 -> 64
+// channels: 1024 images 10.4 us, 20.2 in 16 x 16 tiles; 256 images 9.2 and 7.5).
+constexpr int SMALL_MIN = 257;
+template <int KC, int NO, int S, bool DG>
+static pvr_status conv_tiled(const uint16_t *in, const uint16_t *mask, const uint16_t *W,
+                             const float *bias, uint16_t *out, int B, int Hi, int Wi, int relu,
+                             hipStream_t stream) {
+  const int Ho = (Hi - 1) / S + 1, Wo = (Wi - 1) / S + 1;
+  if (Ho <= 8 && Wo <= 8 && B >= SMALL_MIN)
+    return tile_launch<KC, NO, S, 8, 8, 4 / S, 8, DG>(in, mask, W, bias, out, B, Hi, Wi, Ho, Wo, relu, stream);
+  if constexpr (S == 2 && KC == 32)  // four wavefronts, two workgroups a compute unit by LDS
+    return tile_launch<KC, NO, S, 16, 8, 1, 4, DG>(in, mask, W, bias, out, B, Hi, Wi, Ho, Wo, relu, stream);
+  else
+    return tile_launch<KC, NO, S, 16, 16 / S, 1, 8, DG>(in, mask, W, bias, out, B, Hi, Wi, Ho, Wo, relu, stream);
+}
+
+// ---------------------------------------------------------------------------
+// forward pass of a layer of fewer than 32 input channels: K = 9 CIN <= 32 in
+// one matrix step, each lane gathering its taps from memory; the workgroup (16
+// waves) loops over tiles of 256 output pixels, one 16-pixel column block per
+// wave.  Bound by the output's stores.
 // ---------------------------------------------------------------------------
 constexpr int FW_THREADS = 1024;                       // 16 waves share the staged weights
 constexpr int FW_TILE = (FW_THREADS / 64) * 16;       // 16 output pixels per wave
@@ -80,27 +316,6 @@ struct FwdShape {
   static constexpr int LDS_BYTES = COUT * LS * 2;
 };
 
-// bias, ReLU, BF16: lane (kq, r16) holds channels nt*16 + 4kq .. +3 of
-// pixel p, one 8-byte store per 16-channel block
-template <int COUT, int NT>
-__device__ __forceinline__ void conv_store(uint16_t *__restrict__ out, long long p, int kq,
-                                           const f32x4 (&acc)[NT], const float (&bb)[NT][4],
-                                           int relu) {
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    uint16_t h4[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float v = acc[nt][i] + bb[nt][i];
-      if (relu) v = v > 0.f ? v : 0.f;
-      h4[i] = f2bf(v);
-    }
-    const uint2 wv = make_uint2((uint32_t)h4[0] | ((uint32_t)h4[1] << 16),
-                                (uint32_t)h4[2] | ((uint32_t)h4[3] << 16));
-    *reinterpret_cast<uint2 *>(out + p * COUT + nt * 16 + 4 * kq) = wv;
-  }
-}
-
 template <int CIN, int COUT, int S>
 __global__ void __launch_bounds__(FW_THREADS)
 k_conv_fwd(const uint16_t *__restrict__ in, const uint16_t *__restrict__ W,
@@ -109,17 +324,9 @@ k_conv_fwd(const uint16_t *__restrict__ in, const uint16_t *__restrict__ W,
   using SH = FwdShape<CIN, COUT>;
   constexpr int NT = COUT / 16, K = SH::K, KP = SH::KP, LS = SH::LS;
   __shared__ __attribute__((aligned(16))) uint16_t Wl[COUT * LS];
-  if constexpr (K % 8 == 0) {
-    for (int e = threadIdx.x; e < COUT * (K / 8); e += FW_THREADS) {
-      const int co = e / (K / 8), k8 = e % (K / 8);
-      *reinterpret_cast<uint4 *>(&Wl[co * LS + 8 * k8]) =
-          *reinterpret_cast<const uint4 *>(W + (long long)co * K + 8 * k8);
-    }
-  } else {
-    for (int e = threadIdx.x; e < COUT * KP; e += FW_THREADS) {
-      const int co = e / KP, k = e % KP;
-      Wl[co * LS + k] = k < K ? W[co * K + k] : (uint16_t)0;
-    }
+  for (int e = threadIdx.x; e < COUT * KP; e += FW_THREADS) {
+    const int co = e / KP, k = e % KP;
+    Wl[co * LS + k] = k < K ? W[co * K + k] : (uint16_t)0;
   }
   __syncthreads();
   const int Ho = (H - 1) / S + 1, Wo = (Wd - 1) / S + 1;
@@ -132,106 +339,35 @@ k_conv_fwd(const uint16_t *__restrict__ in, const uint16_t *__restrict__ W,
   for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
     for (int i = 0; i < 4; ++i) bb[nt][i] = bias[nt * 16 + 4 * kq + i];
-  // U tiles per wave and pass, their loads all issued before the first MFMA
-  // (2 and 4 were measured no faster than 1 on the 64x64 layers)
-  constexpr int U = 1;
-  for (long long t0 = blockIdx.x; t0 < n_tiles; t0 += (long long)U * gridDim.x) {
-    long long pu[U];
-    bool act[U], pv[U];
+  for (long long tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+    const long long pbase = tile * FW_TILE + wave * 16;
+    if (pbase >= P) continue;  // wave-uniform; no barrier below
+    const long long p = pbase + r16;
+    const bool pv = p < P;
+    const long long pp = pv ? p : 0;
+    const int pb = (int)(pp / (Ho * Wo));
+    const int rr = (int)(pp % (Ho * Wo));
+    const int py = rr / Wo, px = rr % Wo;
+    // lane group kq holds taps 4 kq .. 4 kq + 3, both channels (one dword each)
+    static_assert(CIN == 2, "two input channels");
+    uint32_t d[4];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const long long tile = t0 + (long long)u * gridDim.x;
-      const long long pbase = tile * FW_TILE + wave * 16;
-      act[u] = tile < n_tiles && pbase < P;  // wave-uniform
-      pu[u] = pbase + r16;
-      pv[u] = act[u] && pu[u] < P;
+    for (int j = 0; j < 4; ++j) {
+      const int tap = 4 * kq + j;
+      const int iy = py * S + tap / 3 - 1, ix = px * S + tap % 3 - 1;
+      d[j] = (pv && tap < 9 && iy >= 0 && iy < H && ix >= 0 && ix < Wd)
+                 ? *reinterpret_cast<const uint32_t *>(in + (((long long)pb * H + iy) * Wd + ix) * 2)
+                 : 0u;
     }
-    if constexpr (CIN >= 32) {
-      constexpr int CB = CIN / 32, T = 9 * CB;
-      bf16x8 a[U][T];
+    V8 ta;
+    ta.u = make_uint4(d[0], d[1], d[2], d[3]);
+    f32x4 acc[NT];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const long long pp = pv[u] ? pu[u] : 0;
-        const int pb = (int)(pp / (Ho * Wo));
-        const int rr = (int)(pp % (Ho * Wo));
-        const int py = rr / Wo, px = rr % Wo;
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-          const int tap = t / CB, cb = t % CB;
-          const int iy = py * S + tap / 3 - 1, ix = px * S + tap % 3 - 1;
-          if (pv[u] && iy >= 0 && iy < H && ix >= 0 && ix < Wd)
-            a[u][t] = load8(in + (((long long)pb * H + iy) * Wd + ix) * CIN + cb * 32 + 8 * kq);
-          else
-            a[u][t] = zero8();
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (!act[u]) continue;
-        f32x4 acc[NT];
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-          const int tap = t / CB, cb = t % CB;
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt) {
-            const bf16x8 w = *reinterpret_cast<const bf16x8 *>(
-                &Wl[(nt * 16 + r16) * LS + tap * CIN + cb * 32 + 8 * kq]);
-            acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, a[u][t], acc[nt], 0, 0, 0);
-          }
-        }
-        if (pv[u]) conv_store<COUT, NT>(out, pu[u], kq, acc, bb, relu);
-      }
-    } else {
-      // K = 9 CIN <= 32: the whole K in one step, zero padded
-      V8 ta[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const long long pp = pv[u] ? pu[u] : 0;
-        const int pb = (int)(pp / (Ho * Wo));
-        const int rr = (int)(pp % (Ho * Wo));
-        const int py = rr / Wo, px = rr % Wo;
-        if constexpr (CIN == 2) {
-          // lane group kq holds taps 4 kq .. 4 kq + 3, both channels (one dword each)
-          uint32_t d[4];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int tap = 4 * kq + j;
-            const int iy = py * S + tap / 3 - 1, ix = px * S + tap % 3 - 1;
-            d[j] = (pv[u] && tap < 9 && iy >= 0 && iy < H && ix >= 0 && ix < Wd)
-                       ? *reinterpret_cast<const uint32_t *>(in + (((long long)pb * H + iy) * Wd + ix) * 2)
-                       : 0u;
-          }
-          ta[u].u = make_uint4(d[0], d[1], d[2], d[3]);
-        } else {
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            const int k = 8 * kq + i;
-            uint16_t v = 0;
-            if (k < K && pv[u]) {
-              const int tap = k / CIN, ci = k % CIN;
-              const int iy = py * S + tap / 3 - 1, ix = px * S + tap % 3 - 1;
-              if (iy >= 0 && iy < H && ix >= 0 && ix < Wd)
-                v = in[(((long long)pb * H + iy) * Wd + ix) * CIN + ci];
-            }
-            ta[u].h[i] = v;
-          }
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (!act[u]) continue;
-        f32x4 acc[NT];
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-          const bf16x8 w = *reinterpret_cast<const bf16x8 *>(&Wl[(nt * 16 + r16) * LS + 8 * kq]);
-          acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, ta[u].v, (f32x4){0.f, 0.f, 0.f, 0.f},
-                                                            0, 0, 0);
-        }
-        if (pv[u]) conv_store<COUT, NT>(out, pu[u], kq, acc, bb, relu);
-      }
+    for (int nt = 0; nt < NT; ++nt) {
+      const bf16x8 w = *reinterpret_cast<const bf16x8 *>(&Wl[(nt * 16 + r16) * LS + 8 * kq]);
+      acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, ta.v, (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
     }
+    if (pv) conv_store<COUT, NT>(out, p, kq, acc, bb, relu);
   }
 }
 
@@ -245,108 +381,458 @@ static unsigned persistent_grid(long long n_tiles, int lds_bytes) {
 }
 
 // ---------------------------------------------------------------------------
-// data gradient: gin = conv^T(gpre), gpre = gout * [out > 0]
-// M = input pixels, N = CIN, K = 9 * COUT; Wt = [3][3][CIN][COUT], staged
-// into LDS as rows of K per input channel; tiles and persistence as the
-// forward pass.
+// The first two layers at once (2 -> 32 channels, then 32 -> 32 with stride 2,
+// both with ReLU), for a forward pass that keeps no activations: a workgroup
+// computes the 33 x 17 first-layer pixels under a tile of 16 x 8 outputs into LDS
+// (BF16, zero outside the image, as the layer by itself would store them) and
+// the second layer from there; both layers' weights stay in registers.  Bound by
+// vector issue (the first layer's bias, ReLU and rounding).  1024 images of 64 x 64:
+// 54 us; 85 + 70 layer by layer, which write and read 268 MB in between.
 // ---------------------------------------------------------------------------
-template <int CIN, int COUT>
-struct DgradShape {
-  static constexpr int K = 9 * COUT;
-  static constexpr int LS = K + 8;
-  static constexpr int LDS_BYTES = CIN * LS * 2;
-};
+constexpr int ST_W = 16, ST_H = 8, ST_WAVES = 4;           // output tile
+constexpr int ST_XW = 2 * ST_W + 3, ST_XH = 2 * ST_H + 3;  // input tile of the first layer
 
-template <int CIN, int COUT, int S>
-__global__ void __launch_bounds__(FW_THREADS)
-k_conv_dgrad(const uint16_t *__restrict__ gout, const uint16_t *__restrict__ out,
-             const uint16_t *__restrict__ Wt, uint16_t *__restrict__ gin, int B, int H, int Wd) {
-  using SH = DgradShape<CIN, COUT>;
-  constexpr int NT = CIN / 16;
-  constexpr int CB = COUT / 32, T = 9 * CB;
-  constexpr int LS = SH::LS;
-  __shared__ __attribute__((aligned(16))) uint16_t Wl[CIN * LS];
-  for (int e = threadIdx.x; e < 9 * CIN * (COUT / 8); e += FW_THREADS) {
-    const int co8 = e % (COUT / 8), r = e / (COUT / 8);  // r = tap * CIN + ci
-    const int tap = r / CIN, ci = r % CIN;
-    *reinterpret_cast<uint4 *>(&Wl[ci * LS + tap * COUT + 8 * co8]) =
-        *reinterpret_cast<const uint4 *>(Wt + (long long)r * COUT + 8 * co8);
-  }
-  __syncthreads();
-  const int Ho = (H - 1) / S + 1, Wo = (Wd - 1) / S + 1;
-  const long long P = (long long)B * H * Wd;
-  const long long n_tiles = (P + FW_TILE - 1) / FW_TILE;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+__global__ void __launch_bounds__(64 * ST_WAVES, 3)
+k_conv_stem(const uint32_t *__restrict__ in, const uint16_t *__restrict__ W1,
+            const float *__restrict__ b1, const uint16_t *__restrict__ W2,
+            const float *__restrict__ b2, uint16_t *__restrict__ out, int H, int Wd, int Ho, int Wo,
+            int n_tiles, int ntx, int nty) {
+  using SH = TileShape<32, 32, 2, ST_W, ST_H, 1, ST_WAVES>;
+  constexpr int XN = ST_XW * ST_XH, NX = (XN + SH::THREADS - 1) / SH::THREADS;
+  static_assert(SH::IW == 33 && SH::IH == 17, "two blocks and a column");
+  __shared__ __attribute__((aligned(16))) uint16_t It[SH::I_ELEMS];
+  __shared__ uint32_t Xt[XN + 1];  // the last entry stays zero
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int kq = lane >> 4, r16 = lane & 15;
-  for (long long tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-    const long long pbase = tile * FW_TILE + wave * 16;
-    if (pbase >= P) continue;  // wave-uniform; no barrier below
-    const long long p = pbase + r16;
-    const bool pv = p < P;
-    const long long pp = pv ? p : 0;
-    const int pb = (int)(pp / (H * Wd));
-    const int rr = (int)(pp % (H * Wd));
-    const int py = rr / Wd, px = rr % Wd;
-    f32x4 acc[NT];
+  const int per = ntx * nty;
+  bf16x8 w1[2], w2[9][2];
+  float bb1[2][4], bb2[2][4];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    bf16x8 a[T];
+  for (int nt = 0; nt < 2; ++nt) {
+    V8 v;
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-      const int tap = t / CB, cb = t % CB;
-      const int ny = py + 1 - tap / 3, nx = px + 1 - tap % 3;  // = oy * S
-      bool ok = pv && ny >= 0 && nx >= 0 && (ny % S) == 0 && (nx % S) == 0;
-      const int oy = ny / S, ox = nx / S;
-      ok = ok && oy < Ho && ox < Wo;
-      if (ok) {
-        const long long o = (((long long)pb * Ho + oy) * Wo + ox) * COUT + cb * 32 + 8 * kq;
-        V8 g, y;
-        g.u = *reinterpret_cast<const uint4 *>(gout + o);
-        y.u = *reinterpret_cast<const uint4 *>(out + o);
+    for (int i = 0; i < 8; ++i) {
+      const int k = 8 * kq + i;
+      v.h[i] = k < 18 ? W1[(nt * 16 + r16) * 18 + k] : (uint16_t)0;
+    }
+    w1[nt] = v.v;
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-          if (!(bf2f(y.h[i]) > 0.f)) g.h[i] = 0;
-        a[t] = g.v;
-      } else {
-        a[t] = zero8();
+    for (int tap = 0; tap < 9; ++tap) w2[tap][nt] = load8(W2 + (nt * 16 + r16) * 288 + tap * 32 + 8 * kq);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      bb1[nt][i] = b1[nt * 16 + 4 * kq + i];
+      bb2[nt][i] = b2[nt * 16 + 4 * kq + i];
+    }
+  }
+  // LDS entry of the lane's tap 4 kq + j for the pixel block at row 0, column r16,
+  // and its step a row and a column (taps from 9 on stay at the zero)
+  int tap_at[4], tap_row[4], tap_col[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int tap = 4 * kq + j;
+    tap_at[j] = tap < 9 ? (tap / 3) * ST_XW + tap % 3 : XN;
+    tap_row[j] = tap < 9 ? ST_XW : 0;
+    tap_col[j] = tap < 9 ? 1 : 0;
+  }
+  // a block of 16 first-layer pixels: rows qy, columns qx of the lane's pixel
+  // (on: it is one; edge: some may lie outside the image)
+  const auto first = [&](int qy, int qx, bool on, bool edge, int iy0, int ix0) {
+    V8 a;
+    uint32_t d[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) d[j] = Xt[tap_at[j] + qy * tap_row[j] + qx * tap_col[j]];
+    a.u = make_uint4(d[0], d[1], d[2], d[3]);
+    const bool inside = !edge || ((unsigned)(iy0 + qy) < (unsigned)H && (unsigned)(ix0 + qx) < (unsigned)Wd);
+    uint16_t *o = &It[(qy * SH::IW + SH::slot(qx)) * SH::CS + 4 * kq];
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) {
+      const f32x4 c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1[nt], a.v, (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+      float v[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = fmaxf(c[i] + bb1[nt][i], 0.f);
+      uint2 u = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
+      if (edge) u = inside ? u : make_uint2(0u, 0u);
+      if (on) *reinterpret_cast<uint2 *>(o + nt * 16) = u;
+    }
+  };
+  uint32_t x[NX];
+  const auto load = [&](int tile) {
+    const int im = tile / per, t = tile - im * per;
+    const int y0 = (t / ntx) * (2 * ST_H) - 2, x0 = (t % ntx) * (2 * ST_W) - 2;
+    const uint32_t *src = in + (long long)im * H * Wd;
+#pragma unroll
+    for (int j = 0; j < NX; ++j) {
+      const int e = j * SH::THREADS + threadIdx.x;
+      const int iy = y0 + e / ST_XW, ix = x0 + e % ST_XW;
+      x[j] = e < XN && (unsigned)iy < (unsigned)H && (unsigned)ix < (unsigned)Wd
+                 ? src[(long long)iy * Wd + ix] : 0u;
+    }
+  };
+  const auto put = [&]() {
+#pragma unroll
+    for (int j = 0; j < NX; ++j) {
+      const int e = j * SH::THREADS + threadIdx.x;
+      if (e < XN) Xt[e] = x[j];
+    }
+  };
+  if (threadIdx.x == 0) Xt[XN] = 0u;
+  load(blockIdx.x);
+  put();
+  __syncthreads();
+  for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+    const int im = tile / per, t = tile - im * per;
+    const int oy0 = (t / ntx) * ST_H, ox0 = (t % ntx) * ST_W;
+    const bool more = tile + (int)gridDim.x < n_tiles;
+    if (more) load(tile + gridDim.x);
+    const int iy0 = 2 * oy0 - 1, ix0 = 2 * ox0 - 1;
+    const bool edge = iy0 < 0 || ix0 < 0 || iy0 + SH::IH > H || ix0 + SH::IW > Wd;
+    const auto rows = [&](bool e) {  // two blocks a row, rows in turn; then column 32
+      for (int qy = wave; qy < SH::IH; qy += ST_WAVES) {
+        first(qy, r16, true, e, iy0, ix0);
+        first(qy, 16 + r16, true, e, iy0, ix0);
+      }
+      if (wave == 1) first(r16, 32, true, e, iy0, ix0);
+      if (wave == 2) first(16, 32, r16 == 0, e, iy0, ix0);
+    };
+    if (edge) rows(true);
+    else rows(false);
+    __syncthreads();
+    if (more) put();
+    f32x4 acc[SH::PB][2];
+    int px[SH::PB];
+#pragma unroll
+    for (int b = 0; b < SH::PB; ++b) {
+      const int rr = (wave * SH::PB + b) * 16 + r16;
+      px[b] = ((rr / ST_W) * 2 * SH::IW + rr % ST_W) * SH::CS + 8 * kq;
+      acc[b][0] = acc[b][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap) {
+      const int o = ((tap / 3) * SH::IW + SH::slot(tap % 3)) * SH::CS;
+#pragma unroll
+      for (int b = 0; b < SH::PB; ++b) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8 *>(It + px[b] + o);
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+          acc[b][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2[tap][nt], a, acc[b][nt], 0, 0, 0);
       }
     }
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-      const int tap = t / CB, cb = t % CB;
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const bf16x8 b = *reinterpret_cast<const bf16x8 *>(
-            &Wl[(nt * 16 + r16) * LS + tap * COUT + cb * 32 + 8 * kq]);
-        // weights as the A operand (M = CIN): lane (kq, r16) ends with input
-        // channels nt*16 + 4kq .. +3 of pixel p
-        acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a[t], acc[nt], 0, 0, 0);
-      }
+    for (int b = 0; b < SH::PB; ++b) {
+      const int rr = (wave * SH::PB + b) * 16 + r16, oy = oy0 + rr / ST_W, ox = ox0 + rr % ST_W;
+      if (oy < Ho && ox < Wo)
+        conv_store<32, 2>(out, ((long long)im * Ho + oy) * Wo + ox, kq, acc[b], bb2, 1);
     }
-    if (pv) {
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const uint2 wv = make_uint2((uint32_t)f2bf(acc[nt][0]) | ((uint32_t)f2bf(acc[nt][1]) << 16),
-                                    (uint32_t)f2bf(acc[nt][2]) | ((uint32_t)f2bf(acc[nt][3]) << 16));
-        *reinterpret_cast<uint2 *>(gin + p * CIN + nt * 16 + 4 * kq) = wv;
-      }
-    }
+    __syncthreads();
   }
 }
 
 // ---------------------------------------------------------------------------
-// weight gradient: dW[co][tap][ci] = sum_p gpre[p][co] in[p @ tap][ci]
-// GEMM with M = COUT, N = taps x NC columns (tap, input channel; when
-// CIN < 32 the columns are (tap, ci) flattened and padded to 32 with one
-// "tap"), K = output pixels.  One workgroup (16 waves) takes a chunk of
-// pixels and every (co, tap, ci) tile.  Per step, each of KSPLIT wave groups
+// Data gradient of a stride-2 layer: gin = conv^T(gpre), gpre = gout * [out > 0].
+// An input pixel meets the taps of its own row and column parity only, 1, 2, 2 or
+// 4 of them (2.25 on average instead of 9 mostly empty ones): a 16-pixel matrix
+// column block holds pixels of one parity, and a wavefront takes the four blocks of
+// the same pixel pairs, nine taps in all.  Weights ([tap][CIN][COUT] as rows of K per
+// input channel) and the group's masked gpre (NSUB tiles of 9 x (BW + 1) outputs
+// under 16 x 2 BW inputs, zero outside the image) in LDS, staged as by the tiled
+// convolution.  Bound by memory: 64x64, 32 -> 32 channels, 256 images 26 us; 58
+// with every tap gathered and masked from memory.
+// ---------------------------------------------------------------------------
+template <int CIN, int COUT, int BW>
+struct Dgrad2Shape {
+  static constexpr int NSUB = 16 / BW, K = 9 * COUT, LS = K + 8, CS = COUT + 8, NT = CIN / 16;
+  static constexpr int IW = BW + 1, PIX = 9 * IW, THREADS = 512;
+  static constexpr int CHUNKS = NSUB * PIX * (COUT / 8), NL = (CHUNKS + THREADS - 1) / THREADS;
+  static constexpr int W_ELEMS = CIN * LS, I_ELEMS = NSUB * PIX * CS;
+  static constexpr int LDS_BYTES = (W_ELEMS + I_ELEMS) * 2;
+};
+
+template <int CIN, int COUT, int BW>
+__global__ void __launch_bounds__(512)
+k_dgrad2_tile(const uint16_t *__restrict__ gout, const uint16_t *__restrict__ out,
+              const uint16_t *__restrict__ Wt, uint16_t *__restrict__ gin, int H, int Wd, int Ho,
+              int Wo, int n_sub, int ntx, int nty) {
+  using SH = Dgrad2Shape<CIN, COUT, BW>;
+  constexpr int NL = SH::NL, NT = SH::NT, C8 = COUT / 8, CB = COUT / 32, NSUB = SH::NSUB;
+  __shared__ __attribute__((aligned(16))) uint16_t Wl[SH::W_ELEMS];
+  __shared__ __attribute__((aligned(16))) uint16_t Gt[SH::I_ELEMS];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int kq = lane >> 4, r16 = lane & 15;
+  const int n_groups = (n_sub + NSUB - 1) / NSUB;
+  uint4 g[NL], y[NL];
+  const auto load = [&](int group) {
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+      const int e = j * SH::THREADS + threadIdx.x;
+      g[j] = y[j] = make_uint4(0, 0, 0, 0);
+      const int pix = e / C8, sub = pix / SH::PIX, rr = pix - sub * SH::PIX;
+      const int sid = group * NSUB + sub;
+      const TileAt t = tile_of<BW == 8>(sid, ntx, nty);
+      const int oy = t.y * 8 + rr / SH::IW, ox = t.x * BW + rr % SH::IW;
+      if (e < SH::CHUNKS && sid < n_sub && oy < Ho && ox < Wo) {
+        const long long o = (((long long)t.im * Ho + oy) * Wo + ox) * COUT + 8 * (e % C8);
+        g[j] = *reinterpret_cast<const uint4 *>(gout + o);
+        y[j] = *reinterpret_cast<const uint4 *>(out + o);
+      }
+    }
+  };
+  const auto put = [&]() {
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+      const int e = j * SH::THREADS + threadIdx.x;
+      V8 v, m;
+      v.u = g[j];
+      m.u = y[j];
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (!(bf2f(m.h[i]) > 0.f)) v.h[i] = 0;
+      if (e < SH::CHUNKS) *reinterpret_cast<uint4 *>(&Gt[(e / C8) * SH::CS + 8 * (e % C8)]) = v.u;
+    }
+  };
+  load(blockIdx.x);
+  for (int e = threadIdx.x; e < 9 * CIN * C8; e += SH::THREADS) {
+    const int k8 = e % C8, q = e / C8, tap = q / CIN, ci = q % CIN;
+    *reinterpret_cast<uint4 *>(&Wl[ci * SH::LS + tap * COUT + 8 * k8]) =
+        *reinterpret_cast<const uint4 *>(Wt + (long long)q * COUT + 8 * k8);
+  }
+  put();
+  __syncthreads();
+  // the lane's pixel pair: column bx, row pair rp of tile sub
+  const int u = wave * 16 + r16, bx = u % BW, rp = (u / BW) % 8, sub = u / (BW * 8);
+  const uint16_t *gp = Gt + (sub * SH::PIX + rp * SH::IW + bx) * SH::CS + 8 * kq;
+  const uint16_t *wp = Wl + r16 * SH::LS + 8 * kq;
+  for (int group = blockIdx.x; group < n_groups; group += gridDim.x) {
+    const bool more = group + (int)gridDim.x < n_groups;
+    if (more) load(group + gridDim.x);
+    const int sid = group * NSUB + sub;
+    const TileAt t = tile_of<BW == 8>(sid, ntx, nty);
+    const int py0 = t.y * 16 + 2 * rp, px0 = t.x * (2 * BW) + 2 * bx;
+#pragma unroll
+    for (int cls = 0; cls < 4; ++cls) {
+      const int ay = cls >> 1, ax = cls & 1;  // row and column parity
+      f32x4 acc[NT];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      // odd: taps 0 (the next output on) and 2; even: tap 1
+#pragma unroll
+      for (int ky = 1 - ay; ky < 3; ky += 2)
+#pragma unroll
+        for (int kx = 1 - ax; kx < 3; kx += 2)
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb) {
+            const bf16x8 a = *reinterpret_cast<const bf16x8 *>(
+                gp + ((ky == 0 ? SH::IW : 0) + (kx == 0 ? 1 : 0)) * SH::CS + cb * 32);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+              const bf16x8 w = *reinterpret_cast<const bf16x8 *>(
+                  wp + nt * 16 * SH::LS + (ky * 3 + kx) * COUT + cb * 32);
+              acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, a, acc[nt], 0, 0, 0);
+            }
+          }
+      const int py = py0 + ay, px = px0 + ax;
+      if (sid < n_sub && py < H && px < Wd) {
+        uint16_t *o = gin + (((long long)t.im * H + py) * Wd + px) * CIN + 4 * kq;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+          *reinterpret_cast<uint2 *>(o + nt * 16) =
+              make_uint2(f2bf2(acc[nt][0], acc[nt][1]), f2bf2(acc[nt][2], acc[nt][3]));
+      }
+    }
+    if (!more) break;
+    __syncthreads();
+    put();
+    __syncthreads();
+  }
+}
+
+template <int CIN, int COUT, int BW>
+static pvr_status dgrad2_launch(const uint16_t *gout, const uint16_t *out, const uint16_t *wt,
+                                uint16_t *gin, int B, int H, int W, hipStream_t stream) {
+  using SH = Dgrad2Shape<CIN, COUT, BW>;
+  const int ntx = (W + 2 * BW - 1) / (2 * BW), nty = (H + 15) / 16;
+  const long long n_sub = (long long)B * ntx * nty;
+  if (n_sub > 0x7fff0000LL) return fail(PVR_ESHAPE, "pvr_cnn: more than 2^31 tiles");
+  hipLaunchKernelGGL((k_dgrad2_tile<CIN, COUT, BW>),
+                     dim3(tile_grid<SH>((n_sub + SH::NSUB - 1) / SH::NSUB)), dim3(SH::THREADS), 0, stream,
+                     gout, out, wt, gin, H, W, (H - 1) / 2 + 1, (W - 1) / 2 + 1, (int)n_sub, ntx, nty);
+  HIP_TRY(hipGetLastError());
+  return PVR_OK;
+}
+
+// ---------------------------------------------------------------------------
+// weight gradient: dW[co][tap][ci] = sum_p gpre[p][co] in[p @ tap][ci],
+// gpre = gout * [out > 0], a GEMM with K = output pixels.
+//
+// Layers of 32 and 64 input channels, tiled: a workgroup of 16 wavefronts loops over
+// groups of output tiles, as the tiled convolution.  A group's gpre (masked once)
+// and its input with border, zero outside the image, are staged in LDS as they lie
+// in memory, pixels padded by 8 channels; both matrix operands, eight consecutive
+// pixels of one channel per lane, come from it by transposing reads (four pixels of
+// 16 channels each), so a tap is an address offset and every value is staged once.
+// A wavefront owns 16 output by 16 input channels of all nine taps (and, for the
+// first 16 input channels, the bias: the product with ones); where a layer has fewer
+// such blocks than wavefronts, KS sets of wavefronts share out the pixels and
+// add up through LDS in order.  Each workgroup writes one partial block, added
+// in order by k_wgrad_reduce (deterministic).  Bound by LDS reads, 10 for 9
+// matrix instructions: 32x32, 32 -> 64 channels, 256 images 30 us (reduction 7);
+// 63 (12 + 5) with both operands transposed on their way into LDS, once a tap.
+// ---------------------------------------------------------------------------
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+template <int CIN, int COUT, int S, int TW, int TH, int NSUB>
+struct WgTile {
+  static constexpr int MT = COUT / 16, NC = CIN / 16, KS = 16 / (MT * NC);
+  static constexpr int IW = (TW - 1) * S + 3, IH = (TH - 1) * S + 3, PIX = IW * IH;
+  static constexpr int NE = S == 2 ? (IW + 1) / 2 : 0;
+  static constexpr int CI = CIN + 8, CG = COUT + 8;
+  static constexpr int PXO = NSUB * TW * TH, STEPS = PXO / 32;
+  static constexpr int ICH = NSUB * PIX * (CIN / 8), GCH = PXO * (COUT / 8);
+  static constexpr int NI = (ICH + 1023) / 1024, NG = (GCH + 1023) / 1024;
+  static constexpr int I_ELEMS = NSUB * PIX * CI, G_ELEMS = PXO * CG;
+  static constexpr int SUM_BYTES = KS > 1 ? MT * NC * 10 * 1024 : 0;  // nine taps and the bias
+  static constexpr int TILE_BYTES = (I_ELEMS + G_ELEMS) * 2;
+  static constexpr int LDS_BYTES = TILE_BYTES > SUM_BYTES ? TILE_BYTES : SUM_BYTES;
+  static constexpr long long REC = 9LL * COUT * CIN;  // floats per partial block
+  __device__ static constexpr int slot(int ix) { return S == 2 ? (ix >> 1) + (ix & 1) * NE : ix; }
+};
+
+// Lane (kq, r16): pixels 8 kq .. 8 kq + 7 of channel r16, from p = the address
+// of pixel 8 kq + r16 / 4, channels 4 (r16 % 4) on, STRIDE elements a pixel.
+template <int STRIDE>
+__device__ __forceinline__ bf16x8 read_transposed(const uint16_t *p) {
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p);
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * STRIDE));
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+template <int CIN, int COUT, int S, int TW, int TH, int NSUB>
+__global__ void __launch_bounds__(1024)
+k_wgrad_tile(const uint16_t *__restrict__ gout, const uint16_t *__restrict__ out,
+             const uint16_t *__restrict__ in, float *__restrict__ part, float *__restrict__ bpart,
+             int H, int Wd, int Ho, int Wo, int n_sub, int ntx, int nty) {
+  using SH = WgTile<CIN, COUT, S, TW, TH, NSUB>;
+  constexpr int NI = SH::NI, NG = SH::NG, C8 = CIN / 8, G8 = COUT / 8;
+  __shared__ __attribute__((aligned(16))) uint16_t lds[SH::LDS_BYTES / 2];
+  uint16_t *It = lds, *Gt = lds + SH::I_ELEMS;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int kq = lane >> 4, r16 = lane & 15;
+  const int ks = wave / (SH::MT * SH::NC), wl = wave % (SH::MT * SH::NC);
+  const int cm = wl / SH::NC, cn = wl % SH::NC;
+  const int n_groups = (n_sub + NSUB - 1) / NSUB;
+  uint4 gi[NI], gg[NG], gy[NG];
+  const auto load = [&](int group) {
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      const int e = j * 1024 + threadIdx.x;
+      gi[j] = make_uint4(0, 0, 0, 0);
+      const int pix = e / C8, sub = NSUB == 1 ? 0 : pix / SH::PIX, rr = pix - sub * SH::PIX;
+      const int sid = group * NSUB + sub;
+      const TileAt t = tile_of<TW == 8>(sid, ntx, nty);
+      const int iy = t.y * (TH * S) - 1 + rr / SH::IW, ix = t.x * (TW * S) - 1 + rr % SH::IW;
+      if (e < SH::ICH && sid < n_sub && (unsigned)iy < (unsigned)H && (unsigned)ix < (unsigned)Wd)
+        gi[j] = *reinterpret_cast<const uint4 *>(in + (((long long)t.im * H + iy) * Wd + ix) * CIN + 8 * (e % C8));
+    }
+#pragma unroll
+    for (int j = 0; j < NG; ++j) {
+      const int e = j * 1024 + threadIdx.x;
+      gg[j] = gy[j] = make_uint4(0, 0, 0, 0);
+      const int q = e / G8, sub = NSUB == 1 ? 0 : q / (TW * TH), rr = q - sub * (TW * TH);
+      const int sid = group * NSUB + sub;
+      const TileAt t = tile_of<TW == 8>(sid, ntx, nty);
+      const int oy = t.y * TH + rr / TW, ox = t.x * TW + rr % TW;
+      if (e < SH::GCH && sid < n_sub && oy < Ho && ox < Wo) {
+        const long long o = (((long long)t.im * Ho + oy) * Wo + ox) * COUT + 8 * (e % G8);
+        gg[j] = *reinterpret_cast<const uint4 *>(gout + o);
+        gy[j] = *reinterpret_cast<const uint4 *>(out + o);
+      }
+    }
+  };
+  const auto put = [&]() {
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      const int e = j * 1024 + threadIdx.x;
+      const int pix = e / C8, sub = NSUB == 1 ? 0 : pix / SH::PIX, rr = pix - sub * SH::PIX;
+      if (e < SH::ICH)
+        *reinterpret_cast<uint4 *>(&It[(sub * SH::PIX + (rr / SH::IW) * SH::IW + SH::slot(rr % SH::IW)) * SH::CI +
+                                       8 * (e % C8)]) = gi[j];
+    }
+#pragma unroll
+    for (int j = 0; j < NG; ++j) {
+      const int e = j * 1024 + threadIdx.x;
+      V8 v, m;
+      v.u = gg[j];
+      m.u = gy[j];
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (!(bf2f(m.h[i]) > 0.f)) v.h[i] = 0;
+      if (e < SH::GCH) *reinterpret_cast<uint4 *>(&Gt[(e / G8) * SH::CG + 8 * (e % G8)]) = v.u;
+    }
+  };
+  f32x4 acc[10];  // nine taps; the bias where cn = 0
+#pragma unroll
+  for (int t = 0; t < 10; ++t) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  bf16x8 ones;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) ones[i] = 0x3f80;
+  load(blockIdx.x);
+  put();
+  __syncthreads();
+  for (int group = blockIdx.x; group < n_groups; group += gridDim.x) {
+    const bool more = group + (int)gridDim.x < n_groups;
+    if (more) load(group + gridDim.x);
+    for (int st = ks; st < SH::STEPS; st += SH::KS) {
+      const int q = st * 32 + 8 * kq + (r16 >> 2);  // (its eight pixels lie in one row)
+      const int sub = q / (TW * TH), rr = q % (TW * TH);
+      const uint16_t *gp = Gt + q * SH::CG + cm * 16 + 4 * (r16 & 3);
+      const uint16_t *ip = It + (sub * SH::PIX + (rr / TW) * S * SH::IW + rr % TW) * SH::CI + cn * 16 + 4 * (r16 & 3);
+      const bf16x8 a = read_transposed<SH::CG>(gp);
+#pragma unroll
+      for (int t = 0; t < 9; ++t) {
+        const bf16x8 b = read_transposed<SH::CI>(ip + ((t / 3) * SH::IW + SH::slot(t % 3)) * SH::CI);
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[t], 0, 0, 0);
+      }
+      if (cn == 0) acc[9] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ones, acc[9], 0, 0, 0);
+    }
+    __syncthreads();
+    if (more) {
+      put();
+      __syncthreads();
+    }
+  }
+  if constexpr (SH::KS > 1) {  // the other pixel sets' sums, in order
+    f32x4 *sum = reinterpret_cast<f32x4 *>(lds);
+    for (int g = 1; g < SH::KS; ++g) {
+#pragma unroll
+      for (int t = 0; t < 10; ++t)
+        if (ks == g) sum[(wl * 10 + t) * 64 + lane] = acc[t];
+      __syncthreads();
+#pragma unroll
+      for (int t = 0; t < 10; ++t)
+        if (ks == 0) acc[t] += sum[(wl * 10 + t) * 64 + lane];
+      __syncthreads();
+    }
+    if (ks) return;
+  }
+  float *dst = part + (long long)blockIdx.x * SH::REC;
+#pragma unroll
+  for (int t = 0; t < 9; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      dst[((long long)t * COUT + cm * 16 + 4 * kq + i) * CIN + cn * 16 + r16] = acc[t][i];
+  if (cn == 0 && r16 == 0)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bpart[(long long)blockIdx.x * COUT + cm * 16 + 4 * kq + i] = acc[9][i];
+}
+
+// The first layer (2 input channels): the columns are (tap, ci) flattened and
+// padded to 32 with one "tap".  One workgroup (16 waves) takes a chunk of
+// pixels and every (co, column) tile.  Per step, each of KSPLIT wave groups
 // stages 32 pixels into LDS, transposed so that both MFMA operands are
 // 16-byte reads of 8 consecutive pixels: G[co][px] (gpre, with the ReLU mask)
-// and I[tap][column][px] (the input at every tap, zero outside the image).
-// The waves of a group share the group's tiles; each group writes its own
-// partial block (row chunk * KSPLIT + group), which k_wgrad_reduce adds in
-// order (deterministic).
-// ---------------------------------------------------------------------------
+// and I[column][px] (the input at every tap, zero outside the image).  The
+// waves of a group share the group's tiles; each group writes its own partial
+// block (row chunk * KSPLIT + group).
 template <int CIN>
 struct WCols {
   static constexpr int n = CIN >= 32 ? CIN : ((9 * CIN + 15) / 16) * 16;
@@ -355,14 +841,11 @@ struct WCols {
 template <int CIN, int COUT>
 struct WgradShape {
   static constexpr int NC = WCols<CIN>::n;
-  static constexpr int TAPS = CIN >= 32 ? 9 : 1;
-  static constexpr int TM = COUT / 16, TN = TAPS * NC / 16, TILES = TM * TN;
-  static constexpr int KSPLIT = TILES >= 144 ? 1 : TILES >= 72 ? 2 : TILES >= 36 ? 4 : 16;
-  static constexpr int WPG = 16 / KSPLIT;                 // waves per group
-  static constexpr int TPW = (TILES + WPG - 1) / WPG;     // tiles per wave
+  static constexpr int TN = NC / 16, TILES = COUT / 16 * TN;
+  static constexpr int KSPLIT = 16;                       // one wave a group
   static constexpr int PS = 40;                           // LDS row stride (32 pixels + 8)
-  static constexpr int G_ELEMS = COUT * PS, I_ELEMS = TAPS * NC * PS;
-  static constexpr long long REC = (long long)TAPS * COUT * NC;  // floats per partial block
+  static constexpr int G_ELEMS = COUT * PS, I_ELEMS = NC * PS;
+  static constexpr long long REC = (long long)COUT * NC;  // floats per partial block
 };
 
 // Pixels per chunk (a multiple of 32 KSPLIT), chosen for about 256 chunks.
@@ -379,24 +862,21 @@ k_conv_wgrad(const uint16_t *__restrict__ gout, const uint16_t *__restrict__ out
              const uint16_t *__restrict__ in, float *__restrict__ part,
              float *__restrict__ bpart, int B, int H, int Wd, long long wch) {
   using SH = WgradShape<CIN, COUT>;
-  constexpr int NC = SH::NC, TAPS = SH::TAPS, TN = SH::TN, TILES = SH::TILES;
-  constexpr int KSPLIT = SH::KSPLIT, WPG = SH::WPG, TPW = SH::TPW, PS = SH::PS;
+  constexpr int NC = SH::NC, TN = SH::TN, TILES = SH::TILES, KSPLIT = SH::KSPLIT, PS = SH::PS;
   __shared__ __attribute__((aligned(16))) uint16_t Gs[KSPLIT * SH::G_ELEMS];
   __shared__ __attribute__((aligned(16))) uint16_t Is[KSPLIT * SH::I_ELEMS];
   const int Ho = (H - 1) / S + 1, Wo = (Wd - 1) / S + 1;
   const long long P = (long long)B * Ho * Wo;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int kq = lane >> 4, r16 = lane & 15;
-  const int kg = wave / WPG, wl = wave % WPG;
-  if (CIN < 32) {
-    // the padding columns (tap, ci) >= 9 CIN stay zero
-    for (int e = threadIdx.x; e < KSPLIT * SH::I_ELEMS; e += 1024) Is[e] = 0;
-    __syncthreads();
-  }
-  f32x4 acc[TPW];
+  const int kg = wave;
+  // the padding columns (tap, ci) >= 9 CIN stay zero
+  for (int e = threadIdx.x; e < KSPLIT * SH::I_ELEMS; e += 1024) Is[e] = 0;
+  __syncthreads();
+  f32x4 acc[TILES];
 #pragma unroll
-  for (int q = 0; q < TPW; ++q) acc[q] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  float bsum = 0.f;  // bias partial of (group kg, channel wl * 64 + lane) when < COUT
+  for (int q = 0; q < TILES; ++q) acc[q] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  float bsum = 0.f;  // bias partial of (group kg, channel lane) when < COUT
   const long long p0 = (long long)blockIdx.x * wch;
   const long long p1 = p0 + wch < P ? p0 + wch : P;
   for (long long ps = p0; ps < p1; ps += 32 * KSPLIT) {
@@ -420,26 +900,7 @@ k_conv_wgrad(const uint16_t *__restrict__ gout, const uint16_t *__restrict__ out
       for (int i = 0; i < 8; ++i) dst[i * PS] = gv.h[i];
     }
     // stage the input at every tap transposed: Is[g][tap][col][px]
-    if constexpr (CIN >= 32) {
-      for (int e = threadIdx.x; e < KSPLIT * 9 * 32 * (CIN / 8); e += 1024) {
-        const int c8 = e % (CIN / 8), r = e / (CIN / 8);  // r = (g * 9 + tap) * 32 + px
-        const int px = r % 32, gt = r / 32;
-        const int tap = gt % 9, g = gt / 9;
-        const long long p = ps + g * 32 + px;
-        V8 iv;
-        iv.u = make_uint4(0, 0, 0, 0);
-        if (p < p1) {
-          const int b = (int)(p / (Ho * Wo));
-          const int rr = (int)(p % (Ho * Wo));
-          const int iy = (rr / Wo) * S + tap / 3 - 1, ix = (rr % Wo) * S + tap % 3 - 1;
-          if (iy >= 0 && iy < H && ix >= 0 && ix < Wd)
-            iv.u = *reinterpret_cast<const uint4 *>(in + (((long long)b * H + iy) * Wd + ix) * CIN + 8 * c8);
-        }
-        uint16_t *dst = Is + g * SH::I_ELEMS + (tap * NC + 8 * c8) * PS + px;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) dst[i * PS] = iv.h[i];
-      }
-    } else {
+    {
       for (int e = threadIdx.x; e < KSPLIT * 32 * 9; e += 1024) {
         const int tap = e % 9, r = e / 9;  // r = g * 32 + px
         const int g = r / 32, px = r % 32;
@@ -461,42 +922,32 @@ k_conv_wgrad(const uint16_t *__restrict__ gout, const uint16_t *__restrict__ out
     }
     __syncthreads();
     {
-      const int co = wl * 64 + lane;
+      const int co = lane;
       if (co < COUT) {
         const uint16_t *gr = Gs + kg * SH::G_ELEMS + co * PS;
         for (int px = 0; px < 32; ++px) bsum += bf2f(gr[px]);
       }
     }
 #pragma unroll
-    for (int q = 0; q < TPW; ++q) {
-      const int t = wl * TPW + q;
-      if (t < TILES) {
-        const int tm = t / TN, tn = t % TN;
-        const bf16x8 a = *reinterpret_cast<const bf16x8 *>(
-            Gs + kg * SH::G_ELEMS + (tm * 16 + r16) * PS + 8 * kq);
-        const bf16x8 b = *reinterpret_cast<const bf16x8 *>(
-            Is + kg * SH::I_ELEMS + (tn * 16 + r16) * PS + 8 * kq);
-        acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[q], 0, 0, 0);
-      }
+    for (int q = 0; q < TILES; ++q) {
+      const bf16x8 a = *reinterpret_cast<const bf16x8 *>(
+          Gs + kg * SH::G_ELEMS + (q / TN * 16 + r16) * PS + 8 * kq);
+      const bf16x8 b = *reinterpret_cast<const bf16x8 *>(
+          Is + kg * SH::I_ELEMS + (q % TN * 16 + r16) * PS + 8 * kq);
+      acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[q], 0, 0, 0);
     }
     __syncthreads();
   }
-  // partial block of this group: part[row][tap][co][col], row = chunk * KSPLIT + group
+  // partial block of this group: part[row][co][col], row = chunk * KSPLIT + group
   const long long row = (long long)blockIdx.x * KSPLIT + kg;
   float *dst = part + row * SH::REC;
 #pragma unroll
-  for (int q = 0; q < TPW; ++q) {
-    const int t = wl * TPW + q;
-    if (t < TILES) {
-      const int tm = t / TN, tn = t % TN;
-      const int tap = tn / (NC / 16), col = (tn % (NC / 16)) * 16 + r16;
+  for (int q = 0; q < TILES; ++q)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        dst[((long long)tap * COUT + tm * 16 + 4 * kq + i) * NC + col] = acc[q][i];
-    }
-  }
+    for (int i = 0; i < 4; ++i)
+      dst[(q / TN * 16 + 4 * kq + i) * NC + q % TN * 16 + r16] = acc[q][i];
   {
-    const int co = wl * 64 + lane;
+    const int co = lane;
     if (co < COUT) bpart[row * COUT + co] = bsum;
   }
 }
@@ -561,30 +1012,38 @@ __global__ void k_wgrad_finish(const double *__restrict__ partial, int ranges, i
 // ---------------------------------------------------------------------------
 // pair packing: channel 0 = observed patch, channel 1 = simulated patch, each
 // normalised to zero mean / unit variance over the patch's valid samples
-// (invalid samples 0).  One workgroup per pair; patches are 64 x 64.
+// (invalid samples 0).  One workgroup per pair; patches are 64 x 64.  Bound by
+// memory: a thread's 16 samples of each array are read at once and kept for both
+// passes (1024 pairs, 67 MB: 18 us; 36 reading them twice, one at a time).
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256)
 k_pack_pairs(const PatchDev *__restrict__ patches, const int *__restrict__ ids,
              const float *__restrict__ invz, const float *__restrict__ y,
-             const float *__restrict__ ys, uint16_t *__restrict__ outp, int side, int M) {
+             const float *__restrict__ ys, uint16_t *__restrict__ outp, int M) {
   __shared__ double red[5][4];
   const int bi = blockIdx.x;
-  const int n = side * side;
+  constexpr int n = PVR_CNN_SIDE * PVR_CNN_SIDE, N = n / 256;  // samples, of them a thread's
   const int id = ids[bi];
   if (id < 0 || id >= M) {  // not a patch of the plan: an all-zero pair (uniform per workgroup)
     uint32_t *o32 = reinterpret_cast<uint32_t *>(outp) + (long long)bi * n;
     for (int l = threadIdx.x; l < n; l += 256) o32[l] = 0u;
     return;
   }
-  const PatchDev pt = patches[id];
+  const long long off = patches[id].off + threadIdx.x;
+  float yu[N], yv[N], z[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    z[i] = invz[off + 256 * i];
+    yu[i] = y[off + 256 * i];
+    yv[i] = ys[off + 256 * i];
+  }
   double a[5] = {0, 0, 0, 0, 0};
-  for (int l = threadIdx.x; l < n; l += 256) {
-    const long long j = pt.off + l;
-    if (invz[j] > 0.f) {
-      const double u = y[j], v = ys[j];
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (z[i] > 0.f) {
+      const double u = yu[i], v = yv[i];
       a[0] += 1; a[1] += u; a[2] += u * u; a[3] += v; a[4] += v * v;
     }
-  }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int k = 0; k < 5; ++k) {
@@ -602,14 +1061,14 @@ k_pack_pairs(const PatchDev *__restrict__ patches, const int *__restrict__ ids,
   const double s1 = sqrt(fmax(a[4] / c - m1 * m1, 0.0)) + 1e-3;
   const double r0 = 1.0 / s0, r1 = 1.0 / s1;
   uint32_t *o32 = reinterpret_cast<uint32_t *>(outp) + (long long)bi * n;
-  for (int l = threadIdx.x; l < n; l += 256) {
-    const long long j = pt.off + l;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
     float u = 0.f, v = 0.f;
-    if (invz[j] > 0.f) {
-      u = (float)((y[j] - m0) * r0);
-      v = (float)((ys[j] - m1) * r1);
+    if (z[i] > 0.f) {
+      u = (float)((yu[i] - m0) * r0);
+      v = (float)((yv[i] - m1) * r1);
     }
-    o32[l] = (uint32_t)f2bf(u) | ((uint32_t)f2bf(v) << 16);  // both channels of pixel l
+    o32[threadIdx.x + 256 * i] = f2bf2(u, v);  // both channels of a pixel
   }
 }
 
@@ -774,6 +1233,34 @@ __global__ void k_to_bf16(const float *__restrict__ w, int n, uint16_t *__restri
 
 static int out_size(int n, int s) { return (n - 1) / s + 1; }
 
+template <int CIN, int COUT, int S>
+static pvr_status conv_fwd(const uint16_t *in, const uint16_t *w, const float *bias, uint16_t *out,
+                           int B, int H, int W, int relu, hipStream_t stream) {
+  if constexpr (CIN >= 32) {
+    return conv_tiled<CIN, COUT, S, false>(in, nullptr, w, bias, out, B, H, W, relu, stream);
+  } else {
+    const long long P = (long long)B * out_size(H, S) * out_size(W, S);
+    const dim3 grid(persistent_grid((P + FW_TILE - 1) / FW_TILE, FwdShape<CIN, COUT>::LDS_BYTES));
+    hipLaunchKernelGGL((k_conv_fwd<CIN, COUT, S>), grid, dim3(FW_THREADS), 0, stream, in, w, bias,
+                       out, B, H, W, relu);
+    HIP_TRY(hipGetLastError());
+    return PVR_OK;
+  }
+}
+
+template <int CIN, int COUT, int S>
+static pvr_status conv_dgrad(const uint16_t *gout, const uint16_t *out, const uint16_t *wt,
+                             uint16_t *gin, int B, int H, int W, hipStream_t stream) {
+  if constexpr (S == 1) {
+    return conv_tiled<COUT, CIN, 1, true>(gout, out, wt, nullptr, gin, B, H, W, 0, stream);
+  } else {
+    // images of at most 16 x 16 two at a time where there are many, as above (64 -> 64
+    // channels: 1024 images 18.0 us, 23.4 in 32 x 16 tiles; 256 images 9.0 and 8.0)
+    if (W <= 16 && H <= 16 && B >= SMALL_MIN) return dgrad2_launch<CIN, COUT, 8>(gout, out, wt, gin, B, H, W, stream);
+    return dgrad2_launch<CIN, COUT, 16>(gout, out, wt, gin, B, H, W, stream);
+  }
+}
+
 extern "C" pvr_status pvr_cnn_conv_fwd(const uint16_t *in, const uint16_t *w, const float *bias,
                                        uint16_t *out, int32_t B, int32_t H, int32_t W,
                                        int32_t cin, int32_t cout, int32_t stride, int32_t relu,
@@ -785,20 +1272,37 @@ extern "C" pvr_status pvr_cnn_conv_fwd(const uint16_t *in, const uint16_t *w, co
   PVR_ALIGNED("pvr_cnn_conv_fwd", out, 16);
   if (!in || !w || !bias || !out || B <= 0 || H <= 0 || W <= 0)
     return fail(PVR_EINVAL, "pvr_cnn_conv_fwd: invalid argument");
-  const long long P = (long long)B * out_size(H, stride) * out_size(W, stride);
-  const long long n_tiles = (P + FW_TILE - 1) / FW_TILE;
-#define LAUNCH(CI, CO, ST)                                                                     \
-  if (cin == CI && cout == CO && stride == ST) {                                               \
-    const dim3 grid(persistent_grid(n_tiles, FwdShape<CI, CO>::LDS_BYTES));                    \
-    hipLaunchKernelGGL((k_conv_fwd<CI, CO, ST>), grid, dim3(FW_THREADS), 0, stream, in, w,     \
-                       bias, out, B, H, W, relu);                                              \
-    HIP_TRY(hipGetLastError());                                                                \
-    return PVR_OK;                                                                             \
-  }
+#define LAUNCH(CI, CO, ST)                                                  \
+  if (cin == CI && cout == CO && stride == ST)                              \
+    return conv_fwd<CI, CO, ST>(in, w, bias, out, B, H, W, relu, stream);
   CONV_CASES(LAUNCH)
 #undef LAUNCH
   return fail(PVR_EUNSUPPORTED, "pvr_cnn_conv_fwd: no kernel for cin %d cout %d stride %d", cin,
               cout, stride);
+  PVR_API_END();
+}
+
+extern "C" pvr_status pvr_cnn_stem_fwd(const uint16_t *in, const uint16_t *w1, const float *b1,
+                                       const uint16_t *w2, const float *b2, uint16_t *out,
+                                       int32_t B, int32_t H, int32_t W, hipStream_t stream) {
+  PVR_API_BEGIN();
+  PVR_ALIGNED("pvr_cnn_stem_fwd", in, 16);
+  PVR_ALIGNED("pvr_cnn_stem_fwd", w1, 16);
+  PVR_ALIGNED("pvr_cnn_stem_fwd", b1, 4);
+  PVR_ALIGNED("pvr_cnn_stem_fwd", w2, 16);
+  PVR_ALIGNED("pvr_cnn_stem_fwd", b2, 4);
+  PVR_ALIGNED("pvr_cnn_stem_fwd", out, 16);
+  if (!in || !w1 || !b1 || !w2 || !b2 || !out || B <= 0 || H <= 0 || W <= 0)
+    return fail(PVR_EINVAL, "pvr_cnn_stem_fwd: invalid argument");
+  const int Ho = out_size(H, 2), Wo = out_size(W, 2);
+  const int ntx = (Wo + ST_W - 1) / ST_W, nty = (Ho + ST_H - 1) / ST_H;
+  const long long n = (long long)B * ntx * nty;
+  if (n > 0x7fff0000LL) return fail(PVR_ESHAPE, "pvr_cnn_stem_fwd: more than 2^31 tiles");
+  hipLaunchKernelGGL(k_conv_stem, dim3((unsigned)std::min(n, 768LL)), dim3(64 * ST_WAVES), 0, stream,
+                     reinterpret_cast<const uint32_t *>(in), w1, b1, w2, b2, out, H, W, Ho, Wo, (int)n,
+                     ntx, nty);
+  HIP_TRY(hipGetLastError());
+  return PVR_OK;
   PVR_API_END();
 }
 
@@ -812,17 +1316,10 @@ extern "C" pvr_status pvr_cnn_conv_dgrad(const uint16_t *gout, const uint16_t *o
   PVR_ALIGNED("pvr_cnn_conv_dgrad", wt, 16);
   PVR_ALIGNED("pvr_cnn_conv_dgrad", gin, 16);
   if (!gout || !out || !wt || !gin || B <= 0) return fail(PVR_EINVAL, "pvr_cnn_conv_dgrad: invalid argument");
-  const long long P = (long long)B * H * W;
-  const long long n_tiles = (P + FW_TILE - 1) / FW_TILE;
-#define LAUNCH(CI, CO, ST)                                                                       \
-  if (cin == CI && cout == CO && stride == ST && CI >= 16) {                                     \
-    constexpr int CIX = CI >= 16 ? CI : 16;                                                      \
-    const dim3 grid(persistent_grid(n_tiles, DgradShape<CIX, CO>::LDS_BYTES));                   \
-    hipLaunchKernelGGL((k_conv_dgrad<CIX, CO, ST>), grid, dim3(FW_THREADS), 0, stream,           \
-                       gout, out, wt, gin, B, H, W);                                             \
-    HIP_TRY(hipGetLastError());                                                                  \
-    return PVR_OK;                                                                               \
-  }
+#define LAUNCH(CI, CO, ST)                                                \
+  if constexpr (CI >= 16)                                                 \
+    if (cin == CI && cout == CO && stride == ST)                          \
+      return conv_dgrad<(CI >= 16 ? CI : 16), CO, ST>(gout, out, wt, gin, B, H, W, stream);
   CONV_CASES(LAUNCH)
 #undef LAUNCH
   return fail(PVR_EUNSUPPORTED, "pvr_cnn_conv_dgrad: no kernel for cin %d cout %d stride %d", cin,
@@ -830,29 +1327,96 @@ extern "C" pvr_status pvr_cnn_conv_dgrad(const uint16_t *gout, const uint16_t *o
   PVR_API_END();
 }
 
-// Rows (partial blocks) of the weight-gradient scratch for a layer shape.
+// The launch of a layer's weight gradient: partial blocks (rows), floats of each.
+struct WgradPlan {
+  long long rows, rec, wch;  // wch: pixels per chunk (first layer)
+  int n_sub, ntx, nty;       // tiles (other layers)
+  int sub;                   // of them a group
+  bool small;                // 8 x 8 tiles
+};
+// Workgroups of the tiled kernel, each with a partial block to write (147 KB of a
+// 64 -> 64 layer) and reduce: at most one a compute unit, two groups each where there
+// are enough for WG_MIN_ROWS (16x16, 64 -> 64, 256 images: 27.9 us, one group each
+// 29.2, four 36.5).
+constexpr int WG_MAX_ROWS = 256, WG_MIN_ROWS = 64, WG_EACH = 2;
+
 template <int CIN, int COUT>
-static long long wgrad_rows(long long P, long long *wch) {
-  using SH = WgradShape<CIN, COUT>;
-  const long long c = wgrad_chunk(P, SH::KSPLIT);
-  if (wch) *wch = c;
-  return (P + c - 1) / c * SH::KSPLIT;
+static bool wgrad_plan(int B, int H, int W, int stride, WgradPlan &pl) {
+  const int Ho = out_size(H, stride), Wo = out_size(W, stride);
+  if constexpr (CIN < 32) {
+    using SH = WgradShape<CIN, COUT>;
+    const long long P = (long long)B * Ho * Wo;
+    pl.wch = wgrad_chunk(P, SH::KSPLIT);
+    pl.rows = (P + pl.wch - 1) / pl.wch * SH::KSPLIT;
+    pl.rec = SH::REC;
+    return true;
+  } else {
+    pl.small = Ho <= 8 && Wo <= 8;
+    const int tw = pl.small ? 8 : 16, th = pl.small ? 8 : 16 / stride;
+    pl.ntx = (Wo + tw - 1) / tw;
+    pl.nty = (Ho + th - 1) / th;
+    const long long n_sub = (long long)B * pl.ntx * pl.nty;
+    pl.n_sub = (int)n_sub;
+    pl.sub = pl.small && n_sub > WG_MIN_ROWS ? 4 / stride : 1;
+    const long long groups = (n_sub + pl.sub - 1) / pl.sub;
+    pl.rows = std::min(groups, std::max((long long)WG_MIN_ROWS, std::min(groups / WG_EACH, (long long)WG_MAX_ROWS)));
+    pl.rec = 9LL * CIN * COUT;
+    return n_sub <= 0x7fff0000LL;
+  }
 }
+
+static long long wgrad_ranges(long long rows) { return (rows + RED_ROWS - 1) / RED_ROWS; }
 
 extern "C" int64_t pvr_cnn_wgrad_scratch(int32_t B, int32_t H, int32_t W, int32_t cin,
                                          int32_t cout, int32_t stride) {
-  const long long P = (long long)B * out_size(H, stride) * out_size(W, stride);
-#define SCR(CI, CO, ST)                                                                  \
-  if (cin == CI && cout == CO) {                                                         \
-    using SH = WgradShape<CI, CO>;                                                       \
-    const long long rows = wgrad_rows<CI, CO>(P, nullptr);                               \
-    const long long ranges = (rows + RED_ROWS - 1) / RED_ROWS;                            \
-    return rows * (SH::REC + CO) * (long long)sizeof(float) +                            \
-           (ranges > 1 ? ranges * (9LL * CI * CO + CO) * (long long)sizeof(double) : 0); \
+  if (stride != 1 && stride != 2) return 0;
+  WgradPlan pl = {};
+#define SCR(CI, CO, ST)                                                                     \
+  if (cin == CI && cout == CO) {                                                            \
+    wgrad_plan<CI, CO>(B, H, W, stride, pl);                                                \
+    const long long ranges = wgrad_ranges(pl.rows);                                         \
+    return pl.rows * (pl.rec + CO) * (long long)sizeof(float) +                             \
+           (ranges > 1 ? ranges * (9LL * CI * CO + CO) * (long long)sizeof(double) : 0);    \
   }
   CONV_CASES(SCR)
 #undef SCR
   return 0;
+}
+
+template <int CIN, int COUT, int S>
+static pvr_status conv_wgrad(const uint16_t *gout, const uint16_t *out, const uint16_t *in,
+                             float *scratch, float *dw, float *db, int B, int H, int W,
+                             hipStream_t stream) {
+  WgradPlan pl = {};
+  if (!wgrad_plan<CIN, COUT>(B, H, W, S, pl)) return fail(PVR_ESHAPE, "pvr_cnn: more than 2^31 tiles");
+  float *part = scratch, *bpart = scratch + pl.rows * pl.rec;
+  if constexpr (CIN < 32) {
+    const int chunks = (int)(pl.rows / WgradShape<CIN, COUT>::KSPLIT);
+    hipLaunchKernelGGL((k_conv_wgrad<CIN, COUT, S>), dim3(chunks), dim3(1024), 0, stream, gout, out,
+                       in, part, bpart, B, H, W, pl.wch);
+  } else {
+    const int Ho = out_size(H, S), Wo = out_size(W, S);
+#define WG_LAUNCH(TW, TH, NSUB)                                                                \
+  hipLaunchKernelGGL((k_wgrad_tile<CIN, COUT, S, TW, TH, NSUB>), dim3((unsigned)pl.rows), dim3(1024), \
+                     0, stream, gout, out, in, part, bpart, H, W, Ho, Wo, pl.n_sub, pl.ntx, pl.nty)
+    if (!pl.small) WG_LAUNCH(16, 16 / S, 1);
+    else if (pl.sub == 1) WG_LAUNCH(8, 8, 1);
+    else WG_LAUNCH(8, 8, 4 / S);
+#undef WG_LAUNCH
+  }
+  HIP_TRY(hipGetLastError());
+  const int nred = COUT * 9 * CIN + COUT;  // weights, then biases
+  const int ranges = (int)wgrad_ranges(pl.rows);
+  double *partial = ranges > 1 ? (double *)(bpart + pl.rows * COUT) : nullptr;
+  hipLaunchKernelGGL((k_wgrad_reduce<CIN, COUT>), dim3((nred + 63) / 64, ranges), dim3(RED_WAVES * 64),
+                     0, stream, part, bpart, (int)pl.rows, dw, db, partial);
+  HIP_TRY(hipGetLastError());
+  if (ranges > 1) {
+    hipLaunchKernelGGL(k_wgrad_finish, dim3((nred + 255) / 256), dim3(256), 0, stream, partial, ranges,
+                       nred - COUT, nred, dw, db);
+    HIP_TRY(hipGetLastError());
+  }
+  return PVR_OK;
 }
 
 extern "C" pvr_status pvr_cnn_conv_wgrad(const uint16_t *gout, const uint16_t *out,
@@ -868,31 +1432,9 @@ extern "C" pvr_status pvr_cnn_conv_wgrad(const uint16_t *gout, const uint16_t *o
   PVR_ALIGNED("pvr_cnn_conv_wgrad", db, 4);
   if (!gout || !out || !in || !scratch || !dw || !db || B <= 0)
     return fail(PVR_EINVAL, "pvr_cnn_conv_wgrad: invalid argument");
-  const long long P = (long long)B * out_size(H, stride) * out_size(W, stride);
-  const int nred = cout * 9 * cin + cout;  // weights, then biases
-#define LAUNCH(CI, CO, ST)                                                                       \
-  if (cin == CI && cout == CO && stride == ST) {                                                 \
-    using SH = WgradShape<CI, CO>;                                                               \
-    long long wch = 0;                                                                           \
-    const long long rows = wgrad_rows<CI, CO>(P, &wch);                                          \
-    const int chunks = (int)(rows / SH::KSPLIT);                                                 \
-    float *part = scratch;                                                                       \
-    float *bpart = scratch + rows * SH::REC;                                                     \
-    hipLaunchKernelGGL((k_conv_wgrad<CI, CO, ST>), dim3(chunks), dim3(1024), 0, stream, gout,    \
-                       out, in, part, bpart, B, H, W, wch);                                      \
-    HIP_TRY(hipGetLastError());                                                                  \
-    const int ranges = (int)((rows + RED_ROWS - 1) / RED_ROWS);                                  \
-    double *partial = ranges > 1 ? (double *)(bpart + rows * CO) : nullptr;                      \
-    hipLaunchKernelGGL((k_wgrad_reduce<CI, CO>), dim3((nred + 63) / 64, ranges),                 \
-                       dim3(RED_WAVES * 64), 0, stream, part, bpart, (int)rows, dw, db, partial); \
-    HIP_TRY(hipGetLastError());                                                                  \
-    if (ranges > 1) {                                                                            \
-      hipLaunchKernelGGL(k_wgrad_finish, dim3((nred + 255) / 256), dim3(256), 0, stream, partial, \
-                         ranges, nred - CO, nred, dw, db);                                       \
-      HIP_TRY(hipGetLastError());                                                                \
-    }                                                                                            \
-    return PVR_OK;                                                                               \
-  }
+#define LAUNCH(CI, CO, ST)                                                           \
+  if (cin == CI && cout == CO && stride == ST)                                       \
+    return conv_wgrad<CI, CO, ST>(gout, out, in, scratch, dw, db, B, H, W, stream);
   CONV_CASES(LAUNCH)
 #undef LAUNCH
   return fail(PVR_EUNSUPPORTED, "pvr_cnn_conv_wgrad: no kernel for cin %d cout %d stride %d", cin,
@@ -916,7 +1458,7 @@ extern "C" pvr_status pvr_cnn_pack_pairs(const pvr_plan *p, const int32_t *patch
       return fail(PVR_ESHAPE, "pvr_cnn_pack_pairs: patch %d is not %dx%d", s, PVR_CNN_SIDE,
                   PVR_CNN_SIDE);
   hipLaunchKernelGGL(k_pack_pairs, dim3(B), dim3(256), 0, stream, p->d_patch, patch_ids, p->d_invz,
-                     y_obs, y_sim, out, PVR_CNN_SIDE, p->M);
+                     y_obs, y_sim, out, p->M);
   HIP_TRY(hipGetLastError());
   return PVR_OK;
   PVR_API_END();

@@ -138,9 +138,13 @@ class Net:
     def forward(self, B: int, target=None):
         """Forward pass on buffers(B)['x']; with target also the loss and the
         head gradients.  Returns the prediction tensor [B*6]."""
+        return self._layers(B, 0, target)
+
+    def _layers(self, B: int, first: int, target=None):
+        """The layers from `first` on and the head."""
         L, bf = self.L, self.buffers(B)
-        x = bf["x"]
-        for (H, W), layer, out in zip(bf["shapes"], self.conv, bf["acts"]):
+        x = bf["acts"][first - 1] if first else bf["x"]
+        for (H, W), layer, out in list(zip(bf["shapes"], self.conv, bf["acts"]))[first:]:
             _ck(L.pvr_cnn_conv_fwd(_p(x), _p(layer["wb"]), _p(layer["b"]), _p(out), B, H, W,
                                    layer["cin"], layer["cout"], layer["s"], 1, _s()))
             x = out
@@ -188,9 +192,13 @@ class Net:
 
     def predict(self, plan, y_obs, y_sim, ids, B: int):
         """Scaled 6-DoF corrections [B, 6] for the patches ids [B] (int32,
-        device) of a built plan."""
+        device) of a built plan.  The first two layers run as one pass, which
+        leaves no first activation (buffers(B)["acts"][0])."""
         self.pack(plan, ids, y_obs, y_sim, B)
-        return self.forward(B).view(B, 6)
+        bf, (c0, c1) = self.buffers(B), self.conv[:2]
+        _ck(self.L.pvr_cnn_stem_fwd(_p(bf["x"]), _p(c0["wb"]), _p(c0["b"]), _p(c1["wb"]),
+                                    _p(c1["b"]), _p(bf["acts"][1]), B, SIDE, SIDE, _s()))
+        return self._layers(B, 2).view(B, 6)
 
 
 def make_pairs(plan, X, theta_ref, offsets, noise_sd: float, seed: int):

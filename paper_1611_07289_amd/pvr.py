@@ -106,7 +106,7 @@ EXPORTS = ["pvr_last_error", "pvr_version", "pvr_plan_create", "pvr_plan_destroy
            "pvr_register_patches", "pvr_simulate_grad_theta", "pvr_simulate_grad_theta_f64",
            "pvr_ncc_grad", "pvr_plan_set_tiles", "pvr_plan_set_timing", "pvr_plan_kernel_time",
            "pvr_plan_set_psf",
-           "pvr_cnn_conv_fwd", "pvr_cnn_conv_dgrad",
+           "pvr_cnn_conv_fwd", "pvr_cnn_stem_fwd", "pvr_cnn_conv_dgrad",
            "pvr_cnn_wgrad_scratch", "pvr_cnn_conv_wgrad", "pvr_cnn_pack_pairs",
            "pvr_cnn_head_scratch", "pvr_cnn_head", "pvr_cnn_adam",
            "pvr_slic_centres", "pvr_slic_init", "pvr_slic_assign", "pvr_slic_update", "pvr_slic",
@@ -164,6 +164,7 @@ def load(path: str = LIB_PATH):
     L.pvr_plan_set_timing.argtypes = [P, i32]
     L.pvr_plan_kernel_time.argtypes = [P, i32, P, P]
     L.pvr_cnn_conv_fwd.argtypes = [P, P, P, P, i32, i32, i32, i32, i32, i32, i32, P]
+    L.pvr_cnn_stem_fwd.argtypes = [P, P, P, P, P, P, i32, i32, i32, P]
     L.pvr_cnn_conv_dgrad.argtypes = [P, P, P, P, i32, i32, i32, i32, i32, i32, P]
     L.pvr_cnn_wgrad_scratch.argtypes = [i32, i32, i32, i32, i32, i32]
     L.pvr_cnn_wgrad_scratch.restype = i64
