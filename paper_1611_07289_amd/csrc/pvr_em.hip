@@ -21,7 +21,7 @@ using namespace pvr;
 
 constexpr int EM_T = 256;     // per-patch workgroups
 constexpr int EMP_T = 1024;   // per-problem workgroups
-constexpr int PSTAT = 10;     // doubles per patch in the scratch table
+constexpr int PSTAT = 5;      // doubles per patch of the residual statistics
 constexpr int EMP_LDS = 12288; // patches per problem whose potentials fit the LDS copy
 
 // Workgroup reductions in a fixed order: a butterfly inside every wave, then
@@ -36,12 +36,45 @@ __device__ __forceinline__ double combine(double a, double b) {
   return fmax(a, b);
 }
 
+// The value of lane ^ O (O = 32, 16: swaps of half wavefronts and rows of 16;
+// 8 .. 1: rotations within a row, where the values repeat every 2 O lanes, as
+// they do in a butterfly from 32 down), a few cycles instead of an LDS
+// permutation's hundred.
+template <int O>
+__device__ __forceinline__ double from_xor(double x) {
+  const uint2 u = __builtin_bit_cast(uint2, x);
+  uint2 r;
+  if constexpr (O == 32 || O == 16) {
+    // {own half or row's low, high}: the sum of both is wanted, so either order
+    // will do; the other lane's value is the one that is not this lane's
+    const auto a = O == 32 ? __builtin_amdgcn_permlane32_swap(u.x, u.x, false, false)
+                           : __builtin_amdgcn_permlane16_swap(u.x, u.x, false, false);
+    const auto b = O == 32 ? __builtin_amdgcn_permlane32_swap(u.y, u.y, false, false)
+                           : __builtin_amdgcn_permlane16_swap(u.y, u.y, false, false);
+    const bool high = threadIdx.x & O;
+    r = make_uint2(high ? a[0] : a[1], high ? b[0] : b[1]);
+  } else {
+    r = make_uint2(__builtin_amdgcn_update_dpp(0u, u.x, 0x120 + O, 0xf, 0xf, false),
+                   __builtin_amdgcn_update_dpp(0u, u.y, 0x120 + O, 0xf, 0xf, false));
+  }
+  return __builtin_bit_cast(double, r);
+}
+// Reduction over the wavefront in every lane, by a butterfly from lane ^ 32 down.
+template <Op OP>
+__device__ __forceinline__ double wave_reduce(double x) {
+  x = combine<OP>(x, from_xor<32>(x));
+  x = combine<OP>(x, from_xor<16>(x));
+  x = combine<OP>(x, from_xor<8>(x));
+  x = combine<OP>(x, from_xor<4>(x));
+  x = combine<OP>(x, from_xor<2>(x));
+  return combine<OP>(x, from_xor<1>(x));
+}
+
 template <int NT, Op OP>
 __device__ __forceinline__ double breduce(double v, double *lds) {
   constexpr int NW = NT / 64;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = combine<OP>(v, __shfl_xor(v, o, 64));
+  v = wave_reduce<OP>(v);
   if (lane == 0) lds[wave] = v;
   __syncthreads();
   double r = lds[0];
@@ -58,9 +91,7 @@ __device__ __forceinline__ void bsumk(double (&v)[K], double *lds) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int q = 0; q < K; ++q) {
-    double x = v[q];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+    const double x = wave_reduce<Op::Sum>(v[q]);
     if (lane == 0) lds[q * NW + wave] = x;
   }
   __syncthreads();
@@ -121,8 +152,27 @@ k_em_problem(const ProbDev *__restrict__ probs, const double *__restrict__ pstat
   double mn = INFINITY, mx = -INFINITY, ym = 0, se2 = 0, cnt = 0;
   const int r0 = chunk_stats ? (planes ? pr.pblk_begin : pr.chunk_begin) : pr.patch_begin;
   const int r1 = chunk_stats ? (planes ? pr.pblk_end : pr.chunk_end) : pr.patch_end;
-  for (int s = r0 + threadIdx.x; s < r1; s += EMP_T) {
-    const double *o = chunk_stats ? chunk_stats + 5 * (long long)s : pstat + PSTAT * s;
+  const double *rec = chunk_stats ? chunk_stats : pstat;
+  const long long stride = chunk_stats ? 5 : PSTAT;
+  // four records per thread in flight, taken in the order of one at a time
+  int s = r0 + threadIdx.x;
+  for (; s + 3 * EMP_T < r1; s += 4 * EMP_T) {
+    double o[4][5];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int k = 0; k < 5; ++k) o[u][k] = rec[stride * (s + u * EMP_T) + k];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      mn = fmin(mn, o[u][0]);
+      mx = fmax(mx, o[u][1]);
+      ym = fmax(ym, o[u][2]);
+      se2 += o[u][3];
+      cnt += o[u][4];
+    }
+  }
+  for (; s < r1; s += EMP_T) {
+    const double *o = rec + stride * s;
     mn = fmin(mn, o[0]);
     mx = fmax(mx, o[1]);
     ym = fmax(ym, o[2]);
@@ -134,14 +184,11 @@ k_em_problem(const ProbDev *__restrict__ probs, const double *__restrict__ pstat
   {
     constexpr int NW = EMP_T / 64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      mn = fmin(mn, __shfl_xor(mn, o, 64));
-      mx = fmax(mx, __shfl_xor(mx, o, 64));
-      ym = fmax(ym, __shfl_xor(ym, o, 64));
-      se2 += __shfl_xor(se2, o, 64);
-      cnt += __shfl_xor(cnt, o, 64);
-    }
+    mn = wave_reduce<Op::Min>(mn);
+    mx = wave_reduce<Op::Max>(mx);
+    ym = wave_reduce<Op::Max>(ym);
+    se2 = wave_reduce<Op::Sum>(se2);
+    cnt = wave_reduce<Op::Sum>(cnt);
     if (lane == 0) {
       lds[0 * NW + wave] = mn;
       lds[1 * NW + wave] = mx;
@@ -183,7 +230,7 @@ k_em_problem(const ProbDev *__restrict__ probs, const double *__restrict__ pstat
 __global__ void __launch_bounds__(EM_T)
 k_em_estep(const PatchDev *__restrict__ patches, const float *__restrict__ invz,
            const float *__restrict__ e, const pvr_em_state *__restrict__ em,
-           float *__restrict__ p_out, float *__restrict__ pbar, double *__restrict__ pstat) {
+           float *__restrict__ p_out, float *__restrict__ pbar, double *__restrict__ esum, int M) {
   __shared__ double lds[8 * (EM_T / 64)];
   const int s = blockIdx.x;
   const PatchDev pt = patches[s];
@@ -232,8 +279,10 @@ k_em_estep(const PatchDev *__restrict__ patches, const float *__restrict__ invz,
   bsumk<EM_T, 4>(red, lds);
   ns = red[0]; sp2 = red[1]; sp = red[2]; spe2 = red[3];
   if (threadIdx.x == 0) {
-    double *o = pstat + PSTAT * s;
-    o[5] = ns; o[6] = sp2; o[7] = sp; o[8] = spe2;
+    esum[s] = ns;
+    esum[M + s] = sp2;
+    esum[2LL * M + s] = sp;
+    esum[3LL * M + s] = spe2;
     if (pbar) pbar[s] = ns > 0 ? (float)sqrt(sp2 / ns) : 0.f;
   }
 }
@@ -262,32 +311,22 @@ __device__ __forceinline__ double inlier_resp(double v, const Mix &m) {
   return 1.0 / (1.0 + exp(l0 - l1));
 }
 
-// The same in single precision for the mixture iterations (the sums over
-// patches stay FP64; the responsibilities differ from the FP64 ones by ~1e-7
-// relative, which moves the fitted parameters by as little).  The final
-// patch posteriors use inlier_resp.
-struct MixF {
-  float mu0, mu1, h0, h1, c0, c1;
-};
-// The constants of make_mix in single precision from the FP64 parameters
-// (single-precision logarithms: the constants only enter inlier_resp_f).
-__device__ __forceinline__ MixF make_mix_f(double mu0, double sd0, double mu1, double sd1,
-                                          double w1) {
-  const float s0 = (float)sd0, s1 = (float)sd1, wf = (float)w1;
-  MixF m;
-  m.mu0 = (float)mu0;
-  m.mu1 = (float)mu1;
-  m.h0 = 0.5f / (s0 * s0);
-  m.h1 = 0.5f / (s1 * s1);
-  m.c1 = w1 > 0 ? __logf(wf) - __logf(s1) : -INFINITY;
-  m.c0 = w1 < 1 ? __logf(1.f - wf) - __logf(s0) : -INFINITY;
-  return m;
+// The same for the mixture iterations: the exponent in FP64, its whole part
+// taken off before the single-precision exponential, so the responsibilities (FP32)
+// are right to ~1e-7 relative whatever the exponent (up to hundreds where the
+// components are narrow); the sums over patches stay FP64.
+__device__ __forceinline__ float inlier_resp_f(double v, const Mix &m) {
+  const double d0 = v - m.mu0, d1 = v - m.mu1;
+  const double l = (m.c0 - d0 * d0 * m.h0) - (m.c1 - d1 * d1 * m.h1);
+  // +-inf when a component has zero weight: 2^200 is inf, 1 / (1 + inf) = 0
+  const double t = fmin(fmax(l * 1.4426950408889634, -200.0), 200.0), n = rint(t);
+  return __builtin_amdgcn_rcpf(1.f + ldexpf(__builtin_amdgcn_exp2f((float)(t - n)), (int)n));
 }
-__device__ __forceinline__ float inlier_resp_f(float v, const MixF &m) {
-  const float d0 = v - m.mu0, d1 = v - m.mu1;
-  const float l = (m.c0 - d0 * d0 * m.h0) - (m.c1 - d1 * d1 * m.h1);
-  // l = +-inf when a component has zero weight: exp gives inf or 0, 1/(1+inf) = 0
-  return __builtin_amdgcn_rcpf(1.f + __expf(l));
+
+// Lane l's value in every lane.
+__device__ __forceinline__ double lane_value(double x, int l) {
+  const int2 u = __builtin_bit_cast(int2, x);
+  return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_readlane(u.x, l), __builtin_amdgcn_readlane(u.y, l)));
 }
 
 // Two-component mixture on the potentials of one problem, patch weights and
@@ -296,68 +335,93 @@ __device__ __forceinline__ float inlier_resp_f(float v, const MixF &m) {
 // on the float bit patterns (potentials are >= 0, so the patterns are ordered
 // like the values).
 //
-// The potentials of the problem's patches are first copied to a compact
-// array (-1 marks a patch that takes no part): in LDS when the problem has
-// at most EMP_LDS patches, else in the plan's scratch array, so the 20
-// mixture iterations touch only that array.  One pass per iteration gathers
+// The potentials of the problem's patches (FP64: where the components are narrow,
+// 1e-3 at least, an FP32 one's rounding would move a patch's posterior by 1e-4) are
+// first gathered into a compact array (-1 marks a patch that takes no part): in LDS when
+// the problem has at most EMP_LDS patches, else in the plan's scratch array, so the
+// 20 mixture iterations touch only that array.  One pass per iteration gathers
 // the high component's sums of r, r v and r v^2; the low component's follow
 // from the totals (sum 1, sum v, sum v^2), and each variance is
 // E[v^2] - mean^2 (values in [0, 1], FP64: the cancellation costs ~1e-16 /
 // var relative, against a floor of 1e-6 on the variance).  Inside the
 // iterations the responsibilities are single precision (inlier_resp_f).
-__global__ void __launch_bounds__(EMP_T)
-k_em_patches(const ProbDev *__restrict__ probs, const float *__restrict__ pbar,
-             const uint8_t *__restrict__ active, const double *__restrict__ pstat,
-             float *__restrict__ gval, float *__restrict__ patch_w, pvr_em_state *__restrict__ em,
-             int fix_w, int use_lds) {
-  __shared__ double lds[8 * (EMP_T / 64)];
+//
+// Bound by the chain of the iterations: the wavefronts' sums, a barrier, the
+// wavefronts' sums in order, the step to the next parameters with its divisions, roots and
+// logarithms side by side in lanes.  Up to 256 patches four wavefronts (64: one),
+// one a SIMD, take the step each for itself; beyond, sixteen, of which one takes it
+// for all, at one more barrier (at 128^3 59 us, each for itself 68).  The order
+// of addition is that of EMP_T lanes throughout: the lanes beyond a problem's
+// patches would add zeros.  32^3, 216 patches 32 us, 256^3, 11 760 patches 190; 79 and
+// 216 with 16 wavefronts always, LDS permutations, one lane taking the step and flat
+// reads of the potentials.
+// K sums of the workgroup into every lane, in the order of bsumk; two calls with
+// the same lds need a barrier in between.
+template <int NT, int K>
+__device__ __forceinline__ void wsumk(double (&v)[K], double *lds) {
+  constexpr int NW = NT / 64;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const double x = wave_reduce<Op::Sum>(v[k]);
+    if (lane == 0) lds[k * NW + wave] = x;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    v[k] = lds[k * NW];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v[k] += lds[k * NW + w];
+  }
+}
+
+template <int NT, bool LDS>
+__global__ void __launch_bounds__(NT)
+k_em_patches(const ProbDev *__restrict__ probs,
+             const uint8_t *__restrict__ active, const double *__restrict__ esum, int M,
+             double *__restrict__ gval, float *__restrict__ patch_w, pvr_em_state *__restrict__ em,
+             int fix_w) {
+  constexpr int U = NT < EMP_T ? 1 : 4;            // patches of a lane in flight
+  constexpr bool ONE = NT > 256;                   // one wavefront takes the step
+  __shared__ double lds[2][4 * (NT / 64)];         // in turn: one barrier a sum
+  __shared__ double par[3];                        // variances, weight
+  __shared__ Mix mixs;
+  __shared__ int stop;
   __shared__ unsigned int hist[256];
   __shared__ unsigned int sel_prefix, sel_rank;
-  __shared__ double mixp[5];  // mu0, sd0, mu1, sd1, w1
-  __shared__ MixF mixf;
-  __shared__ int mix_stop;
-  extern __shared__ float sval[];
+  __shared__ double sval[LDS ? (NT < EMP_T ? NT : EMP_LDS) : 1];
   const ProbDev pr = probs[blockIdx.x];
-  const int t = threadIdx.x;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int pb = pr.patch_begin, np = pr.patch_end - pr.patch_begin;
-  float *V = use_lds ? sval : gval + pb;
-  double n = 0, s_all = 0, q_all = 0;
-  // the patches taking part (valid samples, active) and their potentials;
-  // the three reads of a patch are independent and four patches per thread
-  // are in flight, taken in the same order as one at a time
-  auto take = [&](int q, double ns, uint8_t act, float pv) {
-    const float v = (ns > 0 && act != 0) ? pv : -1.f;
-    V[q] = v;
-    if (v >= 0.f) {
-      n += 1.0;
-      s_all += (double)v;
-      q_all += (double)v * (double)v;
-    }
-  };
+  double *V = LDS ? sval : gval + pb;  // (a choice at run time would make every read a flat one)
+  // the patches taking part (valid samples, active) and their potentials; the
+  // reads of a patch, and of U patches, are independent
+  double n, s_all, q_all;
   {
-    int q = t;
-    for (; q + 3 * EMP_T < np; q += 4 * EMP_T) {
-      double ns[4];
-      uint8_t act[4];
-      float pv[4];
+    double r3[3] = {0, 0, 0};
+    for (int q0 = t; q0 < np; q0 += U * EMP_T) {
+      double ns[U], sp2[U];
+      uint8_t act[U];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int s = pb + q + u * EMP_T;
-        ns[u] = pstat[PSTAT * s + 5];
+      for (int u = 0; u < U; ++u) {
+        const int s = pb + min(q0 + u * EMP_T, np - 1);
+        ns[u] = esum[s];
+        sp2[u] = esum[M + s];
         act[u] = active[s];
-        pv[u] = pbar[s];
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) take(q + u * EMP_T, ns[u], act[u], pv[u]);
+      for (int u = 0; u < U; ++u) {
+        if (q0 + u * EMP_T >= np) continue;
+        const double v = (ns[u] > 0 && act[u] != 0) ? sqrt(sp2[u] / ns[u]) : -1.0;
+        V[q0 + u * EMP_T] = v;
+        if (v >= 0) {
+          r3[0] += 1.0;
+          r3[1] += v;
+          r3[2] += v * v;
+        }
+      }
     }
-    for (; q < np; q += EMP_T) {
-      const int s = pb + q;
-      take(q, pstat[PSTAT * s + 5], active[s], pbar[s]);
-    }
-  }
-  {
-    double r3[3] = {n, s_all, q_all};
-    bsumk<EMP_T, 3>(r3, lds);  // its barriers also publish V
+    wsumk<NT, 3>(r3, lds[0]);  // its barrier also publishes V
     n = r3[0]; s_all = r3[1]; q_all = r3[2];
   }
   const int nu = (int)n;
@@ -370,15 +434,25 @@ k_em_patches(const ProbDev *__restrict__ probs, const float *__restrict__ pbar,
     __syncthreads();
     for (int pass = 0; pass < 4; ++pass) {
       const int shift = 24 - 8 * pass;
-      for (int b = t; b < 256; b += EMP_T) hist[b] = 0;
+      for (int b = t; b < 256; b += NT) hist[b] = 0;
       __syncthreads();
       const unsigned pref = sel_prefix;
       const unsigned mask_hi = pass == 0 ? 0u : (0xffffffffu << (32 - 8 * pass));
-      for (int q = t; q < np; q += EMP_T) {
-        const float v = V[q];
-        if (!(v >= 0.f)) continue;
-        const unsigned bits = __float_as_uint(v);
-        if ((bits & mask_hi) == pref) atomicAdd(&hist[(bits >> shift) & 255u], 1u);
+      for (int q0 = t - lane; q0 < np; q0 += NT) {
+        const float v = q0 + lane < np ? (float)V[q0 + lane] : -1.f;
+        const unsigned bits = __float_as_uint(v), bin = (bits >> shift) & 255u;
+        bool on = v >= 0.f && (bits & mask_hi) == pref;
+        // the potentials crowd in a few bins: equal ones of a wavefront at once
+        for (int k = 0; k < 4; ++k) {
+          const unsigned long long left = __ballot(on);
+          if (!left) break;
+          const int first = __builtin_ctzll(left);
+          const unsigned b = __builtin_amdgcn_readlane(bin, first);
+          const unsigned long long same = __ballot(on && bin == b);
+          if (lane == first) atomicAdd(&hist[b], (unsigned)__popcll(same));
+          on = on && bin != b;
+        }
+        if (on) atomicAdd(&hist[bin], 1u);
       }
       __syncthreads();
       // the bin holding rank r: wave 0 scans the 256 counts (4 per lane)
@@ -411,119 +485,134 @@ k_em_patches(const ProbDev *__restrict__ probs, const float *__restrict__ pbar,
       __syncthreads();
     }
     const double tv = (double)__uint_as_float(sel_prefix);
-    double c_lt = 0, s_lt = 0, q_lt = 0;
+    double red3[3] = {0, 0, 0};
     for (int q = t; q < np; q += EMP_T) {
       const double v = V[q];
-      if (v >= 0 && v < tv) { c_lt += 1; s_lt += v; q_lt += v * v; }
+      if (v >= 0 && (float)v < (float)tv) { red3[0] += 1; red3[1] += v; red3[2] += v * v; }
     }
-    double red3[3] = {c_lt, s_lt, q_lt};
-    bsumk<EMP_T, 3>(red3, lds);
-    c_lt = red3[0]; s_lt = red3[1]; q_lt = red3[2];
-    // the mixture state lives in LDS and is updated by one lane: its FP64
-    // divisions, square roots and logarithms would otherwise run in all 16
-    // waves of the workgroup
-    if (t == 0) {
-      const double fill = n_lo - c_lt;
-      const double s0 = s_lt + fill * tv, q0 = q_lt + fill * tv * tv;
-      const double n_hi = nu - n_lo;
-      const double m0 = s0 / n_lo, m1 = (s_all - s0) / n_hi;
-      mixp[0] = m0;
-      mixp[1] = fmax(sqrt(fmax(q0 / n_lo - m0 * m0, 0.0)), 1e-3);
-      mixp[2] = m1;
-      mixp[3] = fmax(sqrt(fmax((q_all - q0) / n_hi - m1 * m1, 0.0)), 1e-3);
-      mixp[4] = 0.9;
-      mixf = make_mix_f(mixp[0], mixp[1], mixp[2], mixp[3], mixp[4]);
-      mix_stop = 0;
-    }
-    __syncthreads();
+    wsumk<NT, 3>(red3, lds[1]);
+    const double c_lt = red3[0], s_lt = red3[1], q_lt = red3[2];
+    Mix mx;
+    double var0 = 1, var1 = 1;
+    // the parameters from the components' sums of r v and r v^2 and their weights
+    // (n1 / nu returned), and the constants of make_mix at the weight `wt` (0: that
+    // one): every lane's result, the operations side by side in lanes
+    const auto step = [&](double v1, double v0, double q1, double q0, double n1, double n0, double wt) {
+      const double num = lane == 0 ? v1 : lane == 1 ? v0 : lane == 2 ? q1 : lane == 3 ? q0 : n1;
+      const double den = lane == 4 ? (double)nu : (lane & 1) ? n0 : n1;
+      const double m = num / den;
+      mx.mu1 = lane_value(m, 0);
+      mx.mu0 = lane_value(m, 1);
+      w1 = wt > 0 ? wt : lane_value(m, 4);
+      const double mu = (lane & 1) ? mx.mu0 : mx.mu1, sq = (lane & 1) ? lane_value(m, 3) : lane_value(m, 2);
+      const double var = fmax(sq - mu * mu, 1e-6);  // sd at least 1e-3
+      const double h = 0.5 / var;
+      const double lg = log(lane < 2 ? var : lane == 2 ? w1 : 1.0 - w1);
+      var1 = lane_value(var, 0);
+      var0 = lane_value(var, 1);
+      mx.h1 = lane_value(h, 0);
+      mx.h0 = lane_value(h, 1);
+      mx.c1 = lane_value(lg, 2) - 0.5 * lane_value(lg, 0);
+      mx.c0 = lane_value(lg, 3) - 0.5 * lane_value(lg, 1);
+    };
+    const double fill = n_lo - c_lt;
+    const double s0 = s_lt + fill * tv, q0 = q_lt + fill * tv * tv;
+    step(s_all - s0, s0, q_all - q0, q0, nu - n_lo, n_lo, 0.9);
     for (int it = 0; it < 20; ++it) {
-      double r1s = 0, r1v = 0, r1q = 0;
-      const MixF mx = mixf;
+      double red[3] = {0, 0, 0};  // sums of r1, r1 v, r1 v^2
+#pragma unroll 4
       for (int q = t; q < np; q += EMP_T) {
-        const float vf = V[q];
-        if (!(vf >= 0.f)) continue;
-        const double v = vf;
-        const double r1 = inlier_resp_f(vf, mx);
-        r1s += r1;
-        r1v += r1 * v;
-        r1q += r1 * v * v;
-      }
-      double red[3] = {r1s, r1v, r1q};
-      bsumk<EMP_T, 3>(red, lds);
-      if (t == 0) {
-        r1s = red[0]; r1v = red[1]; r1q = red[2];
-        const double r0s = nu - r1s;
-        if (!(r1s > 0) || !(r0s > 0)) {
-          mix_stop = 1;
-        } else {
-          const double m1 = r1v / r1s, m0 = (s_all - r1v) / r0s;
-          mixp[2] = m1;
-          mixp[0] = m0;
-          mixp[3] = fmax(sqrt(fmax(r1q / r1s - m1 * m1, 0.0)), 1e-3);
-          mixp[1] = fmax(sqrt(fmax((q_all - r1q) / r0s - m0 * m0, 0.0)), 1e-3);
-          mixp[4] = r1s / nu;
-          mixf = make_mix_f(mixp[0], mixp[1], mixp[2], mixp[3], mixp[4]);
+        const double v = V[q];
+        const double r1 = inlier_resp_f(v, mx);
+        if (v >= 0) {
+          red[0] += r1;
+          red[1] += r1 * v;
+          red[2] += r1 * v * v;
         }
       }
-      __syncthreads();
-      if (mix_stop) break;
+      bool last = false;
+      if constexpr (ONE) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          const double x = wave_reduce<Op::Sum>(red[k]);
+          if (lane == 0) lds[0][k * (NT / 64) + wave] = x;
+        }
+        __syncthreads();
+        if (wave == 0) {
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            red[k] = lds[0][k * (NT / 64)];
+#pragma unroll
+            for (int w = 1; w < NT / 64; ++w) red[k] += lds[0][k * (NT / 64) + w];
+          }
+          const double r1s = red[0], r0s = nu - r1s;
+          last = !(r1s > 0) || !(r0s > 0);
+          if (!last) step(red[1], s_all - red[1], red[2], q_all - red[2], r1s, r0s, 0.0);
+          if (lane == 0) {
+            mixs = mx;
+            par[0] = var0; par[1] = var1; par[2] = w1;
+            stop = last;
+          }
+        }
+        __syncthreads();
+        mx = mixs;
+        last = stop;
+      } else {
+        wsumk<NT, 3>(red, lds[it & 1]);
+        const double r1s = red[0], r0s = nu - r1s;
+        last = !(r1s > 0) || !(r0s > 0);  // (the same in every lane)
+        if (!last) step(red[1], s_all - red[1], red[2], q_all - red[2], r1s, r0s, 0.0);
+      }
+      if (last) break;
     }
-    mu0 = mixp[0]; sd0 = mixp[1]; mu1 = mixp[2]; sd1 = mixp[3]; w1 = mixp[4];
+    if constexpr (ONE) {
+      var0 = par[0]; var1 = par[1]; w1 = par[2];
+    }
+    mu0 = mx.mu0; sd0 = sqrt(var0); mu1 = mx.mu1; sd1 = sqrt(var1);
   }
   const bool swap = fit && mu0 > mu1;
   const Mix mfin = make_mix(mu0, sd0, mu1, sd1, w1);
-  // patch weights, then the M-step sums over the problem's patches
-  double swpe2 = 0, swp = 0, sw = 0, nex = 0;
-  // one patch: its weight (given, or from the fitted mixture) and its terms
-  // of the M-step sums, from its partials o = (N_s, sum p, sum p e^2)
-  auto weigh = [&](int q, double o5, double o7, double o8, float wgiven) {
-    const int s = pb + q;
-    double W;
-    const bool u = V[q] >= 0.f;
-    if (fix_w) {
-      W = wgiven;
-    } else {
-      double pi = 0;
-      if (u) {
-        pi = fit ? inlier_resp((double)V[q], mfin) : 1.0;
-        if (swap) pi = 1.0 - pi;
-      }
-      W = (u && pi >= 0.5) ? pi : 0.0;
-      patch_w[s] = (float)W;
-      W = (double)(float)W;
-    }
-    swpe2 += W * o8;
-    swp += W * o7;
-    sw += W * o5;
-    nex += (u && W == 0) ? 1.0 : 0.0;
-  };
-  // four patches' partials per thread in flight, in the order of one at a time
-  {
-    int q = t;
-    for (; q + 3 * EMP_T < np; q += 4 * EMP_T) {
-      double o5[4], o7[4], o8[4];
-      float wg[4];
+  // patch weights (given, or from the fitted mixture), then the M-step sums over
+  // the problem's patches from their partials o = (N_s, sum p, sum p e^2)
+  double red4[4] = {0, 0, 0, 0};
+  for (int q0 = t; q0 < np; q0 += U * EMP_T) {
+    double o5[U], o7[U], o8[U];
+    float wg[U];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int s = pb + q + u * EMP_T;
-        const double *o = pstat + PSTAT * s;
-        o5[u] = o[5];
-        o7[u] = o[7];
-        o8[u] = o[8];
-        wg[u] = fix_w ? patch_w[s] : 0.f;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) weigh(q + u * EMP_T, o5[u], o7[u], o8[u], wg[u]);
+    for (int u = 0; u < U; ++u) {
+      const int s = pb + min(q0 + u * EMP_T, np - 1);
+      o5[u] = esum[s];
+      o7[u] = esum[2LL * M + s];
+      o8[u] = esum[3LL * M + s];
+      wg[u] = fix_w ? patch_w[s] : 0.f;
     }
-    for (; q < np; q += EMP_T) {
-      const int s = pb + q;
-      const double *o = pstat + PSTAT * s;
-      weigh(q, o[5], o[7], o[8], fix_w ? patch_w[s] : 0.f);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int q = q0 + u * EMP_T, s = pb + q;
+      if (q >= np) continue;
+      double W;
+      const bool on = V[q] >= 0;
+      if (fix_w) {
+        W = wg[u];
+      } else {
+        double pi = 0;
+        if (on) {
+          pi = fit ? inlier_resp(V[q], mfin) : 1.0;
+          if (swap) pi = 1.0 - pi;
+        }
+        W = (on && pi >= 0.5) ? pi : 0.0;
+        patch_w[s] = (float)W;
+        W = (double)(float)W;
+      }
+      red4[0] += W * o8[u];
+      red4[1] += W * o7[u];
+      red4[2] += W * o5[u];
+      red4[3] += (on && W == 0) ? 1.0 : 0.0;
     }
   }
-  double red4b[4] = {swpe2, swp, sw, nex};
-  bsumk<EMP_T, 4>(red4b, lds);
-  swpe2 = red4b[0]; swp = red4b[1]; sw = red4b[2]; nex = red4b[3];
+  __syncthreads();  // both halves of lds are free
+  wsumk<NT, 4>(red4, lds[0]);
+  const double swpe2 = red4[0], swp = red4[1], sw = red4[2], nex = red4[3];
   if (t == 0) {
     pvr_em_state &st = em[blockIdx.x];
     const double floor2 = (1e-4 * st.y_abs_max) * (1e-4 * st.y_abs_max);
@@ -569,7 +658,7 @@ extern "C" pvr_status pvr_robust_weights(pvr_plan *p, const float *resid, const 
                      init, p->d_status);
   HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(k_em_estep, dim3(p->M), dim3(EM_T), 0, stream, p->d_patch, p->d_invz, resid,
-                     em, pp, pb, p->d_pstat);
+                     em, pp, pb, p->d_pstat + PSTAT * (long long)p->M, p->M);
   HIP_TRY(hipGetLastError());
   // the adjoint's inputs need the posteriors only, not the patch weights: on
   // request they are prepared on the plan's second stream while the patch
@@ -583,10 +672,15 @@ extern "C" pvr_status pvr_robust_weights(pvr_plan *p, const float *resid, const 
     if (st != PVR_OK) return st;
     HIP_TRY(hipEventRecord(p->ev_join, p->side));
   }
-  const int use_lds = p->max_problem_patches <= EMP_LDS;
-  hipLaunchKernelGGL(k_em_patches, dim3(p->P), dim3(EMP_T),
-                     use_lds ? (size_t)p->max_problem_patches * sizeof(float) : 0, stream,
-                     p->d_prob, pb, p->d_active, p->d_pstat, p->d_pval, patch_w, em, fix, use_lds);
+#define PATCHES_LAUNCH(NT, LDS)                                                                   \
+  hipLaunchKernelGGL((k_em_patches<NT, LDS>), dim3(p->P), dim3(NT),                              \
+                     0, stream, p->d_prob, p->d_active, p->d_pstat + PSTAT * (long long)p->M, \
+                     p->M, p->d_pval, patch_w, em, fix)
+  if (p->max_problem_patches <= 64) PATCHES_LAUNCH(64, true);
+  else if (p->max_problem_patches <= 256) PATCHES_LAUNCH(256, true);
+  else if (p->max_problem_patches <= EMP_LDS) PATCHES_LAUNCH(EMP_T, true);
+  else PATCHES_LAUNCH(EMP_T, false);
+#undef PATCHES_LAUNCH
   HIP_TRY(hipGetLastError());
   if (prep) {
     HIP_TRY(hipStreamWaitEvent(stream, p->ev_join, 0));

@@ -713,9 +713,9 @@ struct pvr_plan {
   // scratch
   float2 *d_rq;              // [n_rq]: padded rows (RQ_PAD), the padding always zero
   double2 *d_rq64;           // [N + 2] likewise (workspaces with PVR_WS_F64)
-  double *d_pstat;           // [M][10] per-patch EM partials
+  double *d_pstat;           // [M][5] residual statistics, [4][M] E-step sums
   float *d_pbar;             // [M] potentials when the caller passes none
-  float *d_pval;             // [M] classification scratch (problems beyond the LDS copy)
+  double *d_pval;            // [M] classification scratch (problems beyond the LDS copy)
   pvr::FwdPatch<float> *d_fwd;     // [M] plane-walk constants
   pvr::FwdPatch<double> *d_fwd64;  // [M] the same for the FP64 calls
   double *d_chunk_stats;     // [max(n_sim_blocks, n_pblocks)][5] residual statistics of the last
