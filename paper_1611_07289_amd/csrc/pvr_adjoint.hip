@@ -205,13 +205,11 @@ __device__ __forceinline__ void adj_patch_sinc(const GEO &g, const PatchDev &pt,
   const int pitch = Rq<T>::pitch(pt.w);
   for (int b = -hv; b <= hv; ++b) {
     const T tv = ((T)b - fv) * cv;
-    const bool inb = ((unsigned)(rv + b) < (unsigned)pt.h) & (fabs(tv) < (T)1);
-    const T e = inb ? sinc_poly<T>(tv) * gz : (T)0;
+    const T e = (unsigned)(rv + b) < (unsigned)pt.h ? sinc_lobe<T>(tv) * gz : (T)0;
     const int row = (rv + b) * pitch;
     for (int a = -hu; a <= hu; ++a) {
       const T tu = ((T)a - fu) * cu;
-      const bool ina = ((unsigned)(ru + a) < (unsigned)pt.w) & (fabs(tu) < (T)1);
-      const T gh = ina ? sinc_poly<T>(tu) * e : (T)0;
+      const T gh = (unsigned)(ru + a) < (unsigned)pt.w ? sinc_lobe<T>(tu) * e : (T)0;
       const V2 q = load_rq<V2>(r, (row + ru + a + Rq<T>::lead) * (int)sizeof(V2));
       sn = fma(gh, q.x, sn);
       if (DEN) sd = fma(gh, q.y, sd);
@@ -461,8 +459,8 @@ k_gather_blocks(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ 
 #pragma unroll
             for (int a = -1; a <= 1; ++a) {
               const T tu = ((T)a - (f + du[t])) * g.cu, tv = ((T)a - (h + dv[t])) * g.cv;
-              U[t][a + 1] = fabs(tu) < (T)1 ? sinc_poly<T>(tu) : (T)0;
-              E[t][a + 1] = fabs(tv) < (T)1 ? sinc_poly<T>(tv) * gz : (T)0;
+              U[t][a + 1] = sinc_lobe<T>(tu);
+              E[t][a + 1] = sinc_lobe<T>(tv) * gz;
             }
           }
         } else {

@@ -75,7 +75,7 @@ template <typename T>
 __global__ void __launch_bounds__(SIM_THREADS)
 k_simulate(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ patches,
            const BlockWork *__restrict__ work, const typename GeoOf<T>::type *__restrict__ geo,
-           const T *__restrict__ invz, const T *__restrict__ X, const T *__restrict__ XT,
+           const SincPatch *__restrict__ sp, const T *__restrict__ invz, const T *__restrict__ X, const T *__restrict__ XT,
            const T *__restrict__ y_obs, T *__restrict__ y_sim, T *__restrict__ resid,
            double *__restrict__ chunk_stats, int n_work, int granule) {
   const int wi = xcd_work(blockIdx.x, granule);
@@ -102,7 +102,12 @@ k_simulate(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ patch
       int b[3];
       T f[3];
       sample_centre(g, pr, u, v, pt.slice, b, f);
-      yh = sample_value<T>(g, pr, sinc, xt, b, f, xr, nbytes) * iz;
+      bool planes = false;
+      if constexpr (sizeof(T) == 4) {
+        planes = sinc && sp[wk.patch].on != 0;
+        if (planes) yh = sinc_planes<true>(sp[wk.patch], b, f, xr, nbytes) * iz;
+      }
+      if (!planes) yh = sample_value<T>(g, pr, sinc, xt, b, f, xr, nbytes) * iz;
     }
     if (y_sim) y_sim[j] = yh;
     if (resid) {
@@ -341,7 +346,7 @@ static pvr_status simulate_impl(const pvr_plan *p, const T *X, const T *y_obs, T
   else
     hipLaunchKernelGGL(k_simulate<T>, dim3(xcd_blocks(p->n_sim_blocks, p->sim_granule)),
                        dim3(SIM_THREADS), 0, stream, p->d_prob, p->d_patch, p->d_sim_blocks, geo,
-                       invz, X, XT, y_obs, y_sim, resid, stats, p->n_sim_blocks, p->sim_granule);
+                       p->d_sinc, invz, X, XT, y_obs, y_sim, resid, stats, p->n_sim_blocks, p->sim_granule);
   HIP_TRY(hipGetLastError());
   if (ev) HIP_TRY(hipEventRecord(ev[1], stream));
   // the residual statistics describe these buffers until the next build

@@ -134,7 +134,7 @@ k_geometry(const ProbDev *__restrict__ probs, const StackDev *__restrict__ stack
            double *__restrict__ theta, uint8_t *__restrict__ active, GeoD *__restrict__ gd,
            GeoF *__restrict__ gf, AdjPatch<float> *__restrict__ adj,
            AdjPatch<double> *__restrict__ adj64, FwdPatch<float> *__restrict__ fwd,
-           FwdPatch<double> *__restrict__ fwd64, int *__restrict__ bb, int *__restrict__ gbox,
+           FwdPatch<double> *__restrict__ fwd64, SincPatch *__restrict__ sp, int *__restrict__ bb, int *__restrict__ gbox,
            double *__restrict__ sbox) {
   __shared__ MiniGeo mini[64];
   const int lane = threadIdx.x & 63, role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -161,6 +161,7 @@ k_geometry(const ProbDev *__restrict__ probs, const StackDev *__restrict__ stack
     m.cu = g.cu; m.cv = g.cv; m.ck = g.ck; m.K2 = g.K2; m.cut = g.cut;
     gf[s] = f;
     if (f64) gd[s] = g;
+    if (psf == PVR_PSF_SINC) make_sinc(g, probs[pt.problem], pt, sp[s]);
     active[s] = active_in ? active_in[s] : 1;
   }
   __syncthreads();
@@ -220,8 +221,9 @@ template <typename T>
 __global__ void __launch_bounds__(SIM_THREADS)
 k_normalisers(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ patches,
               const BlockWork *__restrict__ work, const typename GeoOf<T>::type *__restrict__ geo,
-              const uint8_t *__restrict__ mask, const uint8_t *__restrict__ active,
-              uint8_t *__restrict__ keep, float *__restrict__ invz, double *__restrict__ invz64) {
+              const SincPatch *__restrict__ sp, const uint8_t *__restrict__ mask,
+              const uint8_t *__restrict__ active, uint8_t *__restrict__ keep,
+              float *__restrict__ invz, double *__restrict__ invz64) {
   const BlockWork wk = work[blockIdx.x];
   const PatchDev pt = patches[wk.patch];
   const ProbDev pr = probs[pt.problem];
@@ -240,7 +242,12 @@ k_normalisers(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ pa
     T z = 0, acc = 0;
     if (ok && g.psf == PVR_PSF_SINC) {
       const __amdgpu_buffer_rsrc_t none = raw_buffer((const T *)nullptr, 0u);
-      psf_walk_sinc<T, typename GeoOf<T>::type, false>(g, pr, b, f, none, 0u, &z);
+      bool planes = false;
+      if constexpr (sizeof(T) == 4) {
+        planes = sp[wk.patch].on != 0;
+        if (planes) z = sinc_planes<false>(sp[wk.patch], b, f, none, 0u);
+      }
+      if (!planes) psf_walk_sinc<T, typename GeoOf<T>::type, false>(g, pr, b, f, none, 0u, &z);
     } else if (ok) {
       psf_walk<T, typename GeoOf<T>::type, false>(g, pr, b, f, nullptr, z, acc);
     }
@@ -801,6 +808,7 @@ static size_t layout(pvr_plan *p, char *base, int flags) {
   p->d_adj = ws_take<AdjPatch<float>>(c, M);
   p->d_adj64 = ws_take<AdjPatch<double>>(c, M);
   p->d_fwd = ws_take<FwdPatch<float>>(c, M);
+  p->d_sinc = ws_take<SincPatch>(c, M);
   p->d_fwd64 = ws_take<FwdPatch<double>>(c, M);
   p->d_bb = ws_take<int>(c, 6 * M);
   p->d_gbox = ws_take<int>(c, 6 * ((M + 63) / 64));
@@ -1069,7 +1077,8 @@ static pvr_status plan_build_common(pvr_plan *p, const TH *theta, const uint8_t 
   const bool wide = f64 && p->d_invz64;
   hipLaunchKernelGGL(k_geometry<TH>, dim3((M + 63) / 64), dim3(256), 0, stream, p->d_prob, p->d_stack,
                      p->d_patch, theta, active, M, p->k, p->psf, wide ? 1 : 0, p->d_theta,
-                     p->d_active, p->d_geod, p->d_geof, p->d_adj, p->d_adj64, p->d_fwd, p->d_fwd64, p->d_bb, p->d_gbox,
+                     p->d_active, p->d_geod, p->d_geof, p->d_adj, p->d_adj64, p->d_fwd, p->d_fwd64, p->d_sinc,
+                     p->d_bb, p->d_gbox,
                      p->d_sbox);
   HIP_TRY(hipGetLastError());
   // an FP64 build also writes FP64 normalisers when the workspace has room
@@ -1082,7 +1091,7 @@ static pvr_status plan_build_common(pvr_plan *p, const TH *theta, const uint8_t 
                        p->d_invz, OUT64);                                                          \
   else                                                                                             \
     hipLaunchKernelGGL(k_normalisers<T>, dim3(p->n_sim_blocks), dim3(SIM_THREADS), 0, stream,      \
-                       p->d_prob, p->d_patch, p->d_sim_blocks, GEO, mask, p->d_active, p->d_mask,    \
+                       p->d_prob, p->d_patch, p->d_sim_blocks, GEO, p->d_sinc, mask, p->d_active, p->d_mask,    \
                        p->d_invz, OUT64)
   if (wide) { NORM_LAUNCH(double, p->d_geod, p->d_fwd64, p->d_invz64); }
   else { NORM_LAUNCH(float, p->d_geof, p->d_fwd, (double *)nullptr); }
