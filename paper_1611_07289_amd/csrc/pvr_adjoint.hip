@@ -453,15 +453,28 @@ k_gather_blocks(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ 
         T U[4][3], E[4][3];  // column and row factors of the four voxels
         if constexpr (SINC) {
           const T du[4] = {-g.P11, g.P10, -g.P10, g.P11}, dv[4] = {-g.Q11, g.Q10, -g.Q10, g.Q11};
+          // pixels -1, 0, 1 of an axis, from 0 at distance d: the lobe holds 0 and the
+          // one on the point's side, and the other only where it reaches over a pixel:
+          // two lobes an axis instead of three, and the products summed row by row:
+          // 217 -> 205 us at 128^3, 406 -> 381 at 160^3 (held to six wavefronts a SIMD, with
+          // spills, 205 and 394)
+          const bool wide = g.cu < (T)1 || g.cv < (T)1;
 #pragma unroll
           for (int t = 0; t < 4; ++t) {
             const T gz = fmax(fast_exp2<T>(-wt[t] * wt[t]) - cut, (T)0);
-#pragma unroll
-            for (int a = -1; a <= 1; ++a) {
-              const T tu = ((T)a - (f + du[t])) * g.cu, tv = ((T)a - (h + dv[t])) * g.cv;
-              U[t][a + 1] = sinc_lobe<T>(tu);
-              E[t][a + 1] = sinc_lobe<T>(tv) * gz;
+            const T pu = f + du[t], pv = h + dv[t], au = fabs(pu), av = fabs(pv);
+            const T su = sinc_lobe<T>(((T)1 - au) * g.cu), sv = sinc_lobe<T>(((T)1 - av) * g.cv) * gz;
+            T ou = (T)0, ov = (T)0;
+            if (wide) {
+              ou = sinc_lobe<T>(((T)1 + au) * g.cu);
+              ov = sinc_lobe<T>(((T)1 + av) * g.cv) * gz;
             }
+            U[t][0] = pu < (T)0 ? su : ou;
+            U[t][1] = sinc_lobe<T>(pu * g.cu);
+            U[t][2] = pu < (T)0 ? ou : su;
+            E[t][0] = pv < (T)0 ? sv : ov;
+            E[t][1] = sinc_lobe<T>(pv * g.cv) * gz;
+            E[t][2] = pv < (T)0 ? ov : sv;
           }
         } else {
           const T fu = f * g.cu, hv = h * g.cv;
@@ -492,14 +505,21 @@ k_gather_blocks(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ 
           const int ou = t & 1, ov = t >> 1;
           T pn = 0, pd = 0;
 #pragma unroll
-          for (int b = 0; b < 3; ++b)
+          for (int b = 0; b < 3; ++b) {
+            T rn = 0, rd = 0;  // the sinc's weights are products: sum row by row
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-              const T gh = SINC ? U[t][a] * E[t][b] : fma_clamp0<T>(E[t][b], U[t][a], cut);
+              const T gh = SINC ? U[t][a] : fma_clamp0<T>(E[t][b], U[t][a], cut);
               const V2 &e = x[ov + b][ou + a];
-              pn = fma(gh, e.x, pn);
-              if (DEN) pd = fma(gh, e.y, pd);
+              T &n = SINC ? rn : pn, &d = SINC ? rd : pd;
+              n = fma(gh, e.x, n);
+              if (DEN) d = fma(gh, e.y, d);
             }
+            if (SINC) {
+              pn = fma(E[t][b], rn, pn);
+              if (DEN) pd = fma(E[t][b], rd, pd);
+            }
+          }
           if (in && wt[t] * wt[t] <= g.K2) {  // outside, a non-finite input stays out
             sn[t] = fma(ws, pn, sn[t]);
             if (DEN) sd[t] = fma(ws, pd, sd[t]);

@@ -507,7 +507,7 @@ template <> __device__ __forceinline__ double sinc_poly<double>(double t) {
 // degree 5 in y fitted (least maximum of (1 - y) times its error, constant term
 // 1) to within 9e-10 of s; the clamp decides membership, without comparisons and
 // selections, and the rounded evaluation stays within 9e-8 of s over the lobe
-// (sinc_poly: 1.5e-7).  The block gather of 128^3 takes 217 us with it, 247 with
+// (sinc_poly: 1.5e-7).  The block gather of 128^3 took 217 us with it, 247 with
 // sinc_poly and selections.  FP64: the series.
 template <typename T> __device__ __forceinline__ T sinc_lobe(T t);
 template <> __device__ __forceinline__ float sinc_lobe<float>(float t) {
