@@ -348,13 +348,15 @@ __device__ __forceinline__ double lane_value(double x, int l) {
 //
 // Bound by the chain of the iterations: the wavefronts' sums, a barrier, the
 // wavefronts' sums in order, the step to the next parameters with its divisions, roots and
-// logarithms side by side in lanes.  Up to 256 patches four wavefronts (64: one),
-// one a SIMD, take the step each for itself; beyond, sixteen, of which one takes it
-// for all, at one more barrier (at 128^3 59 us, each for itself 68).  The order
-// of addition is that of EMP_T lanes throughout: the lanes beyond a problem's
-// patches would add zeros.  32^3, 216 patches 32 us, 256^3, 11 760 patches 190; 79 and
-// 216 with 16 wavefronts always, LDS permutations, one lane taking the step and flat
-// reads of the potentials.
+// logarithms side by side in lanes.  Few wavefronts shorten the chain, many share the
+// patches.  Up to 1 280 patches four wavefronts (64: one), one a SIMD, take the step
+// each for itself; beyond, eight (up to 4 096) or sixteen, of which one takes it for
+// all, at one more barrier.  Robust weights of one problem with four / eight /
+// sixteen wavefronts (us): 300 patches 45 / 49 / 61, 600 50 / 53 / 63, 1 152 58 / 60 /
+// 70, 1 600 69 / 67 / 75, 3 000 97 / 86 / 89, 4 000 116 / 104 / 106, 6 000 - / 131 /
+// 126.  256^3, 11 760 patches: 178; 216 with LDS permutations, one lane taking the
+// step and flat reads of the potentials.  CAP: potentials the workgroup keeps in LDS
+// (0: none).
 // K sums of the workgroup into every lane, in the order of bsumk; two calls with
 // the same lds need a barrier in between.
 template <int NT, int K>
@@ -375,13 +377,13 @@ __device__ __forceinline__ void wsumk(double (&v)[K], double *lds) {
   }
 }
 
-template <int NT, bool LDS>
+template <int NT, int CAP>
 __global__ void __launch_bounds__(NT)
 k_em_patches(const ProbDev *__restrict__ probs,
              const uint8_t *__restrict__ active, const double *__restrict__ esum, int M,
              double *__restrict__ gval, float *__restrict__ patch_w, pvr_em_state *__restrict__ em,
              int fix_w) {
-  constexpr int U = NT < EMP_T ? 1 : 4;            // patches of a lane in flight
+  constexpr int U = CAP == NT ? 1 : 4;             // patches of a lane in flight
   constexpr bool ONE = NT > 256;                   // one wavefront takes the step
   __shared__ double lds[2][4 * (NT / 64)];         // in turn: one barrier a sum
   __shared__ double par[3];                        // variances, weight
@@ -389,31 +391,31 @@ k_em_patches(const ProbDev *__restrict__ probs,
   __shared__ int stop;
   __shared__ unsigned int hist[256];
   __shared__ unsigned int sel_prefix, sel_rank;
-  __shared__ double sval[LDS ? (NT < EMP_T ? NT : EMP_LDS) : 1];
+  __shared__ double sval[CAP ? CAP : 1];
   const ProbDev pr = probs[blockIdx.x];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int pb = pr.patch_begin, np = pr.patch_end - pr.patch_begin;
-  double *V = LDS ? sval : gval + pb;  // (a choice at run time would make every read a flat one)
+  double *V = CAP ? sval : gval + pb;  // (a choice at run time would make every read a flat one)
   // the patches taking part (valid samples, active) and their potentials; the
   // reads of a patch, and of U patches, are independent
   double n, s_all, q_all;
   {
     double r3[3] = {0, 0, 0};
-    for (int q0 = t; q0 < np; q0 += U * EMP_T) {
+    for (int q0 = t; q0 < np; q0 += U * NT) {
       double ns[U], sp2[U];
       uint8_t act[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int s = pb + min(q0 + u * EMP_T, np - 1);
+        const int s = pb + min(q0 + u * NT, np - 1);
         ns[u] = esum[s];
         sp2[u] = esum[M + s];
         act[u] = active[s];
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        if (q0 + u * EMP_T >= np) continue;
+        if (q0 + u * NT >= np) continue;
         const double v = (ns[u] > 0 && act[u] != 0) ? sqrt(sp2[u] / ns[u]) : -1.0;
-        V[q0 + u * EMP_T] = v;
+        V[q0 + u * NT] = v;
         if (v >= 0) {
           r3[0] += 1.0;
           r3[1] += v;
@@ -486,7 +488,7 @@ k_em_patches(const ProbDev *__restrict__ probs,
     }
     const double tv = (double)__uint_as_float(sel_prefix);
     double red3[3] = {0, 0, 0};
-    for (int q = t; q < np; q += EMP_T) {
+    for (int q = t; q < np; q += NT) {
       const double v = V[q];
       if (v >= 0 && (float)v < (float)tv) { red3[0] += 1; red3[1] += v; red3[2] += v * v; }
     }
@@ -521,7 +523,7 @@ k_em_patches(const ProbDev *__restrict__ probs,
     for (int it = 0; it < 20; ++it) {
       double red[3] = {0, 0, 0};  // sums of r1, r1 v, r1 v^2
 #pragma unroll 4
-      for (int q = t; q < np; q += EMP_T) {
+      for (int q = t; q < np; q += NT) {
         const double v = V[q];
         const double r1 = inlier_resp_f(v, mx);
         if (v >= 0) {
@@ -575,12 +577,12 @@ k_em_patches(const ProbDev *__restrict__ probs,
   // patch weights (given, or from the fitted mixture), then the M-step sums over
   // the problem's patches from their partials o = (N_s, sum p, sum p e^2)
   double red4[4] = {0, 0, 0, 0};
-  for (int q0 = t; q0 < np; q0 += U * EMP_T) {
+  for (int q0 = t; q0 < np; q0 += U * NT) {
     double o5[U], o7[U], o8[U];
     float wg[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int s = pb + min(q0 + u * EMP_T, np - 1);
+      const int s = pb + min(q0 + u * NT, np - 1);
       o5[u] = esum[s];
       o7[u] = esum[2LL * M + s];
       o8[u] = esum[3LL * M + s];
@@ -588,7 +590,7 @@ k_em_patches(const ProbDev *__restrict__ probs,
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int q = q0 + u * EMP_T, s = pb + q;
+      const int q = q0 + u * NT, s = pb + q;
       if (q >= np) continue;
       double W;
       const bool on = V[q] >= 0;
@@ -672,14 +674,16 @@ extern "C" pvr_status pvr_robust_weights(pvr_plan *p, const float *resid, const 
     if (st != PVR_OK) return st;
     HIP_TRY(hipEventRecord(p->ev_join, p->side));
   }
-#define PATCHES_LAUNCH(NT, LDS)                                                                   \
-  hipLaunchKernelGGL((k_em_patches<NT, LDS>), dim3(p->P), dim3(NT),                              \
+#define PATCHES_LAUNCH(NT, CAP)                                                                   \
+  hipLaunchKernelGGL((k_em_patches<NT, CAP>), dim3(p->P), dim3(NT),                              \
                      0, stream, p->d_prob, p->d_active, p->d_pstat + PSTAT * (long long)p->M, \
                      p->M, p->d_pval, patch_w, em, fix)
-  if (p->max_problem_patches <= 64) PATCHES_LAUNCH(64, true);
-  else if (p->max_problem_patches <= 256) PATCHES_LAUNCH(256, true);
-  else if (p->max_problem_patches <= EMP_LDS) PATCHES_LAUNCH(EMP_T, true);
-  else PATCHES_LAUNCH(EMP_T, false);
+  if (p->max_problem_patches <= 64) PATCHES_LAUNCH(64, 64);
+  else if (p->max_problem_patches <= 256) PATCHES_LAUNCH(256, 256);
+  else if (p->max_problem_patches <= 1280) PATCHES_LAUNCH(256, 1280);
+  else if (p->max_problem_patches <= 4096) PATCHES_LAUNCH(512, 4096);
+  else if (p->max_problem_patches <= EMP_LDS) PATCHES_LAUNCH(EMP_T, EMP_LDS);
+  else PATCHES_LAUNCH(EMP_T, 0);
 #undef PATCHES_LAUNCH
   HIP_TRY(hipGetLastError());
   if (prep) {
