@@ -159,8 +159,14 @@ typedef struct {
                                  while the patch classification runs on
                                  `stream` (joined before the call returns on
                                  `stream`), and pvr_backproject skips its own
-                                 pass.  Needs p != NULL; a pvr_simulate or a
-                                 build in between cancels it */
+                                 pass.  Needs p != NULL.  Cancelled (the
+                                 back-projection then prepares its inputs) by
+                                 a pvr_simulate, a build, a back-projection of
+                                 other buffers or a pvr_sr_graph_launch in
+                                 between, and across the start or end of a
+                                 stream capture; a graph of the caller's own
+                                 with calls of this plan must not be replayed
+                                 in between */
 
 typedef struct {
   float alpha;              /* step length (default 1) */

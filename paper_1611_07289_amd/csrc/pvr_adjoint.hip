@@ -589,15 +589,17 @@ static pvr_status backproject_impl(const pvr_plan *p, const T *e, const T *pp, c
                                    T *num, T *den, const T *invz, typename Vec2Of<T>::type *rq,
                                    hipStream_t stream) {
   if (!e || !num) return fail(PVR_EINVAL, "pvr_backproject: e and num are required");
-  if (!p->index_valid) {
+  const unsigned long long capture = capture_id(stream);
+  if (!p->index_valid || (p->index_capture && p->index_capture != capture)) {
     const pvr_status st = plan_build_index(const_cast<pvr_plan *>(p), stream);
     if (st != PVR_OK) return st;
   }
   // the preparation pass, unless pvr_robust_weights (PVR_EM_PREP_ADJOINT)
-  // already ran it for these residuals and posteriors
+  // already ran it for these residuals and posteriors (in this capture, if any)
   const bool prepared = sizeof(T) == 4 && p->rq_fresh && p->rq_e == (const void *)e &&
-                        p->rq_p == (const void *)pp;
+                        p->rq_p == (const void *)pp && p->rq_capture == capture;
   if (!prepared) {
+    if (sizeof(T) == 4) const_cast<pvr_plan *>(p)->rq_fresh = false;  // d_rq changes
     hipLaunchKernelGGL(k_bp_prep<T>, dim3(p->n_sim_blocks), dim3(SIM_THREADS), 0, stream,
                        p->d_patch, p->d_sim_blocks, invz, e, pp, rq);
     HIP_TRY(hipGetLastError());

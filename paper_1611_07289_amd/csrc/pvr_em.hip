@@ -649,7 +649,7 @@ extern "C" pvr_status pvr_robust_weights(pvr_plan *p, const float *resid, const 
   // residual statistics: reused from the forward kernel when the caller vouches
   // that resid is unchanged since the plan's last pvr_simulate wrote it
   const bool fresh = (flags & PVR_EM_RESID_FRESH) && p->stats_valid && p->stats_resid == resid &&
-                     p->stats_y == y_obs;
+                     p->stats_y == y_obs && p->stats_capture == capture_id(stream);
   if (!fresh) {
     hipLaunchKernelGGL(k_em_patch_stats, dim3(p->M), dim3(EM_T), 0, stream, p->d_patch, p->d_invz,
                        resid, y_obs, p->d_pstat);
@@ -689,6 +689,7 @@ extern "C" pvr_status pvr_robust_weights(pvr_plan *p, const float *resid, const 
   if (prep) {
     HIP_TRY(hipStreamWaitEvent(stream, p->ev_join, 0));
     p->rq_fresh = true;
+    p->rq_capture = capture_id(stream);
     p->rq_e = resid;
     p->rq_p = pp;
   }

@@ -323,6 +323,7 @@ static pvr_status simulate_impl(const pvr_plan *p, const T *X, const T *y_obs, T
     HIP_TRY(hipGetLastError());
     if (ev) HIP_TRY(hipEventRecord(ev[1], stream));
     const_cast<pvr_plan *>(p)->stats_valid = false;
+    const_cast<pvr_plan *>(p)->rq_fresh = false;
     return PVR_OK;
   }
   double *stats = (sizeof(T) == 4 && resid) ? p->d_chunk_stats : nullptr;
@@ -354,6 +355,7 @@ static pvr_status simulate_impl(const pvr_plan *p, const T *X, const T *y_obs, T
   mp->rq_fresh = false;  // the residuals may have changed
   mp->stats_valid = stats != nullptr;
   mp->stats_planes = planes;
+  mp->stats_capture = capture_id(stream);
   mp->stats_resid = resid;
   mp->stats_y = y_obs;
   return PVR_OK;

@@ -4,9 +4,8 @@
 // iterations (simulate with residual, robust weights, gather adjoint, update;
 // every problem of the plan in each launch) on a private capture stream and
 // instantiates the graph; replays then issue the whole batch's work without
-// host involvement.  Everything that needs the host (the adjoint's brick
-// index, which sizes its lists with a readback) is prepared before the
-// capture.  Kernel arguments are fixed at capture, so a graph is only valid
+// host involvement.  The adjoint's index is built before the capture, once for
+// every launch.  Kernel arguments are fixed at capture, so a graph is only valid
 // for the plan state it was recorded from: every build, PSF or tile change
 // and index rebuild bumps the plan's generation, and a launch against a
 // newer generation is refused.
@@ -72,7 +71,7 @@ extern "C" pvr_status pvr_sr_graph_create(pvr_plan *plan, float *X, float *X_alt
   if (!plan->built) return fail(PVR_EINVAL, "pvr_sr_graph_create: build the plan first");
   if (plan->timing)
     return fail(PVR_EUNSUPPORTED, "pvr_sr_graph_create: switch kernel timing off before capturing");
-  if (!plan->index_valid) {
+  if (!plan->index_valid || plan->index_capture) {
     const pvr_status st = plan_build_index(plan, stream);
     if (st != PVR_OK) return st;
   }
@@ -123,6 +122,10 @@ extern "C" pvr_status pvr_sr_graph_launch(const pvr_sr_graph *g, hipStream_t str
   if (g->plan->generation != g->generation)
     return fail(PVR_EINVAL, "pvr_sr_graph_launch: the plan changed since the capture "
                             "(build, PSF, tiles or adjoint index); capture again");
+  // the graph writes the residual statistics and the adjoint's inputs of its own
+  // buffers
+  g->plan->stats_valid = false;
+  g->plan->rq_fresh = false;
   HIP_TRY(hipGraphLaunch(g->exec, stream));
   return PVR_OK;
   PVR_API_END();

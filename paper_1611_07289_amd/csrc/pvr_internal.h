@@ -745,6 +745,10 @@ struct pvr_plan {
   int *d_sub_patch;          // [sub_cap]
   long long sub_cap;         // host bound on sub-brick/patch pairs
   bool built, built64, index_valid;
+  // captures (capture_id) that recorded the index's build, the residual
+  // statistics and the prepared adjoint inputs; 0: an ordinary call made them.
+  // Only the calls of the same capture may use what a captured call makes.
+  unsigned long long index_capture, stats_capture, rq_capture;
   // scratch
   float2 *d_rq;              // [n_rq]: padded rows (RQ_PAD), the padding always zero
   double2 *d_rq64;           // [N + 2] likewise (workspaces with PVR_WS_F64)

@@ -1065,6 +1065,7 @@ pvr_status pvr::plan_build_index(pvr_plan *p, hipStream_t stream) {
 #undef LIST_LAUNCH
   HIP_TRY(hipGetLastError());
   p->index_valid = true;
+  p->index_capture = capture_id(stream);
   ++p->generation;
   return PVR_OK;
 }

@@ -27,6 +27,9 @@ size_t reg_state_bytes(const pvr_plan *p, size_t off[4]);
 void launch_fill_i32(int *dst, int v, long long n, hipStream_t stream);
 void launch_fill_f32(float *dst, float v, long long n, hipStream_t stream);
 void launch_fill_f64(double *dst, double v, long long n, hipStream_t stream);
+// The id of the capture that `stream` records into a graph, 0 outside one: what
+// a captured call leaves behind exists for the calls of the same capture only.
+unsigned long long capture_id(hipStream_t stream);
 // The event pair to record around the next launch of kernel k, or nullptr
 // when the plan is not timing (or the kernel's slots are full).
 hipEvent_t *timing_slot(const pvr_plan *p, int k);

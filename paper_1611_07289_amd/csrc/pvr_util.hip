@@ -39,6 +39,16 @@ void launch_fill_i32(int *dst, int v, long long n, hipStream_t s) { fill<int>(ds
 void launch_fill_f32(float *dst, float v, long long n, hipStream_t s) { fill<float>(dst, v, n, s); }
 void launch_fill_f64(double *dst, double v, long long n, hipStream_t s) { fill<double>(dst, v, n, s); }
 
+unsigned long long capture_id(hipStream_t stream) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  unsigned long long id = 0;
+  if (hipStreamGetCaptureInfo(stream, &cs, &id) != hipSuccess) {
+    (void)hipGetLastError();  // the null stream beside another stream's capture
+    return 0;
+  }
+  return cs == hipStreamCaptureStatusActive ? id : 0;
+}
+
 void plan_free(pvr_plan *p) {
   if (!p) return;
   // the caller frees the workspace once this returns: let the device finish
