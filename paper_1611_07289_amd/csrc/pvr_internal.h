@@ -137,6 +137,7 @@ struct AdjPatch {
 };
 constexpr int ADJ_MAP = 63;    // the bits of cls that fix the lane's voxels
 constexpr int ADJ_FAST = 64;   // the deviations are small enough for the block gather
+constexpr int ADJ_OFF = 128;   // (in the gather) the lane's voxels off that path
 __host__ __device__ __forceinline__ int adj_normal_axis(int cls) { return 3 - (cls & 3) - ((cls >> 2) & 3); }
 
 template <typename T> struct GeoOf;
