@@ -130,11 +130,14 @@ k_grad_theta(const ProbDev *__restrict__ probs, const StackDev *__restrict__ sta
   grad_out(sum6, grad + 6 * s);
 }
 
-// FP64 by the plane walk, 2 x 2 samples per lane; patches off it are left to
-// k_grad_theta's walk, sample by sample.  187 000 samples at 48^3: 123 -> 83 us
-// (two walks before, the derivative at every voxel, an FP64 exponential for
-// each voxel and walk; here ten for thirty-six).
-__global__ void __launch_bounds__(GR_THREADS)
+// FP64 by the plane walk, a lane's 2 x 2 samples two at a time; patches off it are
+// walked sample by sample, as by k_grad_theta.  187 000 samples at 48^3: 117 -> 88 us
+// (two walks before, the derivative at every voxel, an FP64 exponential for each
+// voxel and walk; here eight for eighteen).  Two wavefronts a SIMD: all four samples
+// at once take six exponentials less but 420 registers, so that one wavefront ran,
+// no faster on the walk (88 us) and slow off it (all patches turned by 60 degrees:
+// 336 us, 133 here and before).
+__global__ void __launch_bounds__(GR_THREADS, 2)
 k_grad_theta_planes(const ProbDev *__restrict__ probs, const StackDev *__restrict__ stacks,
                     const PatchDev *__restrict__ patches, const GeoD *__restrict__ geo,
                     const FwdPatch<double> *__restrict__ fwd, const double *__restrict__ theta,
@@ -142,11 +145,14 @@ k_grad_theta_planes(const ProbDev *__restrict__ probs, const StackDev *__restric
                     const double *__restrict__ gy, double *__restrict__ grad) {
   __shared__ GradConst gc;
   __shared__ GradMomT<double> gm;
+  __shared__ FwdPatch<double> fw;
   const int s = blockIdx.x;
   const PatchDev pt = patches[s];
   const ProbDev pr = probs[pt.problem];
   const GeoD &g = geo[s];
-  const FwdPatch<double> &fw = fwd[s];
+  static_assert(sizeof fw % 4 == 0, "copied by words");
+  for (int i = threadIdx.x; i < (int)sizeof fw / 4; i += GR_THREADS)
+    reinterpret_cast<int *>(&fw)[i] = reinterpret_cast<const int *>(fwd + s)[i];
   shared_grad_const(pr, stacks[pt.stack], pt, theta + 6 * s, gc);
   if (threadIdx.x == 0) make_grad_mom(gc, fw.rows ? fw.ax : g.perm, gm);
   __syncthreads();
@@ -158,6 +164,24 @@ k_grad_theta_planes(const ProbDev *__restrict__ probs, const StackDev *__restric
 #pragma unroll
     for (int k = 0; k < 6; ++k) sum6[k] += gj * (a6[k] * iz);
   };
+  if (!fw.rows) {  // off the walk: sample by sample, as k_grad_theta
+    const int n = pt.w * pt.h;
+    for (int l = threadIdx.x; l < n; l += GR_THREADS) {
+      const long long j = pt.off + l;
+      const double gj = gy[j], iz = invz[j];
+      if (!(iz > 0) || gj == 0.0) continue;
+      const int u = pt.x0 + l % pt.w, v = pt.y0 + l / pt.w;
+      int b[3];
+      double f[3], qt[3], a6[6] = {0, 0, 0, 0, 0, 0}, z = 0, acc = 0;
+      sample_centre(g, pr, u, v, pt.slice, b, f);
+      grad_q(gc, g.H, u, v, pt.slice, qt);
+      psf_walk<double, GeoD, true>(g, pr, b, f, Xp, z, acc);
+      grad_walk<double>(g, pr, gc, b, f, qt, Xp, acc * iz, a6);
+      add(gj, iz, a6);
+    }
+    grad_out(sum6, grad + 6 * s);
+    return;
+  }
   const int nbu = (pt.w + 1) / 2, nblk = nbu * ((pt.h + 1) / 2);
   for (int blk = threadIdx.x; blk < nblk; blk += GR_THREADS) {
     const int u0 = 2 * (blk % nbu), v0 = 2 * (blk / nbu);
@@ -172,13 +196,14 @@ k_grad_theta_planes(const ProbDev *__restrict__ probs, const StackDev *__restric
     }
     const bool live = iz[0] > 0 || iz[1] > 0 || iz[2] > 0 || iz[3] > 0;
     if (!live) continue;
-    if (fw.rows) {
-      double xb, a[4], z[4], mx[4][9], me[4][9];
-      if (fw.rows == 3) plane_walk_grad<double, 3>(fw, u0, v0, true, xr, nbytes, xb, a, z, mx, me);
-      else plane_walk_grad<double, 4>(fw, u0, v0, true, xr, nbytes, xb, a, z, mx, me);
+#pragma unroll 1
+    for (int j = 0; j < 2; ++j) {
+      double xb, a[2], z[2], mx[2][9], me[2][9];
+      if (fw.rows == 3) plane_walk_grad<double, 3>(fw, u0, v0, j, xr, nbytes, xb, a, z, mx, me);
+      else plane_walk_grad<double, 4>(fw, u0, v0, j, xr, nbytes, xb, a, z, mx, me);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int p = t ^ fw.flip;  // the sub-window's pixel
+      for (int t = 0; t < 2; ++t) {
+        const int p = (2 * j + t) ^ fw.flip;  // the sub-window's pixel
         const double izp = p == 0 ? iz[0] : p == 1 ? iz[1] : p == 2 ? iz[2] : iz[3];
         const double gp = p == 0 ? gj[0] : p == 1 ? gj[1] : p == 2 ? gj[2] : gj[3];
         if (!(izp > 0)) continue;
@@ -189,21 +214,6 @@ k_grad_theta_planes(const ProbDev *__restrict__ probs, const StackDev *__restric
         grad_q(gc, g.H, pt.x0 + u0 + (p & 1), pt.y0 + v0 + (p >> 1), pt.slice, qt);
         grad_from_moments(gm, m, qt, a6);
         add(gp, izp, a6);
-      }
-    } else {
-#pragma unroll 1
-      for (int t = 0; t < 4; ++t) {
-        const double izt = t == 0 ? iz[0] : t == 1 ? iz[1] : t == 2 ? iz[2] : iz[3];
-        const double gt = t == 0 ? gj[0] : t == 1 ? gj[1] : t == 2 ? gj[2] : gj[3];
-        if (!(izt > 0)) continue;
-        const int u = pt.x0 + u0 + (t & 1), v = pt.y0 + v0 + (t >> 1);
-        int b[3];
-        double f[3], qt[3], a6[6] = {0, 0, 0, 0, 0, 0}, z = 0, acc = 0;
-        sample_centre(g, pr, u, v, pt.slice, b, f);
-        grad_q(gc, g.H, u, v, pt.slice, qt);
-        psf_walk<double, GeoD, true>(g, pr, b, f, Xp, z, acc);
-        grad_walk<double>(g, pr, gc, b, f, qt, Xp, acc * izt, a6);
-        add(gt, izt, a6);
       }
     }
   }
@@ -216,6 +226,8 @@ static pvr_status grad_impl(const pvr_plan *p, const T *X, const T *gy, T *grad,
   if (!X || !gy || !grad) return fail(PVR_EINVAL, "pvr_simulate_grad_theta: NULL argument");
   if (p->psf != PVR_PSF_GAUSSIAN)
     return fail(PVR_EUNSUPPORTED, "pvr_simulate_grad_theta: the theta-derivative is implemented for the Gaussian PSF");
+  const auto *geo = (const typename GeoOf<T>::type *)(sizeof(T) == 4 ? (const void *)p->d_geof
+                                                                     : (const void *)p->d_geod);
   if constexpr (sizeof(T) == 8) {
     if (p->planes64) {
       hipLaunchKernelGGL(k_grad_theta_planes, dim3(p->M), dim3(GR_THREADS), 0, stream, p->d_prob,
@@ -224,10 +236,8 @@ static pvr_status grad_impl(const pvr_plan *p, const T *X, const T *gy, T *grad,
       return PVR_OK;
     }
   }
-  const void *geo = sizeof(T) == 4 ? (const void *)p->d_geof : (const void *)p->d_geod;
-  hipLaunchKernelGGL(k_grad_theta<T>, dim3(p->M), dim3(GR_THREADS), 0, stream, p->d_prob,
-                     p->d_stack, p->d_patch, (const typename GeoOf<T>::type *)geo, p->d_theta,
-                     invz, X, gy, grad);
+  hipLaunchKernelGGL(k_grad_theta<T>, dim3(p->M), dim3(GR_THREADS), 0, stream, p->d_prob, p->d_stack,
+                     p->d_patch, geo, p->d_theta, invz, X, gy, grad);
   HIP_TRY(hipGetLastError());
   return PVR_OK;
 }

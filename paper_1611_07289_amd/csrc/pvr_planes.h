@@ -471,15 +471,17 @@ __device__ __forceinline__ float sinc_planes(const SincPatch &g, const int b[3],
 }
 
 // The plane walk with the derivative's moments (pvr_grad.h: psf_walk_grad, along
-// the axes a, b, c): relative to the value xb of one voxel near the block,
-// per sample acc = sum g_hat (X - xb), z = sum g_hat, and the nine offset
-// moments of e^{-Q/2} (X - xb) in mx and of e^{-Q/2} in me.  In a plane the
+// the axes a, b, c), for the two samples of the block's sub-window row j: relative
+// to the value xb of one voxel near the block, per sample acc = sum g_hat (X - xb),
+// z = sum g_hat, and the nine offset moments of e^{-Q/2} (X - xb) in mx and of
+// e^{-Q/2} in me.  (All four at once share more exponentials but hold 420
+// registers, one wavefront a SIMD.)  In a plane the
 // moments are taken about each sample's nearest voxel, where they are sums and
 // differences, and moved to the sample's centre once.
 template <typename T, int NB>
-__device__ __forceinline__ void plane_walk_grad(const FwdPatch<T> &g, int u, int v, bool live,
+__device__ __forceinline__ void plane_walk_grad(const FwdPatch<T> &g, int u, int v, int j,
                                                 __amdgpu_buffer_rsrc_t xr, unsigned nbytes, T &xb,
-                                                T acc[4], T z[4], T mx[4][9], T me[4][9]) {
+                                                T acc[2], T z[2], T mx[2][9], T me[2][9]) {
   const double du = u, dv = v;
   const double xa = fma(g.Ha[0], du, fma(g.Ha[1], dv, g.Ha[2]));
   const double xbd = fma(g.Hb[0], du, fma(g.Hb[1], dv, g.Hb[2]));
@@ -495,25 +497,25 @@ __device__ __forceinline__ void plane_walk_grad(const FwdPatch<T> &g, int u, int
     xb = load_vox<T>(xr, (unsigned)(c * g.st_c + b * g.st_b + a * g.st_a) * (unsigned)sizeof(T));
   }
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
+  for (int t = 0; t < 2; ++t) {
     acc[t] = z[t] = (T)0;
 #pragma unroll
     for (int q = 0; q < 9; ++q) mx[t][q] = me[t][q] = (T)0;
   }
-  const T cut = g.cut;
 #pragma unroll 1
   for (int k = -g.half; k <= g.half; ++k) {
+    asm volatile("" ::: "memory");  // the constants (in LDS) are read again: held, they would spill
+    const T cut = g.cut;
     const T kk = (T)k;
     const T qa = fma(kk, g.fta, f0), qb = fma(kk, g.ftb, h0);
     const T sa = round_val<false>(qa), sb = round_val<NB == 4>(qb);
     const T f = qa - sa, h = qb - sb, wz = z0 + kk;
-    const int ia = ia0 + (int)sa, ib = ib0 + (int)sb, ic = ic0 + k;
-    const bool inside = !live || ((unsigned)ic < (unsigned)g.nc && ia >= 0 && ia + 4 <= g.na &&
-                                  ib >= 0 && ib + NB + 1 <= g.nb);
-    T x[NB + 1][4];
-    load_rows<NB>(g, xr, nbytes, ia, ib, ic, inside, x);
+    const int ia = ia0 + (int)sa, ib = ib0 + j + (int)sb, ic = ic0 + k;
+    const bool inside = (unsigned)ic < (unsigned)g.nc && ia >= 0 && ia + 4 <= g.na && ib >= 0 && ib + NB <= g.nb;
+    T x[NB][4];
+    load_rows<NB - 1>(g, xr, nbytes, ia, ib, ic, inside, x);
 #pragma unroll
-    for (int r = 0; r <= NB; ++r)
+    for (int r = 0; r < NB; ++r)
 #pragma unroll
       for (int i = 0; i < 4; ++i) x[r][i] -= xb;
     const T m = g.Aab2 * f * h;
@@ -527,38 +529,32 @@ __device__ __forceinline__ void plane_walk_grad(const FwdPatch<T> &g, int u, int
     V[1] = fast_exp2<T>(eb);
     V[2] = fast_exp2<T>(eb - g.Abb + slb);
     if constexpr (NB == 4) V[3] = fast_exp2<T>(fma((T)-4, g.Abb, fma((T)2, slb, eb)));
-    T ca[4] = {(T)1, (T)1, (T)1, (T)1}, cb[NB + 1];
+    T ca[4] = {(T)1, (T)1, (T)1, (T)1}, cb[NB];
 #pragma unroll
-    for (int j = 0; j <= NB; ++j) cb[j] = (T)1;
+    for (int r = 0; r < NB; ++r) cb[r] = (T)1;
     const bool edge = !__all(inside);  // voxels outside the grid do not count
     if (edge) {
       const bool pc = (unsigned)ic < (unsigned)g.nc;
 #pragma unroll
       for (int i = 0; i < 4; ++i) ca[i] = (unsigned)(ia + i) < (unsigned)g.na ? (T)1 : (T)0;
 #pragma unroll
-      for (int j = 0; j <= NB; ++j) cb[j] = pc && (unsigned)(ib + j) < (unsigned)g.nb ? (T)1 : (T)0;
+      for (int r = 0; r < NB; ++r) cb[r] = pc && (unsigned)(ib + r) < (unsigned)g.nb ? (T)1 : (T)0;
     }
     const T xm = g.kap[XM], xp = g.kap[XP];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int i = t & 1, j = t >> 1;
-      const T ga = t == 0 ? -g.ga11 : t == 1 ? g.ga10 : t == 2 ? -g.ga10 : g.ga11;
-      const T gb = t == 0 ? -g.gb11 : t == 1 ? g.gb10 : t == 2 ? -g.gb10 : g.gb11;
-      const T da = t == 0 ? -g.da11 : t == 1 ? g.da10 : t == 2 ? -g.da10 : g.da11;
-      const T db = t == 0 ? -g.db11 : t == 1 ? g.db10 : t == 2 ? -g.db10 : g.db11;
-      const T ka = g.kap[t == 0 ? IA11 : t == 1 ? KA10 : t == 2 ? IA10 : KA11];
-      const T ja = g.kap[t == 0 ? KA11 : t == 1 ? IA10 : t == 2 ? KA10 : IA11];
-      const T kb = g.kap[t == 0 ? IB11 : t == 1 ? KB10 : t == 2 ? IB10 : KB11];
-      const T jb = g.kap[t == 0 ? KB11 : t == 1 ? IB10 : t == 2 ? KB10 : IB11];
-      const T w = wz - (t == 0 ? -g.e11 : t == 1 ? g.e10 : t == 2 ? -g.e10 : g.e11);
-      const T D = (t == 0 || t == 3) ? g.D11 : g.D10;
-      const T S = fast_exp2<T>(-fma(g.Scc * w, w, fma(f, ga, fma(h, gb, D + m))));
-      const T Um = U[0] * ja * ca[i], Uc = U[1] * ca[i + 1], Up = U[2] * ka * ca[i + 2];
+    for (int t = 0; t < 2; ++t) {  // sub-window (t, j)
+      const bool same = t == j;
+      const auto pick = [&](T v11, T v10) { const T v = same ? v11 : v10; return t ? v : -v; };
+      const T w = wz - pick(g.e11, g.e10), D = same ? g.D11 : g.D10;
+      const T ka = g.kap[(same ? KA11 : KA10) + (t ? 0 : 1)], ja = g.kap[(same ? KA11 : KA10) + (t ? 1 : 0)];
+      const T kb = g.kap[(same ? KB11 : KB10) + (t ? 0 : 1)], jb = g.kap[(same ? KB11 : KB10) + (t ? 1 : 0)];
+      const T S = fast_exp2<T>(-fma(g.Scc * w, w, fma(f, pick(g.ga11, g.ga10), fma(h, pick(g.gb11, g.gb10), D + m))));
+      const T Um = U[0] * ja * ca[t], Uc = U[1] * ca[t + 1], Up = U[2] * ka * ca[t + 2];
       // plane moments about the nearest voxel: m00, m10, m20, m01, m11, m02
       T px[6] = {(T)0, (T)0, (T)0, (T)0, (T)0, (T)0}, pe[6] = {(T)0, (T)0, (T)0, (T)0, (T)0, (T)0};
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
-        T E = V[b] * S * cb[j + b];
+        T E = V[b] * S * cb[b];
         if (b == 0) E *= jb;
         if (b == 2) E *= kb;
         if (b == 3) E *= kb * kb;
@@ -568,7 +564,7 @@ __device__ __forceinline__ void plane_walk_grad(const FwdPatch<T> &g, int u, int
         const T g0 = clamp01<T>(w0 - cut), g1 = clamp01<T>(w1 - cut),
                     g2 = clamp01<T>(w2 - cut);
         const T e0 = g0 > (T)0 ? w0 : (T)0, e1 = g1 > (T)0 ? w1 : (T)0, e2 = g2 > (T)0 ? w2 : (T)0;
-        const T v0 = x[j + b][i], v1 = x[j + b][i + 1], v2 = x[j + b][i + 2];
+        const T v0 = x[b][t], v1 = x[b][t + 1], v2 = x[b][t + 2];
         acc[t] = fma(g0, v0, acc[t]);
         acc[t] = fma(g1, v1, acc[t]);
         acc[t] = fma(g2, v2, acc[t]);
@@ -586,7 +582,7 @@ __device__ __forceinline__ void plane_walk_grad(const FwdPatch<T> &g, int u, int
       }
       // about the sample's centre, at (fa, hb) from its nearest voxel (the plane's
       // conditional centre lies t w beside it)
-      const T fa = fma(-g.fta, w, f + da), hb = fma(-g.ftb, w, h + db);
+      const T fa = fma(-g.fta, w, f + pick(g.da11, g.da10)), hb = fma(-g.ftb, w, h + pick(g.db11, g.db10));
       auto move = [&](const T p[6], T o[9]) {
         const T sa1 = fma(-fa, p[0], p[1]), sb1 = fma(-hb, p[0], p[3]);
         o[0] += sa1;
