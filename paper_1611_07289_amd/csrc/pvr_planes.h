@@ -330,9 +330,10 @@ __device__ __forceinline__ void plane_walk(const FwdPatch<T> &g, int u, int v, b
 // of 37 x 37 patches, whole forward pass: 483 us by rows, 387 here; putting the
 // tested voxels off to the end of six planes gained nothing (421 and 419 in an
 // earlier form).  The error against 64 bits falls from 2.1e-7 to 1.3e-7, most of it
-// by summing plane by plane.  Patches whose parallelogram reaches 3/2 voxels or more, or
-// whose normal runs along the copy's fastest axis (make_sinc), keep the row walk,
-// and so does the registration, which compares the values of trials.
+// by summing plane by plane.  Patches whose parallelogram reaches 3/2 voxels or more,
+// whose normal runs along the copy's fastest axis, or which lie so nearly along the
+// axes with zeros over a voxel away that the rows cost less (make_sinc), keep the row
+// walk, and so does the registration, which compares the values of trials.
 __host__ __device__ inline void make_sinc(const GeoD &g, const ProbDev &pr, const PatchDev &pt,
                                           SincPatch &o) {
   o.on = 0;
@@ -355,6 +356,14 @@ __host__ __device__ inline void make_sinc(const GeoD &g, const ProbDev &pr, cons
   const bool ok = fabs(det) > 1e-6 && ra < 1.5 - 1e-3 && rb < 1.5 - 1e-3 && g.ext[c] < 64.0 &&
                   o.st_b < 1 << 23;  // (24-bit products)
   if (!ok) return;
+  // What the rows cost goes with the cross-section of the support's bounding box (4
+  // area voxels), what the planes cost with the parallelogram (4 share voxels, of
+  // which the cell holds four).  The line fits the crossovers of the forward pass at
+  // 96^3 (rows / planes, us): zeros 1 voxel off at rest 75 / 70, 1.05 at rest 89 / 102,
+  // at 3 degrees 116 / 122, at 10 147 / 130, 1.1 at 6 degrees 134 / 138, at 15 174 / 154,
+  // 1.2 at rest 114 / 142, at 10 degrees 167 / 170, at 15 195 / 174.
+  const double share = 1.0 / fabs(det), area = g.ext[a] * g.ext[b];
+  if (area < fmin(1.0 + 8.0 * (share - 1.0), 3.3) - 0.02) return;
   for (int i = 0; i < 3; ++i) {
     o.Lu[i] = (float)L[ax[i]];
     o.Lv[i] = (float)L[3 + ax[i]];
