@@ -22,9 +22,12 @@ static pvr_status make_tiles(pvr_plan *p, int tile_w, int tile_h);
 // Which walks the plan uses, from every stack's first patch at rest: the block
 // gather (make_adj) and the plane walks (make_fwd) where at least half of the
 // samples lie in stacks on their fast path, i.e. pixels about as wide as voxels
-// and the PSF about as wide as a pixel; the patches of such a plan that leave
-// it (a large tilt) run the per-voxel or per-sample walk inside the same
-// kernels at what it costs in its own.
+// and the PSF about as wide as a pixel.  The motion is not known here: the patches
+// of such a plan that leave it (a large tilt, or a stack of another kind) run the
+// per-voxel or per-sample walk inside the same kernels.  What that costs against
+// the walks' own kernels, all patches turned by 60 degrees (us, own / here): forward
+// 128^3 562 / 513, 32^3 17 / 18; adjoint 128^3 420 / 346, 192^3 with 37 x 37 patches
+// 1494 / 1540; FP64 48^3 forward 52 / 51, adjoint 144 / 150, derivative 133 / 133.
 static void choose_walks(pvr_plan *p) {
   std::vector<char> adj(p->S, 0), fwd(p->S, 0), fwd64(p->S, 0), seen(p->S, 0);
   long long n_adj = 0, n_fwd = 0, n_fwd64 = 0;
@@ -275,63 +278,58 @@ k_normalisers_planes(const ProbDev *__restrict__ probs, const PatchDev *__restri
   const typename GeoOf<T>::type &g = geo[wk.patch];
   const FwdPatch<T> &fw = fwd[wk.patch];
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  const PlaneLane pl = plane_lane(pt, wk.l0);
-  const int nbu = (pt.w + 1) / 2;
-  const int u0 = 2 * (pl.blk % nbu), v0 = 2 * (pl.blk / nbu);
   const bool act = active[wk.patch] != 0;
-  bool ok[4];  // pixel (u0 + i, v0 + j) at 2 j + i
-  T z[4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const int u = u0 + (t & 1), v = v0 + (t >> 1);
-    int b[3];
-    T f[3];
-    ok[t] = pl.on && u < pt.w && v < pt.h && act &&
-            sample_centre(g, pr, pt.x0 + u, pt.y0 + v, pt.slice, b, f);
-    if (pl.on && u < pt.w && v < pt.h) {
-      const long long j = pt.off + (long long)v * pt.w + u;
-      const uint8_t kept = mask ? mask[j] : 1;
-      if (pl.part == 0) keep[j] = kept;
-      ok[t] = ok[t] && kept;
-    }
-    z[t] = 0;
-  }
-  const bool live = ok[0] || ok[1] || ok[2] || ok[3];
   const __amdgpu_buffer_rsrc_t none = raw_buffer((const T *)nullptr, 0u);
+  const auto put = [&](long long j, bool ok, T z) {
+    const T iz = ok && z > (T)0 ? (T)1 / z : (T)0;
+    invz[j] = (float)iz;
+    if (invz64) invz64[j] = (double)iz;
+  };
   if (fw.rows) {
+    const PlaneLane pl = plane_lane(pt, wk.l0);
+    const int nbu = (pt.w + 1) / 2;
+    const int u0 = 2 * (pl.blk % nbu), v0 = 2 * (pl.blk / nbu);
+    bool ok[4];  // pixel (u0 + i, v0 + j) at 2 j + i
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int u = u0 + (t & 1), v = v0 + (t >> 1);
+      int b[3];
+      T f[3];
+      ok[t] = pl.on && u < pt.w && v < pt.h && act &&
+              sample_centre(g, pr, pt.x0 + u, pt.y0 + v, pt.slice, b, f);
+      if (pl.on && u < pt.w && v < pt.h) {
+        const long long j = pt.off + (long long)v * pt.w + u;
+        const uint8_t kept = mask ? mask[j] : 1;
+        if (pl.part == 0) keep[j] = kept;
+        ok[t] = ok[t] && kept;
+      }
+    }
+    const bool live = ok[0] || ok[1] || ok[2] || ok[3];
     T zw[4] = {0, 0, 0, 0};  // by sub-window
     if (__any(live)) {
       if (fw.rows == 3) plane_walk<T, 3, false, true>(fw, u0, v0, live, pl.part, pl.parts, none, 0u, nullptr, zw);
       else plane_walk<T, 4, false, true>(fw, u0, v0, live, pl.part, pl.parts, none, 0u, nullptr, zw);
     }
     combine_parts(pl, zw, reinterpret_cast<T(*)[4]>(lds));
+    if (pl.part != 0 || !pl.on) return;
     const bool fu = fw.flip & 1, fv = fw.flip & 2;
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      const T a = fu ? zw[t ^ 1] : zw[t], b = fu ? zw[t ^ 3] : zw[t ^ 2];
-      z[t] = fv ? b : a;
+      const int u = u0 + (t & 1), v = v0 + (t >> 1);
+      const T a = fu ? zw[t ^ 1] : zw[t], c = fu ? zw[t ^ 3] : zw[t ^ 2];
+      if (u < pt.w && v < pt.h) put(pt.off + (long long)v * pt.w + u, ok[t], fv ? c : a);
     }
-  } else if (pl.part == 0) {
-#pragma unroll 1
-    for (int t = 0; t < 4; ++t) {
-      if (!(t == 0 ? ok[0] : t == 1 ? ok[1] : t == 2 ? ok[2] : ok[3])) continue;
+  } else {
+    each_pixel(pt, wk.l0, [&](int u, int v) {
+      const long long j = pt.off + (long long)v * pt.w + u;
+      const uint8_t kept = mask ? mask[j] : 1;
+      keep[j] = kept;
       int b[3];
-      T f[3], zs = 0, acc = 0;
-      sample_centre(g, pr, pt.x0 + u0 + (t & 1), pt.y0 + v0 + (t >> 1), pt.slice, b, f);
-      psf_walk<T, typename GeoOf<T>::type, false>(g, pr, b, f, nullptr, zs, acc);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) z[k] = k == t ? zs : z[k];
-    }
-  }
-  if (pl.part != 0 || !pl.on) return;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const int u = u0 + (t & 1), v = v0 + (t >> 1);
-    if (u >= pt.w || v >= pt.h) continue;
-    const T iz = ok[t] && z[t] > (T)0 ? (T)1 / z[t] : (T)0;
-    const long long j = pt.off + (long long)v * pt.w + u;
-    invz[j] = (float)iz;
-    if (invz64) invz64[j] = (double)iz;
+      T f[3], z = 0, acc = 0;
+      const bool ok = sample_centre(g, pr, pt.x0 + u, pt.y0 + v, pt.slice, b, f) && act && kept;
+      if (ok) psf_walk<T, typename GeoOf<T>::type, false>(g, pr, b, f, nullptr, z, acc);
+      put(j, ok, z);
+    });
   }
 }
 

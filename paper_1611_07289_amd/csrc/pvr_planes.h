@@ -137,6 +137,20 @@ __device__ __forceinline__ void combine_parts(const PlaneLane &p, T s[4], T (*ld
   }
 }
 
+// The same work item one sample at a time, for patches off the walk: calls f(u, v)
+// for the item's pixels, every thread of the workgroup its share, a wavefront 16
+// blocks at a time (two rows of 32 pixels where they lie side by side).
+template <typename F>
+__device__ __forceinline__ void each_pixel(const PatchDev &pt, int l0, F &&f) {
+  const int nbu = (pt.w + 1) / 2, nb = min(PLANE_BLOCKS, nbu * ((pt.h + 1) / 2) - l0);
+#pragma unroll 1
+  for (int q = threadIdx.x; q < 4 * ((nb + 15) & ~15); q += PLANE_BLOCKS) {
+    const int o = (q >> 6) * 16 + ((q & 31) >> 1), blk = l0 + o;
+    const int u = 2 * (blk % nbu) + (q & 1), v = 2 * (blk / nbu) + ((q >> 5) & 1);
+    if (o < nb && u < pt.w && v < pt.h) f(u, v);
+  }
+}
+
 template <typename T>
 __host__ __device__ inline void make_fwd(const GeoD &g, const ProbDev &pr, const PatchDev &pt, FwdPatch<T> &o) {
   double ex[10];
