@@ -105,7 +105,12 @@ k_simulate(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ patch
       bool planes = false;
       if constexpr (sizeof(T) == 4) {
         planes = sinc && sp[wk.patch].on != 0;
-        if (planes) yh = sinc_planes<true>(sp[wk.patch], b, f, xr, nbytes) * iz;
+        if (planes) {
+          yh = sinc_planes<true>(sp[wk.patch], b, f, xr, nbytes) * iz;
+          // its cells hold voxels of weight zero too: a value that is not finite may come
+          // from them
+          planes = __builtin_isfinite(yh);
+        }
       }
       if (!planes) yh = sample_value<T>(g, pr, sinc, xt, b, f, xr, nbytes) * iz;
     }
@@ -166,8 +171,11 @@ k_simulate_planes(const ProbDev *__restrict__ probs, const PatchDev *__restrict_
       }
     }
   };
+  int blk = 0;
+  unsigned own = 0;  // pixels of the lane's block (2 j + i) that take their own walk
   if (fw.rows) {
     const PlaneLane pl = plane_lane(pt, wk.l0);
+    blk = pl.blk;
     const int nbu = (pt.w + 1) / 2;
     const int u0 = 2 * (pl.blk % nbu), v0 = 2 * (pl.blk / nbu);
     T iz[4], y[4];  // pixel (u0 + i, v0 + j) at 2 j + i
@@ -190,13 +198,19 @@ k_simulate_planes(const ProbDev *__restrict__ probs, const PatchDev *__restrict_
       const T a = fu ? yw[t ^ 1] : yw[t], b = fu ? yw[t ^ 3] : yw[t ^ 2];
       y[t] = iz[t] > (T)0 ? (fv ? b : a) * iz[t] : (T)0;
     }
+    // the walk weighs every voxel of its windows, by zero outside the support: a value
+    // that is not finite may come from out there, and the sample is walked again by
+    // itself, which reaches no further than the support's rows
 #pragma unroll
     for (int t = 0; t < 4; ++t)
-      if (pl.part == 0 && pl.on && u0 + (t & 1) < pt.w && v0 + (t >> 1) < pt.h)
-        put(j0 + (t >> 1) * pt.w + (t & 1), iz[t], y[t]);
-  } else {
+      if (pl.part == 0 && pl.on && u0 + (t & 1) < pt.w && v0 + (t >> 1) < pt.h) {
+        if (__builtin_isfinite(y[t])) put(j0 + (t >> 1) * pt.w + (t & 1), iz[t], y[t]);
+        else own |= 1u << t;
+      }
+  }
+  if (!fw.rows || __any(own != 0)) {
     const typename GeoOf<T>::type &g = geo[wk.patch];
-    each_pixel(pt, wk.l0, [&](int u, int v) {
+    each_pixel<true>(pt, wk.l0, !fw.rows, blk, own, [&](int u, int v) {
       const long long j = pt.off + (long long)v * pt.w + u;
       const T iz = invz[j];
       T y = 0;

@@ -37,9 +37,10 @@ __device__ __forceinline__ void shared_grad_const(const ProbDev &pr, const Stack
   __syncthreads();
 }
 
-// sum6 over the workgroup in a fixed order into grad[0..6)
+// sum6 over the workgroup in a fixed order into grad[0..6); whether all are finite
+// (the same in every thread)
 template <typename T>
-__device__ __forceinline__ void grad_out(const double sum6[6], T *__restrict__ grad) {
+__device__ __forceinline__ bool grad_out(const double sum6[6], T *__restrict__ grad) {
   __shared__ double red[6][GR_THREADS / 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
@@ -50,11 +51,12 @@ __device__ __forceinline__ void grad_out(const double sum6[6], T *__restrict__ g
     if (lane == 0) red[k][wave] = x;
   }
   __syncthreads();
-  if (threadIdx.x < 6) {
-    double x = 0;
-    for (int w = 0; w < GR_THREADS / 64; ++w) x += red[threadIdx.x][w];
-    grad[threadIdx.x] = (T)x;
+  double x = 0;
+  if (lane < 6) {
+    for (int w = 0; w < GR_THREADS / 64; ++w) x += red[lane][w];
+    if (wave == 0) grad[lane] = (T)x;
   }
+  return __all(__builtin_isfinite(x));
 }
 
 // q = x_world - (c + t) of pixel (u, v), x_world = Vl x_vox + o
@@ -164,58 +166,62 @@ k_grad_theta_planes(const ProbDev *__restrict__ probs, const StackDev *__restric
 #pragma unroll
     for (int k = 0; k < 6; ++k) sum6[k] += gj * (a6[k] * iz);
   };
-  if (!fw.rows) {  // off the walk: sample by sample, as k_grad_theta
-    const int n = pt.w * pt.h;
-    for (int l = threadIdx.x; l < n; l += GR_THREADS) {
-      const long long j = pt.off + l;
-      const double gj = gy[j], iz = invz[j];
-      if (!(iz > 0) || gj == 0.0) continue;
-      const int u = pt.x0 + l % pt.w, v = pt.y0 + l / pt.w;
-      int b[3];
-      double f[3], qt[3], a6[6] = {0, 0, 0, 0, 0, 0}, z = 0, acc = 0;
-      sample_centre(g, pr, u, v, pt.slice, b, f);
-      grad_q(gc, g.H, u, v, pt.slice, qt);
-      psf_walk<double, GeoD, true>(g, pr, b, f, Xp, z, acc);
-      grad_walk<double>(g, pr, gc, b, f, qt, Xp, acc * iz, a6);
-      add(gj, iz, a6);
-    }
-    grad_out(sum6, grad + 6 * s);
-    return;
-  }
-  const int nbu = (pt.w + 1) / 2, nblk = nbu * ((pt.h + 1) / 2);
-  for (int blk = threadIdx.x; blk < nblk; blk += GR_THREADS) {
-    const int u0 = 2 * (blk % nbu), v0 = 2 * (blk / nbu);
-    double iz[4], gj[4];  // pixel (u0 + i, v0 + j) at 2 j + i; off: 0
+  if (fw.rows) {
+    const int nbu = (pt.w + 1) / 2, nblk = nbu * ((pt.h + 1) / 2);
+    for (int blk = threadIdx.x; blk < nblk; blk += GR_THREADS) {
+      const int u0 = 2 * (blk % nbu), v0 = 2 * (blk / nbu);
+      double iz[4], gj[4];  // pixel (u0 + i, v0 + j) at 2 j + i; off: 0
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int u = u0 + (t & 1), v = v0 + (t >> 1);
-      const long long j = pt.off + (long long)v * pt.w + u;
-      const bool in = u < pt.w && v < pt.h;
-      gj[t] = in ? gy[j] : 0.0;
-      iz[t] = in && gj[t] != 0.0 ? invz[j] : 0.0;
-    }
-    const bool live = iz[0] > 0 || iz[1] > 0 || iz[2] > 0 || iz[3] > 0;
-    if (!live) continue;
+      for (int t = 0; t < 4; ++t) {
+        const int u = u0 + (t & 1), v = v0 + (t >> 1);
+        const long long j = pt.off + (long long)v * pt.w + u;
+        const bool in = u < pt.w && v < pt.h;
+        gj[t] = in ? gy[j] : 0.0;
+        iz[t] = in && gj[t] != 0.0 ? invz[j] : 0.0;
+      }
+      const bool live = iz[0] > 0 || iz[1] > 0 || iz[2] > 0 || iz[3] > 0;
+      if (!live) continue;
 #pragma unroll 1
-    for (int j = 0; j < 2; ++j) {
-      double xb, a[2], z[2], mx[2][9], me[2][9];
-      if (fw.rows == 3) plane_walk_grad<double, 3>(fw, u0, v0, j, xr, nbytes, xb, a, z, mx, me);
-      else plane_walk_grad<double, 4>(fw, u0, v0, j, xr, nbytes, xb, a, z, mx, me);
+      for (int j = 0; j < 2; ++j) {
+        double xb, a[2], z[2], mx[2][9], me[2][9];
+        if (fw.rows == 3) plane_walk_grad<double, 3>(fw, u0, v0, j, xr, nbytes, xb, a, z, mx, me);
+        else plane_walk_grad<double, 4>(fw, u0, v0, j, xr, nbytes, xb, a, z, mx, me);
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const int p = (2 * j + t) ^ fw.flip;  // the sub-window's pixel
-        const double izp = p == 0 ? iz[0] : p == 1 ? iz[1] : p == 2 ? iz[2] : iz[3];
-        const double gp = p == 0 ? gj[0] : p == 1 ? gj[1] : p == 2 ? gj[2] : gj[3];
-        if (!(izp > 0)) continue;
-        const double dl = a[t] * izp;
-        double m[9], qt[3], a6[6];
+        for (int t = 0; t < 2; ++t) {
+          const int p = (2 * j + t) ^ fw.flip;  // the sub-window's pixel
+          const double izp = p == 0 ? iz[0] : p == 1 ? iz[1] : p == 2 ? iz[2] : iz[3];
+          const double gp = p == 0 ? gj[0] : p == 1 ? gj[1] : p == 2 ? gj[2] : gj[3];
+          if (!(izp > 0)) continue;
+          const double dl = a[t] * izp;
+          double m[9], qt[3], a6[6];
 #pragma unroll
-        for (int c = 0; c < 9; ++c) m[c] = fma(-dl, me[t][c], mx[t][c]);
-        grad_q(gc, g.H, pt.x0 + u0 + (p & 1), pt.y0 + v0 + (p >> 1), pt.slice, qt);
-        grad_from_moments(gm, m, qt, a6);
-        add(gp, izp, a6);
+          for (int c = 0; c < 9; ++c) m[c] = fma(-dl, me[t][c], mx[t][c]);
+          grad_q(gc, g.H, pt.x0 + u0 + (p & 1), pt.y0 + v0 + (p >> 1), pt.slice, qt);
+          grad_from_moments(gm, m, qt, a6);
+          add(gp, izp, a6);
+        }
       }
     }
+    // a voxel of the walk's windows outside every support may have made a sum not finite
+    if (grad_out(sum6, grad + 6 * s)) return;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) sum6[k] = 0.0;
+    __syncthreads();
+  }
+  // sample by sample, as k_grad_theta
+  const int n = pt.w * pt.h;
+  for (int l = threadIdx.x; l < n; l += GR_THREADS) {
+    const long long j = pt.off + l;
+    const double gj = gy[j], iz = invz[j];
+    if (!(iz > 0) || gj == 0.0) continue;
+    const int u = pt.x0 + l % pt.w, v = pt.y0 + l / pt.w;
+    int b[3];
+    double f[3], qt[3], a6[6] = {0, 0, 0, 0, 0, 0}, z = 0, acc = 0;
+    sample_centre(g, pr, u, v, pt.slice, b, f);
+    grad_q(gc, g.H, u, v, pt.slice, qt);
+    psf_walk<double, GeoD, true>(g, pr, b, f, Xp, z, acc);
+    grad_walk<double>(g, pr, gc, b, f, qt, Xp, acc * iz, a6);
+    add(gj, iz, a6);
   }
   grad_out(sum6, grad + 6 * s);
 }

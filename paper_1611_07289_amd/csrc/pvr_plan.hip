@@ -320,7 +320,7 @@ k_normalisers_planes(const ProbDev *__restrict__ probs, const PatchDev *__restri
       if (u < pt.w && v < pt.h) put(pt.off + (long long)v * pt.w + u, ok[t], fv ? c : a);
     }
   } else {
-    each_pixel(pt, wk.l0, [&](int u, int v) {
+    each_pixel<false>(pt, wk.l0, true, 0, 0u, [&](int u, int v) {
       const long long j = pt.off + (long long)v * pt.w + u;
       const uint8_t kept = mask ? mask[j] : 1;
       keep[j] = kept;

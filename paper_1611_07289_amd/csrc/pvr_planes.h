@@ -139,15 +139,20 @@ __device__ __forceinline__ void combine_parts(const PlaneLane &p, T s[4], T (*ld
 
 // The same work item one sample at a time, for patches off the walk: calls f(u, v)
 // for the item's pixels, every thread of the workgroup its share, a wavefront 16
-// blocks at a time (two rows of 32 pixels where they lie side by side).
-template <typename F>
-__device__ __forceinline__ void each_pixel(const PatchDev &pt, int l0, F &&f) {
+// blocks at a time (two rows of 32 pixels where they lie side by side).  MIXED and
+// not all: for the pixels of the lane's own block `blk` that `bits` names (2 j + i).
+template <bool MIXED, typename F>
+__device__ __forceinline__ void each_pixel(const PatchDev &pt, int l0, bool all, int blk,
+                                           unsigned bits, F &&f) {
   const int nbu = (pt.w + 1) / 2, nb = min(PLANE_BLOCKS, nbu * ((pt.h + 1) / 2) - l0);
+  const int end = MIXED && !all ? 4 * PLANE_BLOCKS : 4 * ((nb + 15) & ~15);
 #pragma unroll 1
-  for (int q = threadIdx.x; q < 4 * ((nb + 15) & ~15); q += PLANE_BLOCKS) {
-    const int o = (q >> 6) * 16 + ((q & 31) >> 1), blk = l0 + o;
-    const int u = 2 * (blk % nbu) + (q & 1), v = 2 * (blk / nbu) + ((q >> 5) & 1);
-    if (o < nb && u < pt.w && v < pt.h) f(u, v);
+  for (int q = threadIdx.x; q < end; q += PLANE_BLOCKS) {
+    const int o = (q >> 6) * 16 + ((q & 31) >> 1), i = q / PLANE_BLOCKS;
+    const bool mine = MIXED && !all;
+    const int b = mine ? blk : l0 + o;
+    const int u = 2 * (b % nbu) + ((mine ? i : q) & 1), v = 2 * (b / nbu) + (mine ? i >> 1 : (q >> 5) & 1);
+    if (mine ? ((bits >> i) & 1u) != 0 : o < nb && u < pt.w && v < pt.h) f(u, v);
   }
 }
 
