@@ -42,12 +42,13 @@ template <> struct Rq<double> {
 };
 
 // rq_j = (p_j e_j / Z_j, p_j / Z_j) for valid samples, 0 otherwise (the
-// patch weight W_s is applied by the gather, per patch).
+// patch weight W_s is applied by the gather, per patch).  Sets *odd where one is not
+// finite (see k_gather_blocks).
 template <typename T>
 __global__ void __launch_bounds__(SIM_THREADS)
 k_bp_prep(const PatchDev *__restrict__ patches, const BlockWork *__restrict__ work,
           const T *__restrict__ invz, const T *__restrict__ e, const T *__restrict__ p,
-          typename Vec2Of<T>::type *__restrict__ rq) {
+          typename Vec2Of<T>::type *__restrict__ rq, unsigned *__restrict__ odd) {
   const BlockWork wk = work[blockIdx.x];
   const PatchDev pt = patches[wk.patch];
   const int n = pt.w * pt.h;
@@ -56,12 +57,14 @@ k_bp_prep(const PatchDev *__restrict__ patches, const BlockWork *__restrict__ wo
       sizeof(T) == 4 ? rq + pt.rq_off + RQ_PAD : rq + pt.off;
   // one sample (invalid samples, 1/Z = 0, get 0); a padded row adds RQ_PAD
   // entries per pixel row before it
+  bool bad = false;
   auto one = [&](int l, T iz, T pj, T ej) {
     typename Vec2Of<T>::type o;
     if (iz > (T)0) {
       const T q = pj * iz;
       o.x = q * ej;
       o.y = q;
+      bad = bad || !__builtin_isfinite(o.x) || !__builtin_isfinite(q);
     } else {
       o.x = 0;
       o.y = 0;
@@ -87,6 +90,7 @@ k_bp_prep(const PatchDev *__restrict__ patches, const BlockWork *__restrict__ wo
     const long long j = pt.off + l;
     one(l, invz[j], p ? p[j] : (T)1, e[j]);
   }
+  if (bad) *odd = 1u;
 }
 
 // A buffer load never faults: outside the patch's view it returns 0, so
@@ -299,6 +303,11 @@ k_backproject(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ pa
 // the sums move through LDS.  The order (axis, then patch, then candidate) is
 // fixed: the result is bitwise repeatable.
 //
+// A voxel's three rows and columns of the shared window may hold a sample that its
+// own nearest pixel's do not, weighed by zero, and zero times a value that is not
+// finite is NaN: where the inputs hold one (odd[slot], set by k_bp_prep), every patch
+// goes voxel by voxel.  The other slot is cleared for the next preparation.
+//
 // A brick's lists are split over `parts` pairs of wavefronts (entry q to part
 // (q - q0) mod parts, each part with its own LDS sums, added in part order at
 // the end), so that a small grid still fills the chip: gather_parts.
@@ -374,12 +383,14 @@ k_gather_blocks(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ 
                 const AdjPatch<T> *__restrict__ adj, const int *__restrict__ brick_prob,
                 const int *__restrict__ off, const int *__restrict__ list,
                 const typename Vec2Of<T>::type *__restrict__ rq, const T *__restrict__ patch_w,
-                T *__restrict__ num, T *__restrict__ den, int n_bricks, int granule) {
+                T *__restrict__ num, T *__restrict__ den, int n_bricks, int granule,
+                unsigned *__restrict__ odd, int slot) {
   using GEO = typename GeoOf<T>::type;
   using V2 = typename Vec2Of<T>::type;
   using Acc = GbAcc<T, DEN>;
   constexpr int NV = BRICK * BRICK * BRICK;
   extern __shared__ __attribute__((aligned(16))) char lds[];
+  const int may_fast = odd[slot] ? 0 : ADJ_FAST;
   const int bi = xcd_work(blockIdx.x, granule);
   if (bi >= n_bricks) return;
   const ProbDev pr = probs[brick_prob[bi]];
@@ -426,7 +437,7 @@ k_gather_blocks(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ 
       const T ws = patch_w ? patch_w[s] : (T)1;
       if (ws == (T)0) continue;
       const AdjPatch<T> &g = adj[s];
-      const bool fast = g.cls & ADJ_FAST;
+      const bool fast = g.cls & may_fast;
       const int cls = fast ? g.cls & ADJ_MAP : (an == 0 ? 1 : 0) | (an == 2 ? 1 : 2) << 2 | ADJ_OFF;
       if (cls != cur) {  // (uniform; the patches of a stack share their class)
         if (cur >= 0) flush();
@@ -565,6 +576,7 @@ k_gather_blocks(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ 
     }
     if (cur >= 0) flush();
   }
+  if (bi == 0 && threadIdx.x == 0) odd[1 - slot] = 0u;
   __syncthreads();
   for (int v = threadIdx.x; v < NV; v += blockDim.x) {
     Acc r = reinterpret_cast<Acc *>(lds)[v];
@@ -585,8 +597,9 @@ k_gather_blocks(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ 
 // The preparation pass on its own (FP32), for pvr_robust_weights.
 pvr_status pvr::launch_bp_prep(const pvr_plan *p, const float *e, const float *pp,
                                hipStream_t stream) {
+  const_cast<pvr_plan *>(p)->odd_slot[0] ^= 1;
   hipLaunchKernelGGL(k_bp_prep<float>, dim3(p->n_sim_blocks), dim3(SIM_THREADS), 0, stream,
-                     p->d_patch, p->d_sim_blocks, p->d_invz, e, pp, p->d_rq);
+                     p->d_patch, p->d_sim_blocks, p->d_invz, e, pp, p->d_rq, p->d_odd + p->odd_slot[0]);
   HIP_TRY(hipGetLastError());
   return PVR_OK;
 }
@@ -596,6 +609,7 @@ static pvr_status backproject_impl(const pvr_plan *p, const T *e, const T *pp, c
                                    T *num, T *den, const T *invz, typename Vec2Of<T>::type *rq,
                                    hipStream_t stream) {
   if (!e || !num) return fail(PVR_EINVAL, "pvr_backproject: e and num are required");
+  const int f64 = sizeof(T) == 8;
   const unsigned long long capture = capture_id(stream);
   if (!p->index_valid || (p->index_capture && p->index_capture != capture)) {
     const pvr_status st = plan_build_index(const_cast<pvr_plan *>(p), stream);
@@ -607,8 +621,9 @@ static pvr_status backproject_impl(const pvr_plan *p, const T *e, const T *pp, c
                         p->rq_p == (const void *)pp && p->rq_capture == capture;
   if (!prepared) {
     if (sizeof(T) == 4) const_cast<pvr_plan *>(p)->rq_fresh = false;  // d_rq changes
+    const_cast<pvr_plan *>(p)->odd_slot[f64] ^= 1;
     hipLaunchKernelGGL(k_bp_prep<T>, dim3(p->n_sim_blocks), dim3(SIM_THREADS), 0, stream,
-                       p->d_patch, p->d_sim_blocks, invz, e, pp, rq);
+                       p->d_patch, p->d_sim_blocks, invz, e, pp, rq, p->d_odd + 2 * f64 + p->odd_slot[f64]);
     HIP_TRY(hipGetLastError());
   }
   const void *geo = sizeof(T) == 4 ? (const void *)p->d_geof : (const void *)p->d_geod;
@@ -633,7 +648,8 @@ static pvr_status backproject_impl(const pvr_plan *p, const T *e, const T *pp, c
   hipLaunchKernelGGL((k_gather_blocks<T, D, SC>), grid, dim3(GB_THREADS * parts),                 \
                      sizeof(GbAcc<T, D>) * BRICK * BRICK * BRICK * parts, stream, p->d_prob,      \
                      p->d_patch, geot, (const AdjPatch<T> *)adj, p->d_brick_prob, p->d_sub_off,   \
-                     p->d_sub_patch, rq, patch_w, num, den, p->n_bricks, p->bp_granule)
+                     p->d_sub_patch, rq, patch_w, num, den, p->n_bricks, p->bp_granule, \
+                     p->d_odd + 2 * f64, p->odd_slot[f64])
     if (den) {
       if (sinc) GB_LAUNCH(true, true);
       else GB_LAUNCH(true, false);
