@@ -671,11 +671,13 @@ static pvr_status dgrad2_launch(const uint16_t *gout, const uint16_t *out, const
 // 16 channels each), so a tap is an address offset and every value is staged once.
 // A wavefront owns 16 output by 16 input channels of all nine taps (and, for the
 // first 16 input channels, the bias: the product with ones); where a layer has fewer
-// such blocks than wavefronts, KS sets of wavefronts share out the pixels and
-// add up through LDS in order.  Each workgroup writes one partial block, added
-// in order by k_wgrad_reduce (deterministic).  Bound by LDS reads, 10 for 9
-// matrix instructions: 32x32, 32 -> 64 channels, 256 images 30 us (reduction 7);
-// 63 (12 + 5) with both operands transposed on their way into LDS, once a tap.
+// such blocks than wavefronts, KS sets of wavefronts share out the pixels.  After
+// every `chain` steps of 32 pixels each set writes its sums as a partial block and
+// starts anew: k_wgrad_reduce adds the blocks in FP64, in order (deterministic), so
+// that no FP32 sum grows longer than wgrad_chain's pixels.  Bound by LDS reads, 10 for 9
+// matrix instructions, and by the blocks written and reduced: 32x32, 32 -> 64 channels,
+// 256 images 44.6 us with the reduction (35 with the KS sets' sums added in FP32, half
+// the blocks); 73 with both operands transposed on their way into LDS, once a tap.
 // ---------------------------------------------------------------------------
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
@@ -689,9 +691,6 @@ struct WgTile {
   static constexpr int ICH = NSUB * PIX * (CIN / 8), GCH = PXO * (COUT / 8);
   static constexpr int NI = (ICH + 1023) / 1024, NG = (GCH + 1023) / 1024;
   static constexpr int I_ELEMS = NSUB * PIX * CI, G_ELEMS = PXO * CG;
-  static constexpr int SUM_BYTES = KS > 1 ? MT * NC * 10 * 1024 : 0;  // nine taps and the bias
-  static constexpr int TILE_BYTES = (I_ELEMS + G_ELEMS) * 2;
-  static constexpr int LDS_BYTES = TILE_BYTES > SUM_BYTES ? TILE_BYTES : SUM_BYTES;
   static constexpr long long REC = 9LL * COUT * CIN;  // floats per partial block
   __device__ static constexpr int slot(int ix) { return S == 2 ? (ix >> 1) + (ix & 1) * NE : ix; }
 };
@@ -710,10 +709,10 @@ template <int CIN, int COUT, int S, int TW, int TH, int NSUB>
 __global__ void __launch_bounds__(1024)
 k_wgrad_tile(const uint16_t *__restrict__ gout, const uint16_t *__restrict__ out,
              const uint16_t *__restrict__ in, float *__restrict__ part, float *__restrict__ bpart,
-             int H, int Wd, int Ho, int Wo, int n_sub, int ntx, int nty) {
+             int H, int Wd, int Ho, int Wo, int n_sub, int ntx, int nty, int chain, int blocks) {
   using SH = WgTile<CIN, COUT, S, TW, TH, NSUB>;
   constexpr int NI = SH::NI, NG = SH::NG, C8 = CIN / 8, G8 = COUT / 8;
-  __shared__ __attribute__((aligned(16))) uint16_t lds[SH::LDS_BYTES / 2];
+  __shared__ __attribute__((aligned(16))) uint16_t lds[SH::I_ELEMS + SH::G_ELEMS];
   uint16_t *It = lds, *Gt = lds + SH::I_ELEMS;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int kq = lane >> 4, r16 = lane & 15;
@@ -775,13 +774,34 @@ k_wgrad_tile(const uint16_t *__restrict__ gout, const uint16_t *__restrict__ out
   bf16x8 ones;
 #pragma unroll
   for (int i = 0; i < 8; ++i) ones[i] = 0x3f80;
+  // the set's partial blocks: block 0, 1, .. of each set in turn
+  long long row = ((long long)blockIdx.y * gridDim.x + blockIdx.x) * blocks * SH::KS + ks;
+  int left = chain;
+  const auto write = [&]() {
+    float *dst = part + row * SH::REC;
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        dst[((long long)t * COUT + cm * 16 + 4 * kq + i) * CIN + cn * 16 + r16] = acc[t][i];
+    if (cn == 0 && r16 == 0)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) bpart[row * COUT + cm * 16 + 4 * kq + i] = acc[9][i];
+#pragma unroll
+    for (int t = 0; t < 10; ++t) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    row += SH::KS;
+    left = chain;
+    --blocks;
+  };
   load(blockIdx.x);
   put();
   __syncthreads();
   for (int group = blockIdx.x; group < n_groups; group += gridDim.x) {
     const bool more = group + (int)gridDim.x < n_groups;
     if (more) load(group + gridDim.x);
-    for (int st = ks; st < SH::STEPS; st += SH::KS) {
+    for (int st = ks + SH::KS * blockIdx.y; st < SH::STEPS; st += SH::KS * gridDim.y) {
+      if (left == 0) write();
+      --left;
       const int q = st * 32 + 8 * kq + (r16 >> 2);  // (its eight pixels lie in one row)
       const int sub = q / (TW * TH), rr = q % (TW * TH);
       const uint16_t *gp = Gt + q * SH::CG + cm * 16 + 4 * (r16 & 3);
@@ -800,29 +820,7 @@ k_wgrad_tile(const uint16_t *__restrict__ gout, const uint16_t *__restrict__ out
       __syncthreads();
     }
   }
-  if constexpr (SH::KS > 1) {  // the other pixel sets' sums, in order
-    f32x4 *sum = reinterpret_cast<f32x4 *>(lds);
-    for (int g = 1; g < SH::KS; ++g) {
-#pragma unroll
-      for (int t = 0; t < 10; ++t)
-        if (ks == g) sum[(wl * 10 + t) * 64 + lane] = acc[t];
-      __syncthreads();
-#pragma unroll
-      for (int t = 0; t < 10; ++t)
-        if (ks == 0) acc[t] += sum[(wl * 10 + t) * 64 + lane];
-      __syncthreads();
-    }
-    if (ks) return;
-  }
-  float *dst = part + (long long)blockIdx.x * SH::REC;
-#pragma unroll
-  for (int t = 0; t < 9; ++t)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      dst[((long long)t * COUT + cm * 16 + 4 * kq + i) * CIN + cn * 16 + r16] = acc[t][i];
-  if (cn == 0 && r16 == 0)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) bpart[(long long)blockIdx.x * COUT + cm * 16 + 4 * kq + i] = acc[9][i];
+  while (blocks > 0) write();  // the last sums, and zeros where a workgroup had fewer groups
 }
 
 // The first layer (2 input channels): the columns are (tap, ci) flattened and
@@ -1332,13 +1330,21 @@ struct WgradPlan {
   long long rows, rec, wch;  // wch: pixels per chunk (first layer)
   int n_sub, ntx, nty;       // tiles (other layers)
   int sub;                   // of them a group
+  int wgs, split;            // workgroups, and of them to a group
+  int chain, blocks;         // steps of a partial block, blocks of a set of wavefronts
   bool small;                // 8 x 8 tiles
 };
-// Workgroups of the tiled kernel, each with a partial block to write (147 KB of a
-// 64 -> 64 layer) and reduce: at most one a compute unit, two groups each where there
-// are enough for WG_MIN_ROWS (16x16, 64 -> 64, 256 images: 27.9 us, one group each
-// 29.2, four 36.5).
-constexpr int WG_MAX_ROWS = 256, WG_MIN_ROWS = 64, WG_EACH = 2;
+// Steps of 32 pixels that a set of wavefronts (KS share a layer's pixels) adds up in
+// FP32 before it writes a partial block: about 256 KS blocks a layer.  The rounding
+// of a weight's sum grows with it.
+static int wgrad_chain(long long P, int ks) {
+  const long long c = ((P + 255) / 256 + 32LL * ks - 1) / (32LL * ks);
+  return c < 1 ? 1 : (int)c;
+}
+// Workgroups of the tiled kernel: at most one a compute unit, its groups of tiles as
+// even as they go; a group of more than one partial block is split over several
+// workgroups while there are fewer (16x16, 64 -> 64, 4 images: 11.4 us, 24.6 unsplit).
+constexpr int WG_MAX = 256, WG_ONE_TILE = 64;
 
 template <int CIN, int COUT>
 static bool wgrad_plan(int B, int H, int W, int stride, WgradPlan &pl) {
@@ -1357,9 +1363,16 @@ static bool wgrad_plan(int B, int H, int W, int stride, WgradPlan &pl) {
     pl.nty = (Ho + th - 1) / th;
     const long long n_sub = (long long)B * pl.ntx * pl.nty;
     pl.n_sub = (int)n_sub;
-    pl.sub = pl.small && n_sub > WG_MIN_ROWS ? 4 / stride : 1;
+    pl.sub = pl.small && n_sub > WG_ONE_TILE ? 4 / stride : 1;
     const long long groups = (n_sub + pl.sub - 1) / pl.sub;
-    pl.rows = std::min(groups, std::max((long long)WG_MIN_ROWS, std::min(groups / WG_EACH, (long long)WG_MAX_ROWS)));
+    constexpr int KS = 16 / ((COUT / 16) * (CIN / 16));
+    const long long per = std::max(1LL, (groups + WG_MAX - 1) / WG_MAX), wgs = (groups + per - 1) / per;
+    const int steps = (pl.sub * tw * th / 32 + KS - 1) / KS;  // of a set, a group
+    pl.chain = wgrad_chain((long long)B * Ho * Wo, KS);
+    pl.split = wgs < WG_MAX && wgs > 0 ? (int)std::min<long long>((steps + pl.chain - 1) / pl.chain, WG_MAX / wgs) : 1;
+    pl.wgs = (int)wgs;
+    pl.blocks = (int)((per * ((steps + pl.split - 1) / pl.split) + pl.chain - 1) / pl.chain);
+    pl.rows = wgs * pl.split * pl.blocks * KS;
     pl.rec = 9LL * CIN * COUT;
     return n_sub <= 0x7fff0000LL;
   }
@@ -1397,8 +1410,8 @@ static pvr_status conv_wgrad(const uint16_t *gout, const uint16_t *out, const ui
   } else {
     const int Ho = out_size(H, S), Wo = out_size(W, S);
 #define WG_LAUNCH(TW, TH, NSUB)                                                                \
-  hipLaunchKernelGGL((k_wgrad_tile<CIN, COUT, S, TW, TH, NSUB>), dim3((unsigned)pl.rows), dim3(1024), \
-                     0, stream, gout, out, in, part, bpart, H, W, Ho, Wo, pl.n_sub, pl.ntx, pl.nty)
+  hipLaunchKernelGGL((k_wgrad_tile<CIN, COUT, S, TW, TH, NSUB>), dim3(pl.wgs, pl.split), dim3(1024), 0, stream, \
+                     gout, out, in, part, bpart, H, W, Ho, Wo, pl.n_sub, pl.ntx, pl.nty, pl.chain, pl.blocks)
     if (!pl.small) WG_LAUNCH(16, 16 / S, 1);
     else if (pl.sub == 1) WG_LAUNCH(8, 8, 1);
     else WG_LAUNCH(8, 8, 4 / S);
