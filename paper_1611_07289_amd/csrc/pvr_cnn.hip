@@ -1313,7 +1313,8 @@ extern "C" pvr_status pvr_cnn_conv_dgrad(const uint16_t *gout, const uint16_t *o
   PVR_ALIGNED("pvr_cnn_conv_dgrad", out, 16);
   PVR_ALIGNED("pvr_cnn_conv_dgrad", wt, 16);
   PVR_ALIGNED("pvr_cnn_conv_dgrad", gin, 16);
-  if (!gout || !out || !wt || !gin || B <= 0) return fail(PVR_EINVAL, "pvr_cnn_conv_dgrad: invalid argument");
+  if (!gout || !out || !wt || !gin || B <= 0 || H <= 0 || W <= 0)
+    return fail(PVR_EINVAL, "pvr_cnn_conv_dgrad: invalid argument");
 #define LAUNCH(CI, CO, ST)                                                \
   if constexpr (CI >= 16)                                                 \
     if (cin == CI && cout == CO && stride == ST)                          \
@@ -1443,7 +1444,7 @@ extern "C" pvr_status pvr_cnn_conv_wgrad(const uint16_t *gout, const uint16_t *o
   PVR_ALIGNED("pvr_cnn_conv_wgrad", scratch, 16);
   PVR_ALIGNED("pvr_cnn_conv_wgrad", dw, 4);
   PVR_ALIGNED("pvr_cnn_conv_wgrad", db, 4);
-  if (!gout || !out || !in || !scratch || !dw || !db || B <= 0)
+  if (!gout || !out || !in || !scratch || !dw || !db || B <= 0 || H <= 0 || W <= 0)
     return fail(PVR_EINVAL, "pvr_cnn_conv_wgrad: invalid argument");
 #define LAUNCH(CI, CO, ST)                                                           \
   if (cin == CI && cout == CO && stride == ST)                                       \
