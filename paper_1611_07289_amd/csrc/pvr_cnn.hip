@@ -47,13 +47,6 @@ __device__ __forceinline__ bf16x8 load8(const uint16_t *p) {
   t.u = *reinterpret_cast<const uint4 *>(p);
   return t.v;
 }
-__device__ __forceinline__ bf16x8 zero8() {
-  V8 t;
-  t.u = make_uint4(0, 0, 0, 0);
-  return t.v;
-}
-
-constexpr int CT = 256;  // threads per conv workgroup (4 waves)
 
 }  // namespace
 

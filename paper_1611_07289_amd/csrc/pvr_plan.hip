@@ -536,7 +536,8 @@ k_adj_lists(const ProbDev *__restrict__ probs, const int *__restrict__ brick_pro
       c[w] += __popcll(bal);
     }
   };
-  if (n > LIST_HITS || p1 - p0 > 1 << 24) {  // (24 bits of a hit hold the patch)
+  static_assert(PVR_MAX_PROBLEM_PATCHES <= 1 << 24, "24 bits of a hit hold the patch");
+  if (n > LIST_HITS) {
     each(put);
     return;
   }
