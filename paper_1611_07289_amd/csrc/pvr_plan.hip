@@ -827,7 +827,7 @@ static size_t layout(pvr_plan *p, char *base, int flags) {
   p->d_cursor = ws_take<unsigned long long>(c, 2);
   p->d_reg_stats = ws_take<unsigned long long>(c, 4);
   {
-    size_t off[4];
+    size_t off[5];
     p->d_reg = ws_take<char>(c, (long long)reg_state_bytes(p, off));
   }
   p->d_status = ws_take<unsigned>(c, 1);
