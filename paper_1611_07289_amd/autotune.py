@@ -1,14 +1,17 @@
 """Autotuner for the launch shapes of a plan's two PSF kernels.
 
 Forward pass: the global-memory walk with its XCD granule (how many
-consecutive 1024-sample chunks one XCD takes at a time), or LDS-staged tiles
-of tile_w x tile_h pixels per workgroup.  Adjoint: the XCD granule of its
+consecutive work items one XCD takes at a time: of 256 blocks of 2 x 2 samples
+where samples share their walk, else of 1024 samples), or LDS-staged tiles of
+tile_w x tile_h pixels per workgroup.  Adjoint: the XCD granule of its
 brick list.  Every candidate is applied (pvr_plan_set_tiles,
 pvr_plan_set_granules) and its kernel timed with HIP events over a few
 repetitions (median); the fastest of each kernel is kept and remembered in a
 JSON cache keyed by the workload signature (problem sizes, patch sizes,
-stack frames), so later plans of the same workload skip the search.  The
-launch shapes change no result (every output keeps its summation order).
+stack frames, PSF and cutoff), so later plans of the same workload skip the
+search.  Granules change no result (every output keeps its summation order);
+tiles walk every sample by itself and agree with walks that samples share to
+the FP32 rounding of a sample.
 """
 from __future__ import annotations
 
@@ -30,13 +33,15 @@ CACHE = os.environ.get("PVR_AUTOTUNE_CACHE",
 
 
 def signature(plan) -> str:
+    """The cache key; its prefix changes with the kernels that were timed."""
     h = hashlib.sha1()
     h.update(np.asarray([plan.N, plan.M, plan.V, plan.P], np.int64).tobytes())
     h.update(bytes(plan._g))
     h.update(bytes(plan._s))
+    h.update(np.asarray([plan.psf, plan.cutoff_k], np.float64).tobytes())
     wh = np.asarray([(p.w, p.h) for p in plan._p], np.int32)
     h.update(np.unique(wh, axis=0).tobytes())
-    return "v2-" + h.hexdigest()[:16]
+    return "v3-" + h.hexdigest()[:16]
 
 
 def _load_cache(path: str) -> Dict:

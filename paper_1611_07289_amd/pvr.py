@@ -275,6 +275,8 @@ class Plan:
                                  ctypes.addressof(self._p), len(self._p),
                                  float(cutoff_k), ctypes.byref(h)))
         self.h = h
+        self.cutoff_k = float(cutoff_k)
+        self.psf = PVR_PSF_GAUSSIAN
         info = self.info()
         self.N = int(info.n_samples)
         self.V = int(info.n_voxels)
