@@ -144,6 +144,13 @@ constexpr int TILE_X = 32, TILE_Y = 8, TILE_WAVES = SLIC_T / 64;
 // drift launch, which takes 5 us); beyond it the cells near the tile are.
 constexpr int SLIC_LIST_ALL = 256;
 
+// v, but no NaN whose bits without the sign are all ones (quietened or not): a D^2 of
+// all ones is a pixel's start and would not be taken.
+__device__ __forceinline__ float not_all_ones(float v) {
+  const unsigned b = __float_as_uint(v);
+  return (b | 0x80400000u) == ~0u ? __uint_as_float(b & ~1u) : v;
+}
+
 template <bool DRIFT>
 __global__ void __launch_bounds__(SLIC_T)
 k_slic_gather(const float *__restrict__ img, int n_img, int h, int w, int a, int kx, int ky, int K,
@@ -198,7 +205,8 @@ k_slic_gather(const float *__restrict__ img, int n_img, int h, int w, int a, int
     const unsigned long long hit = __ballot(in);
     if (in) {
       const int slot = __popcll(hit & ((1ull << lane) - 1ull));
-      cc.w = cc.w * cc.w / (float)(a * a);
+      cc.z = not_all_ones(cc.z);
+      cc.w = not_all_ones(cc.w * cc.w / (float)(a * a));
       list_c[wv][slot] = cc;
       list_k[wv][slot] = k;
     }
