@@ -644,8 +644,6 @@ extern "C" pvr_status pvr_robust_weights(pvr_plan *p, const float *resid, const 
   PVR_TRY_STATUS(debug_finite(p, "pvr_robust_weights", "y_obs", y_obs, p->N, stream));
   const int init = (flags & PVR_EM_INIT) != 0;
   const int fix = (flags & PVR_EM_FIX_W) != 0;
-  // p_bar is needed by the classification even when the caller does not want it
-  float *pb = pbar ? pbar : p->d_pbar;
   // residual statistics: reused from the forward kernel when the caller vouches
   // that resid is unchanged since the plan's last pvr_simulate wrote it
   const bool fresh = (flags & PVR_EM_RESID_FRESH) && p->stats_valid && p->stats_resid == resid &&
@@ -660,7 +658,7 @@ extern "C" pvr_status pvr_robust_weights(pvr_plan *p, const float *resid, const 
                      init, p->d_status);
   HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(k_em_estep, dim3(p->M), dim3(EM_T), 0, stream, p->d_patch, p->d_invz, resid,
-                     em, pp, pb, p->d_pstat + PSTAT * (long long)p->M, p->M);
+                     em, pp, pbar, p->d_pstat + PSTAT * (long long)p->M, p->M);
   HIP_TRY(hipGetLastError());
   // the adjoint's inputs need the posteriors only, not the patch weights: on
   // request they are prepared on the plan's second stream while the patch

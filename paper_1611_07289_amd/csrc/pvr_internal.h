@@ -756,7 +756,6 @@ struct pvr_plan {
   unsigned *d_odd;           // [4] FP32, FP64: two slots, non-finite adjoint inputs prepared there
   int odd_slot[2];           // ... the slot of the last preparation
   double *d_pstat;           // [M][5] residual statistics, [4][M] E-step sums
-  float *d_pbar;             // [M] potentials when the caller passes none
   double *d_pval;            // [M] classification scratch (problems beyond the LDS copy)
   pvr::FwdPatch<float> *d_fwd;     // [M] plane-walk constants
   pvr::SincPatch *d_sinc;          // [M] the sinc PSF's

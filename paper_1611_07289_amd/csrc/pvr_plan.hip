@@ -820,7 +820,6 @@ static size_t layout(pvr_plan *p, char *base, int flags) {
   p->d_rq = ws_take<float2>(c, p->n_rq);
   p->d_odd = ws_take<unsigned>(c, 4);
   p->d_pstat = ws_take<double>(c, 9 * M);
-  p->d_pbar = ws_take<float>(c, M);
   p->d_pval = ws_take<double>(c, M);
   p->d_chunk_stats = ws_take<double>(c, 5LL * std::max(p->n_sim_blocks, p->n_pblocks));
   p->d_xt = p->any_xt ? ws_take<float>(c, p->V) : nullptr;
