@@ -20,14 +20,14 @@ Extra objects on the JSON line:
   hbm_equivalent  the iteration time against the HBM floor of a stored-weight
                 implementation of the same iteration (bytes it would move /
                 8 TB/s);
-  roofline      dominant kernel (k_simulate or k_backproject): algorithmic
+  roofline      kernel of the dominant pass (forward or adjoint): algorithmic
                 work per launch / its average duration from the event pairs
                 the library records around each launch on its stream, against
                 the chip's peak; traffic = counter-measured HBM-side bytes
                 per launch when taken on the current library sources;
   kernels_ms    average duration of every call of the step (HIP events on
                 the library's stream);
-  hot_kernels_ms  the two PSF kernels alone;
+  hot_kernels_ms  the kernels of the two PSF passes alone;
   cpu_baseline  the FP64 oracle timed on the host on a bounded sample;
   full_pvr      (uterus256 and sinc256, unless --no-full-pvr) seconds and
                 PSNR of a whole reconstruction from zero motion -- initial
@@ -111,6 +111,16 @@ def measured_traffic(kernel: str, workload: str):
         return None
     e = d.get("kernels", {}).get(kernel)
     return None if e is None else float(e["fetch_bytes"]) + float(e["write_bytes"])
+
+
+def kernel_of(name: str, sinc: bool = False, forward: str = "walk") -> str:
+    """The kernel that a pass (k_simulate: forward, k_backproject: adjoint)
+    launches on these workloads' voxel-sized pixels."""
+    if name == "k_backproject":
+        return "k_gather_blocks"
+    if forward.startswith("tiles"):
+        return "k_simulate_tiles"
+    return "k_simulate" if sinc else "k_simulate_planes"
 
 
 def log(msg):
@@ -400,8 +410,8 @@ def main():
     log(f"[bench] {ms_step:.3f} ms/step, {value / 1e9:.3f} G samples/s; "
         + ", ".join(f"{n} {v:.3f} ms" for n, v in per.items()))
 
-    # the hot kernels alone (event pairs the library records around each
-    # launch on its stream during the timed steps)
+    # the passes' hot kernels alone (event pairs the library records around
+    # each launch on its stream during the timed steps)
     kern = {}
     for name, kid in (("k_simulate", pvr.PVR_KERNEL_SIMULATE),
                       ("k_backproject", pvr.PVR_KERNEL_BACKPROJECT)):
@@ -423,7 +433,7 @@ def main():
         fpn = FLOP_PER_NNZ_FWD if dom == "k_simulate" else FLOP_PER_NNZ_ADJ
     nnz_dom = nnz if dom == "k_simulate" else nnz_adj
     achieved = nnz_dom * fpn / (kern[dom] * 1e-3) / 1e12
-    roofline = {"bound": "alu", "kernel": dom, "achieved": achieved,
+    roofline = {"bound": "alu", "kernel": kernel_of(dom, sinc), "achieved": achieved,
                 "peak": FP32_VALU_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": achieved / FP32_VALU_PEAK_TFLOPS,
                 "traffic": measured_traffic(dom, args.workload),
@@ -566,7 +576,8 @@ def batched_bench(args, probs, dev):
     fpn = FLOP_PER_NNZ_FWD if dom == "k_simulate" else FLOP_PER_NNZ_ADJ
     nnz_dom = nnz if dom == "k_simulate" else nnz_adj
     achieved = nnz_dom * fpn / (kern[dom] * 1e-3) / 1e12
-    roofline = {"bound": "alu", "kernel": dom, "achieved": achieved,
+    launch = tuned.get("forward") or tuned["fixed"]
+    roofline = {"bound": "alu", "kernel": kernel_of(dom, forward=launch), "achieved": achieved,
                 "peak": FP32_VALU_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": achieved / FP32_VALU_PEAK_TFLOPS, "traffic": None,
                 "kernel_ms": kern[dom], "nnz_per_launch": nnz_dom, "flop_per_nnz": fpn,
@@ -785,7 +796,8 @@ def register_roofline(stats, reg_ms, nnz_per_sample):
             + stats["samples_exact"] * (nnz_per_sample * FLOP_PER_NNZ_REG_EXACT
                                         + FLOP_PER_SAMPLE_REG_EXACT))
     ach = flop / max(reg_ms * 1e-3, 1e-12) / 1e12
-    return {"bound": "alu", "kernel": "k_register", "achieved": ach,
+    kernels = "k_reg_grad, k_reg_eval" if stats["samples_exact"] else "k_reg_eval"
+    return {"bound": "alu", "kernel": kernels, "achieved": ach,
             "peak": FP32_VALU_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": ach / FP32_VALU_PEAK_TFLOPS,
             "kernel_ms": reg_ms, "work": stats, "nnz_per_sample": nnz_per_sample}
 
