@@ -307,10 +307,11 @@ pvr_status pvr_plan_set_tiles(pvr_plan *plan, int32_t tile_w, int32_t tile_h,
 
 /* Launch order of the two PSF kernels (a tuning knob, used by the
  * autotuner): workgroups are dealt to the 8 XCDs round-robin, each XCD with
- * its own L2; the work lists (forward chunks of 1024 samples, patch-major;
+ * its own L2; the work lists (forward: 256 blocks of 2 x 2 samples where
+ * samples share their walk, else chunks of 1024 samples, patch-major;
  * adjoint bricks of 8^3 voxels, x fastest) are regrouped into granules of
  * g consecutive items so that XCD x takes granules x, x + 8, ....  Defaults:
- * forward 1, adjoint 64.  Results do not depend on the granules (every
+ * forward 4, adjoint 32.  Results do not depend on the granules (every
  * output keeps its summation order).  Both in [1, 4096].  (host) */
 pvr_status pvr_plan_set_granules(pvr_plan *plan, int32_t sim_granule, int32_t bp_granule);
 

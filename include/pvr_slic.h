@@ -18,8 +18,8 @@
  *          the image), intensity of the nearest pixel, t = t0;
  *  assign: every pixel takes, among the centres whose 2a x 2a window covers
  *          it (|x - c_x| <= a and |y - c_y| <= a), the one of least D^2 (FP32),
- *          ties to the lower index; the result does not depend on the order
- *          of evaluation (a packed atomic minimum);
+ *          ties to the lower index (each pixel goes through the centres in
+ *          reach in ascending order);
  *  update: every centre becomes the mean (x, y, intensity) of its pixels (FP64
  *          sums in a fixed order) and t the largest |I_p - mean intensity|
  *          over them, at least t_min; a centre without pixels is unchanged.
@@ -41,11 +41,11 @@
  *          (for a box from pvr_slic_boxes: the dilated superpixel), else 0.
  *          Boxes must lie in the image and hold at most 65536 pixels.
  *          The table is staged into the caller's device workspace
- *          (pvr_slic_pack_workspace(M) bytes, 16-byte aligned) through a
- *          host array on the stack, synchronising `stream` once per 1024
- *          patches before the packing kernel is launched; the workspace
- *          must stay allocated until that kernel has run.  The library
- *          allocates no memory.
+ *          (pvr_slic_pack_workspace(M) bytes, 16-byte aligned) by one copy,
+ *          `stream` synchronised once before the packing is launched (the
+ *          table may then change); the offsets are summed on the device.
+ *          The workspace must stay allocated until the packing has run.
+ *          The library allocates no memory.
  * Errors: PVR_EINVAL for NULL pointers, non-positive sizes, a beyond 2^20 or
  * gamma < 0, PVR_ESHAPE when n_img * h * w exceeds 2^31, h or w exceeds
  * 2^20, K exceeds 2^20, n_img exceeds 65535, a packed box leaves its image

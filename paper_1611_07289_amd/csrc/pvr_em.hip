@@ -354,8 +354,8 @@ __device__ __forceinline__ double lane_value(double x, int l) {
 // all, at one more barrier.  Robust weights of one problem with four / eight /
 // sixteen wavefronts (us): 300 patches 45 / 49 / 61, 600 50 / 53 / 63, 1 152 58 / 60 /
 // 70, 1 600 69 / 67 / 75, 3 000 97 / 86 / 89, 4 000 116 / 104 / 106, 6 000 - / 131 /
-// 126.  256^3, 11 760 patches: 178; 216 with LDS permutations, one lane taking the
-// step and flat reads of the potentials.  CAP: potentials the workgroup keeps in LDS
+// 126.  256^3, 11 760 patches, the fit alone: 170 us; 216 with LDS permutations, one
+// lane taking the step and flat reads of the potentials.  CAP: potentials the workgroup keeps in LDS
 // (0: none).
 // K sums of the workgroup into every lane, in the order of bsumk; two calls with
 // the same lds need a barrier in between.
