@@ -42,13 +42,13 @@ template <> struct Rq<double> {
 };
 
 // rq_j = (p_j e_j / Z_j, p_j / Z_j) for valid samples, 0 otherwise (the
-// patch weight W_s is applied by the gather, per patch).  Sets *odd where one is not
-// finite (see k_gather_blocks).
+// patch weight W_s is applied by the gather, per patch).  Leaves its number in *odd
+// where one is not finite (see k_gather_blocks).
 template <typename T>
 __global__ void __launch_bounds__(SIM_THREADS)
 k_bp_prep(const PatchDev *__restrict__ patches, const BlockWork *__restrict__ work,
           const T *__restrict__ invz, const T *__restrict__ e, const T *__restrict__ p,
-          typename Vec2Of<T>::type *__restrict__ rq, unsigned *__restrict__ odd) {
+          typename Vec2Of<T>::type *__restrict__ rq, unsigned *__restrict__ odd, unsigned call) {
   const BlockWork wk = work[blockIdx.x];
   const PatchDev pt = patches[wk.patch];
   const int n = pt.w * pt.h;
@@ -90,7 +90,7 @@ k_bp_prep(const PatchDev *__restrict__ patches, const BlockWork *__restrict__ wo
     const long long j = pt.off + l;
     one(l, invz[j], p ? p[j] : (T)1, e[j]);
   }
-  if (bad) *odd = 1u;
+  if (bad) *odd = call;
 }
 
 // A buffer load never faults: outside the patch's view it returns 0, so
@@ -305,8 +305,8 @@ k_backproject(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ pa
 //
 // A voxel's three rows and columns of the shared window may hold a sample that its
 // own nearest pixel's do not, weighed by zero, and zero times a value that is not
-// finite is NaN: where the inputs hold one (odd[slot], set by k_bp_prep), every patch
-// goes voxel by voxel.  The other slot is cleared for the next preparation.
+// finite is NaN: where the inputs hold one (k_bp_prep left its number, `call`, in *odd),
+// every patch goes voxel by voxel.
 //
 // A brick's lists are split over `parts` pairs of wavefronts (entry q to part
 // (q - q0) mod parts, each part with its own LDS sums, added in part order at
@@ -385,13 +385,13 @@ k_gather_blocks(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ 
                 const int *__restrict__ off, const int *__restrict__ list,
                 const typename Vec2Of<T>::type *__restrict__ rq, const T *__restrict__ patch_w,
                 T *__restrict__ num, T *__restrict__ den, int n_bricks, int granule,
-                unsigned *__restrict__ odd, int slot) {
+                const unsigned *__restrict__ odd, unsigned call) {
   using GEO = typename GeoOf<T>::type;
   using V2 = typename Vec2Of<T>::type;
   using Acc = GbAcc<T, DEN>;
   constexpr int NV = BRICK * BRICK * BRICK;
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  const int may_fast = odd[slot] ? 0 : ADJ_FAST;
+  const int may_fast = *odd == call ? 0 : ADJ_FAST;
   const int bi = xcd_work(blockIdx.x, granule);
   if (bi >= n_bricks) return;
   const ProbDev pr = probs[brick_prob[bi]];
@@ -577,7 +577,6 @@ k_gather_blocks(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ 
     }
     if (cur >= 0) flush();
   }
-  if (bi == 0 && threadIdx.x == 0) odd[1 - slot] = 0u;
   __syncthreads();
   for (int v = threadIdx.x; v < NV; v += blockDim.x) {
     Acc r = reinterpret_cast<Acc *>(lds)[v];
@@ -595,14 +594,26 @@ k_gather_blocks(const ProbDev *__restrict__ probs, const PatchDev *__restrict__ 
   }
 }
 
-// The preparation pass on its own (FP32), for pvr_robust_weights.
-pvr_status pvr::launch_bp_prep(const pvr_plan *p, const float *e, const float *pp,
-                               hipStream_t stream) {
-  const_cast<pvr_plan *>(p)->odd_slot[0] ^= 1;
-  hipLaunchKernelGGL(k_bp_prep<float>, dim3(p->n_sim_blocks), dim3(SIM_THREADS), 0, stream,
-                     p->d_patch, p->d_sim_blocks, p->d_invz, e, pp, p->d_rq, p->d_odd + p->odd_slot[0]);
+// The preparation pass.  Each has a number of its own, so that what an earlier one left
+// in d_odd says nothing of this one; a captured one keeps its number from replay to
+// replay and clears the place first.
+template <typename T>
+static pvr_status prepare(const pvr_plan *p, const T *invz, const T *e, const T *pp,
+                          typename Vec2Of<T>::type *rq, hipStream_t stream) {
+  const int f64 = sizeof(T) == 8;
+  unsigned &call = const_cast<pvr_plan *>(p)->odd_call[f64];
+  if (++call == 0) call = 1;
+  if (capture_id(stream)) launch_fill_i32((int *)p->d_odd + f64, 0, 1, stream);
+  hipLaunchKernelGGL(k_bp_prep<T>, dim3(p->n_sim_blocks), dim3(SIM_THREADS), 0, stream, p->d_patch,
+                     p->d_sim_blocks, invz, e, pp, rq, p->d_odd + f64, call);
   HIP_TRY(hipGetLastError());
   return PVR_OK;
+}
+
+// On its own (FP32), for pvr_robust_weights.
+pvr_status pvr::launch_bp_prep(const pvr_plan *p, const float *e, const float *pp,
+                               hipStream_t stream) {
+  return prepare<float>(p, p->d_invz, e, pp, p->d_rq, stream);
 }
 
 template <typename T>
@@ -622,10 +633,8 @@ static pvr_status backproject_impl(const pvr_plan *p, const T *e, const T *pp, c
                         p->rq_p == (const void *)pp && p->rq_capture == capture;
   if (!prepared) {
     if (sizeof(T) == 4) const_cast<pvr_plan *>(p)->rq_fresh = false;  // d_rq changes
-    const_cast<pvr_plan *>(p)->odd_slot[f64] ^= 1;
-    hipLaunchKernelGGL(k_bp_prep<T>, dim3(p->n_sim_blocks), dim3(SIM_THREADS), 0, stream,
-                       p->d_patch, p->d_sim_blocks, invz, e, pp, rq, p->d_odd + 2 * f64 + p->odd_slot[f64]);
-    HIP_TRY(hipGetLastError());
+    const pvr_status st = prepare<T>(p, invz, e, pp, rq, stream);
+    if (st != PVR_OK) return st;
   }
   const void *geo = sizeof(T) == 4 ? (const void *)p->d_geof : (const void *)p->d_geod;
   const dim3 grid(xcd_blocks(p->n_bricks, p->bp_granule));
@@ -650,7 +659,7 @@ static pvr_status backproject_impl(const pvr_plan *p, const T *e, const T *pp, c
                      sizeof(GbAcc<T, D>) * BRICK * BRICK * BRICK * parts, stream, p->d_prob,      \
                      p->d_patch, geot, (const AdjPatch<T> *)adj, p->d_brick_prob, p->d_sub_off,   \
                      p->d_sub_patch, rq, patch_w, num, den, p->n_bricks, p->bp_granule, \
-                     p->d_odd + 2 * f64, p->odd_slot[f64])
+                     p->d_odd + f64, p->odd_call[f64])
     if (den) {
       if (sinc) GB_LAUNCH(true, true);
       else GB_LAUNCH(true, false);

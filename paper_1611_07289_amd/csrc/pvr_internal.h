@@ -753,8 +753,8 @@ struct pvr_plan {
   // scratch
   float2 *d_rq;              // [n_rq]: padded rows (RQ_PAD), the padding always zero
   double2 *d_rq64;           // [N + 2] likewise (workspaces with PVR_WS_F64)
-  unsigned *d_odd;           // [4] FP32, FP64: two slots, non-finite adjoint inputs prepared there
-  int odd_slot[2];           // ... the slot of the last preparation
+  unsigned *d_odd;           // [2] FP32, FP64: the last preparation with an input that is not finite
+  unsigned odd_call[2];      // ... and the number of the last one
   double *d_pstat;           // [M][5] residual statistics, [4][M] E-step sums
   double *d_pval;            // [M] classification scratch (problems beyond the LDS copy)
   pvr::FwdPatch<float> *d_fwd;     // [M] plane-walk constants

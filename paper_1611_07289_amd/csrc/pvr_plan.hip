@@ -818,7 +818,7 @@ static size_t layout(pvr_plan *p, char *base, int flags) {
   p->d_sub_off = ws_take<int>(c, 9 * nb);
   p->d_sub_patch = ws_take<int>(c, p->sub_cap);
   p->d_rq = ws_take<float2>(c, p->n_rq);
-  p->d_odd = ws_take<unsigned>(c, 4);
+  p->d_odd = ws_take<unsigned>(c, 2);
   p->d_pstat = ws_take<double>(c, 9 * M);
   p->d_pval = ws_take<double>(c, M);
   p->d_chunk_stats = ws_take<double>(c, 5LL * std::max(p->n_sim_blocks, p->n_pblocks));
@@ -894,7 +894,7 @@ extern "C" pvr_status pvr_plan_attach(pvr_plan *p, void *workspace, size_t bytes
   if (p->d_rq64) launch_fill_f64((double *)p->d_rq64, 0.0, 2 * (p->N + 2), stream);
   launch_fill_i32((int *)p->d_status, 0, 1, stream);
   launch_fill_i32((int *)p->d_cursor, 0, 4, stream);
-  launch_fill_i32((int *)p->d_odd, 0, 4, stream);
+  launch_fill_i32((int *)p->d_odd, 0, 2, stream);
   launch_fill_i32((int *)p->d_reg_stats, 0, 8, stream);
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipStreamSynchronize(stream));  // the uploads read pageable host tables of the plan

@@ -112,3 +112,36 @@ def test_adjoint_is_itself_again_after_a_value_that_is_not_finite(graph):
         run()
         torch.cuda.synchronize()
         assert torch.equal(num, clean)
+
+
+def test_a_captured_adjoint_is_itself_again_in_every_replay():
+    """One adjoint to a graph, so that every replay prepares where the last one did,
+    with an eager one between replays."""
+    g, st, P = _problem(synth.orthogonal_frames([30.0]), 24, 22, 26)
+    plan = pvr.Plan([g], [st], [P])
+    plan.build(dev(_motion(P.M, 9.0, 1.5).astype(np.float32)))
+    e0 = torch.randn(plan.N, device="cuda")
+    e, other = e0.clone(), e0.clone()
+    num, num2 = torch.empty(plan.V, device="cuda"), torch.empty(plan.V, device="cuda")
+    plan.backproject(e, None, None, num, None)
+    torch.cuda.synchronize()
+    clean = num.clone()
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    G = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(G, stream=s):
+        plan.backproject(e, None, None, num, None)
+    for value in (float("nan"), float("inf")):
+        e[1234] = value
+        G.replay()
+        torch.cuda.synchronize()
+        assert not torch.isfinite(num).all()
+        e.copy_(e0)
+        for _ in range(3):
+            G.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(num, clean)
+            G.replay()
+            plan.backproject(other, None, None, num2, None)
+            torch.cuda.synchronize()
+            assert torch.equal(num, clean) and torch.equal(num2, clean)
